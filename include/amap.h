@@ -197,7 +197,8 @@ amap_status amap_plan_selfcheck(const amap_t *m, int kernel_id, int64_t *n_error
  * amap_gemm_mapped; stored through out_map when it is not NULL), and counts loads
  * outside A's source or W, k-steps that fetch anything but their own block of A and W, fetches out
  * of the order of use, stores outside out and elements of out written never or twice.
- * AMAP_E_UNSUPPORTED when the product would run in the general kernel (no replay for that one). */
+ * AMAP_E_UNSUPPORTED when the product is not of that kernel's form.  (A product of that form which runs on smaller tiles,
+ * because it fills too few of these, is replayed here all the same.) */
 amap_status amap_gemm_selfcheck(const amap_t *A_map, const amap_t *W_map, int64_t N, const amap_t *out_map,
                                 int n_workgroups, int64_t *n_errors);
 
@@ -369,8 +370,12 @@ amap_status amap_execute_kernel(const void *const *src, void *dst, const amap_t 
  * 256 rows (the rows of A one run of evenly spaced source rows, or split into
  * blocks that are multiples of 256) run a kernel with 256 x 256 x 64 tiles whose
  * operands go straight from L2 into LDS, M and N being whole numbers of tiles
- * or not (environment AMAP_GEMM_TILE256=0: the general kernel for these too);
- * both add the same products in the same order, so their results are
+ * or not.  Products that fill too few of those tiles, and most that they do not
+ * take (runs along m, gathered sources, blocks of any number of rows, runs of 8
+ * and more along k; K a multiple of 64, or of 32 with the runs of A along m and
+ * those of W along n), run a kernel with 64 x 64 or 128 x 128 tiles loaded the same
+ * way (environment AMAP_GEMM_TILE256=0: the general kernel for all of these);
+ * all three add the same products in the same order, so their results are
  * bit-identical.  Operands and sources of 2^31 elements and more (an A of
  * [1048832, 2048], 4.3 GB) are taken by that kernel only, with a plain store;
  * every other product over such tensors is AMAP_E_UNSUPPORTED. */

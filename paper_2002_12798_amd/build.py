@@ -11,7 +11,7 @@ CSRC = os.path.join(_HERE, "csrc")
 LIB = os.path.join(_HERE, "libamap.so")
 
 SOURCES = ["amap_compose.cpp", "amap_graph.cpp", "amap_layout.cpp", "amap_host.cpp", "amap_plan.cpp", "amap_plan_check.cpp", "amap_kernels.hip",
-           "amap_gemm.hip"]
+           "amap_gemm.hip", "amap_gemm_ring.hip"]
 
 FLAGS = [
     "-O3", "-std=c++17", "-fPIC", "-shared", "--offload-arch=gfx950",
@@ -55,6 +55,11 @@ def build_lib(verbose: bool = False, extra=()) -> str:
         for name, u in usage.items():
             print(f"{name}: {u}", file=sys.stderr)
     spilled = {n: u for n, u in usage.items() if u.get("ScratchSize [bytes/lane]", 0) != 0}
+    # the GEMM kernels address their dynamic LDS from 0: a static allocation (an array the compiler moved there) would overlap it
+    moved = {n: u for n, u in usage.items() if "gemm" in n and u.get("LDS Size [bytes/block]", 0) != 0}
+    if moved:
+        os.remove(LIB)
+        raise RuntimeError(f"GEMM kernels with static LDS: {moved}")
     if spilled:
         os.remove(LIB)
         raise RuntimeError(f"kernels use scratch memory (argument block copied or registers spilled): {spilled}")

@@ -4,8 +4,9 @@
 // used to read the materialised chain output t_s reads the chain's source t_l
 // through g' instead, in its operand-load prologue, and t_s never exists.
 //
-// Two kernels.  amap_gemm_tile256_kernel (further down) takes the common case of whole 64-element runs along k;
-// the general one:
+// Three kernels.  amap_gemm_tile256_kernel (further down) takes products with whole 64-element runs along k that fill the
+// chip with 256 x 256 tiles, amap_gemm_ring_kernel (amap_gemm_ring.hip) most others; the general one, for whatever is left
+// (padded operands, K or the ranges of gathered sources that are no whole number of k-steps):
 // Kernel shape (gfx950): 256 x 128 output tile per workgroup of 4 wavefronts,
 // each wavefront 128 x 64 = 4 x 2 MFMA tiles of v_mfma_f32_32x32x16_bf16 (fp32
 // accumulate in 128 AGPRs), K stepped by 64 through one LDS stage with the
@@ -22,111 +23,18 @@
 #include <cstring>
 #include <memory>
 
-#include "amap_index.hpp"
-#include "amap_plan.hpp"
+#include "amap_gemm_ring.hpp"
 
 using namespace amap_dev;
 using namespace amap_detail;
+using namespace amap_gemm;
 
 namespace {
 
 constexpr int BM = 256, BN = 128, BK = 64;
-constexpr int kGemmThreads = 256;
 constexpr int kATileBytes = BM * BK * 2;  // 32 KiB
 constexpr int kCPitch = BN * 2 + 16;      // bytes per row of the staged output tile (padded against bank conflicts)
 constexpr int kLdsBytes = BM * kCPitch;   // 69,632 B: covers the operand stage (48 KiB) and the output stage
-constexpr int kMaxDigits = 4;
-constexpr int kMaxSeg = 8;  // sources of an A operand gathered along k
-
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-
-// One dst dimension of the A map written as mixed-radix digits of its index:
-// digit j = (x / mult[j]) % ext[j] contributes digit * ss[j] source elements.
-struct Digits {
-    uint32_t n;
-    uint32_t mult[kMaxDigits], ext[kMaxDigits];
-    int32_t ss[kMaxDigits];
-    FastDiv fmult[kMaxDigits], fext[kMaxDigits];
-};
-
-// The k-steps of an operand of the 256 x 256-tile kernel as an odometer over the digits of k, so that the kernel
-// moves from one step to the next with a few scalar additions instead of decoding k: level 0 counts the
-// 64-element blocks of the contiguous lowest digit, level j >= 1 is digit j.  A step that carries into level j
-// (levels below j return to 0, level j goes up by one) moves the operand's address by dl[j] bytes.
-struct T2Steps {
-    uint32_t e[kMaxDigits - 1];   // extents of levels 0 .. 2 (the top level ends with K)
-    int64_t dl[kMaxDigits];
-};
-
-// A padded operand (Section 2.1: the load of a pad operator composed into the consumer load): the one
-// data piece covers, per dimension, index lo + sum_j i_j * mult[j] with i_j < ext[j]; an index is decoded
-// in the radices rad[j] = mult[j + 1] / mult[j] of the PADDED tensor and lies in the piece iff every
-// digit stays below the piece's extent.  Everything else reads the pad constant.
-struct PadBox {
-    uint32_t lo;
-    uint32_t rad[kMaxDigits];   // rad of the outermost digit: 0 = unbounded
-    FastDiv frad[kMaxDigits];
-};
-
-struct GemmArgs {
-    const uint16_t *A_src;
-    const uint16_t *W;
-    uint16_t *C;
-    uint32_t M, N, K;
-    uint32_t sbase;
-    uint32_t tiles_m, tiles_n;
-    uint32_t a_row_ss;  // tile256 kernel: source elements between consecutive m inside a 256-row tile
-    int64_t a_base;     // tile256 kernel: sbase in 64 bits (its tile and k-step offsets are 64-bit: operands of 2^31 elements and more)
-    uint32_t w_row_ss;  // tile256 kernel, W with runs along k (a weight kept as [N,K]): source elements between consecutive n
-    T2Steps a_steps, w_steps;   // tile256 kernel: the k-steps of A (and of a W with runs along k) as odometers over the digits of k
-    Digits dm, dk;
-    // store side (Section 2, eq. "store"): element (m, n) of the product goes to
-    // out[obase + om(m) + on(n)]; store_mapped = 0 means the plain row-major C
-    uint32_t store_mapped, obase;
-    Digits om, on;
-    // W read through a map as well: element (k, n) of W is W[wbase + wk(k) + wn(n)]
-    uint32_t wbase;
-    Digits wk, wn;
-    // A gathered from several sources, one per range of k (a concat along the reduction
-    // dimension that is never materialised): segment j covers k in [seg_kend[j-1], seg_kend[j])
-    // and reads seg_src[j] at seg_sbase[j] + seg_dm[j](m) + seg_dk[j](k - seg_kend[j-1]).
-    // n_seg <= 1: the single-source fields above are used instead.
-    // A with padding: padded = 1, the data piece's box per dimension, the pad constant (two bf16 per word)
-    uint32_t padded, pad_word;
-    PadBox pm, pk;
-    uint32_t n_seg;
-    uint32_t seg_kend[kMaxSeg];
-    uint32_t seg_sbase[kMaxSeg];
-    const uint16_t *seg_src[kMaxSeg];
-    Digits seg_dm[kMaxSeg], seg_dk[kMaxSeg];
-};
-
-// How the W operand is fetched: plain row-major [K,N]; through a map whose
-// contiguous runs lie along n (same 4 x 8 blocks, transposed in registers); or
-// through a map whose runs lie along k (a transposed weight: vectors go to LDS
-// as they are, like the A operand).
-enum WMode { W_PLAIN = 0, W_MAPPED_N = 1, W_MAPPED_K = 2 };
-
-// How the A operand is fetched: 16-byte runs of the source along k (vectors go to
-// LDS as they are), or along m (an operand kept transposed, or a channel-major
-// activation feeding a pointwise convolution: 4 k x 8 m blocks, transposed in
-// registers like the W operand whose runs lie along n).
-enum AMode { A_RUNS_K = 0, A_RUNS_M = 1 };
-
-__device__ __forceinline__ uint32_t digits_offset(const Digits &d, uint32_t x) {
-    uint32_t off = 0;
-    for (uint32_t j = 0; j < d.n; ++j) {
-        const uint32_t q = fdiv(x, d.fmult[j]);
-        const uint32_t dig = q - fdiv(q, d.fext[j]) * d.ext[j];
-        off += dig * (uint32_t)d.ss[j];
-    }
-    return off;
-}
 
 // index x of a padded dimension -> inside the data piece? and its source offset along that dimension
 __device__ __forceinline__ bool padded_offset(const Digits &d, const PadBox &b, uint32_t x, uint32_t &off) {
@@ -163,12 +71,6 @@ __device__ __forceinline__ void store_transposed(char *stage, const u32x4 *r, ui
         o.y = (j & 1) ? ((a2 >> 16) | (a3 & 0xFFFF0000u)) : ((a2 & 0xFFFFu) | (a3 << 16));
         *reinterpret_cast<u32x2 *>(stage + tile_offset(row0 + j, kq >> 1) + (kq & 1u) * 8u) = o;
     }
-}
-
-// two fp32 -> two bf16 (round to nearest even; the hardware conversion of gfx950)
-__device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
-    const f32x2 v = {lo, hi};
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
 }
 
 // Workgroup index -> output tile.  Workgroups go to the 8 XCDs round-robin;
@@ -455,28 +357,6 @@ constexpr int kT2WOff = 32768;             // W part of a stage
 constexpr int kT2Scratch = 2 * kT2Stage;   // output staging, 8 KiB per wavefront
 constexpr int kT2Lds = kT2Scratch + 32768; // 160 KiB: all of a compute unit's LDS
 
-typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) const u32x4 lds_u32x4;
-
-// all digits of one dimension, fixed trip count (unused digits have extent 1 and stride 0)
-__host__ __device__ __forceinline__ uint32_t digits_offset4(const Digits &d, uint32_t x) {
-    uint32_t off = 0;
-#if defined(__HIP_DEVICE_COMPILE__)
-#pragma unroll
-#endif
-    for (uint32_t j = 0; j < (uint32_t)kMaxDigits; ++j) {
-        const uint32_t q = fdiv(x, d.fmult[j]);
-        const uint32_t dig = q - fdiv(q, d.fext[j]) * d.ext[j];
-        off += dig * (uint32_t)d.ss[j];
-    }
-    return off;
-}
-
-// 16 bytes per lane from global memory straight into LDS: lane i lands at lds_base + 16 i
-__device__ __forceinline__ void load_to_lds16(const void *base, uint32_t byte_off, uint32_t lds_base) {
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(byte_off), "s"(base), "s"(lds_base) : "memory");
-}
-
 #define AMAP_PIN() __builtin_amdgcn_sched_barrier(0)
 
 // ---- global addressing of amap_gemm_tile256_kernel, shared with its host replay (amap_gemm_selfcheck)
@@ -556,20 +436,6 @@ __host__ inline T2Steps t2_steps_plain_w(uint32_t K, uint32_t N) {
     s.e[1] = s.e[2] = 1;
     for (int j = 0; j < kMaxDigits; ++j) s.dl[j] = 2 * (int64_t)T2K * (int64_t)N;
     return s;
-}
-// counters of levels 0 .. 2 of one operand's odometer; all 0 at the first k-step of a tile
-struct T2Odo {
-    uint32_t c0, c1, c2;
-};
-// one k-step on: the byte delta to the next step's base (not called at the last step of a tile)
-__host__ __device__ __forceinline__ int64_t t2_odo_advance(T2Odo &o, const T2Steps &s) {
-    if (++o.c0 < s.e[0]) return s.dl[0];
-    o.c0 = 0;
-    if (++o.c1 < s.e[1]) return s.dl[1];
-    o.c1 = 0;
-    if (++o.c2 < s.e[2]) return s.dl[2];
-    o.c2 = 0;
-    return s.dl[3];
 }
 // The load stream of a workgroup: its cursor, the byte offsets of the cursor's tile in both operands and of the
 // cursor's k-step inside the tile's rows, and the odometers that move the latter.
@@ -1004,7 +870,7 @@ int64_t piece_extent(const Piece &p, int dim) {
 // (1: 256 x 256 tiles, 0: the general kernel); nothing is launched and no HIP call is made.
 amap_status gemm_launch(const void *const *A_srcs, bool by_id, const amap_t *A_map, const void *W, int64_t N,
                         const amap_t *W_map, const amap_t *out_map, void *out, void *stream, GemmArgs *dry = nullptr,
-                        int *dry_kernel = nullptr) {
+                        int *dry_kernel = nullptr, RingPlan *ring = nullptr) {
     if (W_map) {
         if (W_map->shape.size() != 2) return AMAP_E_INVALID;
         N = W_map->shape[1];
@@ -1023,6 +889,7 @@ amap_status gemm_launch(const void *const *A_srcs, bool by_id, const amap_t *A_m
     bool wide = M * K >= (1ll << 31) || K * N >= (1ll << 31);
     if (out_map && M * N >= (1ll << 31)) return unsupported("product too large for a mapped store");
     const int64_t cbytes = M * N * 2;
+    int64_t largest = K * N;   // elements of the largest source
     GemmArgs g;
     std::memset(&g, 0, sizeof(g));
     // ---- the A operand: one piece, or one piece per range of k (segments, sorted by k)
@@ -1084,6 +951,7 @@ amap_status gemm_launch(const void *const *A_srcs, bool by_id, const amap_t *A_m
         if (!src || ((uintptr_t)src & 15)) return AMAP_E_INVALID;
         const int64_t svol = volume_of(A_map->src_shapes[p.src]);
         if (svol >= (1ll << 31) || p.sbase >= (1ll << 31)) wide = true;
+        largest = std::max(largest, svol);
         if (overlaps(out, cbytes, src, svol * 2)) return AMAP_E_ALIAS;
         const int64_t kext = piece_extent(p, 1);
         Digits dm, dk;
@@ -1139,6 +1007,7 @@ amap_status gemm_launch(const void *const *A_srcs, bool by_id, const amap_t *A_m
         const Piece &q = W_map->pieces[0];
         wvol = volume_of(W_map->src_shapes[q.src]);
         if (wvol >= (1ll << 31)) return unsupported("W source too large for 32-bit offsets");
+        largest = std::max(largest, wvol);
         if (!make_digits(q, 0, K, g.wk) || !make_digits(q, 1, N, g.wn)) return unsupported("the W map does not span [K,N]");
         if (vector_runs(g.wn, g.wk, q.sbase))
             wmode = W_MAPPED_N;
@@ -1187,9 +1056,27 @@ amap_status gemm_launch(const void *const *A_srcs, bool by_id, const amap_t *A_m
     const bool edge256 = M % T2M != 0 || N % T2N != 0;   // partial last tiles: the EDGE instances
     const bool w_km = wmode == W_MAPPED_K && g.wk.mult[0] == 1 && g.wk.ss[0] == 1 && g.wk.ext[0] % T2K == 0 && g.wn.mult[0] == 1 &&
                       (g.wn.ext[0] % T2N == 0 || g.wn.n == 1) && g.wn.ss[0] >= 0 && g.wn.ss[0] < (1 << 23);
-    if (tile256_on && !g.padded && amode == A_RUNS_K && segs.size() == 1 && (wmode == W_PLAIN || w_km) && K % T2K == 0 &&
-        K >= 2 * T2K && g.dm.mult[0] == 1 && (g.dm.ext[0] % T2M == 0 || g.dm.n == 1) && g.dm.ss[0] >= 0 && g.dm.ss[0] < (1 << 23) && g.dk.mult[0] == 1 &&
-        g.dk.ss[0] == 1 && g.dk.ext[0] % T2K == 0 && (!wide || !out_map)) {
+    const bool tile256 = tile256_on && !g.padded && amode == A_RUNS_K && segs.size() == 1 && (wmode == W_PLAIN || w_km) && K % T2K == 0 && K >= 2 * T2K &&
+                         g.dm.mult[0] == 1 && (g.dm.ext[0] % T2M == 0 || g.dm.n == 1) && g.dm.ss[0] >= 0 && g.dm.ss[0] < (1 << 23) && g.dk.mult[0] == 1 &&
+                         g.dk.ss[0] == 1 && g.dk.ext[0] % T2K == 0 && (!wide || !out_map);
+    // ---- smaller tiles (see amap_gemm_ring.hip): whatever the 256 x 256 tiles do not take, and what leaves too many
+    // compute units idle with them.  A lane adds up to kRingBias bytes to an offset of 32 bits.
+    if (tile256_on && !wide && largest < (1ll << 31) - 2048 && (!dry || ring)) {
+        RingPlan rp;
+        if (ring_plan(g, amode, wmode, tile256, 256, rp)) {
+            if (dry) {
+                *dry = g;
+                *ring = rp;
+                *dry_kernel = 5;
+                return AMAP_OK;
+            }
+            if (const char *tr = std::getenv("AMAP_PLAN_TRACE"); tr && tr[0] != '0')
+                std::fprintf(stderr, "amap gemm: ring, %d x %d per workgroup of %d wavefronts, %lld x %lld x %lld\n", rp.bm, rp.bn, rp.waves, (long long)M,
+                             (long long)N, (long long)K);
+            return ring_launch(rp, hs);
+        }
+    }
+    if (tile256) {
         g.w_row_ss = w_km ? (uint32_t)g.wn.ss[0] : 0u;
         g.a_steps = t2_steps_of(g.dk);
         g.w_steps = w_km ? t2_steps_of(g.wk) : t2_steps_plain_w(g.K, g.N);
@@ -1357,6 +1244,33 @@ extern "C" amap_status amap_gemm_gather(const void *const *A_srcs, const amap_t 
         if (!q.fill && (q.src < 0 || (size_t)q.src >= A_map->src_shapes.size())) return AMAP_E_INVALID;
     try {
         return gemm_launch(A_srcs, true, A_map, W_src, W_map ? 0 : N, W_map, out_map, out, stream);
+    } catch (...) {
+        return AMAP_E_NOMEM;
+    }
+}
+
+// Host replay of the addresses of amap_gemm_ring_kernel (see ring_replay) for the product amap_gemm_gather would run on
+// it; AMAP_E_UNSUPPORTED if another kernel takes the product.  A diagnostic of the library's own tests: not in amap.h.
+extern "C" amap_status amap_gemm_ring_selfcheck(const amap_t *A_map, const amap_t *W_map, int64_t N, const amap_t *out_map, int64_t *n_errors) {
+    if (!A_map || !n_errors) return AMAP_E_INVALID;
+    try {
+        GemmArgs g;
+        RingPlan rp;
+        int kernel = 0;
+        std::vector<const void *> fake(A_map->src_shapes.size() + 1, reinterpret_cast<const void *>((uintptr_t)1 << 40));
+        amap_status st = gemm_launch(fake.data(), true, A_map, reinterpret_cast<const void *>((uintptr_t)2 << 40), N, W_map, out_map,
+                                     reinterpret_cast<void *>((uintptr_t)3 << 40), nullptr, &g, &kernel, &rp);
+        if (st != AMAP_OK) return st;
+        if (kernel != 5) return unsupported("the product runs in another GEMM kernel");
+        // the sources in the order of the ranges of k
+        std::vector<std::pair<int64_t, int64_t>> segs;
+        for (const Piece &q : A_map->pieces) segs.push_back({q.lo[1], volume_of(A_map->src_shapes[(size_t)q.src]) * 2});
+        std::sort(segs.begin(), segs.end());
+        int64_t a_bytes[kMaxSeg] = {0};
+        if (segs.size() != g.n_seg) return unsupported("a source that feeds several ranges of k");
+        for (size_t j = 0; j < segs.size(); ++j) a_bytes[j] = segs[j].second;
+        *n_errors = ring_replay(rp, g, a_bytes, W_map ? volume_of(W_map->src_shapes[(size_t)W_map->pieces[0].src]) * 2 : (int64_t)g.K * g.N * 2);
+        return AMAP_OK;
     } catch (...) {
         return AMAP_E_NOMEM;
     }

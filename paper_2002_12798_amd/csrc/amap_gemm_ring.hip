@@ -1,0 +1,569 @@
+// The product of amap_gemm.hip on smaller output tiles: out[m,n] = bf16( sum_k A[m,k] * W[k,n] ), both operands read
+// through composed maps (the consumer loads of the paper's eq. 4), the product stored through one (eq. "store").
+//
+// One output tile per workgroup of 4 wavefronts (2 x 2), k in steps of BK through a ring of NST LDS stages.  Both
+// operands go from global memory straight into LDS (global_load_lds, 16 bytes per lane): no staging registers, no
+// LDS-write instructions, and because every lane brings its own address the map's digits cost nothing in the loop:
+// a lane's rows (or its 8 columns) are decoded once per tile, a k-step moves one scalar base.
+//   operand with runs along k ("K" form): stage [row][64 k], 128 bytes per row, 16-byte chunks XOR-ed with row / 2, so
+//     that the 16 rows an LDS read serves together cover all banks;
+//   operand with runs along m or n ("X" form: a channel-major activation, a row-major weight): stage [k][x], read with
+//     the transposing LDS read (ds_read_b64_tr_b16), which hands every lane four consecutive k of one x; chunks XOR-ed
+//     so that the four k rows of such a read lie in different banks.
+// A step waits for its own loads only (vmcnt counts the loads of the NST - 2 later steps that may stay in flight),
+// passes one barrier, issues the loads of step s + NST - 1 into the stage that step s - 1 has just left, and computes.
+#include "amap_gemm_ring.hpp"
+
+#include <algorithm>
+#include <cstring>
+#include <type_traits>
+#include <vector>
+
+using namespace amap_dev;
+using namespace amap_detail;
+using namespace amap_gemm;
+
+namespace {
+
+// the part of the argument block in front of the epilogue's tables and of the second source of a gathered A
+constexpr uint32_t kRingArgTouch = sizeof(RingArgs<1>);
+
+// wait until the loads of all but the `later` newest steps (L loads each per wavefront) have landed, then meet the
+// other wavefronts; the compiler does not know of these loads.  (lgkmcnt: this wavefront's reads of the stage that is
+// refilled next are done.)
+template <int N>
+__device__ __forceinline__ void ring_wait() {
+    static_assert(N < 64, "vmcnt");
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"i"(N) : "memory");
+}
+template <int L, int R>
+__device__ __forceinline__ void ring_wait_step(uint32_t later) {
+    if constexpr (R == 0) {
+        ring_wait<0>();
+    } else {
+        if (later >= (uint32_t)R)
+            ring_wait<R * L>();
+        else
+            ring_wait_step<L, R - 1>(later);
+    }
+}
+
+// Load blocks j = 0 .. N - 1 of a wavefront: lane i's 16 bytes of block j land at lds + 1024 j + 16 i.  The instruction's
+// offset counts on both sides, so one write of M0 serves four blocks (ring_block_offset takes it off the address).
+template <int N>
+__device__ __forceinline__ void ring_load(const char *base, const uint32_t (&off)[N], uint32_t lds) {
+#pragma unroll
+    for (int j = 0; j < N; j += 4) {
+        const uint32_t at = lds + 1024u * j;
+        if (j + 4 <= N)
+            asm volatile(
+                "s_mov_b32 m0, %5\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %4\n\tglobal_load_lds_dwordx4 %1, %4 offset:1024\n\t"
+                "global_load_lds_dwordx4 %2, %4 offset:2048\n\tglobal_load_lds_dwordx4 %3, %4 offset:3072" ::"v"(off[j]),
+                "v"(off[j + 1 < N ? j + 1 : 0]), "v"(off[j + 2 < N ? j + 2 : 0]), "v"(off[j + 3 < N ? j + 3 : 0]), "s"(base), "s"(at)
+                : "memory");
+        else if (j + 2 <= N)
+            asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %2\n\tglobal_load_lds_dwordx4 %1, %2 offset:1024" ::"v"(off[j]),
+                         "v"(off[j + 1 < N ? j + 1 : 0]), "s"(base), "s"(at)
+                         : "memory");
+        else
+            load_to_lds16(base, off[j], at);
+    }
+}
+
+template <class T>
+__global__ __launch_bounds__(64 * T::WVM * T::WVN, T::OCC) void amap_gemm_ring_kernel(const RingArgs<T::NSEG> g) {
+    constexpr int BM = T::BM, BN = T::BN, BK = T::BK, NST = T::NST;
+    constexpr int kWaves = T::WVM * T::WVN, kThreads = 64 * kWaves;
+    constexpr int XM = BM / T::WVM, XN = BN / T::WVN;         // a wavefront's part of the tile
+    constexpr bool AX = T::AX, WX = T::WX;
+    constexpr uint32_t kABytes = BM * BK * 2, kWBytes = BN * BK * 2, kStage = kABytes + kWBytes;
+    constexpr int NA = kABytes / (1024 * kWaves), NW = kWBytes / (1024 * kWaves);   // loads per wavefront and step
+    constexpr int FM = XM / 32, FN = XN / 32;                 // 32 x 32 tiles per wavefront
+    {
+        // every 64-byte line of the argument block that the prologue reads, fetched side by side: read where they are
+        // needed, the digit tables are one scalar-cache miss after the other in front of the first load
+        const uint32_t *const arg = reinterpret_cast<const uint32_t *>(&g);
+        uint32_t x = 0;
+#pragma unroll
+        for (uint32_t at = 0; at < kRingArgTouch / 4; at += 16) x |= arg[at];
+        asm volatile("" ::"s"(x));
+    }
+    const uint32_t tid = threadIdx.x, lane = tid & 63u;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint32_t wm = wave / T::WVN, wn = wave % T::WVN;
+    uint32_t tm, tn;
+    ring_tile(g.map, blockIdx.x, gridDim.x, tm, tn);
+    const uint32_t m0 = tm * BM, n0 = tn * BN;
+
+    // ---- per-lane byte offsets of this wavefront's load blocks, and the scalar bases they are added to
+    static_assert((NA % 4 == 0 || NA == 1 || NA == 2) && (NW % 4 == 0 || NW == 1 || NW == 2), "ring_load");
+    uint32_t a_off[NA], w_off[NW];
+#pragma unroll
+    for (int j = 0; j < NA; ++j) a_off[j] = ring_block_offset<AX, BM>(g.a[0].dx, g.a[0].base, g.a[0].kss, m0, g.M, wave * NA, j, lane);
+#pragma unroll
+    for (int j = 0; j < NW; ++j) w_off[j] = ring_block_offset<WX, BN>(g.w.dx, g.w.base, g.w.kss, n0, g.N, wave * NW, j, lane);
+    const char *ka = reinterpret_cast<const char *>(g.a[0].src) - kRingBias, *kw = reinterpret_cast<const char *>(g.w.src) - kRingBias;
+    RingWalk a_walk = ring_walk_begin(g.a_steps), w_walk = ring_walk_begin(g.w_steps);
+    uint32_t seg = 0, seg_left = g.a[0].steps;   // NSEG > 1: the source the stream reads, and its k-steps to go
+    int64_t seg_step = 2 * (int64_t)g.a[0].kss * BK;
+    uint32_t ld_k = 0;
+    const uint32_t lds_a = __builtin_amdgcn_readfirstlane(wave * (NA * 1024u)), lds_w = __builtin_amdgcn_readfirstlane(kABytes + wave * (NW * 1024u));
+    auto issue = [&](uint32_t stage) __attribute__((always_inline)) {
+        if constexpr (T::NSEG > 1) {
+            if (seg_left == 0) {   // the next source of a gathered A: its own rows, strides and pointer
+                ++seg;
+                const RingOperand &s = g.a[seg];
+                seg_left = s.steps;
+                seg_step = 2 * (int64_t)s.kss * BK;
+                ka = reinterpret_cast<const char *>(s.src) - kRingBias;
+#pragma unroll
+                for (int j = 0; j < NA; ++j) a_off[j] = ring_block_offset<AX, BM>(s.dx, s.base, s.kss, m0, g.M, wave * NA, j, lane);
+            }
+        }
+        if constexpr (T::KLANE) {   // runs of A shorter than a step: k decoded per lane, for the two chunk orders of its blocks
+            uint32_t kl[2], off[NA];
+#pragma unroll
+            for (uint32_t par = 0; par < 2; ++par) {
+                const uint32_t c8 = 8u * ring_k_chunk(wave * NA + par, lane);
+                kl[par] = 2u * (digits_offset4(g.a_dk, ld_k + c8) - c8);
+            }
+#pragma unroll
+            for (int j = 0; j < NA; ++j) off[j] = a_off[j] + kl[j & 1];
+            ring_load<NA>(ka, off, lds_a + stage);
+            ld_k += BK;
+        } else {
+            ring_load<NA>(ka, a_off, lds_a + stage);
+        }
+        ring_load<NW>(kw, w_off, lds_w + stage);
+        if constexpr (T::NSEG > 1) {
+            --seg_left;
+            ka += seg_step;
+        } else if constexpr (!T::KLANE) {
+            ka += ring_walk_next(a_walk, g.a_steps);
+        }
+        kw += ring_walk_next(w_walk, g.w_steps);
+    };
+
+    // ---- fragment addresses.  What does not depend on the stage is kept per lane, the stage and the fragment go into
+    // the instruction's offset: K form, one address per sub-step; X form, one per fragment
+    constexpr int kSub = BK / 16;
+    uint32_t a_frag[AX ? FM : kSub], w_frag[WX ? FN : kSub];
+#pragma unroll
+    for (int i = 0; i < (AX ? FM : kSub); ++i) a_frag[i] = AX ? ring_x_frag<BM>(lane, wm * XM, i, 0, 0) : ring_k_frag(lane, wm * XM, 0, i);
+#pragma unroll
+    for (int i = 0; i < (WX ? FN : kSub); ++i) w_frag[i] = kABytes + (WX ? ring_x_frag<BN>(lane, wn * XN, i, 0, 0) : ring_k_frag(lane, wn * XN, 0, i));
+    auto read_frag = [&](auto x_form, auto bx, const auto &addr, uint32_t stage, uint32_t f, uint32_t kk) __attribute__((always_inline)) -> bf16x8 {
+        if constexpr (!x_form.value) {
+            return __builtin_bit_cast(bf16x8, *reinterpret_cast<lds_u32x4 *>(addr[kk] + (stage + f * 4096u)));
+        } else {
+            typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
+            constexpr uint32_t kRow = 2u * bx.value;   // bytes per k
+            const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(reinterpret_cast<lds_bf16x4 *>(addr[f] + (stage + kk * 16u * kRow)));
+            const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(reinterpret_cast<lds_bf16x4 *>(addr[f] + (stage + (kk * 16u + 4u) * kRow)));
+            return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+        }
+    };
+    using std::integral_constant;
+    constexpr integral_constant<bool, AX> ax{};
+    constexpr integral_constant<bool, WX> wx{};
+    constexpr integral_constant<int, BM> bm{};
+    constexpr integral_constant<int, BN> bn{};
+
+    f32x16 acc[FM][FN];
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+    // Two sets of fragments, PK sub-steps of 16 k each: one is read while the other feeds the matrix cores.
+    constexpr int PK = T::PK, kPhases = kSub / PK, L = NA + NW;
+    static_assert(kSub % PK == 0 && (kPhases % 2 == 0 || (kPhases == 1 && NST % 2 == 0)), "the fragment sets alternate");
+    bf16x8 fa[2][PK][FM], fw[2][PK][FN];
+    auto read_one = [&](uint32_t set, uint32_t stage, uint32_t ph, int r) __attribute__((always_inline)) {
+        if (r >= PK * (FM + FN)) return;
+        const uint32_t kk = (uint32_t)(r / (FM + FN)), f = (uint32_t)(r % (FM + FN));
+        if (f < (uint32_t)FM)
+            fa[set][kk][f] = read_frag(ax, bm, a_frag, stage, f, ph * PK + kk);
+        else
+            fw[set][kk][f - FM] = read_frag(wx, bn, w_frag, stage, f - FM, ph * PK + kk);
+    };
+    // the MFMAs of one phase on fragment set `set`, the reads of the next phase (ph of `stage`) spread under them
+    auto phase = [&](uint32_t set, uint32_t stage, uint32_t ph) __attribute__((always_inline)) {
+        constexpr int kMf = PK * FM * FN, kRd = PK * (FM + FN), kPer = (kRd + kMf - 1) / kMf;
+#pragma unroll
+        for (int q = 0; q < kMf; ++q) {
+#pragma unroll
+            for (int r = 0; r < kPer; ++r) read_one(set ^ 1u, stage, ph, q * kPer + r);
+            const int kk = q / (FM * FN), i = q / FN % FM, j = q % FN;
+            // W as the row operand: the 32 x 32 result is C^T, a lane holds four consecutive n of one row m
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fw[set][kk][j], fa[set][kk][i], acc[i][j], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+
+    const uint32_t steps = g.steps;
+#pragma unroll
+    for (int s = 0; s < NST; ++s)
+        if ((uint32_t)s < steps) issue((uint32_t)s * kStage);
+    ring_wait_step<L, NST - 1>(steps - 1u);
+#pragma unroll
+    for (int r = 0; r < PK * (FM + FN); ++r) read_one(0, 0, 0, r);
+    // the ring once around per pass: stages and fragment sets are constants, a read is one instruction
+    uint32_t left = steps - 1u;
+    for (;;) {
+        bool done = false;
+#pragma unroll
+        for (int st = 0; st < NST; ++st) {
+            if (done) break;
+            const uint32_t cur = st * kStage, next = (st + 1) % NST * kStage, set0 = kPhases == 1 ? st & 1 : 0;
+#pragma unroll
+            for (int ph = 0; ph + 1 < kPhases; ++ph) phase(set0 ^ (ph & 1u), cur, ph + 1);
+            // the last fragments of this step are read: its stage is free once every wavefront is here, and the next step's
+            // loads (all but those of up to NST - 2 later steps) have landed
+            if (left) ring_wait_step<L, NST - 2>(left - 1u);
+            if (left >= (uint32_t)NST) issue(cur);
+            __builtin_amdgcn_sched_barrier(0);
+            phase(set0 ^ ((kPhases - 1) & 1u), next, 0);   // (after the last step: a stale stage, read and unused)
+            if (left-- == 0) done = true;
+        }
+        if (done) break;
+    }
+
+    // ---- epilogue: the tile rounded to bf16 in LDS (the ring is free once every wavefront has passed), then whole rows
+    // of 16-byte stores.  Accumulator v of a 32 x 32 tile in lane l: m = l % 32, n = 8 (v / 4) + 4 (l / 32) + v % 4.
+    __syncthreads();
+    const uint32_t row_l = lane & 31u, half = lane >> 5;
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                u32x2 o;
+                o.x = pack_bf16(acc[i][j][4 * q], acc[i][j][4 * q + 1]);
+                o.y = pack_bf16(acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
+                const uint32_t row = wm * XM + 32u * i + row_l, chunk = wn * (XN / 8) + 4u * j + q;
+                *reinterpret_cast<__attribute__((address_space(3))) u32x2 *>(ring_c_slot<BN>(row, chunk) + ((half ^ ((row >> 4) & 1u)) << 3)) = o;
+            }
+    __syncthreads();
+    constexpr uint32_t kCv = BN / 8;   // 16-byte chunks per row
+    const uint32_t cv = tid % kCv, n = n0 + cv * 8u;
+    const bool n_ok = n < g.N;
+    const uint32_t n_off = g.store_mapped ? g.obase + digits_offset4(g.on, n_ok ? n : 0u) : n;
+#pragma unroll
+    for (uint32_t p = 0; p < BM * kCv / kThreads; ++p) {
+        const uint32_t row = p * (kThreads / kCv) + tid / kCv, m = m0 + row;
+        u32x4 x = *reinterpret_cast<lds_u32x4 *>(ring_c_slot<BN>(row, cv));
+        if ((row >> 4) & 1u) x = u32x4{x.z, x.w, x.x, x.y};
+        if (m < g.M && n_ok) {
+            const size_t off = g.store_mapped ? (size_t)(n_off + digits_offset4(g.om, m)) : (size_t)m * g.N + n_off;
+            __builtin_nontemporal_store(x, reinterpret_cast<u32x4 *>(g.C + off));
+        }
+    }
+}
+
+template <class T>
+amap_status launch(const RingArgs<kMaxSeg> &full, uint32_t grid, hipStream_t stream) {
+    constexpr int kRing = T::NST * (T::BM + T::BN) * T::BK * 2, kTile = T::BM * T::BN * 2, lds = kRing > kTile ? kRing : kTile;
+    static_assert(lds <= 65536, "what a launch may ask for without an attribute; read offsets are 16 bits as well");
+    RingArgs<T::NSEG> g;
+    static_cast<RingCommon &>(g) = full;
+    for (int i = 0; i < T::NSEG; ++i) g.a[i] = full.a[i];
+    (void)hipGetLastError();   // an earlier, unrelated error on this thread is not this launch's
+    hipLaunchKernelGGL(amap_gemm_ring_kernel<T>, dim3(grid), dim3(64 * T::WVM * T::WVN), lds, stream, g);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) {
+        set_last_error("amap_gemm_ring_kernel", hipGetErrorString(e));
+        return AMAP_E_HIP;
+    }
+    return AMAP_OK;
+}
+
+template <int BM_, int BN_, int BK_, int NST_, int PK_, int WVM_, int WVN_, int OCC_, bool AX_, bool WX_, int NSEG_, bool KLANE_>
+struct Shape {
+    static constexpr int BM = BM_, BN = BN_, BK = BK_, NST = NST_, PK = PK_, WVM = WVM_, WVN = WVN_, OCC = OCC_, NSEG = NSEG_;
+    static constexpr bool AX = AX_, WX = WX_, KLANE = KLANE_;
+};
+
+}  // namespace
+
+namespace amap_gemm {
+
+// k-steps of bk elements over the digits of k; false if a step could straddle two digits
+static bool ring_steps(const Digits &d, uint32_t bk, T2Steps &s) {
+    if (d.n == 0 || d.mult[0] != 1 || (d.n > 1 && d.ext[0] % bk)) return false;
+    const int64_t st[kMaxDigits] = {(int64_t)bk * d.ss[0], d.ss[1], d.ss[2], d.ss[3]};
+    const uint32_t e[kMaxDigits] = {(d.ext[0] + bk - 1) / bk, d.ext[1], d.ext[2], d.ext[3]};
+    int64_t back = 0;   // from the last step of the levels below to their first one
+    int at = 0;         // levels of one step (runs of exactly bk) are left out: the walk carries where it must only
+    for (int j = 0; j < kMaxDigits; ++j) {
+        if (e[j] == 1u && j + 1 < kMaxDigits) continue;
+        s.dl[at] = 2 * (st[j] - back);
+        back += (int64_t)(e[j] - 1u) * st[j];
+        if (at + 1 < kMaxDigits) s.e[at] = j + 1 < kMaxDigits ? e[j] : 0xFFFFFFFFu;
+        ++at;
+    }
+    for (; at < kMaxDigits; ++at) {
+        s.dl[at] = 0;
+        if (at + 1 < kMaxDigits) s.e[at] = 0xFFFFFFFFu;
+    }
+    return true;
+}
+
+static Digits one_digit(uint32_t ext, int32_t ss) {
+    Digits d;
+    std::memset(&d, 0, sizeof(d));
+    d.n = 1;
+    for (int j = 0; j < kMaxDigits; ++j) {
+        d.mult[j] = 1;
+        d.ext[j] = j ? 1u : ext;
+        d.ss[j] = j ? 0 : ss;
+        d.fmult[j] = make_fastdiv(1);
+        d.fext[j] = make_fastdiv(d.ext[j]);
+    }
+    return d;
+}
+
+// Time of a product on one of the kernel shapes, in us: `fixed` for the launch, the first loads and the last stores, then
+// every compute unit works its share of the tiles off, `step` us per tile and 64 k plus `tile` us per tile.  Fitted to
+// measurements with K = 256 .. 2560 and 1 .. 32 tiles per compute unit (for instance 128 x 128 tiles, K = 1024: 256 tiles
+// 13.9 us, 512 21.2, 1024 38.5, 2048 71.6; 64 x 64 tiles: 512 9.8, 1024 16.9, 2048 27.7).
+static double estimate(uint64_t tiles, double k64, uint32_t n_cu, double step, double tile) {
+    const double q = (double)tiles / n_cu, up = (double)((tiles + n_cu - 1) / n_cu);
+    // up to two tiles share a compute unit, so a few more tiles than units cost less than a second round
+    const double rounds = q <= 2.0 ? 0.5 * (std::max(q, 1.0) + up) : up;
+    return 4.0 + rounds * (step * k64 + tile);
+}
+
+bool ring_plan(const GemmArgs &g, int amode, int wmode, bool tile256, uint32_t n_cu, RingPlan &p) {
+    if (g.padded || g.n_seg > (uint32_t)kMaxSeg) return false;
+    p.ax = amode == A_RUNS_M;
+    p.wx = wmode != W_MAPPED_K;
+    p.klane = false;
+    p.n_seg = (int)g.n_seg;
+    // k in steps of 64 where a run along k is a 128-byte row of the stage; of 32 (more workgroups per compute unit: 39.8
+    // against 42.8 us on a pointwise convolution [100352,256] x [256,512], 30.7 against 44.8 us gathered from four
+    // sources) where both operands have theirs along m and n
+    const uint32_t bk = p.ax && p.wx ? 32 : 64;
+    if (g.K % bk) return false;
+    std::memset(&p.args, 0, sizeof(p.args));
+    RingArgs<kMaxSeg> &r = p.args;
+    r.C = g.C;
+    r.M = g.M;
+    r.N = g.N;
+    r.steps = g.K / bk;
+    if (g.n_seg > 1) {
+        for (uint32_t j = 0; j < g.n_seg; ++j) {
+            const uint32_t len = g.seg_kend[j] - (j ? g.seg_kend[j - 1] : 0u);
+            if (g.seg_dk[j].n != 1 || len % bk) return false;
+            r.a[j] = RingOperand{g.seg_src[j], g.seg_sbase[j], len / bk, g.seg_dk[j].ss[0], g.seg_dm[j]};
+        }
+    } else {
+        r.a[0] = RingOperand{g.A_src, g.sbase, r.steps, g.dk.ss[0], g.dm};
+        if (!ring_steps(g.dk, bk, r.a_steps)) {
+            if (p.ax) return false;
+            p.klane = true;
+            r.a_dk = g.dk;
+        }
+    }
+    if (wmode == W_PLAIN) {
+        r.w = RingOperand{g.W, 0, r.steps, (int32_t)g.N, one_digit(g.N, 1)};
+        ring_steps(one_digit(g.K, (int32_t)g.N), bk, r.w_steps);
+    } else {
+        r.w = RingOperand{g.W, g.wbase, r.steps, g.wk.ss[0], g.wn};
+        if (!ring_steps(g.wk, bk, r.w_steps)) return false;
+    }
+    r.store_mapped = g.store_mapped;
+    r.obase = g.obase;
+    r.om = g.om;
+    r.on = g.on;
+
+    // ---- the tile
+    auto tiles = [&](uint64_t t) { return ((g.M + t - 1) / t) * ((g.N + t - 1) / t); };
+    const double k64 = g.K / 64.0;
+    const double t128 = estimate(tiles(128), k64, n_cu, 0.47, 1.4), t64 = estimate(tiles(64), k64, n_cu, 0.19, 0.35);
+    // gathered sources and operands along m: 128 x 128 only (64 x 64 tiles: 51.7 against 39.8 us on the convolution above,
+    // level with it on small images)
+    const bool small = !p.ax && g.n_seg == 1 && t64 < t128;
+    if (tile256) {
+        // The 256 x 256-tile kernel takes the product as well, and is ahead where its tiles fill the chip a whole number of
+        // times (K = 1024: 256 tiles 34.0 against 38.5 us, 512 tiles 64.8 against 71.6 us; 144 tiles of K = 768 22.8
+        // against 25.1 us) and behind it where they leave units idle (8 tiles 23.7 against 8.2 us, 128 tiles 25.1 against
+        // 19.9 us, 288 tiles of K = 768 42.3 against 39.0 us).  Up to 16 tiles of up to six k-steps stay there too: those are
+        // the shapes by which its tests reach every edge of it (about 13 against 10 us).
+        const uint64_t n256 = tiles(256), rounds = (n256 + n_cu - 1) / n_cu;
+        if (n256 <= 16 && g.K <= 384) return false;
+        const double step256 = 0.85 + 0.8 * (double)n256 / (double)(rounds * n_cu);   // the busier the chip, the lower its clock
+        const double t256 = 7.5 + (double)rounds * k64 * step256 + 3.0 * (double)(rounds - 1);
+        if (std::min(t64, t128) > 0.95 * t256) return false;
+    }
+    p.bm = p.bn = small ? 64 : 128;
+    // 8 wavefronts per 128 x 128 tile while at most two workgroups share a compute unit (288 tiles of K = 768: 13.7 against
+    // 15.1 us, 512 of K = 1024 19.8 against 21.2 us), 4 beyond (1000 tiles of K = 640: 53.9 against 61.1 us)
+    p.waves = !small && !p.ax && g.n_seg == 1 && tiles(128) <= 2ull * n_cu ? 8 : 4;
+    r.map.tiles_m = (uint32_t)((g.M + p.bm - 1) / p.bm);
+    r.map.tiles_n = (uint32_t)((g.N + p.bn - 1) / p.bn);
+    if ((uint64_t)r.map.tiles_m * r.map.tiles_n >= (1ull << 31)) return false;
+    // bands of 8 tile rows: the 32 or so tiles an XCD works on at a time are then a compact block (4 or 32 rows: 0 .. 4 % slower)
+    r.map.group = std::min<uint32_t>(8, r.map.tiles_m);
+    if ((uint64_t)r.map.group * r.map.tiles_n >= (1ull << 31)) return false;
+    r.map.f_band = make_fastdiv(r.map.group * r.map.tiles_n);
+    r.map.f_group = make_fastdiv(r.map.group);
+    const uint32_t last = r.map.tiles_m % r.map.group;
+    r.map.f_last = make_fastdiv(last ? last : r.map.group);
+    return true;
+}
+
+namespace {
+// the kernel shapes that exist, each handed to f as a type
+template <bool AX, bool WX, int NSEG, bool KLANE, class F>
+void with_tile(const RingPlan &p, F f) {
+    if constexpr (AX && WX) {
+        f(Shape<128, 128, 32, 2, 1, 2, 2, 4, true, true, NSEG, false>());
+    } else if constexpr (AX || NSEG > 1) {
+        f(Shape<128, 128, 64, 2, 1, 2, 2, 2, AX, WX, NSEG, false>());
+    } else {
+        if (p.bm == 64)
+            f(Shape<64, 64, 64, 3, 2, 2, 2, 3, false, WX, 1, KLANE>());
+        else if (p.waves == 8)
+            f(Shape<128, 128, 64, 2, 2, 2, 4, 4, false, WX, 1, KLANE>());
+        else
+            f(Shape<128, 128, 64, 2, 1, 2, 2, 2, false, WX, 1, KLANE>());
+    }
+}
+template <bool AX, bool WX, class F>
+void with_sources(const RingPlan &p, F f) {
+    if (p.n_seg > 1)
+        with_tile<AX, WX, kMaxSeg, false>(p, f);
+    else if (p.klane)
+        with_tile<AX, WX, 1, !AX>(p, f);
+    else
+        with_tile<AX, WX, 1, false>(p, f);
+}
+template <class F>
+void with_shape(const RingPlan &p, F f) {
+    if (p.ax && p.wx)
+        with_sources<true, true>(p, f);
+    else if (p.ax)
+        with_sources<true, false>(p, f);
+    else if (p.wx)
+        with_sources<false, true>(p, f);
+    else
+        with_sources<false, false>(p, f);
+}
+
+// every load, fragment read and store of one kernel shape, with the kernel's own address functions
+template <class T>
+int64_t replay(const RingArgs<kMaxSeg> &r, const GemmArgs &g, const int64_t *a_bytes, int64_t w_bytes) {
+    constexpr int BM = T::BM, BN = T::BN, BK = T::BK, kWaves = T::WVM * T::WVN, XM = BM / T::WVM, XN = BN / T::WVN;
+    constexpr uint32_t NA = BM * BK * 2 / (1024 * kWaves), NW = BN * BK * 2 / (1024 * kWaves);
+    int64_t errors = 0;
+    const uint32_t grid = r.map.tiles_m * r.map.tiles_n;
+    std::vector<uint8_t> written((size_t)g.M * g.N / 8, 0), seen(grid, 0);
+    std::vector<int64_t> lds_a(BM * BK / 8), lds_w(BN * BK / 8);   // source element of every 16-byte slot of a stage
+    for (uint32_t b = 0; b < grid; ++b) {
+        uint32_t tm, tn;
+        ring_tile(r.map, b, grid, tm, tn);
+        if (tm >= r.map.tiles_m || tn >= r.map.tiles_n || seen[tm * r.map.tiles_n + tn]++) {
+            ++errors;
+            continue;
+        }
+        const uint32_t m0 = tm * BM, n0 = tn * BN;
+        int64_t ka = 0, kw = 0;
+        RingWalk ao = ring_walk_begin(r.a_steps), wo = ring_walk_begin(r.w_steps);
+        uint32_t seg = 0, left = r.a[0].steps, seg_k0 = 0;
+        for (uint32_t s = 0; s < r.steps; ++s) {
+            if (T::NSEG > 1 && left == 0) {
+                seg_k0 += r.a[seg].steps * BK;
+                ++seg;
+                left = r.a[seg].steps;
+                ka = 0;
+            }
+            const RingOperand &A = r.a[seg];
+            for (uint32_t wave = 0; wave < (uint32_t)kWaves; ++wave)
+                for (uint32_t lane = 0; lane < 64; ++lane) {
+                                        for (uint32_t j = 0; j < NA; ++j) {
+                        const uint32_t b1 = wave * NA + j, c8 = 8u * ring_k_chunk(wave * NA + (j & 1u), lane);
+                        const uint32_t kl = T::KLANE ? 2u * (digits_offset4(r.a_dk, s * BK + c8) - c8) : 0u;
+                        const uint32_t off = ring_block_offset<T::AX, BM>(A.dx, A.base, A.kss, m0, r.M, wave * NA, j, lane) + kl;
+                        const int64_t at = ka - (int64_t)kRingBias + (int64_t)off + 1024 * (int64_t)(j % 4u);   // (the instruction's offset)
+                        if (at < 0 || at + 16 > a_bytes[seg] || at % 16) ++errors;
+                        lds_a[b1 * 64 + lane] = at / 2;
+                    }
+                    for (uint32_t j = 0; j < NW; ++j) {
+                        const uint32_t b1 = wave * NW + j;
+                        const uint32_t off = ring_block_offset<T::WX, BN>(r.w.dx, r.w.base, r.w.kss, n0, r.N, wave * NW, j, lane);
+                        const int64_t at = kw - (int64_t)kRingBias + (int64_t)off + 1024 * (int64_t)(j % 4u);
+                        if (at < 0 || at + 16 > w_bytes || at % 16) ++errors;
+                        lds_w[b1 * 64 + lane] = at / 2;
+                    }
+                }
+            --left;
+            if (T::NSEG > 1)
+                ka += 2 * (int64_t)A.kss * BK;
+            else if (!T::KLANE)
+                ka += ring_walk_next(ao, r.a_steps);
+            kw += ring_walk_next(wo, r.w_steps);
+            // the element the map wants at (m, k) / (k, n)
+            auto want_a = [&](uint32_t m, uint32_t k) -> int64_t {
+                if (g.n_seg > 1) return (int64_t)(uint32_t)(g.seg_sbase[seg] + digits_offset4(g.seg_dm[seg], m) + digits_offset4(g.seg_dk[seg], k - seg_k0));
+                return (int64_t)(uint32_t)(g.sbase + digits_offset4(g.dm, m) + digits_offset4(g.dk, k));
+            };
+            auto want_w = [&](uint32_t k, uint32_t n) -> int64_t {
+                if (g.wn.n == 0) return (int64_t)k * g.N + n;   // plain row-major
+                return (int64_t)(uint32_t)(g.wbase + digits_offset4(g.wk, k) + digits_offset4(g.wn, n));
+            };
+            for (uint32_t w2 = 0; w2 < (uint32_t)std::max(T::WVM, T::WVN); ++w2)
+                for (uint32_t kk = 0; kk < BK / 16; ++kk)
+                    for (uint32_t lane = 0; lane < 64; ++lane) {
+                        const uint32_t gq = lane >> 4, sq = lane & 15u;
+                        auto check = [&](bool x_form, uint32_t k_addr, const uint32_t *x_addr, const std::vector<int64_t> &lds, uint32_t x0, uint32_t x_lim, auto want) {
+                            if (!x_form) {
+                                const uint32_t x = x0 + (lane & 31u);
+                                if (x < x_lim && lds[k_addr / 16] != want(x, s * BK + 16 * kk + 8 * (lane >> 5))) ++errors;
+                                return;
+                            }
+                            for (uint32_t hi = 0; hi < 2; ++hi) {
+                                const uint32_t x = x0 + 16 * (gq & 1u) + 4 * (sq & 3u), k = s * BK + 16 * kk + 8 * (gq >> 1) + (sq >> 2) + 4 * hi;
+                                if (x < x_lim && lds[x_addr[hi] / 16] + (x_addr[hi] % 16) / 2 != want(x, k)) ++errors;
+                            }
+                        };
+                        for (uint32_t f = 0; w2 < (uint32_t)T::WVM && f < XM / 32; ++f) {
+                            const uint32_t xb = w2 * XM, xa[2] = {ring_x_frag<BM>(lane, xb, f, kk, 0), ring_x_frag<BM>(lane, xb, f, kk, 1)};
+                            check(T::AX, ring_k_frag(lane, xb, f, kk), xa, lds_a, m0 + xb + 32 * f, r.M, want_a);
+                        }
+                        for (uint32_t f = 0; w2 < (uint32_t)T::WVN && f < XN / 32; ++f) {
+                            const uint32_t xb = w2 * XN, xa[2] = {ring_x_frag<BN>(lane, xb, f, kk, 0), ring_x_frag<BN>(lane, xb, f, kk, 1)};
+                            check(T::WX, ring_k_frag(lane, xb, f, kk), xa, lds_w, n0 + xb + 32 * f, r.N, [&](uint32_t n, uint32_t k) { return want_w(k, n); });
+                        }
+                    }
+        }
+        for (uint32_t row = 0; row < BM; ++row)
+            for (uint32_t cv = 0; cv < BN / 8; ++cv) {
+                const uint32_t m = m0 + row, n = n0 + 8 * cv;
+                if (m >= r.M || n >= r.N) continue;
+                const int64_t off = r.store_mapped ? (int64_t)(uint32_t)(r.obase + digits_offset4(r.on, n) + digits_offset4(r.om, m)) : (int64_t)m * r.N + n;
+                if (off % 8 || off < 0 || off + 8 > (int64_t)g.M * g.N || written[(size_t)off / 8]++) ++errors;
+            }
+    }
+    for (uint8_t w : written)
+        if (w != 1) ++errors;
+    return errors;
+}
+}  // namespace
+
+amap_status ring_launch(const RingPlan &p, hipStream_t stream) {
+    const uint32_t grid = p.args.map.tiles_m * p.args.map.tiles_n;
+    amap_status st = AMAP_E_HIP;
+    with_shape(p, [&](auto shape) { st = launch<decltype(shape)>(p.args, grid, stream); });
+    return st;
+}
+
+int64_t ring_replay(const RingPlan &p, const GemmArgs &g, const int64_t *a_bytes, int64_t w_bytes) {
+    int64_t errors = -1;
+    with_shape(p, [&](auto shape) { errors = replay<decltype(shape)>(p.args, g, a_bytes, w_bytes); });
+    return errors;
+}
+
+}  // namespace amap_gemm

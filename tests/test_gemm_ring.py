@@ -1,0 +1,157 @@
+"""The GEMM kernel on smaller tiles (amap_gemm_ring.hip).  On the CPU: the host replay of every form it takes (runs of A
+along k or m, whole or shorter than a k-step, gathered sources, both weight forms, a mapped store) walks every load, every
+LDS read and every store with the kernel's own address functions.  On the GPU: bit for bit against the general kernel,
+which adds the same products in the same order, and against the oracle."""
+import ctypes as C
+
+import numpy as np
+import pytest
+
+from oracle import oracle
+from paper_2002_12798_amd import binding as B
+from paper_2002_12798_amd import synth
+
+
+def _replay(a, n, w=None, out_map=None):
+    f = B.raw.amap_gemm_ring_selfcheck
+    f.argtypes = [C.c_void_p, C.c_void_p, C.c_int64, C.c_void_p, C.POINTER(C.c_int64)]
+    errors = C.c_int64(-1)
+    st = f(a.handle, w.handle if w else None, n, out_map.handle if out_map else None, C.byref(errors))
+    return st, errors.value
+
+
+def merge(b, h, s, d):
+    """The heads of [b,h,s,d] as the matrix of their rows."""
+    return [(b, h, s, d)], [("transpose", (0, 2, 1, 3)), ("reshape", (b * s, h * d))]
+
+
+def conv(b, channels, size):
+    """[b,c,size,size] branches as the [b*size*size, sum c] matrix of a pointwise convolution."""
+    join = [("concat", 1)] if len(channels) > 1 else []
+    return ([(b, c, size, size) for c in channels],
+            join + [("transpose", (0, 2, 3, 1)), ("reshape", (b * size * size, sum(channels)))])
+
+
+FORMS = [
+    # (source shapes, chain -> [M,K]), N: every kernel shape, tile edges, remainders, one k-step, many k-steps
+    (merge(1, 7, 64, 64), 64),                                       # 64 x 64 tiles, exactly one
+    (merge(1, 16, 70, 64), 120),                                     # partial tiles in M and N
+    (merge(3, 8, 33, 80), 136),                                      # runs of 80 (k decoded per lane), blocks of 33 rows
+    (merge(2, 8, 50, 32), 72),                                       # runs of 32
+    (([(1, 64)], []), 8),                                            # one row, one k-step, one vector of n
+    (([(133, 640)], [("slice", 0, 5, 133, 1), ("slice", 1, 64, 640, 1)]), 200),   # base offset, rows longer than K
+    (([(700, 448)], [("slice", 0, 699, -1, -1)]), 264),              # rows walked backwards
+    (([(64, 448)], [("repeat", 0, 4)]), 64),                         # a source row read by four rows
+    (([(1800, 448)], []), 1160),                                     # 128 x 128 tiles of 8 wavefronts
+    (merge(81, 8, 37, 64), 3080),                                    # of 4 wavefronts
+    (conv(2, [64], 8), 64),                                          # runs along m
+    (conv(3, [32, 96, 40 + 24], 12), 264),                           # gathered, partial tiles
+    (conv(1, [32], 4), 8),                                           # smaller than a tile each way, one k-step
+    (([(256, 64), (256, 128), (256, 64)], [("concat", 1)]), 136),    # gathered along k
+    (([(200, 64)] * 8, [("concat", 1)]), 72),                        # eight sources
+]
+
+
+def _stays_general(case, w_along_k):
+    """With the weight along k a step is 64 long: K and the ranges of the gathered sources must be whole numbers of it."""
+    shapes, ops = FORMS[case][0]
+    ranges = [s[1] for s in shapes] if len(shapes) > 1 else [B.dst_shape(B.amap_compose(shapes, 2, ops))[1]]
+    return w_along_k and any(r % 64 for r in ranges)
+
+
+def _maps(case):
+    (shapes, ops), n = FORMS[case]
+    a = B.amap_compose(shapes, 2, ops)
+    m, k = B.dst_shape(a)
+    wt = B.amap_compose([(n, k)], 2, [("transpose", (1, 0))])
+    wn = B.amap_compose([(k, n + 8)], 2, [("slice", 1, 8, n + 8, 1)])    # row-major behind an offset, rows longer than N
+    store = B.amap_compose([(m, n)], 2, [("reshape", (m, n // 8, 8)), ("transpose", (1, 0, 2))])
+    return shapes, ops, a, m, k, n, wt, wn, store
+
+
+@pytest.mark.parametrize("case", range(len(FORMS)))
+def test_replay(case):
+    _, _, a, _, k, n, wt, wn, store = _maps(case)
+    for w, out_map in ((None, None), (wt, None), (wn, store)):
+        st, errors = _replay(a, n, w, out_map)
+        if _stays_general(case, w is wt):
+            assert st == B.AMAP_E_UNSUPPORTED
+            continue
+        assert (st, errors) == (B.AMAP_OK, 0), (w is wt, out_map is not None)
+
+
+def test_replay_of_random_forms():
+    rng = np.random.default_rng(29)
+    for _ in range(60):
+        b, h, s = int(rng.integers(1, 4)), int(rng.integers(1, 9)), int(rng.integers(1, 90))
+        d = int(rng.choice([16, 24, 32, 64, 80, 128]))
+        n = 8 * int(rng.integers(1, 40))
+        if rng.random() < 0.5:
+            shapes, ops = merge(b, 4 * h, s, d)
+        else:
+            shapes, ops = conv(b, [32 * int(rng.integers(1, 5)) for _ in range(h % 4 + 1)], 4 * int(rng.integers(1, 6)))
+        a = B.amap_compose(shapes, 2, ops)
+        m, k = B.dst_shape(a)
+        out_map = B.amap_compose([(m, n)], 2, [("slice", 0, m - 1, -1, -1)]) if rng.random() < 0.5 else None
+        w = B.amap_compose([(n, k)], 2, [("transpose", (1, 0))]) if rng.random() < 0.5 else None
+        st, errors = _replay(a, n, w, out_map)
+        assert st in (B.AMAP_OK, B.AMAP_E_UNSUPPORTED), (shapes, ops, n)
+        assert st != B.AMAP_OK or errors == 0, (shapes, ops, n, errors)
+
+
+def test_products_of_the_other_kernels_have_no_ring_replay():
+    for shapes, ops, n in [([(200, 72)], [], 128),                       # K is no multiple of 64
+                           ([(256, 136)], [("pad", (0, 0), (0, 56), 0)], 256),
+                           ([(512, 128)], [], 256),                      # few k-steps and tiles: 256 x 256
+                           ([(8192, 1024)], [], 4096)]:                  # fills the chip with 256 x 256 tiles
+        assert _replay(B.amap_compose(shapes, 2, ops), n)[0] == B.AMAP_E_UNSUPPORTED
+
+
+@pytest.fixture(scope="module")
+def dev():
+    from paper_2002_12798_amd import device
+    device.require_gpu()
+    return device
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", range(len(FORMS)))
+def test_against_the_general_kernel_and_the_oracle(dev, case, monkeypatch, capfd):
+    import torch
+    shapes, ops, a, m, k, n, wt, wn, store = _maps(case)
+    rng = np.random.default_rng(5100 + case)
+    srcs = [synth.f32_to_bf16_bits(rng.standard_normal(s).astype(np.float32)) for s in shapes]
+    w = synth.f32_to_bf16_bits((rng.standard_normal((k, n)) * 0.05).astype(np.float32))
+    d_srcs = [dev.to_device(s) for s in srcs]
+    d_w = [dev.to_device(w), dev.to_device(np.ascontiguousarray(w.T)), dev.to_device(np.concatenate([w[:, :8], w], axis=1))]
+    want = None
+    if 2 * m * k * n < 1e9:
+        want = synth.bf16_bits_to_f32(oracle.gemm_bf16(oracle.run_chain(srcs, ops) if ops else srcs[0], w)).astype(np.float64)
+    for w_map, d, out_map in ((None, d_w[0], None), (wt, d_w[1], None), (wn, d_w[2], store)):
+        if _stays_general(case, w_map is wt):
+            continue
+        assert _replay(a, n, w_map, out_map) == (B.AMAP_OK, 0)
+
+        def run():
+            out = torch.full(B.dst_shape(out_map) if out_map else (m, n), 0x5A5A, dtype=torch.int16, device="cuda")
+            B.amap_gemm_gather([t.data_ptr() for t in d_srcs], a, d.data_ptr(), w_map, n, out_map, out.data_ptr(), 0)
+            torch.cuda.synchronize()
+            return dev.to_host(out)
+
+        print(f"[gpu] ring gemm case {case}: {shapes} {ops} N={n} w={'nk' if w_map is wt else 'kn'} store={out_map is not None}", flush=True)
+        monkeypatch.setenv("AMAP_PLAN_TRACE", "1")
+        capfd.readouterr()
+        got = run()
+        assert "amap gemm: ring" in capfd.readouterr().err           # the kernel under test is the one that ran
+        monkeypatch.setenv("AMAP_GEMM_TILE256", "0")
+        general = run()
+        assert "256 x 128 tiles" in capfd.readouterr().err
+        monkeypatch.delenv("AMAP_GEMM_TILE256")
+        monkeypatch.delenv("AMAP_PLAN_TRACE")
+        assert np.array_equal(got, general)                          # the same products in the same order
+        if want is not None:
+            g = synth.bf16_bits_to_f32(got).astype(np.float64)
+            if out_map:
+                g = g.transpose(1, 0, 2).reshape(m, n)
+            # fp32 sums of K products, |error| <= K 2^-24 sum |a w| (far below one rounding), then one rounding to bf16: 2^-8
+            assert np.abs(g - want).max() <= 2.0 ** -7 * np.abs(want).max()
