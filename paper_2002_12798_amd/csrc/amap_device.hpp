@@ -21,6 +21,7 @@ struct FastDiv {
 inline FastDiv make_fastdiv(uint32_t d) {
     uint32_t l = 0;
     while ((1ull << l) < d) ++l;
+    if ((1ull << l) == d) return FastDiv{1, l};   // most extents: without the 64-bit division
     uint64_t m = ((1ull << 32) * ((1ull << l) - d)) / d + 1;
     return FastDiv{(uint32_t)m, l};
 }

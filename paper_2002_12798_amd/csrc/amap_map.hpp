@@ -88,6 +88,14 @@ struct KPiece {
     }
 };
 
+// Kept by the map it belongs to and not copied with it: a copy is made without regard to a thread that fills the slot.
+struct ReverseSlot {
+    std::shared_ptr<const amap> map;
+    ReverseSlot() = default;
+    ReverseSlot(const ReverseSlot &) {}
+    ReverseSlot &operator=(const ReverseSlot &) { return *this; }
+};
+
 }  // namespace amap_detail
 
 struct amap {
@@ -100,6 +108,7 @@ struct amap {
     std::vector<amap_detail::Piece> pieces;
     std::vector<amap_detail::KPiece> kpieces;      // derived from pieces when strided
     std::shared_ptr<void> plan;                    // device launch plan (owned by the executor)
+    mutable amap_detail::ReverseSlot reversed;     // the reverse of the map, once a product was stored through it (see reverse_of)
     mutable int64_t distinct_reads = -1;           // distinct source elements read, once counted (see distinct_source_elements)
 };
 

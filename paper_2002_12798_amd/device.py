@@ -38,8 +38,14 @@ def empty_dst(m, fill=None) -> torch.Tensor:
     return t
 
 
+# torch.cuda.current_stream() builds a Stream object (2.8 us); the handle alone is 0.2 us away
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def current_stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    if _raw_stream is None or not torch.cuda.is_initialized():
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def execute(m, srcs, dst=None, kernel_id=None, stream=None) -> torch.Tensor:
@@ -63,10 +69,9 @@ def execute_multi(maps, srcs, dsts=None, stream=None):
 def gemm_fused(a_src: torch.Tensor, a_map, w: torch.Tensor, out=None, stream=None, out_map=None) -> torch.Tensor:
     """out = A x W with A read through a_map; with out_map the product is stored through
     that map (out then has out_map's dst shape)."""
-    info = B.amap_describe(a_map)
     n = w.shape[1]
     if out is None:
-        shape = (info.shape[0], n) if out_map is None else B.dst_shape(out_map)
+        shape = (B.amap_describe(a_map).shape[0], n) if out_map is None else B.dst_shape(out_map)
         out = torch.empty(shape, dtype=torch.int16, device=require_gpu())
     st = current_stream() if stream is None else stream
     if out_map is None:

@@ -107,6 +107,21 @@ def test_products_of_the_other_kernels_have_no_ring_replay():
         assert _replay(B.amap_compose(shapes, 2, ops), n)[0] == B.AMAP_E_UNSUPPORTED
 
 
+def test_one_store_map_used_by_several_threads():
+    """The reverse of a store map is made at its first use and kept with it: the first uses race here."""
+    import threading
+    a = B.amap_compose([(300, 448)], 2, [])
+    for _ in range(20):
+        store = B.amap_compose([(300, 136)], 2, [("reshape", (300, 17, 8)), ("transpose", (1, 0, 2))])
+        got = []
+        threads = [threading.Thread(target=lambda: got.append(_replay(a, 136, None, store))) for _ in range(4)]
+        for t in threads:
+            t.start()
+        for t in threads:
+            t.join()
+        assert got == [(B.AMAP_OK, 0)] * 4
+
+
 @pytest.fixture(scope="module")
 def dev():
     from paper_2002_12798_amd import device
