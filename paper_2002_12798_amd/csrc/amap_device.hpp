@@ -113,13 +113,12 @@ struct DevPiece {
     // and serves the other side with 16-byte vectors along r whose elements it picks one by one.
     uint32_t flat;
     // FLAT, column-blocked ("ragged") form, for rows too long for LDS: rag_cb > 0.  A workgroup takes
-    // rows x rag_cb elements (tilesQ blocks along c, the fastest-running part of the workgroup index).  On
+    // 64 rows x rag_cb elements (tilesQ blocks along c, the fastest-running part of the workgroup index).  On
     // the contiguous side a row segment starts at any element: loads take 16-byte vectors from the segment's
-    // start (under-aligned) and single elements at its end; stores take the aligned 16-byte slots the
-    // segment covers (rag_s = rag_cb / V + 1 of them), whole where the slot lies inside the segment and
-    // element by element at the two ends.  LDS rows are rag_w elements apart.
-    uint32_t rag_cb, rag_w, rag_s;
-    FastDiv fd_rag_s;
+    // start (under-aligned) and single elements at its end; stores take aligned 16-byte slots (see RagRow), for
+    // which a block loads up to V - 1 columns more than its own.  1 << rag_slog = rag_cb / V slots per row; LDS
+    // rows are rag_w elements apart.
+    uint32_t rag_cb, rag_w, rag_slog;
     // XLANE only.  A dst row (the whole P run, fills beside it included) is xl_npv vectors long; a wavefront
     // takes xl_rows consecutive Q positions (a multiple of V, xl_rows * xl_npv <= 64): lane l stores vector
     // l % xl_npv of row l / xl_npv, so the stores of a wavefront are one contiguous run of dst.  n_units =

@@ -84,6 +84,13 @@ AMAP_HD bool launch_is_tile16(const LaunchArgs &a, int es) {
         if (!rows_is_plain(a.p[k], es)) return false;
     return true;
 }
+// ---- the same with a flat tile piece in front
+AMAP_HD bool launch_is_flat(const LaunchArgs &a, int es) {
+    if (a.n_pieces == 0 || a.p[0].kind != PK_FLAT || a.p[0].n_blocks == 0 || (es << a.p[0].vlog) != 16) return false;
+    for (uint32_t k = 1; k < a.n_pieces; ++k)
+        if (!rows_is_plain(a.p[k], es)) return false;
+    return true;
+}
 // ---- a launch of several plain row pieces (the outputs of one multi-output call, a copy with its fills)
 AMAP_HD bool launch_is_plain_rows(const LaunchArgs &a, int es) {
     for (uint32_t k = 0; k < a.n_pieces; ++k)
@@ -134,6 +141,7 @@ AMAP_HD FlatUnit flat_unit(const DevPiece &P, uint32_t t) {
 // column-blocked form: workgroup t -> block (rows from r0, columns from c0), offsets of (r0, c0)
 struct RagUnit {
     uint32_t doff, soff, rcount, c0, ccount;
+    uint32_t lcount;   // columns to load: with dst as the contiguous side up to V - 1 more than the block's own
 };
 AMAP_HD RagUnit rag_unit(const DevPiece &P, uint32_t t) {
     uint32_t rest = fdiv(t, P.fdTQ);
@@ -156,7 +164,26 @@ AMAP_HD RagUnit rag_unit(const DevPiece &P, uint32_t t) {
     u.rcount = rleft < (1u << P.lqlog) ? rleft : (1u << P.lqlog);
     u.c0 = c0;
     u.ccount = cleft < P.rag_cb ? cleft : P.rag_cb;
+    const uint32_t reach = P.rag_cb + (P.flat == 2 ? (1u << P.vlog) - 1u : 0u);
+    u.lcount = cleft < reach ? cleft : reach;
     return u;
+}
+
+// dst as the contiguous side: the elements of row r that the block stores, dst offsets [lo, hi), from the aligned slot x0
+// on.  A block starts at the first 16-byte slot boundary behind its first column and ends at the one behind the next
+// block's, so that only the two ends of a row are stored element by element, not the ends of every block's segment.
+struct RagRow {
+    uint32_t a, lo, hi, x0;   // a: dst offset of the row's first column of the block (LDS column 0)
+};
+AMAP_HD RagRow rag_row(const DevPiece &P, const RagUnit &u, uint32_t r) {
+    const uint32_t V = 1u << P.vlog, left = P.eP - u.c0;
+    RagRow w;
+    w.a = u.doff + r * P.eP;
+    const uint32_t end = w.a + left, next = (w.a + u.ccount + V - 1u) & ~(V - 1u);
+    w.lo = u.c0 ? (w.a + V - 1u) & ~(V - 1u) : w.a;
+    w.hi = u.ccount == left || next > end ? end : next;
+    w.x0 = w.lo & ~(V - 1u);
+    return w;
 }
 
 // position c of a row -> element offset on the side where the row is not contiguous: the row's loops

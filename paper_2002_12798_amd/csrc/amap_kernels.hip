@@ -580,107 +580,144 @@ __device__ __forceinline__ void flat_body(const DevPiece &P, char *dst, uint32_t
     }
 }
 
-// The same for rows too long for LDS: blocks of rows x rag_cb columns (see DevPiece::rag_cb).
+// The same for rows too long for LDS: blocks of 64 rows x rag_cb columns (see DevPiece::rag_cb).  What bounds it is the
+// number of LDS and address instructions, not memory: 2-byte elements therefore pass LDS two columns at a time, as dwords
+// (the same dword of eight rows is two vectors along the rows), and the contiguous side is walked in aligned 16-byte slots of
+// which a row has a power of two per block.  bf16 [64,55,55,96] to channel-major 20.0 -> 15.4 us
+// (74 MB: 4.8 TB/s), [64,35,35,288] 25.7 -> 23.8 us (90 MB, more than stays in the last-level cache).
+template <int ES>
+__device__ __forceinline__ void rag_load_rows(uint32_t (&v)[4], const char *src, uint32_t at, uint32_t n) {
+    // n < V elements along the rows (a row count that is no whole number of vectors)
+    typedef typename std::conditional<ES == 2, uint16_t, uint32_t>::type elem_t;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[k] = 0;
+    for (uint32_t k = 0; k < n; ++k) {
+        const uint32_t e = reinterpret_cast<const elem_t *>(src)[at + k];
+        if constexpr (ES == 2)
+            v[k / 2] |= e << (16 * (k & 1));
+        else
+            v[k] = e;
+    }
+}
+
 template <int ES, int NT>
 __device__ __forceinline__ void rag_body(const DevPiece &P, char *dst, uint32_t t, uint32_t tid, char *smem) {
     constexpr uint32_t V = 16 / ES;
-    constexpr uint32_t VLOG = ES == 2 ? 3 : 2;
-    const uint32_t RVLOG = P.lqlog - VLOG;
-    constexpr int kBatch = 4;
+    constexpr uint32_t VLOG = ES == 2 ? 3 : 2, RVLOG = 6 - VLOG;   // 64 rows: 8 or 16 vectors along them
+    constexpr uint32_t CP = ES == 2 ? 2 : 1;                       // columns per LDS access
     typedef typename std::conditional<ES == 2, uint16_t, uint32_t>::type elem_t;
     const RagUnit U = rag_unit(P, t);
-    const uint32_t C = P.eP, W = P.rag_w, S = P.rag_s, threads = 64u << P.nwlog;
-    const uint32_t nrag = U.rcount * S, nstr = U.ccount << RVLOG;
+    const uint32_t C = P.eP, W = P.rag_w, threads = 64u << P.nwlog;
     elem_t *const lds = reinterpret_cast<elem_t *>(smem);
+    uint32_t *const lds32 = reinterpret_cast<uint32_t *>(smem);
     const char *const src = (const char *)P.src;
 
     if (P.flat == 1) {
-        for (uint32_t item = tid; item < nrag; item += threads) {
-            const uint32_t r = fdiv(item, P.fd_rag_s), col = (item - r * S) * V;
-            if (col >= U.ccount) continue;
-            const uint32_t a = U.soff + r * C + col, at = r * W + col;
-            if (col + V <= U.ccount) {
-                uint32_t v[4];
-                gld<16, false>(v, src + (size_t)a * ES);
-#pragma unroll
-                for (int k = 0; k < 4; ++k) reinterpret_cast<uint32_t *>(smem)[(at * ES) / 4 + k] = v[k];
-            } else {
-                for (uint32_t i = 0; col + i < U.ccount; ++i) lds[at + i] = reinterpret_cast<const elem_t *>(src)[a + i];
-            }
-        }
-        __syncthreads();
-        for (uint32_t vi = tid; vi < nstr; vi += threads) {
-            const uint32_t rv = vi & ((1u << RVLOG) - 1), c = vi >> RVLOG;
-            if (rv * V >= U.rcount) continue;
-            uint32_t v[4] = {0, 0, 0, 0};
-#pragma unroll
-            for (uint32_t k = 0; k < V; ++k) {
-                const uint32_t x = lds[(rv * V + k) * W + c];
-                if constexpr (ES == 2)
-                    v[k / 2] |= x << (16 * (k & 1));
-                else
-                    v[k] = x;
-            }
-            gst<16, (NT & PF_NT_STORE) != 0>(dst + (size_t)(U.doff + flat_c_offset(P, U.c0 + c) + rv * V) * ES, v);
-        }
-    } else {
-        for (uint32_t v0 = tid; v0 < nstr; v0 += kBatch * threads) {
+        constexpr int kBatch = 4;
+        const uint32_t n = U.rcount << P.rag_slog;
+        for (uint32_t i0 = tid; i0 < n; i0 += kBatch * threads) {
             uint32_t v[kBatch][4];
 #pragma unroll
             for (int b = 0; b < kBatch; ++b) {
-                const uint32_t vi = v0 + b * threads, rv = vi & ((1u << RVLOG) - 1), c = vi >> RVLOG;
-                if (vi < nstr && rv * V < U.rcount) {
-                    const uint32_t a = U.soff + flat_c_offset(P, U.c0 + c) + rv * V;
-                    if (rv * V + V <= U.rcount) {
-                        gld<16, (NT & PF_NT_LOAD) != 0>(v[b], src + (size_t)a * ES);
-                    } else {  // the last rows of a row count that is no whole number of vectors
+                const uint32_t i = i0 + b * threads, r = i >> P.rag_slog, col = (i & ((1u << P.rag_slog) - 1)) * V;
+                if (i < n && col + V <= U.ccount) gld<16, false>(v[b], src + (size_t)(U.soff + r * C + col) * ES);
+            }
 #pragma unroll
-                        for (int k = 0; k < 4; ++k) v[b][k] = 0;
-                        for (uint32_t k = 0; rv * V + k < U.rcount; ++k) {
-                            const uint32_t e = reinterpret_cast<const elem_t *>(src)[a + k];
-                            if constexpr (ES == 2)
-                                v[b][k / 2] |= e << (16 * (k & 1));
-                            else
-                                v[b][k] = e;
-                        }
-                    }
+            for (int b = 0; b < kBatch; ++b) {
+                const uint32_t i = i0 + b * threads, r = i >> P.rag_slog, col = (i & ((1u << P.rag_slog) - 1)) * V;
+                if (i >= n || col >= U.ccount) continue;
+                const uint32_t at = r * W + col;
+                if (col + V <= U.ccount) {
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) lds32[(at * ES) / 4 + k] = v[b][k];
+                } else {
+                    for (uint32_t e = 0; col + e < U.ccount; ++e) lds[at + e] = reinterpret_cast<const elem_t *>(src)[U.soff + r * C + col + e];
+                }
+            }
+        }
+        __syncthreads();
+        const uint32_t ns = ((U.ccount + CP - 1) / CP) << RVLOG;
+        for (uint32_t i = tid; i < ns; i += threads) {
+            const uint32_t rv = i & ((1u << RVLOG) - 1), c = (i >> RVLOG) * CP;
+            if (rv * V >= U.rcount) continue;
+            if constexpr (ES == 2) {
+                uint32_t w[8], v0[4], v1[4];
+#pragma unroll
+                for (int k = 0; k < 8; ++k) w[k] = lds32[((rv * V + k) * W + c) >> 1];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    v0[k] = (w[2 * k] & 0xFFFFu) | (w[2 * k + 1] << 16);
+                    v1[k] = (w[2 * k] >> 16) | (w[2 * k + 1] & 0xFFFF0000u);
+                }
+                gst<16, (NT & PF_NT_STORE) != 0>(dst + (size_t)(U.doff + flat_c_offset(P, U.c0 + c) + rv * V) * ES, v0);
+                if (c + 1 < U.ccount) gst<16, (NT & PF_NT_STORE) != 0>(dst + (size_t)(U.doff + flat_c_offset(P, U.c0 + c + 1) + rv * V) * ES, v1);
+            } else {
+                uint32_t v[4];
+#pragma unroll
+                for (uint32_t k = 0; k < 4; ++k) v[k] = lds[(rv * V + k) * W + c];
+                gst<16, (NT & PF_NT_STORE) != 0>(dst + (size_t)(U.doff + flat_c_offset(P, U.c0 + c) + rv * V) * ES, v);
+            }
+        }
+    } else {
+        constexpr int kBatch = 4 / CP;
+        const uint32_t ns = ((U.lcount + CP - 1) / CP) << RVLOG;
+        for (uint32_t i0 = tid; i0 < ns; i0 += kBatch * threads) {
+            uint32_t v[kBatch][CP][4];
+#pragma unroll
+            for (int b = 0; b < kBatch; ++b) {
+                const uint32_t i = i0 + b * threads, rv = i & ((1u << RVLOG) - 1), c = (i >> RVLOG) * CP;
+                if (i >= ns || rv * V >= U.rcount) continue;
+#pragma unroll
+                for (uint32_t q = 0; q < CP; ++q) {
+                    // (the second column of the last pair may not exist: the first again, into LDS columns nobody reads)
+                    const uint32_t at = U.soff + flat_c_offset(P, U.c0 + (c + q < U.lcount ? c + q : c)) + rv * V;
+                    if (rv * V + V <= U.rcount)
+                        gld<16, (NT & PF_NT_LOAD) != 0>(v[b][q], src + (size_t)at * ES);
+                    else
+                        rag_load_rows<ES>(v[b][q], src, at, U.rcount - rv * V);
                 }
             }
 #pragma unroll
             for (int b = 0; b < kBatch; ++b) {
-                const uint32_t vi = v0 + b * threads, rv = vi & ((1u << RVLOG) - 1), c = vi >> RVLOG;
-                if (vi < nstr && rv * V < U.rcount) {
+                const uint32_t i = i0 + b * threads, rv = i & ((1u << RVLOG) - 1), c = (i >> RVLOG) * CP;
+                if (i >= ns || rv * V >= U.rcount) continue;
 #pragma unroll
-                    for (uint32_t k = 0; k < V; ++k) {
-                        if (rv * V + k >= U.rcount) break;
-                        if constexpr (ES == 2)
-                            lds[(rv * V + k) * W + c] = (uint16_t)(v[b][k / 2] >> (16 * (k & 1)));
-                        else
-                            lds[(rv * V + k) * W + c] = v[b][k];
+                for (uint32_t k = 0; k < V; ++k) {   // (rows past the last one: LDS rows nobody reads)
+                    const uint32_t at = (rv * V + k) * W + c;
+                    if constexpr (ES == 2) {
+                        const uint32_t x = v[b][0][k / 2], y = v[b][CP - 1][k / 2];
+                        lds32[at >> 1] = (k & 1) ? ((x >> 16) | (y & 0xFFFF0000u)) : ((x & 0xFFFFu) | (y << 16));
+                    } else {
+                        lds32[at] = v[b][0][k];
                     }
                 }
             }
         }
         __syncthreads();
-        for (uint32_t item = tid; item < nrag; item += threads) {
-            const uint32_t r = fdiv(item, P.fd_rag_s), s = item - r * S;
-            const uint32_t a = U.doff + r * C;                 // first dst element of the row segment
-            const uint32_t x = (a & ~(V - 1)) + s * V;         // the aligned slot
-            const uint32_t lo = x > a ? x : a, hi = x + V < a + U.ccount ? x + V : a + U.ccount;
+        // a row's slots of the block; in the first block of a row one more where the row starts inside a slot
+        const uint32_t n = U.rcount << P.rag_slog, extra = U.c0 == 0 ? U.rcount : 0u;
+        for (uint32_t i = tid; i < n + extra; i += threads) {
+            const uint32_t r = i < n ? i >> P.rag_slog : i - n, slot = i < n ? i & ((1u << P.rag_slog) - 1) : 1u << P.rag_slog;
+            const RagRow R = rag_row(P, U, r);
+            const uint32_t x = R.x0 + slot * V;
+            const uint32_t lo = x > R.lo ? x : R.lo, hi = x + V < R.hi ? x + V : R.hi;
             if (lo >= hi) continue;
             if (hi - lo == V) {
-                uint32_t v[4] = {0, 0, 0, 0};
+                uint32_t v[4];
+                const uint32_t at = r * W + (x - R.a);
+                if constexpr (ES == 2) {   // W is even: the slot starts in the middle of a dword where R.a is odd
+                    uint32_t w[5];
 #pragma unroll
-                for (uint32_t k = 0; k < V; ++k) {
-                    const uint32_t e = lds[r * W + (x - a) + k];
-                    if constexpr (ES == 2)
-                        v[k / 2] |= e << (16 * (k & 1));
-                    else
-                        v[k] = e;
+                    for (int k = 0; k < 5; ++k) w[k] = lds32[(at >> 1) + k];
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) v[k] = __builtin_amdgcn_alignbyte(w[k + 1], w[k], 2u * (at & 1u));
+                } else {
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) v[k] = lds[at + k];
                 }
                 gst<16, false>(dst + (size_t)x * ES, v);
             } else {
-                for (uint32_t p = lo; p < hi; ++p) reinterpret_cast<elem_t *>(dst)[p] = lds[r * W + (p - a)];
+                for (uint32_t p = lo; p < hi; ++p) reinterpret_cast<elem_t *>(dst)[p] = lds[r * W + (p - R.a)];
             }
         }
     }
@@ -774,20 +811,10 @@ __global__ __launch_bounds__(kMaxThreads) void amap_rows_multi_kernel(const Laun
     rows_move<16, NT>(P, dst + (size_t)P.dwin * ES, ES, doff, soff, ok);
 }
 
-// ------------------------------------------------------------------ one tile piece + plain rows
-// The launch of a transposing map (NCHW -> NHWC with or without padding, a concat in front of it):
-// piece 0 is known without a search and its fields sit at fixed places of the argument block; only
-// the workgroups behind it (constant borders) look their piece up.
-template <int ES, int NT, bool GROUPED>
-__global__ __launch_bounds__(kMaxThreads) void amap_tile16_kernel(const LaunchArgs args, char *dst) {
-    extern __shared__ uint4 smem_v[];
-    const uint32_t b = logical_block(args, blockIdx.x, gridDim.x);
-    if (b < args.p[0].n_blocks) {
-        tile_body<ES, 16 / ES, true, NT, GROUPED>(args.p[0], dst + (size_t)args.p[0].dwin * ES, b, threadIdx.x,
-                                                   reinterpret_cast<char *>(smem_v));
-        return;
-    }
-    uint32_t pi = args.p[0].group_n;
+// the plain row pieces (constant borders) from entry `first` on that follow a tile piece in its launch
+template <int ES, int NT>
+__device__ __forceinline__ void rows_behind(const LaunchArgs &args, char *dst, uint32_t b, uint32_t first) {
+    uint32_t pi = first;
     for (uint32_t k = pi + 1; k < args.n_pieces; ++k)
         if (b >= args.p[k].first_block) pi = k;
     const DevPiece &P = args.p[pi];
@@ -802,6 +829,42 @@ __global__ __launch_bounds__(kMaxThreads) void amap_tile16_kernel(const LaunchAr
         rows_offsets_fixed(P, r, doff[u], soff[u]);
     }
     rows_move<16, NT>(P, dst + (size_t)P.dwin * ES, ES, doff, soff, ok);
+}
+
+// ------------------------------------------------------------------ one tile piece + plain rows
+// The launch of a transposing map (NCHW -> NHWC with or without padding, a concat in front of it):
+// piece 0 is known without a search and its fields sit at fixed places of the argument block; only
+// the workgroups behind it (constant borders) look their piece up.
+template <int ES, int NT, bool GROUPED>
+__global__ __launch_bounds__(kMaxThreads) void amap_tile16_kernel(const LaunchArgs args, char *dst) {
+    extern __shared__ uint4 smem_v[];
+    const uint32_t b = logical_block(args, blockIdx.x, gridDim.x);
+    if (b < args.p[0].n_blocks) {
+        tile_body<ES, 16 / ES, true, NT, GROUPED>(args.p[0], dst + (size_t)args.p[0].dwin * ES, b, threadIdx.x,
+                                                   reinterpret_cast<char *>(smem_v));
+        return;
+    }
+    rows_behind<ES, NT>(args, dst, b, args.p[0].group_n);
+}
+
+
+// ------------------------------------------------------------------ one flat tile piece + plain rows
+// The same for a flat tile in front (whole images with an odd number of positions, rows of no whole vectors):
+// 56 instead of 66 VGPRs, so 8 instead of 7 wavefronts per SIMD, and no piece search ([64,55,55,96] 17.3 -> 16.4 us,
+// [4097,4099] transposed 16.8 -> 15.3 us, [64,288,35,35] into a padded channels-last image 25.5 -> 24.1 us).
+template <int ES, int NT, bool RAG>
+__global__ __launch_bounds__(kMaxThreads) void amap_flat_kernel(const LaunchArgs args, char *dst) {
+    extern __shared__ uint4 smem_v[];
+    const uint32_t b = logical_block(args, blockIdx.x, gridDim.x);
+    if (b < args.p[0].n_blocks) {
+        char *const d = dst + (size_t)args.p[0].dwin * ES;
+        if constexpr (RAG)
+            rag_body<ES, NT>(args.p[0], d, b, threadIdx.x, reinterpret_cast<char *>(smem_v));
+        else
+            flat_body<ES, NT>(args.p[0], d, b, threadIdx.x, reinterpret_cast<char *>(smem_v));
+        return;
+    }
+    rows_behind<ES, NT>(args, dst, b, 1);
 }
 
 // ------------------------------------------------------------------ program
@@ -980,6 +1043,29 @@ amap_status launch_pieces(const LaunchArgs &args, uint32_t blocks, size_t lds, i
         }
 #undef AMAP_LAUNCH_T16
         return launch_failed("amap_tile16_kernel") ? AMAP_E_HIP : AMAP_OK;
+    }
+    if (launch_is_flat(args, es)) {
+        say("amap_flat_kernel");
+        const bool rag = args.p[0].rag_cb != 0;
+#define AMAP_LAUNCH_FLAT(ES, NT)                                                                             \
+    do {                                                                                                     \
+        if (rag)                                                                                             \
+            hipLaunchKernelGGL((amap_flat_kernel<ES, NT, true>), grid, block, lds, stream, args, d);         \
+        else                                                                                                 \
+            hipLaunchKernelGGL((amap_flat_kernel<ES, NT, false>), grid, block, lds, stream, args, d);        \
+    } while (0)
+        switch ((es == 2 ? 0 : 4) + (int)(args.nt & 3)) {
+        case 0: AMAP_LAUNCH_FLAT(2, 0); break;
+        case 1: AMAP_LAUNCH_FLAT(2, 1); break;
+        case 2: AMAP_LAUNCH_FLAT(2, 2); break;
+        case 3: AMAP_LAUNCH_FLAT(2, 3); break;
+        case 4: AMAP_LAUNCH_FLAT(4, 0); break;
+        case 5: AMAP_LAUNCH_FLAT(4, 1); break;
+        case 6: AMAP_LAUNCH_FLAT(4, 2); break;
+        default: AMAP_LAUNCH_FLAT(4, 3); break;
+        }
+#undef AMAP_LAUNCH_FLAT
+        return launch_failed("amap_flat_kernel") ? AMAP_E_HIP : AMAP_OK;
     }
     say("amap_pieces_kernel");
 #define AMAP_LAUNCH(ES, NT)                                                                                  \

@@ -334,6 +334,7 @@ static bool plan_inter(const KPiece &kp, int es, uint32_t nwlog, int64_t svol, D
 //   dir 1: the source is the flat side (P's source stride == Q's extent): r = P, c = Q
 //   dir 2: dst is the flat side (Q's dst stride == P's extent): r = Q, c = P
 constexpr uint32_t kFlatLdsBytes = 65536;  // rows of 289 (17 x 17): 32.9 us as whole-vector part + tail, 24.8 us as flat tiles of 37 KiB
+constexpr int64_t kLastLevelCache = 256ll << 20;
 constexpr uint32_t kFlatMinRows = 16;      // 48 channels of 7 x 7 images: 23.6 -> 12.5 us; 16 channels: 21.4 -> 11.6 us
 
 // The loops that continue the source-contiguous loop iQ in the source (x, then y of an image: one run of
@@ -435,12 +436,14 @@ static FlatShape flat_shape(const KPiece &kp, int es) {
         const uint32_t rlog_min = tile_bytes >= 8 ? 5 : 4;
         while (rlog > rlog_min && C * std::min<int64_t>(ER, 1ll << rlog) * es > lds_limit) --rlog;
         int64_t cb = 0;
-        // 128 2-byte columns per block (55 x 55 positions under 96 channels, towards channel-major: 24.4 us; 256 columns: 26.6 us;
-        // gathered rows: 178.8 us).  With the source as the contiguous side and a row of one loop, the cut into a
-        // whole-vector part and a one-element tail is as fast or faster (23.7 against 23.8 us; 75 x 75 fp32: 11.9 against
-        // 17.4 us), so there the blocked form is left to rows of several loops (padded or cropped images).
-        const int64_t cb_env = 256 / es;  // 256-byte row segments (fp32: 64 columns 15.5 us, 128 columns 17.2 us)
-        const bool rag_ok = cb_env >= V && cb_env % V == 0 && tile_bytes < 8 && ER >= 64;
+        // 64 2-byte (32 4-byte) columns per block: 128-byte row segments (bf16 [64,55,55,96] towards channel-major 15.4 us, with
+        // 256-byte segments 16.4, with 512-byte ones 19.2; fp32 [16,55,55,64] 7.9, 8.9, 10.6).  With the source as the
+        // contiguous side and a row of one loop, the cut into a whole-vector part and a one-element tail is as fast or
+        // faster (23.7 against 23.8 us; 75 x 75 fp32: 11.9 against 17.4 us), so there the blocked form is left to rows of
+        // several loops (padded or cropped images).  From 16 rows on (a block of 64 is then partly empty): what is left for
+        // fewer rows are gathered rows (48 channels of 55 x 55: 145.8 -> 15.4 us; 24 channels 24.6 -> 8.5 us).
+        const int64_t cb_rag = 128 / es;
+        const bool rag_ok = tile_bytes < 8;
         // long rows of one loop under few channels, the source contiguous: the cut into a whole-vector part and a
         // one-element tail is faster there (concat of 64 + 64 + 96 + 32 channels of 35 x 35 positions: 26.8 against 34.6 us)
         if (dir == 1 && chain.size() == 1 && rlog == 4 && ER < 128) continue;
@@ -449,12 +452,14 @@ static FlatShape flat_shape(const KPiece &kp, int es) {
             // rows too long for LDS: blocks of 64 rows x cb columns whose row segments start at any element
             if (!rag_ok || !(dir == 2 || chain.size() > 1)) continue;
             rlog = 6;
-            cb = cb_env;
-        } else if (rag_ok && rlog == 4 && dir == 1) {
-            // 16 rows at a time with the source as the contiguous side: the blocked form is faster
-            // (35 x 35 positions under 288 channels: 26.3 against 30.7 us; into a padded image 29.1 against 32.1 us)
+            cb = cb_rag;
+        } else if (rag_ok && rlog == 4 && ER >= 64 && (dir == 1 || 2 * kp.volume() * es > kLastLevelCache / 3)) {
+            // 16 rows at a time: with the source as the contiguous side the blocked form is faster (35 x 35 positions under 288
+            // channels: 20.9 against 30.7 us; into a padded image 23.2 against 32.1 us); with dst as that side it is for pieces that
+            // do not stay in the last-level cache next to their neighbours (90 MB: 23.8 against 24.9 us, 149 MB: 37.2 against
+            // 42.4 us, 241 MB: 56.4 against 59.8 us), and not for smaller ones (80 MB: 16.9 against 15.5 us, 60 MB 14.4 against 12.0 us)
             rlog = 6;
-            cb = cb_env;
+            cb = cb_rag;
         }
         f.dir = dir, f.iR = iR, f.chain = chain, f.C = C, f.ER = ER, f.rlog = rlog, f.cb = cb;
         return f;
@@ -503,9 +508,9 @@ static bool plan_flat(const KPiece &kp, int es, uint32_t nwlog, DevPiece &dp, ui
     lds = (uint32_t)(f.C * std::min<int64_t>(f.ER, rows) * es);
     if (f.cb) {
         dp.rag_cb = (uint32_t)f.cb;
-        dp.rag_w = (uint32_t)(f.cb + (es == 2 ? 2 : 1));  // LDS row stride: an odd number of dwords
-        dp.rag_s = (uint32_t)(f.cb / V + 1);
-        dp.fd_rag_s = make_fastdiv(dp.rag_s);
+        // LDS row stride: an odd number of dwords; with dst as the contiguous side a block loads up to V - 1 columns more
+        dp.rag_w = (uint32_t)(f.cb + (es == 2 ? 2 : 1) + (f.dir == 2 ? V : 0));
+        dp.rag_slog = ilog2((uint32_t)(f.cb / V));
         dp.tilesQ = (uint32_t)((f.C + f.cb - 1) / f.cb);
         dp.fdTQ = make_fastdiv(dp.tilesQ);
         nb *= dp.tilesQ;

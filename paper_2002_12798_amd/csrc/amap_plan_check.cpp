@@ -107,21 +107,25 @@ struct Replay {
 
     // the column-blocked form of a flat tile
     void rag(const DevPiece &P, int sid, uint32_t t, uint32_t lds_bytes) {
-        const uint32_t V = 16u / (uint32_t)m.elem, vlog = V == 8 ? 3 : 2, rvlog = P.lqlog - vlog;
+        const uint32_t V = 16u / (uint32_t)m.elem, vlog = V == 8 ? 3 : 2, rvlog = 6 - vlog, cp = m.elem == 2 ? 2 : 1;
         if (P.lqlog != 6 || P.vlog != vlog || (P.flat != 1 && P.flat != 2) || (P.flat == 1 && P.EQ % V) || t >= P.n_blocks || P.nq < 1 || P.nq > 4 ||
-            P.nloops + P.nq > (uint32_t)kMaxLoops || P.rag_cb % V || P.rag_s != P.rag_cb / V + 1 || P.rag_w < P.rag_cb || (P.rag_w * m.elem) % 4 ||
+            P.nloops + P.nq > (uint32_t)kMaxLoops || P.rag_cb != V << P.rag_slog || P.rag_w < P.rag_cb || (P.rag_w * m.elem) % 4 ||
             (uint64_t)P.rag_w * 64 * m.elem > lds_bytes || (uint64_t)P.tilesQ * P.rag_cb < P.eP) {
             ++errors;
             return;
         }
         const RagUnit U = rag_unit(P, t);
-        const uint32_t C = P.eP, W = P.rag_w, S = P.rag_s, threads = 64u << P.nwlog;
-        const uint32_t nrag = U.rcount * S, nstr = U.ccount << rvlog;
+        const uint32_t C = P.eP, W = P.rag_w, threads = 64u << P.nwlog, slots = 1u << P.rag_slog;
+        if (U.lcount + (cp - 1) > W || U.c0 + U.lcount > C || U.ccount > U.lcount) {
+            ++errors;
+            return;
+        }
         std::vector<int64_t> lds((size_t)lds_bytes / (size_t)m.elem, kUnwritten);
-        auto lds_put = [&](uint64_t e, int64_t code) {
-            if (e >= lds.size() || lds[e] != kUnwritten)
+        // `real`: an element somebody may read; the others (a column or rows that do not exist) only have to stay in bounds
+        auto lds_put = [&](uint64_t e, int64_t code, bool real = true) {
+            if (e >= lds.size() || (real && lds[e] != kUnwritten))
                 ++errors;
-            else
+            else if (real)
                 lds[e] = code;
         };
         auto lds_get = [&](uint64_t e) -> int64_t {
@@ -133,37 +137,51 @@ struct Replay {
         };
         for (int phase = 0; phase < 2; ++phase)
             for (uint32_t tid = 0; tid < threads; ++tid) {
-                const bool rag_side = (phase == 0) == (P.flat == 1);
-                if (!rag_side) {
-                    for (uint32_t vi = tid; vi < nstr; vi += threads) {
-                        const uint32_t rv = vi & ((1u << rvlog) - 1), c = vi >> rvlog;
-                        if (rv * V >= U.rcount) continue;
-                        for (uint32_t k = 0; k < V && rv * V + k < U.rcount; ++k) {
-                            const uint32_t e = (rv * V + k) * W + c, off = flat_c_offset(P, U.c0 + c) + rv * V + k;
-                            if (P.flat == 1 && k == 0 && (P.dwin + (uint32_t)(U.doff + off)) % V) ++errors;
-                            if (P.flat == 1)
-                                write((int64_t)P.dwin + (uint32_t)(U.doff + off), lds_get(e));
-                            else
-                                lds_put(e, code_of(sid, (int64_t)P.swin + (int64_t)(int32_t)(U.soff + off)));
-                        }
-                    }
-                } else if (P.flat == 1) {
-                    for (uint32_t item = tid; item < nrag; item += threads) {
-                        const uint32_t r = fdiv(item, P.fd_rag_s), col = (item - r * S) * V;
+                if (phase == 0 && P.flat == 1) {
+                    for (uint32_t i = tid; i < U.rcount * slots; i += threads) {
+                        const uint32_t r = i / slots, col = i % slots * V;
                         if (col >= U.ccount) continue;
                         const uint32_t a = U.soff + r * C + col, at = r * W + col;
                         if ((at * (uint32_t)m.elem) % 4) ++errors;  // dword LDS stores
-                        for (uint32_t i = 0; i < V && col + i < U.ccount; ++i)
-                            lds_put(at + i, code_of(sid, (int64_t)P.swin + (int64_t)(int32_t)(a + i)));
+                        for (uint32_t e = 0; e < V && col + e < U.ccount; ++e)
+                            lds_put(at + e, code_of(sid, (int64_t)P.swin + (int64_t)(int32_t)(a + e)));
+                    }
+                } else if (P.flat == 1) {
+                    for (uint32_t i = tid; i < ((U.ccount + cp - 1) / cp) << rvlog; i += threads) {
+                        const uint32_t rv = i & ((1u << rvlog) - 1), c = (i >> rvlog) * cp;
+                        if (rv * V >= U.rcount) continue;
+                        for (uint32_t q = 0; q < cp && c + q < U.ccount; ++q) {
+                            const uint32_t d = U.doff + flat_c_offset(P, U.c0 + c + q) + rv * V;
+                            if ((P.dwin + d) % V) ++errors;
+                            for (uint32_t k = 0; k < V; ++k) write((int64_t)P.dwin + (d + k), lds_get((rv * V + k) * W + c + q));
+                        }
+                        if (((uint64_t)(((rv * V + V - 1) * W + c) / cp) + 1) * 4 > lds_bytes) ++errors;
+                    }
+                } else if (phase == 0) {
+                    for (uint32_t i = tid; i < ((U.lcount + cp - 1) / cp) << rvlog; i += threads) {
+                        const uint32_t rv = i & ((1u << rvlog) - 1), c = (i >> rvlog) * cp;
+                        if (rv * V >= U.rcount) continue;
+                        if ((((rv * V) * W + c) * (uint32_t)m.elem) % 4) ++errors;
+                        for (uint32_t q = 0; q < cp; ++q)
+                            for (uint32_t k = 0; k < V; ++k) {
+                                const bool loaded = rv * V + k < U.rcount, real = loaded && c + q < U.lcount;
+                                const uint32_t off = flat_c_offset(P, U.c0 + (c + q < U.lcount ? c + q : c)) + rv * V + k;
+                                const int64_t code = loaded ? code_of(sid, (int64_t)P.swin + (int64_t)(int32_t)(U.soff + off)) : kFill;
+                                lds_put((rv * V + k) * W + c + q, code, real);
+                            }
                     }
                 } else {
-                    for (uint32_t item = tid; item < nrag; item += threads) {
-                        const uint32_t r = fdiv(item, P.fd_rag_s), s = item - r * S;
-                        const uint32_t a = U.doff + r * C, x = (a & ~(V - 1)) + s * V;
-                        const uint32_t lo = x > a ? x : a, hi = x + V < a + U.ccount ? x + V : a + U.ccount;
+                    const uint32_t n = U.rcount * slots, extra = U.c0 == 0 ? U.rcount : 0u;
+                    for (uint32_t i = tid; i < n + extra; i += threads) {
+                        const uint32_t r = i < n ? i / slots : i - n, slot = i < n ? i % slots : slots;
+                        const RagRow R = rag_row(P, U, r);
+                        const uint32_t x = R.x0 + slot * V;
+                        const uint32_t lo = x > R.lo ? x : R.lo, hi = x + V < R.hi ? x + V : R.hi;
                         if (lo >= hi) continue;
                         if (hi - lo == V && (P.dwin + x) % V) ++errors;
-                        for (uint32_t p = lo; p < hi; ++p) write((int64_t)P.dwin + p, lds_get(r * W + (p - a)));
+                        // whole slots of 2-byte elements are read as five dwords
+                        if (hi - lo == V && m.elem == 2 && ((uint64_t)((r * W + (x - R.a)) >> 1) + 5) * 4 > lds_bytes) ++errors;
+                        for (uint32_t p = lo; p < hi; ++p) write((int64_t)P.dwin + p, lds_get(r * W + (p - R.a)));
                     }
                 }
             }
