@@ -99,9 +99,9 @@ __global__ __launch_bounds__(64 * T::WVM * T::WVN, T::OCC) void amap_gemm_ring_k
     static_assert((NA % 4 == 0 || NA == 1 || NA == 2) && (NW % 4 == 0 || NW == 1 || NW == 2), "ring_load");
     uint32_t a_off[NA], w_off[NW];
 #pragma unroll
-    for (int j = 0; j < NA; ++j) a_off[j] = ring_block_offset<AX, BM>(g.a[0].dx, g.a[0].base, g.a[0].kss, m0, g.M, wave * NA, j, lane);
+    for (int j = 0; j < NA; ++j) a_off[j] = ring_block_offset<AX, BM, T::PK == 2>(g.a[0].dx, g.a[0].base, g.a[0].kss, m0, g.M, wave * NA, j, lane);
 #pragma unroll
-    for (int j = 0; j < NW; ++j) w_off[j] = ring_block_offset<WX, BN>(g.w.dx, g.w.base, g.w.kss, n0, g.N, wave * NW, j, lane);
+    for (int j = 0; j < NW; ++j) w_off[j] = ring_block_offset<WX, BN, T::PK == 2>(g.w.dx, g.w.base, g.w.kss, n0, g.N, wave * NW, j, lane);
     const char *ka = reinterpret_cast<const char *>(g.a[0].src) - kRingBias, *kw = reinterpret_cast<const char *>(g.w.src) - kRingBias;
     RingWalk a_walk = ring_walk_begin(g.a_steps), w_walk = ring_walk_begin(g.w_steps);
     uint32_t seg = 0, seg_left = g.a[0].steps;   // NSEG > 1: the source the stream reads, and its k-steps to go
@@ -117,7 +117,7 @@ __global__ __launch_bounds__(64 * T::WVM * T::WVN, T::OCC) void amap_gemm_ring_k
                 seg_step = 2 * (int64_t)s.kss * BK;
                 ka = reinterpret_cast<const char *>(s.src) - kRingBias;
 #pragma unroll
-                for (int j = 0; j < NA; ++j) a_off[j] = ring_block_offset<AX, BM>(s.dx, s.base, s.kss, m0, g.M, wave * NA, j, lane);
+                for (int j = 0; j < NA; ++j) a_off[j] = ring_block_offset<AX, BM, T::PK == 2>(s.dx, s.base, s.kss, m0, g.M, wave * NA, j, lane);
             }
         }
         if constexpr (T::KLANE) {   // runs of A shorter than a step: k decoded per lane, for the two chunk orders of its blocks
@@ -125,7 +125,7 @@ __global__ __launch_bounds__(64 * T::WVM * T::WVN, T::OCC) void amap_gemm_ring_k
 #pragma unroll
             for (uint32_t par = 0; par < 2; ++par) {
                 const uint32_t c8 = 8u * ring_k_chunk(wave * NA + par, lane);
-                kl[par] = 2u * (digits_offset4(g.a_dk, ld_k + c8) - c8);
+                kl[par] = 2u * (ring_digits<T::PK == 2>(g.a_dk, ld_k + c8) - c8);
             }
 #pragma unroll
             for (int j = 0; j < NA; ++j) off[j] = a_off[j] + kl[j & 1];
@@ -250,14 +250,14 @@ __global__ __launch_bounds__(64 * T::WVM * T::WVN, T::OCC) void amap_gemm_ring_k
     constexpr uint32_t kCv = BN / 8;   // 16-byte chunks per row
     const uint32_t cv = tid % kCv, n = n0 + cv * 8u;
     const bool n_ok = n < g.N;
-    const uint32_t n_off = g.store_mapped ? g.obase + digits_offset4(g.on, n_ok ? n : 0u) : n;
+    const uint32_t n_off = g.store_mapped ? g.obase + ring_digits<T::PK == 2>(g.on, n_ok ? n : 0u) : n;
 #pragma unroll
     for (uint32_t p = 0; p < BM * kCv / kThreads; ++p) {
         const uint32_t row = p * (kThreads / kCv) + tid / kCv, m = m0 + row;
         u32x4 x = *reinterpret_cast<lds_u32x4 *>(ring_c_slot<BN>(row, cv));
         if ((row >> 4) & 1u) x = u32x4{x.z, x.w, x.x, x.y};
         if (m < g.M && n_ok) {
-            const size_t off = g.store_mapped ? (size_t)(n_off + digits_offset4(g.om, m)) : (size_t)m * g.N + n_off;
+            const size_t off = g.store_mapped ? (size_t)(n_off + ring_digits<T::PK == 2>(g.om, m)) : (size_t)m * g.N + n_off;
             __builtin_nontemporal_store(x, reinterpret_cast<u32x4 *>(g.C + off));
         }
     }
@@ -307,6 +307,16 @@ static bool ring_steps(const Digits &d, uint32_t bk, T2Steps &s) {
     for (; at < kMaxDigits; ++at) {
         s.dl[at] = 0;
         if (at + 1 < kMaxDigits) s.e[at] = 0xFFFFFFFFu;
+    }
+    return true;
+}
+
+// digit j + 1 counts what digit j wraps (see ring_digits)
+static bool nested(const Digits &d) {
+    uint64_t mult = 1;
+    for (uint32_t j = 0; j < d.n; ++j) {
+        if (d.mult[j] != mult) return false;
+        mult *= d.ext[j];
     }
     return true;
 }
@@ -374,6 +384,9 @@ bool ring_plan(const GemmArgs &g, int amode, int wmode, bool tile256, uint32_t n
         r.w = RingOperand{g.W, g.wbase, r.steps, g.wk.ss[0], g.wn};
         if (!ring_steps(g.wk, bk, r.w_steps)) return false;
     }
+    if (!nested(r.a[0].dx) || !nested(r.w.dx) || (p.klane && !nested(r.a_dk)) || (g.store_mapped && (!nested(g.om) || !nested(g.on)))) return false;
+    for (uint32_t j = 1; j < g.n_seg; ++j)
+        if (!nested(r.a[j].dx)) return false;
     r.store_mapped = g.store_mapped;
     r.obase = g.obase;
     r.om = g.om;
@@ -485,15 +498,15 @@ int64_t replay(const RingArgs<kMaxSeg> &r, const GemmArgs &g, const int64_t *a_b
                 for (uint32_t lane = 0; lane < 64; ++lane) {
                                         for (uint32_t j = 0; j < NA; ++j) {
                         const uint32_t b1 = wave * NA + j, c8 = 8u * ring_k_chunk(wave * NA + (j & 1u), lane);
-                        const uint32_t kl = T::KLANE ? 2u * (digits_offset4(r.a_dk, s * BK + c8) - c8) : 0u;
-                        const uint32_t off = ring_block_offset<T::AX, BM>(A.dx, A.base, A.kss, m0, r.M, wave * NA, j, lane) + kl;
+                        const uint32_t kl = T::KLANE ? 2u * (ring_digits<T::PK == 2>(r.a_dk, s * BK + c8) - c8) : 0u;
+                        const uint32_t off = ring_block_offset<T::AX, BM, T::PK == 2>(A.dx, A.base, A.kss, m0, r.M, wave * NA, j, lane) + kl;
                         const int64_t at = ka - (int64_t)kRingBias + (int64_t)off + 1024 * (int64_t)(j % 4u);   // (the instruction's offset)
                         if (at < 0 || at + 16 > a_bytes[seg] || at % 16) ++errors;
                         lds_a[b1 * 64 + lane] = at / 2;
                     }
                     for (uint32_t j = 0; j < NW; ++j) {
                         const uint32_t b1 = wave * NW + j;
-                        const uint32_t off = ring_block_offset<T::WX, BN>(r.w.dx, r.w.base, r.w.kss, n0, r.N, wave * NW, j, lane);
+                        const uint32_t off = ring_block_offset<T::WX, BN, T::PK == 2>(r.w.dx, r.w.base, r.w.kss, n0, r.N, wave * NW, j, lane);
                         const int64_t at = kw - (int64_t)kRingBias + (int64_t)off + 1024 * (int64_t)(j % 4u);
                         if (at < 0 || at + 16 > w_bytes || at % 16) ++errors;
                         lds_w[b1 * 64 + lane] = at / 2;
@@ -543,7 +556,7 @@ int64_t replay(const RingArgs<kMaxSeg> &r, const GemmArgs &g, const int64_t *a_b
             for (uint32_t cv = 0; cv < BN / 8; ++cv) {
                 const uint32_t m = m0 + row, n = n0 + 8 * cv;
                 if (m >= r.M || n >= r.N) continue;
-                const int64_t off = r.store_mapped ? (int64_t)(uint32_t)(r.obase + digits_offset4(r.on, n) + digits_offset4(r.om, m)) : (int64_t)m * r.N + n;
+                const int64_t off = r.store_mapped ? (int64_t)(uint32_t)(r.obase + ring_digits<T::PK == 2>(r.on, n) + ring_digits<T::PK == 2>(r.om, m)) : (int64_t)m * r.N + n;
                 if (off % 8 || off < 0 || off + 8 > (int64_t)g.M * g.N || written[(size_t)off / 8]++) ++errors;
             }
     }

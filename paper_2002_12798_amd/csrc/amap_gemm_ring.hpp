@@ -46,6 +46,30 @@ struct RingArgs : RingCommon {
     RingOperand a[NSEG];
 };
 
+// Index x of a dimension -> its offset.  The digits of a dimension nest (digit j + 1 counts what digit j wraps; the plan
+// refuses others), so n digits take n - 1 divisions, and the one digit that most dimensions have none; digits_offset4
+// takes eight, with nothing to decide.  The short way is the faster one where a product has few tiles and the decode
+// is not hidden behind another tile's work (shapes of PK = 2: the 64 x 64 tiles, and 128 x 128 up to 512 of them):
+// attention output of one sequence, M = 512, K = N = 1024, 6.5 us of kernel time against 7.0, M = 999, K = N = 768
+// 6.4 / 6.9.  With several tiles a compute unit its branches cost more than they save: 1x1 conv behind a concat,
+// M = 100352, K = 320, N = 256, 27.5 us against 25.7.
+template <bool SHORT>
+AMAP_HD uint32_t ring_digits(const Digits &d, uint32_t x) {
+    if constexpr (!SHORT) return digits_offset4(d, x);
+    if (d.n <= 1) return x * (uint32_t)d.ss[0];
+    uint32_t off = 0;
+#if defined(__HIP_DEVICE_COMPILE__)
+#pragma unroll
+#endif
+    for (uint32_t j = 0; j + 1 < (uint32_t)kMaxDigits; ++j) {
+        if (j + 1 >= d.n) break;
+        const uint32_t q = fdiv(x, d.fext[j]);
+        off += (x - q * d.ext[j]) * (uint32_t)d.ss[j];
+        x = q;
+    }
+    return off + x * (uint32_t)d.ss[d.n - 1];
+}
+
 // A load block is the 1 KiB of LDS that one load instruction of a wavefront fills in lane order.
 // K form: block b = rows 8 b .. 8 b + 7, 64 k each; lane i brings row 8 b + i / 8, physical chunk i % 8.
 AMAP_HD uint32_t ring_k_chunk(uint32_t b, uint32_t lane) { return (lane & 7u) ^ (((b & 1u) << 2) | (lane >> 4)); }
@@ -61,24 +85,24 @@ AMAP_HD uint32_t ring_x_chunk(uint32_t b, uint32_t lane) {
 }
 // byte offset of a lane's 16 bytes of load block b, for the first k-step of the operand; rows (columns) past the last
 // one read the last one again, their products are never stored
-template <bool X, int BX>
+template <bool X, int BX, bool SHORT>
 AMAP_HD uint32_t ring_offset(const Digits &dx, uint32_t base, int32_t kss, uint32_t x0, uint32_t xn, uint32_t b, uint32_t lane) {
     if constexpr (X) {
         uint32_t x = x0 + 8u * ring_x_chunk<BX>(b, lane);
         x = x + 8u <= xn ? x : xn - 8u;
-        return 2u * (base + digits_offset4(dx, x) + ring_x_k<BX>(b, lane) * (uint32_t)kss);
+        return 2u * (base + ring_digits<SHORT>(dx, x) + ring_x_k<BX>(b, lane) * (uint32_t)kss);
     } else {
         uint32_t x = x0 + 8u * b + (lane >> 3);
         x = x < xn ? x : xn - 1u;
-        return 2u * (base + digits_offset4(dx, x) + 8u * ring_k_chunk(b, lane));
+        return 2u * (base + ring_digits<SHORT>(dx, x) + 8u * ring_k_chunk(b, lane));
     }
 }
 // The same for block first + j of a wavefront, less the offset that its load instruction adds on both sides, plus
 // kRingBias, which the scalar base lacks: what a lane adds is zero-extended and must not be negative.
 constexpr uint32_t kRingBias = 3072;
-template <bool X, int BX>
+template <bool X, int BX, bool SHORT>
 AMAP_HD uint32_t ring_block_offset(const Digits &dx, uint32_t base, int32_t kss, uint32_t x0, uint32_t xn, uint32_t first, uint32_t j, uint32_t lane) {
-    return ring_offset<X, BX>(dx, base, kss, x0, xn, first + j, lane) + (kRingBias - 1024u * (j % 4u));
+    return ring_offset<X, BX, SHORT>(dx, base, kss, x0, xn, first + j, lane) + (kRingBias - 1024u * (j % 4u));
 }
 // The walk over the k-steps (see T2Steps): a plain step is one subtraction and one addition, a carry (rare) looks the
 // levels up in the argument block.
