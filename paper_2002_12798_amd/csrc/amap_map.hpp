@@ -93,7 +93,10 @@ struct ReverseSlot {
     std::shared_ptr<const amap> map;
     ReverseSlot() = default;
     ReverseSlot(const ReverseSlot &) {}
-    ReverseSlot &operator=(const ReverseSlot &) { return *this; }
+    ReverseSlot &operator=(const ReverseSlot &) {
+        map.reset();
+        return *this;
+    }
 };
 
 }  // namespace amap_detail
