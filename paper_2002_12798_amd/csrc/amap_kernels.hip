@@ -659,7 +659,10 @@ __device__ __forceinline__ void rag_body(const DevPiece &P, char *dst, uint32_t 
             }
         }
     } else {
-        constexpr int kBatch = 4 / CP;
+        // Loads of a lane in flight, in items of CP vectors.  A block of 2-byte elements has 288 items for 256 lanes; measured
+        // with 1, 2, 3, 4 items: [64,55,55,96] 20.5, 20.7, 19.7, 20.8 us, [64,35,35,288] 25.5, 25.6, 24.7, 25.6 us (all
+        // buffers cold).  4-byte elements: 4 (6: [32,35,35,256] 21.5 against 21.3 us).
+        constexpr int kBatch = ES == 2 ? 3 : 4;
         const uint32_t ns = ((U.lcount + CP - 1) / CP) << RVLOG;
         for (uint32_t i0 = tid; i0 < ns; i0 += kBatch * threads) {
             uint32_t v[kBatch][CP][4];
