@@ -641,17 +641,6 @@ __global__ __launch_bounds__(kGemmThreads, 1) void amap_gemm_tile256_kernel(cons
             AMAP_PIN();
         }
     };
-    // Until the older of the two batches of loads in flight has landed, and every wavefront is here.  In the first step of a
-    // workgroup's next tile the 32 stores of the last one are younger than both (loads and stores complete in order): they
-    // need not have been written ([8192,1024] x [1024,4096], two tiles per workgroup: 62.5 -> 62.0 us; the product stays
-    // bound by the power the matrix cores may draw).
-    auto landed = [&](bool stores_behind) __attribute__((always_inline)) {
-        if (!EDGE && stores_behind)
-            asm volatile("s_waitcnt vmcnt(40) lgkmcnt(0)" ::: "memory");
-        else
-            asm volatile("s_waitcnt vmcnt(8) lgkmcnt(0)" ::: "memory");
-        __builtin_amdgcn_s_barrier();
-    };
     uint32_t cur = 0;
     if (ld.c.tile < ntiles) {
         t2_stream_tile<W_KM>(t2_args_again(), ld);
@@ -702,13 +691,14 @@ __global__ __launch_bounds__(kGemmThreads, 1) void amap_gemm_tile256_kernel(cons
             phase(0, 0, cur, 1, cur, 3, 0, 0);
             // W of the next step has landed (A of it may still be on its way), and every wavefront is done with W in `cur`
             // (the loads only count in vmcnt; the compiler does not know of them)
-            const bool stores_behind = ks == 0 && c_tile != blockIdx.x;
-            landed(stores_behind);
+            asm volatile("s_waitcnt vmcnt(8) lgkmcnt(0)" ::: "memory");
+            __builtin_amdgcn_s_barrier();
             AMAP_PIN();
             phase(1, 1, cur, 2, oth, 0, cur, 1);
             phase(0, 2, cur, 3, oth, 1, 0, 0);
             // A of the next step has landed, and every wavefront is done with A in `cur`
-            landed(stores_behind);
+            asm volatile("s_waitcnt vmcnt(8) lgkmcnt(0)" ::: "memory");
+            __builtin_amdgcn_s_barrier();
             AMAP_PIN();
             // (after the workgroup's last step the fragments read ahead are stale and unused)
             phase(1, 3, oth, 0, oth, 2, cur, 2);
