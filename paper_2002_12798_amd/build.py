@@ -54,16 +54,33 @@ def build_lib(verbose: bool = False, extra=()) -> str:
     if verbose:
         for name, u in usage.items():
             print(f"{name}: {u}", file=sys.stderr)
-    spilled = {n: u for n, u in usage.items() if u.get("ScratchSize [bytes/lane]", 0) != 0}
-    # the GEMM kernels address their dynamic LDS from 0: a static allocation (an array the compiler moved there) would overlap it
-    moved = {n: u for n, u in usage.items() if "gemm" in n and u.get("LDS Size [bytes/block]", 0) != 0}
-    if moved:
+    wrong = check_usage(usage)
+    if wrong:
         os.remove(LIB)
-        raise RuntimeError(f"GEMM kernels with static LDS: {moved}")
-    if spilled:
-        os.remove(LIB)
-        raise RuntimeError(f"kernels use scratch memory (argument block copied or registers spilled): {spilled}")
+        raise RuntimeError("; ".join(wrong))
     return LIB
+
+
+# Wavefronts per SIMD of the map kernels.  They are bound by memory and every form inlined into amap_pieces_kernel shares its
+# registers: 74 instead of 66 VGPRs for the sake of one form took it from 7 to 6 and the cross-lane form from 213 to 230 us
+# ([8192,8,64,64] 2-byte elements to channels-last, 1.07 GB).
+MIN_OCCUPANCY = {"amap_rows_kernel": 8, "amap_rows_multi_kernel": 8, "amap_tile16_kernel": 8, "amap_flat_kernel": 8,
+                 "amap_pieces_kernelILi2E": 7, "amap_pieces_kernelILi4E": 6}
+
+
+def check_usage(usage: dict) -> list:
+    """What is wrong with the kernels' resource figures, one line per fault."""
+    wrong = []
+    for name, u in usage.items():
+        if u.get("ScratchSize [bytes/lane]", 0) != 0:
+            wrong.append(f"{name} uses scratch memory (argument block copied or registers spilled): {u}")
+        # the GEMM kernels address their dynamic LDS from 0: a static allocation (an array the compiler moved there) would overlap it
+        if "gemm" in name and u.get("LDS Size [bytes/block]", 0) != 0:
+            wrong.append(f"{name} is a GEMM kernel with static LDS: {u}")
+        for kernel, least in MIN_OCCUPANCY.items():
+            if kernel in name and u.get("Occupancy [waves/SIMD]", least) < least:
+                wrong.append(f"{name} keeps fewer than {least} wavefronts per SIMD: {u}")
+    return wrong
 
 
 def kernel_usage(stderr: str) -> dict:

@@ -659,10 +659,9 @@ __device__ __forceinline__ void rag_body(const DevPiece &P, char *dst, uint32_t 
             }
         }
     } else {
-        // Loads of a lane in flight, in items of CP vectors.  A block of 2-byte elements has 288 items for 256 lanes; measured
-        // with 1, 2, 3, 4 items: [64,55,55,96] 20.5, 20.7, 19.7, 20.8 us, [64,35,35,288] 25.5, 25.6, 24.7, 25.6 us (all
-        // buffers cold).  4-byte elements: 4 (6: [32,35,35,256] 21.5 against 21.3 us).
-        constexpr int kBatch = ES == 2 ? 3 : 4;
+        // Items of CP vectors a lane has in flight: a block of 2-byte elements has at most 36 * 8 = 288 of them for 256 lanes,
+        // one of 4-byte elements 35 * 16 = 560.
+        constexpr int kBatch = ES == 2 ? 2 : 4;
         const uint32_t ns = ((U.lcount + CP - 1) / CP) << RVLOG;
         for (uint32_t i0 = tid; i0 < ns; i0 += kBatch * threads) {
             uint32_t v[kBatch][CP][4];
@@ -695,6 +694,13 @@ __device__ __forceinline__ void rag_body(const DevPiece &P, char *dst, uint32_t 
                     }
                 }
             }
+            // Everything a pass loads has landed here; said outright (vmcnt 0), or the compiler takes loads of the pass before
+            // for still in flight at its top and waits for the first item's loads before it may form the second's addresses in
+            // the registers those would fill.  In cache / cold: [64,55,55,96] 15.0 / 20.8 -> 14.0 / 19.7 us, [64,35,35,288]
+            // 17.5 / 25.3 -> 16.4 / 24.2, [4097,4099] transposed 15.8 / 19.4 -> 14.3 / 19.0, fp32 [32,35,35,256] 14.7 / 21.3 ->
+            // 13.6 / 20.3.  (A third slot, which no lane ever fills, does the same for 2-byte elements in amap_flat_kernel and
+            // costs amap_pieces_kernel 8 VGPRs and one of 7 wavefronts per SIMD: [8192,8,64,64] to channels-last 213 -> 230 us.)
+            __builtin_amdgcn_s_waitcnt(0x0F70);
         }
         __syncthreads();
         // a row's slots of the block; in the first block of a row one more where the row starts inside a slot
