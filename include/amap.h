@@ -374,7 +374,8 @@ amap_status amap_execute_kernel(const void *const *src, void *dst, const amap_t 
  * take (runs along m, gathered sources, blocks of any number of rows, runs of 8
  * and more along k; K a multiple of 64, or of 32 with the runs of A along m and
  * those of W along n), run a kernel with 64 x 64 or 128 x 128 tiles loaded the same
- * way (environment AMAP_GEMM_TILE256=0: the general kernel for all of these);
+ * way (environment AMAP_GEMM_TILE256=0: the general kernel for all of these;
+ * AMAP_GEMM_TILE256=1: 256 x 256 tiles for every product they take);
  * all three add the same products in the same order, so their results are
  * bit-identical.  Operands and sources of 2^31 elements and more (an A of
  * [1048832, 2048], 4.3 GB) are taken by that kernel only, with a plain store;

@@ -1061,8 +1061,9 @@ amap_status gemm_launch(const void *const *A_srcs, bool by_id, const amap_t *A_m
     g.tiles_n = (uint32_t)((N + BN - 1) / BN);
     hipStream_t hs = reinterpret_cast<hipStream_t>(stream);
     // ---- the common case runs on 256 x 256 tiles (see amap_gemm_tile256_kernel)
-    const char *t256 = std::getenv("AMAP_GEMM_TILE256");   // 0: always the general kernel (tests compare the two)
-    const bool tile256_on = !(t256 && t256[0] == '0');
+    // 0: always the general kernel (tests compare the others with it); 1: the 256 x 256 tiles wherever they take the product
+    const char *t256 = std::getenv("AMAP_GEMM_TILE256");
+    const bool tile256_on = !(t256 && t256[0] == '0'), tile256_first = t256 && t256[0] == '1';
     if (g.padded) edge = true;   // the instances that test every vector also take the padding
     // W: row-major [K,N], or kept as [N,K] and read through a transpose map (whole 64-element runs along k, rows of n evenly
     // spaced inside every 256-row block: blocks that never straddle a digit, or one digit for all of n)
@@ -1074,7 +1075,7 @@ amap_status gemm_launch(const void *const *A_srcs, bool by_id, const amap_t *A_m
                          g.dk.ss[0] == 1 && g.dk.ext[0] % T2K == 0 && (!wide || !out_map);
     // ---- smaller tiles (see amap_gemm_ring.hip): whatever the 256 x 256 tiles do not take, and what leaves too many
     // compute units idle with them.  A lane adds up to kRingBias bytes to an offset of 32 bits.
-    if (tile256_on && !wide && largest < (1ll << 31) - 2048 && (!dry || ring)) {
+    if (tile256_on && !(tile256_first && tile256) && !wide && largest < (1ll << 31) - 2048 && (!dry || ring)) {
         RingPlan rp;
         if (ring_plan(g, amode, wmode, tile256, 256, rp)) {
             if (dry) {

@@ -107,6 +107,17 @@ def test_products_of_the_other_kernels_have_no_ring_replay():
         assert _replay(B.amap_compose(shapes, 2, ops), n)[0] == B.AMAP_E_UNSUPPORTED
 
 
+def test_the_switch_for_256_x_256_tiles(monkeypatch):
+    """AMAP_GEMM_TILE256=1 gives the 256 x 256 kernel every product it takes, and no other."""
+    few_tiles = B.amap_compose([(1800, 448)], 2, [])
+    shapes, ops = conv(2, [64], 8)
+    along_m = B.amap_compose(shapes, 2, ops)
+    assert _replay(few_tiles, 1160) == (B.AMAP_OK, 0) and _replay(along_m, 64) == (B.AMAP_OK, 0)
+    monkeypatch.setenv("AMAP_GEMM_TILE256", "1")
+    assert _replay(few_tiles, 1160)[0] == B.AMAP_E_UNSUPPORTED
+    assert _replay(along_m, 64) == (B.AMAP_OK, 0)
+
+
 def test_one_store_map_used_by_several_threads():
     """The reverse of a store map is made at its first use and kept with it: the first uses race here."""
     import threading

@@ -461,6 +461,7 @@ def test_tile256_kernel_vs_oracle_and_general_kernel(dev, case, monkeypatch, cap
         torch.cuda.synchronize()
         return dev.to_host(out)
 
+    monkeypatch.setenv("AMAP_GEMM_TILE256", "1")                  # however few tiles the product has
     monkeypatch.setenv("AMAP_PLAN_TRACE", "1")
     capfd.readouterr()
     got = run()
@@ -491,6 +492,7 @@ def test_tile256_identity_weight_is_exact(dev, monkeypatch, capfd):
     cols = (np.arange(128) * 5 + 3) % 256
     wf = np.zeros((128, 256), dtype=np.float32)
     wf[np.arange(128), cols] = 1.0
+    monkeypatch.setenv("AMAP_GEMM_TILE256", "1")                  # however few tiles the product has
     monkeypatch.setenv("AMAP_PLAN_TRACE", "1")
     capfd.readouterr()
     got = _gemm(dev, src, shape, ops, synth.f32_to_bf16_bits(wf))
@@ -536,6 +538,7 @@ def test_tile256_kernel_with_the_weight_kept_transposed(dev, case, monkeypatch, 
         torch.cuda.synchronize()
         return dev.to_host(out)
 
+    monkeypatch.setenv("AMAP_GEMM_TILE256", "1")                  # however few tiles the product has
     monkeypatch.setenv("AMAP_PLAN_TRACE", "1")
     capfd.readouterr()
     got = run()
@@ -572,6 +575,7 @@ def test_tile256_transposed_identity_weight_is_exact(dev, monkeypatch, capfd):
     wt[cols, np.arange(128)] = 1.0
     a_map, w_map = B.amap_compose([shape], 2, []), B.amap_compose([(256, 128)], 2, [("transpose", (1, 0))])
     out = torch.empty((512, 256), dtype=torch.int16, device="cuda")
+    monkeypatch.setenv("AMAP_GEMM_TILE256", "1")                  # however few tiles the product has
     monkeypatch.setenv("AMAP_PLAN_TRACE", "1")
     capfd.readouterr()
     d_src, d_wt = dev.to_device(src), dev.to_device(synth.f32_to_bf16_bits(wt))    # (kept alive until the product has run)
@@ -622,6 +626,7 @@ def test_tile256_kernel_with_partial_last_tiles(dev, case, monkeypatch, capfd):
         torch.cuda.synchronize()
         return dev.to_host(out)
 
+    monkeypatch.setenv("AMAP_GEMM_TILE256", "1")                  # however few tiles the product has
     monkeypatch.setenv("AMAP_PLAN_TRACE", "1")
     capfd.readouterr()
     got = run()
@@ -685,6 +690,7 @@ def test_random_products_on_the_tile256_kernel(dev, seed, monkeypatch, capfd):
     d_src = dev.to_device(src)
     d_w = dev.to_device(np.ascontiguousarray(w.T) if w_t else w)
     out = torch.full(B.dst_shape(out_map) if out_map else (M, N), 0x5A5A, dtype=torch.int16, device="cuda")
+    monkeypatch.setenv("AMAP_GEMM_TILE256", "1")                  # however few tiles the product has
     monkeypatch.setenv("AMAP_PLAN_TRACE", "1")
     capfd.readouterr()
     B.amap_gemm_gather([d_src.data_ptr()], a_map, d_w.data_ptr(), w_map, N, out_map, out.data_ptr(), 0)
