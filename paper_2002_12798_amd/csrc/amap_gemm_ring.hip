@@ -403,10 +403,9 @@ bool ring_plan(const GemmArgs &g, int amode, int wmode, bool tile256, uint32_t n
         // The 256 x 256-tile kernel takes the product as well, and is ahead where its tiles fill the chip a whole number of
         // times (K = 1024: 256 tiles 34.0 against 38.5 us, 512 tiles 64.8 against 71.6 us; 144 tiles of K = 768 22.8
         // against 25.1 us) and behind it where they leave units idle (8 tiles 23.7 against 8.2 us, 128 tiles 25.1 against
-        // 19.9 us, 288 tiles of K = 768 42.3 against 39.0 us).  Up to 16 tiles of up to six k-steps stay there too: those are
-        // the shapes by which its tests reach every edge of it (about 13 against 10 us).
+        // 19.9 us, 288 tiles of K = 768 42.3 against 39.0 us; one to 16 tiles of few k-steps most of all: [512,384] x [384,1024]
+        // 12.1 against 4.2 us, [1000,384] x [384,1000] 15.2 against 4.8, [33,128] x [128,512] 8.6 against 3.5).
         const uint64_t n256 = tiles(256), rounds = (n256 + n_cu - 1) / n_cu;
-        if (n256 <= 16 && g.K <= 384) return false;
         const double step256 = 0.85 + 0.8 * (double)n256 / (double)(rounds * n_cu);   // the busier the chip, the lower its clock
         const double t256 = 7.5 + (double)rounds * k64 * step256 + 3.0 * (double)(rounds - 1);
         if (std::min(t64, t128) > 0.95 * t256) return false;

@@ -49,6 +49,9 @@ FORMS = [
     (conv(1, [32], 4), 8),                                           # smaller than a tile each way, one k-step
     (([(256, 64), (256, 128), (256, 64)], [("concat", 1)]), 136),    # gathered along k
     (([(200, 64)] * 8, [("concat", 1)]), 72),                        # eight sources
+    (([(512, 128)], []), 256),                                       # two k-steps in a ring of three stages
+    (([(200, 192)], []), 136),                                       # as many as stages
+    (merge(2, 4, 256, 64), 512),                                     # four
 ]
 
 
@@ -99,12 +102,20 @@ def test_replay_of_random_forms():
         assert st != B.AMAP_OK or errors == 0, (shapes, ops, n, errors)
 
 
-def test_products_of_the_other_kernels_have_no_ring_replay():
+def test_products_of_the_other_kernels_have_no_ring_replay(monkeypatch):
     for shapes, ops, n in [([(200, 72)], [], 128),                       # K is no multiple of 64
                            ([(256, 136)], [("pad", (0, 0), (0, 56), 0)], 256),
-                           ([(512, 128)], [], 256),                      # few k-steps and tiles: 256 x 256
                            ([(8192, 1024)], [], 4096)]:                  # fills the chip with 256 x 256 tiles
         assert _replay(B.amap_compose(shapes, 2, ops), n)[0] == B.AMAP_E_UNSUPPORTED
+    monkeypatch.setenv("AMAP_GEMM_TILE256", "1")
+    assert _replay(B.amap_compose([(512, 128)], 2, []), 256)[0] == B.AMAP_E_UNSUPPORTED   # 256 x 256 when asked for
+
+
+@pytest.mark.parametrize("m, k, n", [(512, 128, 256), (8, 128, 8), (33, 256, 512), (1000, 384, 1000), (1024, 384, 1024), (512, 448, 1024)])
+def test_few_tiles_of_few_k_steps_run_on_small_tiles(m, k, n):
+    """Up to 16 tiles of 256 x 256 leave almost the whole chip idle, however short their walk along k."""
+    a, wt = B.amap_compose([(m, k)], 2, []), B.amap_compose([(n, k)], 2, [("transpose", (1, 0))])
+    assert _replay(a, n) == (B.AMAP_OK, 0) and _replay(a, n, wt) == (B.AMAP_OK, 0)
 
 
 def test_the_switch_for_256_x_256_tiles(monkeypatch):
