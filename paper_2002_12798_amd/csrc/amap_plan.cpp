@@ -334,7 +334,6 @@ static bool plan_inter(const KPiece &kp, int es, uint32_t nwlog, int64_t svol, D
 //   dir 1: the source is the flat side (P's source stride == Q's extent): r = P, c = Q
 //   dir 2: dst is the flat side (Q's dst stride == P's extent): r = Q, c = P
 constexpr uint32_t kFlatLdsBytes = 65536;  // rows of 289 (17 x 17): 32.9 us as whole-vector part + tail, 24.8 us as flat tiles of 37 KiB
-constexpr int64_t kLastLevelCache = 256ll << 20;
 constexpr uint32_t kFlatMinRows = 16;      // 48 channels of 7 x 7 images: 23.6 -> 12.5 us; 16 channels: 21.4 -> 11.6 us
 
 // The loops that continue the source-contiguous loop iQ in the source (x, then y of an image: one run of
@@ -369,10 +368,28 @@ struct FlatShape {
     int64_t cb = 0;          // > 0: column-blocked form with this many columns per block
 };
 
+// Blocks of 16 rows towards a contiguous dst hold 16 * C elements of LDS, so few of them share a compute unit.  They are
+// ahead of the column-blocked form only if the whole launch (every piece of the map) is resident at once and each compute
+// unit has two of them to overlap; a last round that is nearly empty, or one block per compute unit, loses more than their
+// longer runs gain.  us with 16 rows / blocked; in cache, cold:
+//   1.1 .. 1.5 of what is resident   [64,35,35,264] 16.9 / 15.9, 25.7 / 22.4   [80,43,43,128] 16.4 / 13.9, 25.9 / 20.8
+//                                    [96,41,41,128] 16.9 / 15.0, 26.6 / 20.8   fp32 [96,29,29,96] 14.7 / 12.0, 19.7 / 16.2
+//   all resident, 2 and more per CU  [56,35,35,288] 13.9 / 15.0, 23.4 / 21.5   [96,39,39,128] 13.0 / 14.1, 23.0 / 20.8
+//                                    [64,41,41,128] 11.4 / 11.5, 17.1 / 15.6   fp32 [64,27,27,128] 9.6 / 10.5, 13.6 / 14.8
+//   fewer than 2 per CU              [24,35,35,256] 7.9 / 7.7, 11.5 / 9.4      [64,41,41,64] 8.4 / 7.5, 11.3 / 9.2
+// (For launches of the middle kind, which move 84 MB at most, the rule takes a program's tensors to be in the 256 MB
+// last-level cache.)
+static bool rows16_fill_chip_once(int64_t C, int64_t ER, int es, int64_t dst_volume) {
+    constexpr int64_t kComputeUnits = 256, kLdsBytes = 160 << 10, kLdsStep = 1280;   // LDS is handed out in steps of 1280 bytes
+    const int64_t image = C * ER, blocks = (dst_volume + image - 1) / image * ((ER + 15) / 16);
+    const int64_t per_cu = kLdsBytes / ((16 * C * es + kLdsStep - 1) / kLdsStep * kLdsStep);
+    return blocks >= 2 * kComputeUnits && blocks <= per_cu * kComputeUnits;
+}
+
 // The row of the flat side may be several loops that continue one another on that side only (the
 // y and x loops of a 7 x 7 image that lands inside a padded image, or comes from a crop): on the other
 // side every loop of the chain has a stride of its own.
-static FlatShape flat_shape(const KPiece &kp, int es) {
+static FlatShape flat_shape(const KPiece &kp, int es, int64_t dst_volume) {
     FlatShape none, f;
     if (kp.fill || (es != 2 && es != 4)) return none;
     const int n = (int)kp.dims.size();
@@ -453,11 +470,9 @@ static FlatShape flat_shape(const KPiece &kp, int es) {
             if (!rag_ok || !(dir == 2 || chain.size() > 1)) continue;
             rlog = 6;
             cb = cb_rag;
-        } else if (rag_ok && rlog == 4 && ER >= 64 && (dir == 1 || 2 * kp.volume() * es > kLastLevelCache / 3)) {
+        } else if (rag_ok && rlog == 4 && ER >= 64 && (dir == 1 || !rows16_fill_chip_once(C, ER, es, dst_volume))) {
             // 16 rows at a time: with the source as the contiguous side the blocked form is faster (35 x 35 positions under 288
-            // channels: 20.9 against 30.7 us; into a padded image 23.2 against 32.1 us); with dst as that side it is for pieces that
-            // do not stay in the last-level cache next to their neighbours (90 MB: 23.8 against 24.9 us, 149 MB: 37.2 against
-            // 42.4 us, 241 MB: 56.4 against 59.8 us), and not for smaller ones (80 MB: 16.9 against 15.5 us, 60 MB 14.4 against 12.0 us)
+            // channels: 20.9 against 30.7 us; into a padded image 23.2 against 32.1 us)
             rlog = 6;
             cb = cb_rag;
         }
@@ -467,8 +482,8 @@ static FlatShape flat_shape(const KPiece &kp, int es) {
     return none;
 }
 
-static bool plan_flat(const KPiece &kp, int es, uint32_t nwlog, DevPiece &dp, uint32_t &lds) {
-    const FlatShape f = flat_shape(kp, es);
+static bool plan_flat(const KPiece &kp, int es, int64_t dst_volume, uint32_t nwlog, DevPiece &dp, uint32_t &lds) {
+    const FlatShape f = flat_shape(kp, es, dst_volume);
     if (!f.dir) return false;
     const int n = (int)kp.dims.size();
     const int64_t V = 16 / es;
@@ -656,7 +671,7 @@ static int plan_piece(const amap &m, const KPiece &kp, int family, uint32_t nwlo
         const bool forced_tile = family == AMAP_K_TILE && (!tile_ok || narrow < 8);
         const bool planned_flat = family < 0 && narrow < 16;
         // (slot_dim: the caller plans a group of pieces as one tile piece and needs the tile geometry proper)
-        if ((planned_flat || forced_tile) && !slot_dim && env_int("AMAP_FLAT", 1) && plan_flat(kp, es, nwlog, dp, lds)) {
+        if ((planned_flat || forced_tile) && !slot_dim && env_int("AMAP_FLAT", 1) && plan_flat(kp, es, volume_of(m.shape), nwlog, dp, lds)) {
             vec_bytes = 16;
             return AMAP_K_TILE;
         }
@@ -1116,7 +1131,7 @@ static bool plan_strided_nw(const amap &m, int family, int nw_forced, Plan &out,
 // A transposing piece whose P or Q extent is not a whole number of vectors would
 // have to run element by element.  Cut it into a main part with whole vectors
 // and a thin tail (fewer than one vector wide), planned on their own.
-static std::vector<KPiece> split_ragged(const KPiece &kp, int es) {
+static std::vector<KPiece> split_ragged(const KPiece &kp, int es, int64_t dst_volume) {
     std::vector<KPiece> out{kp};
     if (kp.fill) return out;
     const int64_t vmax = 16 / es;
@@ -1128,7 +1143,7 @@ static std::vector<KPiece> split_ragged(const KPiece &kp, int es) {
     if (iP < 0 || iQ < 0 || iP == iQ) return out;
     // a flat tile takes the piece whole (under the same switches as in plan_piece)
     const bool flat_on = env_int("AMAP_FLAT", 1) && env_int("AMAP_GATHER", 1) && env_int("AMAP_VEC_BYTES", 16) >= 16;
-    if (flat_on && flat_shape(kp, es).dir) return out;
+    if (flat_on && flat_shape(kp, es, dst_volume).dir) return out;
     std::vector<int64_t> ds_others;
     for (int k = 0; k < (int)kp.dims.size(); ++k)
         if (k != iP) ds_others.push_back(kp.dims[k].ds);
@@ -1234,7 +1249,7 @@ bool plan_strided(const amap &m0, int family, Plan &out) {
     if (m.strided) {
         std::vector<KPiece> ks;
         for (const KPiece &kp : m0.kpieces)
-            for (KPiece &p : split_ragged(kp, m.elem)) ks.push_back(std::move(p));
+            for (KPiece &p : split_ragged(kp, m.elem, volume_of(m.shape))) ks.push_back(std::move(p));
         if (ks.size() <= 4 * m0.kpieces.size() + 8) m.kpieces = std::move(ks);
     }
     out.windowed = false;
