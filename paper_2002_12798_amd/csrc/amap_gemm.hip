@@ -356,6 +356,10 @@ constexpr int kT2Stage = 65536;            // A [256 rows][64 k] + W [64 k][256 
 constexpr int kT2WOff = 32768;             // W part of a stage
 constexpr int kT2Scratch = 2 * kT2Stage;   // output staging, 8 KiB per wavefront
 constexpr int kT2Lds = kT2Scratch + 32768; // 160 KiB: all of a compute unit's LDS
+constexpr int kT2Batch = 8;                // loads of a wavefront per operand and k-step, 1 KiB each
+constexpr int kT2StoreRows = 8;            // stores of a wavefront per 32 rows of its 128 x 128 block, 1 KiB each
+constexpr int kT2Stores = 4 * kT2StoreRows;
+static_assert(kT2Batch * 4 * 1024 == T2M * T2K * 2 && kT2StoreRows * 1024 == 32 * 128 * 2 && kT2Batch + kT2Stores < 64, "what the waits of the k-loop count");
 
 #define AMAP_PIN() __builtin_amdgcn_sched_barrier(0)
 
@@ -641,6 +645,17 @@ __global__ __launch_bounds__(kGemmThreads, 1) void amap_gemm_tile256_kernel(cons
             AMAP_PIN();
         }
     };
+    // Until the older of the two batches of loads in flight has landed, and every wavefront is here.  In the first step of a
+    // workgroup's next tile the stores of the last one are younger than both (loads and stores complete in order) and need
+    // not have been written.  That counts on kT2Stores stores per wavefront and tile, whatever their values: EDGE masks some,
+    // so its wait does not ([8192,1024] x [1024,4096], two tiles per workgroup: 64.25 -> 63.7 us, runs of one side within 0.2).
+    auto landed = [&](bool stores_behind) __attribute__((always_inline)) {
+        if (!EDGE && stores_behind)
+            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"i"(kT2Batch + kT2Stores) : "memory");
+        else
+            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"i"(kT2Batch) : "memory");
+        __builtin_amdgcn_s_barrier();
+    };
     uint32_t cur = 0;
     if (ld.c.tile < ntiles) {
         t2_stream_tile<W_KM>(t2_args_again(), ld);
@@ -655,11 +670,11 @@ __global__ __launch_bounds__(kGemmThreads, 1) void amap_gemm_tile256_kernel(cons
         cursor_next();
         loads_begin();
 #pragma unroll
-        for (int j = 0; j < 8; ++j) load_one(kT2Stage, j, 1);
+        for (int j = 0; j < kT2Batch; ++j) load_one(kT2Stage, j, 1);
 #pragma unroll
-        for (int j = 0; j < 8; ++j) load_one(kT2Stage, j, 0);
+        for (int j = 0; j < kT2Batch; ++j) load_one(kT2Stage, j, 0);
         cursor_next();
-        asm volatile("s_waitcnt vmcnt(16)" ::: "memory");   // the first step is there, the second may still be on its way
+        asm volatile("s_waitcnt vmcnt(%0)" ::"i"(2 * kT2Batch) : "memory");   // the first step is there, the second may still be on its way
         __builtin_amdgcn_s_barrier();
 #pragma unroll
         for (int r = 0; r < 4; ++r) rd_a(0, 0, 0, r);
@@ -683,7 +698,7 @@ __global__ __launch_bounds__(kGemmThreads, 1) void amap_gemm_tile256_kernel(cons
             //   sub-step 0: last reads of W in `cur`                     -> W of the stream's step goes into `cur`
             //   sub-step 2: last reads of A in `cur`                     -> A of the stream's step goes into `cur`
             // The stream's step is two ahead of this one, possibly in the workgroup's next tile.  Each wavefront
-            // has 8 loads per operand and step; vmcnt(8) therefore waits for the older of the two batches in flight.
+            // has kT2Batch loads per operand and step; vmcnt(kT2Batch) therefore waits for the older of the two batches in flight.
             // Once the stream has passed the workgroup's last tile it stands still: the loads of the last two
             // k-steps fetch that tile's last step again, into stages nobody reads any more.
             const uint32_t oth = kT2Stage - cur;
@@ -691,14 +706,13 @@ __global__ __launch_bounds__(kGemmThreads, 1) void amap_gemm_tile256_kernel(cons
             phase(0, 0, cur, 1, cur, 3, 0, 0);
             // W of the next step has landed (A of it may still be on its way), and every wavefront is done with W in `cur`
             // (the loads only count in vmcnt; the compiler does not know of them)
-            asm volatile("s_waitcnt vmcnt(8) lgkmcnt(0)" ::: "memory");
-            __builtin_amdgcn_s_barrier();
+            const bool stores_behind = ks == 0 && c_tile != blockIdx.x;
+            landed(stores_behind);
             AMAP_PIN();
             phase(1, 1, cur, 2, oth, 0, cur, 1);
             phase(0, 2, cur, 3, oth, 1, 0, 0);
             // A of the next step has landed, and every wavefront is done with A in `cur`
-            asm volatile("s_waitcnt vmcnt(8) lgkmcnt(0)" ::: "memory");
-            __builtin_amdgcn_s_barrier();
+            landed(stores_behind);
             AMAP_PIN();
             // (after the workgroup's last step the fragments read ahead are stale and unused)
             phase(1, 3, oth, 0, oth, 2, cur, 2);
@@ -730,7 +744,7 @@ __global__ __launch_bounds__(kGemmThreads, 1) void amap_gemm_tile256_kernel(cons
                     *reinterpret_cast<__attribute__((address_space(3))) u32x2 *>(scr + row_w * 256u + (chunk << 4) + ((half_w ^ (row_w >> 4)) << 3)) = o;
                 }
 #pragma unroll
-            for (int p = 0; p < 8; ++p) {
+            for (int p = 0; p < kT2StoreRows; ++p) {   // (see landed(): each of them is issued, unless EDGE)
                 const uint32_t row = 4u * p + (lane >> 4), chunk = lane & 15u;
                 u32x4 x = *reinterpret_cast<lds_u32x4 *>(scr + row * 256u + ((chunk ^ (row & 15u)) << 4));
                 if (p >= 4) x = u32x4{x.z, x.w, x.x, x.y};
