@@ -580,7 +580,9 @@ def cpu_baseline(synth, name, min_bytes, budget_s=12.0):
 MAP_SOURCES = ["paper_2002_12798_amd/csrc/amap_kernels.hip", "paper_2002_12798_amd/csrc/amap_index.hpp",
                "paper_2002_12798_amd/csrc/amap_compose.cpp", "paper_2002_12798_amd/csrc/amap_plan.cpp",
                "paper_2002_12798_amd/csrc/amap_device.hpp"]
-GEMM_SOURCES = ["paper_2002_12798_amd/csrc/amap_gemm.hip", "paper_2002_12798_amd/csrc/amap_compose.cpp"]
+GEMM_SOURCES = ["paper_2002_12798_amd/csrc/amap_gemm.hip", "paper_2002_12798_amd/csrc/amap_gemm.hpp",
+                "paper_2002_12798_amd/csrc/amap_gemm_ring.hip", "paper_2002_12798_amd/csrc/amap_gemm_ring.hpp",
+                "paper_2002_12798_amd/csrc/amap_compose.cpp"]
 COPY_ELEMENTS = 53248000               # 2-byte elements moved by `--copy-only`: 106,496,000 B read and as many written
 
 
