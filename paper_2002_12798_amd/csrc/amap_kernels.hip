@@ -580,11 +580,13 @@ __device__ __forceinline__ void flat_body(const DevPiece &P, char *dst, uint32_t
     }
 }
 
-// The same for rows too long for LDS: blocks of 64 rows x rag_cb columns (see DevPiece::rag_cb).  What bounds it is the
-// number of LDS and address instructions, not memory: 2-byte elements therefore pass LDS two columns at a time, as dwords
+// The same for rows too long for LDS: blocks of 64 rows x rag_cb columns (see DevPiece::rag_cb).  What bounds it in cache is
+// the number of LDS and address instructions: 2-byte elements therefore pass LDS two columns at a time, as dwords
 // (the same dword of eight rows is two vectors along the rows), and the contiguous side is walked in aligned 16-byte slots of
-// which a row has a power of two per block.  bf16 [64,55,55,96] to channel-major 20.0 -> 15.4 us
-// (74 MB: 4.8 TB/s), [64,35,35,288] 25.7 -> 23.8 us (90 MB, more than stays in the last-level cache).
+// which a row has a power of two per block.  In cache / cold, against 256-byte segments stored with single elements at both
+// ends of each and passed through LDS one by one: bf16 [64,55,55,96] to channel-major (74 MB) 19.5 / 26.0 -> 14.0 / 19.7 us,
+// fp32 [32,35,35,256] (80 MB) 18.7 / 24.3 -> 13.6 / 20.3, [4097,4099] transposed 19.2 / 25.8 -> 14.3 / 18.9; against blocks of
+// 16 whole rows, bf16 [64,35,35,288] (90 MB) 17.3 / 27.8 -> 16.4 / 24.2.
 template <int ES>
 __device__ __forceinline__ void rag_load_rows(uint32_t (&v)[4], const char *src, uint32_t at, uint32_t n) {
     // n < V elements along the rows (a row count that is no whole number of vectors)
@@ -874,8 +876,8 @@ __global__ __launch_bounds__(kMaxThreads) void amap_tile16_kernel(const LaunchAr
 
 // ------------------------------------------------------------------ one flat tile piece + plain rows
 // The same for a flat tile in front (whole images with an odd number of positions, rows of no whole vectors):
-// 56 instead of 66 VGPRs, so 8 instead of 7 wavefronts per SIMD, and no piece search ([64,55,55,96] 17.3 -> 16.4 us,
-// [4097,4099] transposed 16.8 -> 15.3 us, [64,288,35,35] into a padded channels-last image 25.5 -> 24.1 us).
+// 56 instead of 66 VGPRs, so 8 instead of 7 wavefronts per SIMD, and no piece search (in cache: [64,55,55,96] 17.3 -> 16.4 us,
+// [4097,4099] transposed 16.8 -> 15.3 us, both as they then were, [64,288,35,35] into a padded channels-last image 25.5 -> 24.1 us).
 template <int ES, int NT, bool RAG>
 __global__ __launch_bounds__(kMaxThreads) void amap_flat_kernel(const LaunchArgs args, char *dst) {
     extern __shared__ uint4 smem_v[];

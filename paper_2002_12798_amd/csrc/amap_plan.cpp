@@ -453,12 +453,13 @@ static FlatShape flat_shape(const KPiece &kp, int es, int64_t dst_volume) {
         const uint32_t rlog_min = tile_bytes >= 8 ? 5 : 4;
         while (rlog > rlog_min && C * std::min<int64_t>(ER, 1ll << rlog) * es > lds_limit) --rlog;
         int64_t cb = 0;
-        // 64 2-byte (32 4-byte) columns per block: 128-byte row segments (bf16 [64,55,55,96] towards channel-major 15.4 us, with
-        // 256-byte segments 16.4, with 512-byte ones 19.2; fp32 [16,55,55,64] 7.9, 8.9, 10.6).  With the source as the
+        // 64 2-byte (32 4-byte) columns per block: 128-byte row segments (us in cache / cold with 64, 128, 256, 512 bytes: bf16
+        // [64,55,55,96] 17.0, 14.1, 15.4, 18.1 / 21.5, 19.8, 21.2, 24.2; [64,35,35,288] 17.8, 16.5, 18.1, 21.0 / 25.3, 24.3, 25.1,
+        // 27.2; fp32 [32,35,35,256] 15.8, 13.6, 15.8, 17.8 / 20.4, 20.4, 21.9, 23.8).  With the source as the
         // contiguous side and a row of one loop, the cut into a whole-vector part and a one-element tail is as fast or
         // faster (23.7 against 23.8 us; 75 x 75 fp32: 11.9 against 17.4 us), so there the blocked form is left to rows of
         // several loops (padded or cropped images).  From 16 rows on (a block of 64 is then partly empty): what is left for
-        // fewer rows are gathered rows (48 channels of 55 x 55: 145.8 -> 15.4 us; 24 channels 24.6 -> 8.5 us).
+        // fewer rows are gathered rows ([128,55,55,48] 145 -> 13.8 us in cache, 145 -> 19.7 cold).
         const int64_t cb_rag = 128 / es;
         const bool rag_ok = tile_bytes < 8;
         // long rows of one loop under few channels, the source contiguous: the cut into a whole-vector part and a
