@@ -7,6 +7,7 @@ library is missing the import of this module fails: there is no CPU fallback.
 from __future__ import annotations
 
 import ctypes as C
+import operator
 import os
 
 # PyTorch allocates the device memory and owns the streams this library is
@@ -167,9 +168,7 @@ class Map:
         self._h = C.c_void_p(handle)
         self._reads = None  # what _reads() found out (a map never changes)
 
-    @property
-    def handle(self):
-        return self._h
+    handle = property(operator.attrgetter("_h"))
 
     def __del__(self):
         h, self._h = getattr(self, "_h", None), None
@@ -367,18 +366,21 @@ def _src_array(src_ptrs, maps, what):
     return _ptr_array(src_ptrs, n_src)
 
 
-# Addresses and streams are wrapped by hand: c_void_p() takes integers and None only, a c_void_p argument would also take
-# bytes, strings and arrays and hand the address of host memory to the GPU (0.06 us each).
+# Addresses and streams are integers.  What is not goes through c_void_p(), which takes None and refuses the rest: a c_void_p
+# argument would also take bytes, strings and arrays and hand the address of host memory to the GPU.  (Wrapping the integers
+# as well cost 0.1 us of a call.)
 _addr = C.c_void_p
 
 
 def amap_execute(src_ptrs, dst_ptr, m, stream=0, kernel_id=None):
     """src_ptrs: device addresses (ints) indexed by source id; dst_ptr: device address."""
     arr = _src_array(src_ptrs, [m], "amap_execute")
+    if not type(dst_ptr) is type(stream) is int:
+        dst_ptr, stream = _addr(dst_ptr), _addr(stream)
     if kernel_id is None:
-        _check(_L.amap_execute(arr, _addr(dst_ptr), m.handle, _addr(stream)), "amap_execute")
+        _check(_L.amap_execute(arr, dst_ptr, m.handle, stream), "amap_execute")
     else:
-        _check(_L.amap_execute_kernel(arr, _addr(dst_ptr), m.handle, _addr(stream), int(kernel_id)), "amap_execute_kernel")
+        _check(_L.amap_execute_kernel(arr, dst_ptr, m.handle, stream, int(kernel_id)), "amap_execute_kernel")
 
 
 def amap_execute_kernel(src_ptrs, dst_ptr, m, stream, kernel_id):
@@ -388,29 +390,39 @@ def amap_execute_kernel(src_ptrs, dst_ptr, m, stream, kernel_id):
 def amap_execute_multi(src_ptrs, dst_ptrs, maps, stream=0):
     """One source table, several (map, dst) pairs, packed into shared launches."""
     handles = (C.c_void_p * len(maps))(*[m.handle for m in maps])
-    _check(_L.amap_execute_multi(_src_array(src_ptrs, maps, "amap_execute_multi"), _ptr_array(dst_ptrs), handles, len(maps), _addr(stream)),
+    if type(stream) is not int:
+        stream = _addr(stream)
+    _check(_L.amap_execute_multi(_src_array(src_ptrs, maps, "amap_execute_multi"), _ptr_array(dst_ptrs), handles, len(maps), stream),
            "amap_execute_multi")
 
 
 def amap_gemm_fused(a_src_ptr, a_map, w_ptr, n, out_ptr, stream=0):
-    _check(_L.amap_gemm_fused(_addr(a_src_ptr), a_map.handle, _addr(w_ptr), int(n), _addr(out_ptr), _addr(stream)), "amap_gemm_fused")
+    if not type(a_src_ptr) is type(w_ptr) is type(out_ptr) is type(stream) is int:
+        a_src_ptr, w_ptr, out_ptr, stream = _addr(a_src_ptr), _addr(w_ptr), _addr(out_ptr), _addr(stream)
+    _check(_L.amap_gemm_fused(a_src_ptr, a_map.handle, w_ptr, int(n), out_ptr, stream), "amap_gemm_fused")
 
 
 def amap_gemm_fused_store(a_src_ptr, a_map, w_ptr, n, out_map, out_ptr, stream=0):
-    _check(_L.amap_gemm_fused_store(_addr(a_src_ptr), a_map.handle, _addr(w_ptr), int(n), out_map.handle, _addr(out_ptr), _addr(stream)),
+    if not type(a_src_ptr) is type(w_ptr) is type(out_ptr) is type(stream) is int:
+        a_src_ptr, w_ptr, out_ptr, stream = _addr(a_src_ptr), _addr(w_ptr), _addr(out_ptr), _addr(stream)
+    _check(_L.amap_gemm_fused_store(a_src_ptr, a_map.handle, w_ptr, int(n), out_map.handle, out_ptr, stream),
            "amap_gemm_fused_store")
 
 
 def amap_gemm_mapped(a_src_ptr, a_map, w_src_ptr, w_map, out_map, out_ptr, stream=0):
-    _check(_L.amap_gemm_mapped(_addr(a_src_ptr), a_map.handle, _addr(w_src_ptr), w_map.handle,
-                               out_map.handle if out_map is not None else None, _addr(out_ptr), _addr(stream)), "amap_gemm_mapped")
+    if not type(a_src_ptr) is type(w_src_ptr) is type(out_ptr) is type(stream) is int:
+        a_src_ptr, w_src_ptr, out_ptr, stream = _addr(a_src_ptr), _addr(w_src_ptr), _addr(out_ptr), _addr(stream)
+    _check(_L.amap_gemm_mapped(a_src_ptr, a_map.handle, w_src_ptr, w_map.handle,
+                               out_map.handle if out_map is not None else None, out_ptr, stream), "amap_gemm_mapped")
 
 
 def amap_gemm_gather(a_src_ptrs, a_map, w_src_ptr, w_map, n, out_map, out_ptr, stream=0):
     """a_src_ptrs: device pointers by source id of a_map (None for ids the map does not use)."""
-    _check(_L.amap_gemm_gather(_ptr_array(a_src_ptrs, _reads(a_map)[0]), a_map.handle, _addr(w_src_ptr),
+    if not type(w_src_ptr) is type(out_ptr) is type(stream) is int:
+        w_src_ptr, out_ptr, stream = _addr(w_src_ptr), _addr(out_ptr), _addr(stream)
+    _check(_L.amap_gemm_gather(_ptr_array(a_src_ptrs, _reads(a_map)[0]), a_map.handle, w_src_ptr,
                                w_map.handle if w_map is not None else None, int(n),
-                               out_map.handle if out_map is not None else None, _addr(out_ptr), _addr(stream)), "amap_gemm_gather")
+                               out_map.handle if out_map is not None else None, out_ptr, stream), "amap_gemm_gather")
 
 
 class GraphDME:
