@@ -106,7 +106,21 @@ __global__ __launch_bounds__(64 * T::WVM * T::WVN, T::OCC) void amap_gemm_ring_k
     RingWalk a_walk = ring_walk_begin(g.a_steps), w_walk = ring_walk_begin(g.w_steps);
     uint32_t seg = 0, seg_left = g.a[0].steps;   // NSEG > 1: the source the stream reads, and its k-steps to go
     int64_t seg_step = 2 * (int64_t)g.a[0].kss * BK;
-    uint32_t ld_k = 0;
+    // KLANE, runs of A shorter than a step: what k adds to a lane's two chunk orders.  Decoded from k each step it costs two
+    // chains of divisions and reads of the argument block between a step's barrier and its loads; with runs of one length
+    // (KLANE 1, a head's rows) it follows from the step before.  Runs of 80: M = 300, K = 960, N = 1000 8.4 us decoded, 7.3 us
+    // carried on; M = 6300, K = 1600, N = 4096 108 and 99.5 us; M = 3600, K = 1280, N = 2048 26.8 and 26.1 us; runs of 32:
+    // M = 8000, K = 256, N = 2048 16.9 and 16.3 us.
+    uint32_t ld_k = 0, kl[2] = {}, kl_low[2] = {};
+    auto chunk_of = [&](uint32_t par) __attribute__((always_inline)) { return 8u * ring_k_chunk(wave * NA + par, lane); };
+    if constexpr (T::KLANE) {
+#pragma unroll
+        for (uint32_t par = 0; par < 2; ++par) {
+            const uint32_t c8 = chunk_of(par);
+            kl[par] = 2u * (ring_digits<T::PK == 2>(g.a_dk, c8) - c8);
+            kl_low[par] = c8 - fdiv(c8, g.a_dk.fext[0]) * g.a_dk.ext[0];
+        }
+    }
     const uint32_t lds_a = __builtin_amdgcn_readfirstlane(wave * (NA * 1024u)), lds_w = __builtin_amdgcn_readfirstlane(kABytes + wave * (NW * 1024u));
     auto issue = [&](uint32_t stage) __attribute__((always_inline)) {
         if constexpr (T::NSEG > 1) {
@@ -120,17 +134,11 @@ __global__ __launch_bounds__(64 * T::WVM * T::WVN, T::OCC) void amap_gemm_ring_k
                 for (int j = 0; j < NA; ++j) a_off[j] = ring_block_offset<AX, BM, T::PK == 2>(s.dx, s.base, s.kss, m0, g.M, wave * NA, j, lane);
             }
         }
-        if constexpr (T::KLANE) {   // runs of A shorter than a step: k decoded per lane, for the two chunk orders of its blocks
-            uint32_t kl[2], off[NA];
-#pragma unroll
-            for (uint32_t par = 0; par < 2; ++par) {
-                const uint32_t c8 = 8u * ring_k_chunk(wave * NA + par, lane);
-                kl[par] = 2u * (ring_digits<T::PK == 2>(g.a_dk, ld_k + c8) - c8);
-            }
+        if constexpr (T::KLANE) {
+            uint32_t off[NA];
 #pragma unroll
             for (int j = 0; j < NA; ++j) off[j] = a_off[j] + kl[j & 1];
             ring_load<NA>(ka, off, lds_a + stage);
-            ld_k += BK;
         } else {
             ring_load<NA>(ka, a_off, lds_a + stage);
         }
@@ -142,6 +150,16 @@ __global__ __launch_bounds__(64 * T::WVM * T::WVN, T::OCC) void amap_gemm_ring_k
             ka += ring_walk_next(a_walk, g.a_steps);
         }
         kw += ring_walk_next(w_walk, g.w_steps);
+        if constexpr (T::KLANE) {
+#pragma unroll
+            for (uint32_t par = 0; par < 2; ++par) {
+                if constexpr (T::KLANE == 1)
+                    ring_runs_next(g.a_runs, kl_low[par], kl[par]);
+                else
+                    kl[par] = 2u * (ring_digits<T::PK == 2>(g.a_dk, ld_k + BK + chunk_of(par)) - chunk_of(par));
+            }
+            ld_k += BK;
+        }
     };
 
     // ---- fragment addresses.  What does not depend on the stage is kept per lane, the stage and the fragment go into
@@ -280,10 +298,11 @@ amap_status launch(const RingArgs<kMaxSeg> &full, uint32_t grid, hipStream_t str
     return AMAP_OK;
 }
 
-template <int BM_, int BN_, int BK_, int NST_, int PK_, int WVM_, int WVN_, int OCC_, bool AX_, bool WX_, int NSEG_, bool KLANE_>
+template <int BM_, int BN_, int BK_, int NST_, int PK_, int WVM_, int WVN_, int OCC_, bool AX_, bool WX_, int NSEG_, int KLANE_>
 struct Shape {
     static constexpr int BM = BM_, BN = BN_, BK = BK_, NST = NST_, PK = PK_, WVM = WVM_, WVN = WVN_, OCC = OCC_, NSEG = NSEG_;
-    static constexpr bool AX = AX_, WX = WX_, KLANE = KLANE_;
+    static constexpr bool AX = AX_, WX = WX_;
+    static constexpr int KLANE = KLANE_;   // 0: whole steps of k in a run of A; 1, 2: shorter runs, of one length / of any digits
 };
 
 }  // namespace
@@ -350,7 +369,7 @@ bool ring_plan(const GemmArgs &g, int amode, int wmode, bool tile256, uint32_t n
     if (g.padded || g.n_seg > (uint32_t)kMaxSeg) return false;
     p.ax = amode == A_RUNS_M;
     p.wx = wmode != W_MAPPED_K;
-    p.klane = false;
+    p.klane = 0;
     p.n_seg = (int)g.n_seg;
     // k in steps of 64 where a run along k is a 128-byte row of the stage; of 32 (more workgroups per compute unit: 39.8
     // against 42.8 us on a pointwise convolution [100352,256] x [256,512], 30.7 against 44.8 us gathered from four
@@ -373,8 +392,12 @@ bool ring_plan(const GemmArgs &g, int amode, int wmode, bool tile256, uint32_t n
         r.a[0] = RingOperand{g.A_src, g.sbase, r.steps, g.dk.ss[0], g.dm};
         if (!ring_steps(g.dk, bk, r.a_steps)) {
             if (p.ax) return false;
-            p.klane = true;
+            p.klane = g.dk.n == 2 ? 1 : 2;
             r.a_dk = g.dk;
+            if (p.klane == 1) {
+                const uint32_t e = g.dk.ext[0], s0 = (uint32_t)g.dk.ss[0], s1 = (uint32_t)g.dk.ss[1];
+                r.a_runs = RingRuns{e, bk % e, 2u * (bk % e * s0 + bk / e * s1), 2u * (s1 - e * s0)};
+            }
         }
     }
     if (wmode == W_PLAIN) {
@@ -429,12 +452,12 @@ bool ring_plan(const GemmArgs &g, int amode, int wmode, bool tile256, uint32_t n
 
 namespace {
 // the kernel shapes that exist, each handed to f as a type
-template <bool AX, bool WX, int NSEG, bool KLANE, class F>
+template <bool AX, bool WX, int NSEG, int KLANE, class F>
 void with_tile(const RingPlan &p, F f) {
     if constexpr (AX && WX) {
-        f(Shape<128, 128, 32, 2, 1, 2, 2, 4, true, true, NSEG, false>());
+        f(Shape<128, 128, 32, 2, 1, 2, 2, 4, true, true, NSEG, 0>());
     } else if constexpr (AX || NSEG > 1) {
-        f(Shape<128, 128, 64, 2, 1, 2, 2, 2, AX, WX, NSEG, false>());
+        f(Shape<128, 128, 64, 2, 1, 2, 2, 2, AX, WX, NSEG, 0>());
     } else {
         if (p.bm == 64)
             f(Shape<64, 64, 64, 3, 2, 2, 2, 3, false, WX, 1, KLANE>());
@@ -447,11 +470,13 @@ void with_tile(const RingPlan &p, F f) {
 template <bool AX, bool WX, class F>
 void with_sources(const RingPlan &p, F f) {
     if (p.n_seg > 1)
-        with_tile<AX, WX, kMaxSeg, false>(p, f);
+        with_tile<AX, WX, kMaxSeg, 0>(p, f);
+    else if (p.klane == 1)
+        with_tile<AX, WX, 1, !AX ? 1 : 0>(p, f);
     else if (p.klane)
-        with_tile<AX, WX, 1, !AX>(p, f);
+        with_tile<AX, WX, 1, !AX ? 2 : 0>(p, f);
     else
-        with_tile<AX, WX, 1, false>(p, f);
+        with_tile<AX, WX, 1, 0>(p, f);
 }
 template <class F>
 void with_shape(const RingPlan &p, F f) {
@@ -483,6 +508,12 @@ int64_t replay(const RingArgs<kMaxSeg> &r, const GemmArgs &g, const int64_t *a_b
         }
         const uint32_t m0 = tm * BM, n0 = tn * BN;
         int64_t ka = 0, kw = 0;
+        std::vector<uint32_t> kl(kWaves * 64 * 2), low(kl.size());   // as the kernel's kl, kl_low
+        for (size_t i = 0; T::KLANE && i < kl.size(); ++i) {
+            const uint32_t c8 = 8u * ring_k_chunk((uint32_t)(i / 128) * NA + (i & 1u), (uint32_t)(i / 2 % 64));
+            kl[i] = 2u * (ring_digits<T::PK == 2>(r.a_dk, c8) - c8);
+            low[i] = c8 - fdiv(c8, r.a_dk.fext[0]) * r.a_dk.ext[0];
+        }
         RingWalk ao = ring_walk_begin(r.a_steps), wo = ring_walk_begin(r.w_steps);
         uint32_t seg = 0, left = r.a[0].steps, seg_k0 = 0;
         for (uint32_t s = 0; s < r.steps; ++s) {
@@ -495,10 +526,10 @@ int64_t replay(const RingArgs<kMaxSeg> &r, const GemmArgs &g, const int64_t *a_b
             const RingOperand &A = r.a[seg];
             for (uint32_t wave = 0; wave < (uint32_t)kWaves; ++wave)
                 for (uint32_t lane = 0; lane < 64; ++lane) {
-                                        for (uint32_t j = 0; j < NA; ++j) {
-                        const uint32_t b1 = wave * NA + j, c8 = 8u * ring_k_chunk(wave * NA + (j & 1u), lane);
-                        const uint32_t kl = T::KLANE ? 2u * (ring_digits<T::PK == 2>(r.a_dk, s * BK + c8) - c8) : 0u;
-                        const uint32_t off = ring_block_offset<T::AX, BM, T::PK == 2>(A.dx, A.base, A.kss, m0, r.M, wave * NA, j, lane) + kl;
+                    const size_t at_kl = (wave * 64 + lane) * 2;
+                    for (uint32_t j = 0; j < NA; ++j) {
+                        const uint32_t b1 = wave * NA + j;
+                        const uint32_t off = ring_block_offset<T::AX, BM, T::PK == 2>(A.dx, A.base, A.kss, m0, r.M, wave * NA, j, lane) + (T::KLANE ? kl[at_kl + (j & 1u)] : 0u);
                         const int64_t at = ka - (int64_t)kRingBias + (int64_t)off + 1024 * (int64_t)(j % 4u);   // (the instruction's offset)
                         if (at < 0 || at + 16 > a_bytes[seg] || at % 16) ++errors;
                         lds_a[b1 * 64 + lane] = at / 2;
@@ -509,6 +540,14 @@ int64_t replay(const RingArgs<kMaxSeg> &r, const GemmArgs &g, const int64_t *a_b
                         const int64_t at = kw - (int64_t)kRingBias + (int64_t)off + 1024 * (int64_t)(j % 4u);
                         if (at < 0 || at + 16 > w_bytes || at % 16) ++errors;
                         lds_w[b1 * 64 + lane] = at / 2;
+                    }
+                    for (uint32_t par = 0; T::KLANE && par < 2; ++par) {
+                        if (T::KLANE == 1) {
+                            ring_runs_next(r.a_runs, low[at_kl + par], kl[at_kl + par]);
+                        } else {
+                            const uint32_t c8 = 8u * ring_k_chunk(wave * NA + par, lane);
+                            kl[at_kl + par] = 2u * (ring_digits<T::PK == 2>(r.a_dk, (s + 1) * BK + c8) - c8);
+                        }
                     }
                 }
             --left;

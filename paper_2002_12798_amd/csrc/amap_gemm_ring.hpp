@@ -31,12 +31,26 @@ AMAP_HD void ring_tile(const RingTiles &r, uint32_t b, uint32_t grid, uint32_t &
     tm = first + (at - tn * rows);
 }
 
+// Runs of A along k shorter than a k-step, of one length (k has two digits): where a lane's chunk lies follows from where
+// it lay a step before.  ext = length of a run, rem = elements of a step past its last whole run, step = bytes a step moves
+// the chunk, carry = bytes more where it passes the end of a run.
+struct RingRuns {
+    uint32_t ext, rem, step, carry;
+};
+AMAP_HD void ring_runs_next(const RingRuns &r, uint32_t &low, uint32_t &off) {
+    low += r.rem;
+    const bool over = low >= r.ext;
+    low -= over ? r.ext : 0u;
+    off += r.step + (over ? r.carry : 0u);
+}
+
 struct RingCommon {
     uint16_t *C;
     uint32_t M, N, steps;
     RingTiles map;
     T2Steps a_steps, w_steps;
-    Digits a_dk;      // runs of A shorter than a step: k decoded per lane
+    Digits a_dk;      // runs of A shorter than a step: k per lane
+    RingRuns a_runs;
     RingOperand w;
     uint32_t store_mapped, obase;
     Digits om, on;
@@ -142,7 +156,7 @@ AMAP_HD uint32_t ring_c_slot(uint32_t row, uint32_t cv) {
 struct RingPlan {
     int bm, bn, waves;
     bool ax, wx;
-    bool klane;   // runs of A along k shorter than a k-step
+    int klane;    // runs of A along k shorter than a k-step: 1 of one length (k has two digits), 2 more digits
     int n_seg;
     RingArgs<kMaxSeg> args;
 };

@@ -1,0 +1,75 @@
+"""Branches of the GEMM kernel on smaller tiles beyond the forms of test_gemm_ring.py: runs of A along k of every kind of
+length, with two and with more digits of k.  On the CPU the host replay, on the GPU bit for bit against the general kernel,
+which adds the same products in the same order."""
+import numpy as np
+import pytest
+
+from paper_2002_12798_amd import binding as B
+from paper_2002_12798_amd import synth
+from tests.test_gemm_ring import _replay, dev, merge  # noqa: F401  (dev: fixture)
+
+
+def three_digits(g, h, s, d):
+    """[g,h,s,d] as [s, h * g * d]: k has three digits that no two of merge."""
+    return [(g, h, s, d)], [("transpose", (2, 1, 0, 3)), ("reshape", (s, h * g * d))]
+
+
+RUNS = [
+    # whole runs only in a step (16, 32), a part of one left over (24, 40, 48), a run longer than a step (72, 80, 120)
+    *[(merge(2, 64 // np.gcd(d, 64), 45, d), 136) for d in (16, 24, 32, 40, 48, 72, 80, 120)],
+    (three_digits(5, 4, 70, 16), 72),
+    (three_digits(2, 4, 133, 80), 264),
+    (three_digits(3, 8, 50, 24), 64),
+    (three_digits(2, 4, 1800, 80), 1160),   # 128 x 128 tiles of 8 wavefronts
+    (three_digits(2, 4, 3200, 80), 3080),   # and of 4
+]
+
+
+@pytest.mark.parametrize("case", range(len(RUNS)))
+def test_replay_of_short_runs(case, monkeypatch, capfd):
+    (shapes, ops), n = RUNS[case]
+    a = B.amap_compose(shapes, 2, ops)
+    k = B.dst_shape(a)[1]
+    wt = B.amap_compose([(n, k)], 2, [("transpose", (1, 0))])
+    monkeypatch.setenv("AMAP_PLAN_TRACE", "1")
+    for w in (None, wt):
+        capfd.readouterr()
+        assert _replay(a, n, w) == (B.AMAP_OK, 0)
+        assert "runs shorter than a step" in capfd.readouterr().err
+
+
+def _against_general(dev, shapes, a, n, w_map, monkeypatch, capfd, seed, expect):  # noqa: F811
+    import torch
+    m, k = B.dst_shape(a)
+    rng = np.random.default_rng(seed)
+    srcs = [dev.to_device(synth.f32_to_bf16_bits(rng.standard_normal(s).astype(np.float32))) for s in shapes]
+    w = synth.f32_to_bf16_bits((rng.standard_normal((n, k) if w_map else (k, n)) * 0.05).astype(np.float32))
+    w = dev.to_device(w)
+
+    def run():
+        out = torch.full((m, n), 0x5A5A, dtype=torch.int16, device="cuda")
+        B.amap_gemm_gather([t.data_ptr() for t in srcs], a, w.data_ptr(), w_map, n, None, out.data_ptr(), 0)
+        torch.cuda.synchronize()
+        return dev.to_host(out)
+
+    monkeypatch.setenv("AMAP_PLAN_TRACE", "1")
+    capfd.readouterr()
+    got = run()
+    assert expect in capfd.readouterr().err
+    monkeypatch.setenv("AMAP_GEMM_TILE256", "0")
+    general = run()
+    assert "256 x 128 tiles" in capfd.readouterr().err
+    assert np.array_equal(got, general)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", range(len(RUNS)))
+def test_short_runs_against_the_general_kernel(dev, case, monkeypatch, capfd):  # noqa: F811
+    (shapes, ops), n = RUNS[case]
+    a = B.amap_compose(shapes, 2, ops)
+    k = B.dst_shape(a)[1]
+    for w in (None, B.amap_compose([(n, k)], 2, [("transpose", (1, 0))])):
+        print(f"[gpu] short runs {shapes} N={n} w={'nk' if w else 'kn'}", flush=True)
+        assert _replay(a, n, w) == (B.AMAP_OK, 0)
+        _against_general(dev, shapes, a, n, w, monkeypatch, capfd, 900 + case, "runs shorter than a step")
+        monkeypatch.undo()
