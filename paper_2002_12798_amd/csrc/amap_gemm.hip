@@ -516,9 +516,9 @@ __host__ __device__ __forceinline__ size_t t2_store_col(const GemmArgs &g, uint3
     return (size_t)n_lane;
 }
 template <bool MAPPED>
-__host__ __device__ __forceinline__ size_t t2_store_off(const GemmArgs &g, size_t col_off, uint32_t m) {
-    if constexpr (MAPPED) return col_off + digits_offset4(g.om, m);
-    return (size_t)m * g.N + col_off;
+__host__ __device__ __forceinline__ size_t t2_store_row(const GemmArgs &g, uint32_t m) {
+    if constexpr (MAPPED) return (size_t)digits_offset4(g.om, m);
+    return (size_t)m * g.N;
 }
 
 // Workgroups of the persistent grid: as many as give every one the same number of tiles (288 tiles on 256 compute
@@ -736,6 +736,18 @@ __global__ __launch_bounds__(kGemmThreads, 1) void amap_gemm_tile256_kernel(cons
         const uint32_t m_base = tm * T2M + wm * 128u, n_lane = tn * T2N + wn * 128u + (lane & 15u) * 8u;
         const GemmArgs &gs = t2_args_again();   // the store map's digits
         const size_t col_off = t2_store_col<STORE_MAPPED>(gs, n_lane);
+        // A mapped store: lane l decodes rows l and 64 + l of the block's 128, and every store asks the lane that has its row.
+        // Decoded at each store (sixteen lanes the same row, 32 rows one after the other, in a branch of its own each where rows are
+        // masked) a QKV projection split by heads took, M = 2871, K = 768, N = 2304 26.1 us against 21.9, M = 2048, K = 960,
+        // N = 2880 28.6 against 24.8, M = 6886 54.5 against 50.3; [8192,768] x [768,2304] on 128 x 128 tiles 37.0 against 35.9.
+        uint32_t row_off[2];
+        if constexpr (STORE_MAPPED)
+#pragma unroll
+            for (uint32_t h = 0; h < 2; ++h) {
+                uint32_t m = m_base + 64u * h + lane;
+                if constexpr (EDGE) m = m < g.M ? m : g.M - 1u;
+                row_off[h] = (uint32_t)t2_store_row<true>(gs, m);
+            }
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
 #pragma unroll
@@ -754,7 +766,11 @@ __global__ __launch_bounds__(kGemmThreads, 1) void amap_gemm_tile256_kernel(cons
                 u32x4 x = *reinterpret_cast<lds_u32x4 *>(scr + row * 256u + ((chunk ^ (row & 15u)) << 4));
                 if (p >= 4) x = u32x4{x.z, x.w, x.x, x.y};
                 const uint32_t m = m_base + i * 32u + row;
-                const size_t off = t2_store_off<STORE_MAPPED>(gs, col_off, m);
+                size_t off = col_off;
+                if constexpr (STORE_MAPPED)
+                    off += (uint32_t)__builtin_amdgcn_ds_bpermute((int)(4u * (32u * (i & 1) + row)), (int)row_off[i >> 1]);
+                else
+                    off += t2_store_row<false>(gs, m);
                 if (!EDGE || (m < g.M && n_lane < g.N)) __builtin_nontemporal_store(x, reinterpret_cast<u32x4 *>(g.C + off));
             }
         }
@@ -1454,7 +1470,7 @@ amap_status replay_tile256(const GemmArgs &g, int64_t a_bytes, int64_t w_bytes, 
                             for (uint32_t pp = 0; pp < 8; ++pp) {
                                 const uint32_t m = m_base + i * 32u + 4u * pp + (lane >> 4);
                                 if (EDGE && !(m < g.M && n_lane < g.N)) continue;   // the kernel's store mask
-                                const size_t off = g.store_mapped ? t2_store_off<true>(g, col_off, m) : t2_store_off<false>(g, col_off, m);
+                                const size_t off = col_off + (g.store_mapped ? t2_store_row<true>(g, m) : t2_store_row<false>(g, m));
                                 if (off % 8 || (int64_t)off + 8 > c_elems) {
                                     ++errors;
                                     continue;

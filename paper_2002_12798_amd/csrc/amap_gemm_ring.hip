@@ -269,13 +269,23 @@ __global__ __launch_bounds__(64 * T::WVM * T::WVN, T::OCC) void amap_gemm_ring_k
     const uint32_t cv = tid % kCv, n = n0 + cv * 8u;
     const bool n_ok = n < g.N;
     const uint32_t n_off = g.store_mapped ? g.obase + ring_digits<T::PK == 2>(g.on, n_ok ? n : 0u) : n;
+    // A mapped store: a lane decodes one of its wavefront's rows, and every store asks the lane that has its row (see the
+    // epilogue of the 256 x 256 kernel).  Store p of a wavefront covers kWaveRows rows, the workgroup's wavefronts kRows.
+    constexpr uint32_t kWaveRows = 64 / kCv, kRows = kThreads / kCv, kPasses = BM / kRows;
+    static_assert(kPasses * kWaveRows <= 64, "a row per lane");
+    uint32_t row_off = 0;
+    if (g.store_mapped) {
+        const uint32_t m = m0 + lane / kWaveRows % kPasses * kRows + wave * kWaveRows + lane % kWaveRows;
+        row_off = ring_digits<T::PK == 2>(g.om, m < g.M ? m : g.M - 1u);
+    }
 #pragma unroll
-    for (uint32_t p = 0; p < BM * kCv / kThreads; ++p) {
-        const uint32_t row = p * (kThreads / kCv) + tid / kCv, m = m0 + row;
+    for (uint32_t p = 0; p < kPasses; ++p) {
+        const uint32_t row = p * kRows + tid / kCv, m = m0 + row;
         u32x4 x = *reinterpret_cast<lds_u32x4 *>(ring_c_slot<BN>(row, cv));
         if ((row >> 4) & 1u) x = u32x4{x.z, x.w, x.x, x.y};
+        const uint32_t at = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(4u * (p * kWaveRows + lane / kCv)), (int)row_off);
         if (m < g.M && n_ok) {
-            const size_t off = g.store_mapped ? (size_t)(n_off + ring_digits<T::PK == 2>(g.om, m)) : (size_t)m * g.N + n_off;
+            const size_t off = g.store_mapped ? (size_t)(n_off + at) : (size_t)m * g.N + n_off;
             __builtin_nontemporal_store(x, reinterpret_cast<u32x4 *>(g.C + off));
         }
     }
