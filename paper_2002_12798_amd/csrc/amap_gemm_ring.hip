@@ -1,7 +1,7 @@
 // The product of amap_gemm.hip on smaller output tiles: out[m,n] = bf16( sum_k A[m,k] * W[k,n] ), both operands read
 // through composed maps (the consumer loads of the paper's eq. 4), the product stored through one (eq. "store").
 //
-// One output tile per workgroup of 4 wavefronts (2 x 2), k in steps of BK through a ring of NST LDS stages.  Both
+// One output tile per workgroup of 2 to 8 wavefronts, k in steps of BK through a ring of NST LDS stages.  Both
 // operands go from global memory straight into LDS (global_load_lds, 16 bytes per lane): no staging registers, no
 // LDS-write instructions, and because every lane brings its own address the map's digits cost nothing in the loop:
 // a lane's rows (or its 8 columns) are decoded once per tile, a k-step moves one scalar base.
@@ -12,6 +12,11 @@
 //     so that the four k rows of such a read lie in different banks.
 // A step waits for its own loads only (vmcnt counts the loads of the NST - 2 later steps that may stay in flight),
 // passes one barrier, issues the loads of step s + NST - 1 into the stage that step s - 1 has just left, and computes.
+// What bounds a step on small tiles is LDS: the loads' writes (64 bytes a clock and compute unit on their own) and the
+// fragment reads share about 113 bytes a clock, 48 KB per step of 64 x 64 x 64 (0.18 us; measured 0.14 .. 0.20), 72 KB of
+// 64 x 128 (0.27; 0.23 .. 0.31), 96 KB of 128 x 128 (0.36; 0.40 .. 0.47).  Level or slower: wavefronts that share a tile along k
+// and so read less (64 x 128, M = 2400, K = 1280: 11.0 against 9.9 us), two steps per barrier, more stages, reads or loads
+// placed elsewhere among the matrix instructions.
 #include "amap_gemm_ring.hpp"
 
 #include <algorithm>
@@ -99,9 +104,9 @@ __global__ __launch_bounds__(64 * T::WVM * T::WVN, T::OCC) void amap_gemm_ring_k
     static_assert((NA % 4 == 0 || NA == 1 || NA == 2) && (NW % 4 == 0 || NW == 1 || NW == 2), "ring_load");
     uint32_t a_off[NA], w_off[NW];
 #pragma unroll
-    for (int j = 0; j < NA; ++j) a_off[j] = ring_block_offset<AX, BM, T::PK == 2>(g.a[0].dx, g.a[0].base, g.a[0].kss, m0, g.M, wave * NA, j, lane);
+    for (int j = 0; j < NA; ++j) a_off[j] = ring_block_offset<AX, BM, T::SHORT>(g.a[0].dx, g.a[0].base, g.a[0].kss, m0, g.M, wave * NA, j, lane);
 #pragma unroll
-    for (int j = 0; j < NW; ++j) w_off[j] = ring_block_offset<WX, BN, T::PK == 2>(g.w.dx, g.w.base, g.w.kss, n0, g.N, wave * NW, j, lane);
+    for (int j = 0; j < NW; ++j) w_off[j] = ring_block_offset<WX, BN, T::SHORT>(g.w.dx, g.w.base, g.w.kss, n0, g.N, wave * NW, j, lane);
     const char *ka = reinterpret_cast<const char *>(g.a[0].src) - kRingBias, *kw = reinterpret_cast<const char *>(g.w.src) - kRingBias;
     RingWalk a_walk = ring_walk_begin(g.a_steps), w_walk = ring_walk_begin(g.w_steps);
     uint32_t seg = 0, seg_left = g.a[0].steps;   // NSEG > 1: the source the stream reads, and its k-steps to go
@@ -117,7 +122,7 @@ __global__ __launch_bounds__(64 * T::WVM * T::WVN, T::OCC) void amap_gemm_ring_k
 #pragma unroll
         for (uint32_t par = 0; par < 2; ++par) {
             const uint32_t c8 = chunk_of(par);
-            kl[par] = 2u * (ring_digits<T::PK == 2>(g.a_dk, c8) - c8);
+            kl[par] = 2u * (ring_digits<T::SHORT>(g.a_dk, c8) - c8);
             kl_low[par] = c8 - fdiv(c8, g.a_dk.fext[0]) * g.a_dk.ext[0];
         }
     }
@@ -131,7 +136,7 @@ __global__ __launch_bounds__(64 * T::WVM * T::WVN, T::OCC) void amap_gemm_ring_k
                 seg_step = 2 * (int64_t)s.kss * BK;
                 ka = reinterpret_cast<const char *>(s.src) - kRingBias;
 #pragma unroll
-                for (int j = 0; j < NA; ++j) a_off[j] = ring_block_offset<AX, BM, T::PK == 2>(s.dx, s.base, s.kss, m0, g.M, wave * NA, j, lane);
+                for (int j = 0; j < NA; ++j) a_off[j] = ring_block_offset<AX, BM, T::SHORT>(s.dx, s.base, s.kss, m0, g.M, wave * NA, j, lane);
             }
         }
         if constexpr (T::KLANE) {
@@ -156,7 +161,7 @@ __global__ __launch_bounds__(64 * T::WVM * T::WVN, T::OCC) void amap_gemm_ring_k
                 if constexpr (T::KLANE == 1)
                     ring_runs_next(g.a_runs, kl_low[par], kl[par]);
                 else
-                    kl[par] = 2u * (ring_digits<T::PK == 2>(g.a_dk, ld_k + BK + chunk_of(par)) - chunk_of(par));
+                    kl[par] = 2u * (ring_digits<T::SHORT>(g.a_dk, ld_k + BK + chunk_of(par)) - chunk_of(par));
             }
             ld_k += BK;
         }
@@ -268,7 +273,7 @@ __global__ __launch_bounds__(64 * T::WVM * T::WVN, T::OCC) void amap_gemm_ring_k
     constexpr uint32_t kCv = BN / 8;   // 16-byte chunks per row
     const uint32_t cv = tid % kCv, n = n0 + cv * 8u;
     const bool n_ok = n < g.N;
-    const uint32_t n_off = g.store_mapped ? g.obase + ring_digits<T::PK == 2>(g.on, n_ok ? n : 0u) : n;
+    const uint32_t n_off = g.store_mapped ? g.obase + ring_digits<T::SHORT>(g.on, n_ok ? n : 0u) : n;
     // A mapped store: a lane decodes one of its wavefront's rows, and every store asks the lane that has its row (see the
     // epilogue of the 256 x 256 kernel).  Store p of a wavefront covers kWaveRows rows, the workgroup's wavefronts kRows.
     constexpr uint32_t kWaveRows = 64 / kCv, kRows = kThreads / kCv, kPasses = BM / kRows;
@@ -276,25 +281,32 @@ __global__ __launch_bounds__(64 * T::WVM * T::WVN, T::OCC) void amap_gemm_ring_k
     uint32_t row_off = 0;
     if (g.store_mapped) {
         const uint32_t m = m0 + lane / kWaveRows % kPasses * kRows + wave * kWaveRows + lane % kWaveRows;
-        row_off = ring_digits<T::PK == 2>(g.om, m < g.M ? m : g.M - 1u);
+        row_off = ring_digits<T::SHORT>(g.om, m < g.M ? m : g.M - 1u);
     }
 #pragma unroll
     for (uint32_t p = 0; p < kPasses; ++p) {
         const uint32_t row = p * kRows + tid / kCv, m = m0 + row;
         u32x4 x = *reinterpret_cast<lds_u32x4 *>(ring_c_slot<BN>(row, cv));
         if ((row >> 4) & 1u) x = u32x4{x.z, x.w, x.x, x.y};
-        const uint32_t at = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(4u * (p * kWaveRows + lane / kCv)), (int)row_off);
-        if (m < g.M && n_ok) {
-            const size_t off = g.store_mapped ? (size_t)(n_off + at) : (size_t)m * g.N + n_off;
-            __builtin_nontemporal_store(x, reinterpret_cast<u32x4 *>(g.C + off));
-        }
+        size_t off = (size_t)m * g.N + n_off;
+        if (g.store_mapped) off = n_off + (uint32_t)__builtin_amdgcn_ds_bpermute((int)(4u * (p * kWaveRows + lane / kCv)), (int)row_off);
+        if (m < g.M && n_ok) __builtin_nontemporal_store(x, reinterpret_cast<u32x4 *>(g.C + off));
     }
 }
 
 template <class T>
 amap_status launch(const RingArgs<kMaxSeg> &full, uint32_t grid, hipStream_t stream) {
     constexpr int kRing = T::NST * (T::BM + T::BN) * T::BK * 2, kTile = T::BM * T::BN * 2, lds = kRing > kTile ? kRing : kTile;
-    static_assert(lds <= 65536, "what a launch may ask for without an attribute; read offsets are 16 bits as well");
+    static_assert(lds <= 160 * 1024, "what a compute unit has");
+    if constexpr (lds > 65536) {   // what a launch may ask for without it
+        static thread_local bool reserved = false;
+        if (!reserved && hipFuncSetAttribute(reinterpret_cast<const void *>(amap_gemm_ring_kernel<T>), hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess) {
+            (void)hipGetLastError();
+            set_last_error("amap_gemm_ring_kernel: cannot reserve its LDS stages");
+            return AMAP_E_HIP;
+        }
+        reserved = true;
+    }
     RingArgs<T::NSEG> g;
     static_cast<RingCommon &>(g) = full;
     for (int i = 0; i < T::NSEG; ++i) g.a[i] = full.a[i];
@@ -312,6 +324,7 @@ template <int BM_, int BN_, int BK_, int NST_, int PK_, int WVM_, int WVN_, int 
 struct Shape {
     static constexpr int BM = BM_, BN = BN_, BK = BK_, NST = NST_, PK = PK_, WVM = WVM_, WVN = WVN_, OCC = OCC_, NSEG = NSEG_;
     static constexpr bool AX = AX_, WX = WX_;
+    static constexpr bool SHORT = PK_ == 2 || BM_ * BN_ < 128 * 128;   // see ring_digits
     static constexpr int KLANE = KLANE_;   // 0: whole steps of k in a run of A; 1, 2: shorter runs, of one length / of any digits
 };
 
@@ -364,15 +377,82 @@ static Digits one_digit(uint32_t ext, int32_t ss) {
     return d;
 }
 
-// Time of a product on one of the kernel shapes, in us: `fixed` for the launch, the first loads and the last stores, then
-// every compute unit works its share of the tiles off, `step` us per tile and 64 k plus `tile` us per tile.  Fitted to
-// measurements with K = 256 .. 2560 and 1 .. 32 tiles per compute unit (for instance 128 x 128 tiles, K = 1024: 256 tiles
-// 13.9 us, 512 21.2, 1024 38.5, 2048 71.6; 64 x 64 tiles: 512 9.8, 1024 16.9, 2048 27.7).
-static double estimate(uint64_t tiles, double k64, uint32_t n_cu, double step, double tile) {
+// 64 x 64 or 128 x 128 tiles: time in us, `step` per tile and 64 k plus `tile` per tile of a compute unit's share after 4 us for
+// the launch, the first loads and the last stores.  Fitted to measurements with K = 256 .. 2560 and 1 .. 32 tiles per compute
+// unit (for instance 128 x 128 tiles, K = 1024: 256 tiles 13.9 us, 512 21.2, 1024 38.5, 2048 71.6; 64 x 64 tiles: 512 9.8, 1024
+// 16.9, 2048 27.7).
+static double share_of(uint64_t tiles, double k64, uint32_t n_cu, double step, double tile) {
     const double q = (double)tiles / n_cu, up = (double)((tiles + n_cu - 1) / n_cu);
     // up to two tiles share a compute unit, so a few more tiles than units cost less than a second round
     const double rounds = q <= 2.0 ? 0.5 * (std::max(q, 1.0) + up) : up;
     return 4.0 + rounds * (step * k64 + tile);
+}
+
+// The other shapes against that choice, and the 256 x 256 tiles against both: time in us, `launch` for the launch, the first
+// loads and the last stores, `tile` per tile of the busiest compute unit, and for every 64 k of its tiles s1 where it has one
+// and all units do, s2 for two (they share the unit), `more` for each further one; from s0 to s1 up to one tile per unit (the
+// fewer units work, the faster each).  What lies between whole numbers of tiles per unit counts for `up` of the next one.
+// Fitted to 304 products of K = 32 .. 2560 with 1 to 2000 tiles.
+struct RingCost {
+    float launch, s0, s1, s2, more, tile, up;
+};
+static double estimate(const RingCost &c, uint64_t tiles, double k64, uint32_t n_cu) {
+    const double q = (double)tiles / n_cu, up = (double)((tiles + n_cu - 1) / n_cu), e = q > 1.0 ? q + c.up * (up - q) : 1.0;
+    const double step = c.s0 + (c.s1 - c.s0) * std::min(q, 1.0) + (c.s2 - c.s1) * (std::min(e, 2.0) - 1.0) + c.more * std::max(e - 2.0, 0.0);
+    return c.launch + c.tile * e + step * k64;
+}
+// by RingShape: whole steps of k in a run of A; shorter runs; both operands along m and n
+static const RingCost kCostK[] = {{4.64f, .108f, .134f, .243f, .138f, .06f, .29f}, {4.33f, .140f, .203f, .330f, .198f, .10f, .56f},
+                                  {4.28f, .230f, .306f, .589f, .191f, .05f, .71f},
+                                  {2.92f, .000f, .944f, .953f, .388f, 1.99f, .83f}, {2.00f, .356f, .688f, .914f, .450f, 1.57f, .06f}};
+static const RingCost kCostRuns[] = {{4.25f, .146f, .188f, .261f, .157f, .00f, 1.f}, {4.11f, .196f, .236f, .387f, .230f, .00f, 1.f},
+                                     {4.19f, .271f, .344f, .604f, .359f, .01f, 1.f},
+                                     {4.00f, .400f, .800f, 1.20f, .500f, .90f, .6f}, {3.34f, .409f, .714f, 1.16f, .800f, .41f, .34f}};
+static const RingCost kCostX[] = {{}, {5.86f, .193f, .193f, .398f, .239f, .01f, .00f}, {5.46f, .285f, .358f, .628f, .377f, .11f, .19f},
+                                  {5.18f, .439f, .842f, 1.25f, .742f, .17f, .20f}};
+
+static const struct { int bm, bn, waves; } kRingTile[] = {{32, 64, 2}, {64, 64, 4}, {64, 128, 4}, {128, 128, 4}, {128, 128, 8}};
+
+// The shape of a product's tiles, and its estimate.  Along k the 32 x 64 and 64 x 128 tiles have to promise 5 %: below that the
+// estimate errs as often as it gains (222 products of the 304: 2.3 % faster in the mean, three slower by more than 2 %).
+static RingShape ring_shape(const GemmArgs &g, const RingPlan &p, uint32_t n_cu, double &best) {
+    RingShape shape = RS_128x128;
+    best = 1e30;
+    const double k64 = g.K / 64.0;
+    auto tiles = [&](int bm, int bn) { return (uint64_t)((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn); };
+    const double q128 = (double)tiles(128, 128) / n_cu, q64x128 = (double)tiles(64, 128) / n_cu;
+    auto consider = [&](RingShape s, double less = 1.0) {
+        const double t = estimate((p.ax ? kCostX : p.klane ? kCostRuns : kCostK)[s], tiles(kRingTile[s].bm, kRingTile[s].bn), k64, n_cu);
+        if (t < less * best) best = t, shape = s;
+    };
+    if (p.ax || g.n_seg > 1) {
+        // a weight along k with A along m, sources gathered along k: 128 x 128 only
+        consider(RS_128x128);
+        // Smaller tiles where 128 x 128 leave compute units idle, or N or M half of a tile empty: M = 15408, K = 608, N = 128
+        // 13.7 -> 8.9 us, M = 8624, K = 256, N = 512 9.3 -> 8.2, M = 50176, K = 288, N = 64 10.1 -> 8.7; M = 100352, K = 320, N = 256
+        // stays (25.9 against 29).  Fewer than 16 tiles of at most 8 steps stay too: the call takes what issuing it takes, give or
+        // take 1 us.
+        if (p.ax && p.wx && (tiles(128, 128) >= 16 || g.K > 256)) {
+            consider(RS_64x64);
+            consider(RS_64x128);
+        }
+        return shape;
+    }
+    // 8 wavefronts per 128 x 128 tile while at most two workgroups share a compute unit (288 tiles of K = 768: 13.7 against
+    // 15.1 us with 4) and from three tiles per unit on (M = 7680, K = N = 2048 63.7 against 66.7, M = 4900, K = 1024, N = 3072 36.6
+    // against 38.0); 4 in between (M = 4180, K = 1024, N = 2048 28.9 against 29.8, M = 2682, N = 3072 21.0 against 25.3)
+    const bool small = share_of(tiles(64, 64), k64, n_cu, 0.19, 0.35) < share_of(tiles(128, 128), k64, n_cu, 0.47, 1.4);
+    consider(small ? RS_64x64 : q128 <= 2.0 || q128 > 3.0 ? RS_128x128_W8 : RS_128x128);
+    if (p.klane < 2) {
+        const double old = best;
+        // three stages of 64 x 128 while two workgroups find room on every compute unit: M = 2400, K = 1280, N = 768 10.7 -> 9.5 us,
+        // M = 1322, K = N = 2048 22.3 -> 20.2; beyond, the 128 x 128 tiles, with less LDS traffic, are up to 1.4 times as fast
+        if (q64x128 <= 2.0) consider(RS_64x128, 0.95);
+        // few tiles and a long walk: M = 518, K = 2560, N = 512 12.0 -> 9.8 us.  Fewer than 16 tiles of 64 x 64 stay (M = 70,
+        // K = 1024, N = 120 6.4 and 6.3 us).
+        if (tiles(64, 64) >= 16) consider(RS_32x64, best < old ? 1.0 : 0.95);
+    }
+    return shape;
 }
 
 bool ring_plan(const GemmArgs &g, int amode, int wmode, bool tile256, uint32_t n_cu, RingPlan &p) {
@@ -426,27 +506,21 @@ bool ring_plan(const GemmArgs &g, int amode, int wmode, bool tile256, uint32_t n
     r.on = g.on;
 
     // ---- the tile
-    auto tiles = [&](uint64_t t) { return ((g.M + t - 1) / t) * ((g.N + t - 1) / t); };
-    const double k64 = g.K / 64.0;
-    const double t128 = estimate(tiles(128), k64, n_cu, 0.47, 1.4), t64 = estimate(tiles(64), k64, n_cu, 0.19, 0.35);
-    // gathered sources and operands along m: 128 x 128 only (64 x 64 tiles: 51.7 against 39.8 us on the convolution above,
-    // level with it on small images)
-    const bool small = !p.ax && g.n_seg == 1 && t64 < t128;
+    double t;
+    p.shape = ring_shape(g, p, n_cu, t);
     if (tile256) {
         // The 256 x 256-tile kernel takes the product as well, and is ahead where its tiles fill the chip a whole number of
-        // times (K = 1024: 256 tiles 34.0 against 38.5 us, 512 tiles 64.8 against 71.6 us; 144 tiles of K = 768 22.8
-        // against 25.1 us) and behind it where they leave units idle (8 tiles 23.7 against 8.2 us, 128 tiles 25.1 against
-        // 19.9 us, 288 tiles of K = 768 42.3 against 39.0 us; one to 16 tiles of few k-steps most of all: [512,384] x [384,1024]
-        // 12.1 against 4.2 us, [1000,384] x [384,1000] 15.2 against 4.8, [33,128] x [128,512] 8.6 against 3.5).
-        const uint64_t n256 = tiles(256), rounds = (n256 + n_cu - 1) / n_cu;
-        const double step256 = 0.85 + 0.8 * (double)n256 / (double)(rounds * n_cu);   // the busier the chip, the lower its clock
-        const double t256 = 7.5 + (double)rounds * k64 * step256 + 3.0 * (double)(rounds - 1);
-        if (std::min(t64, t128) > 0.95 * t256) return false;
+        // times (M = 8192, K = 1024, N = 4096 63 against 69 us; M = 4608, N = 2048 25.1 against 27.3) and behind it where they
+        // leave units idle (M = 2048, K = 768, N = 2304 20.9 against 12.9 us, M = 512, K = N = 1024 23.7 against 5.8).  Its time,
+        // fitted to the same products: the busier the chip the lower its clock; partial tiles add their masks.
+        const uint64_t n256 = (uint64_t)((g.M + 255) / 256) * ((g.N + 255) / 256), rounds = (n256 + n_cu - 1) / n_cu, wgs = (n256 + rounds - 1) / rounds;
+        const double step256 = 0.96 + 0.53 * (double)wgs / n_cu;
+        const double t256 = 6.3 + (g.M % 256 || g.N % 256 ? 2.2 : 0.0) + (double)rounds * (g.K / 64.0) * step256 + 5.5 * (double)(rounds - 1);
+        if (t > t256) return false;
     }
-    p.bm = p.bn = small ? 64 : 128;
-    // 8 wavefronts per 128 x 128 tile while at most two workgroups share a compute unit (288 tiles of K = 768: 13.7 against
-    // 15.1 us, 512 of K = 1024 19.8 against 21.2 us), 4 beyond (1000 tiles of K = 640: 53.9 against 61.1 us)
-    p.waves = !small && !p.ax && g.n_seg == 1 && tiles(128) <= 2ull * n_cu ? 8 : 4;
+    p.bm = kRingTile[p.shape].bm;
+    p.bn = kRingTile[p.shape].bn;
+    p.waves = kRingTile[p.shape].waves;
     r.map.tiles_m = (uint32_t)((g.M + p.bm - 1) / p.bm);
     r.map.tiles_n = (uint32_t)((g.N + p.bn - 1) / p.bn);
     if ((uint64_t)r.map.tiles_m * r.map.tiles_n >= (1ull << 31)) return false;
@@ -464,15 +538,30 @@ namespace {
 // the kernel shapes that exist, each handed to f as a type
 template <bool AX, bool WX, int NSEG, int KLANE, class F>
 void with_tile(const RingPlan &p, F f) {
-    if constexpr (AX && WX) {
-        f(Shape<128, 128, 32, 2, 1, 2, 2, 4, true, true, NSEG, 0>());
-    } else if constexpr (AX || NSEG > 1) {
-        f(Shape<128, 128, 64, 2, 1, 2, 2, 2, AX, WX, NSEG, 0>());
-    } else {
-        if (p.bm == 64)
+    switch (p.shape) {
+    case RS_32x64:
+        if constexpr (!AX && NSEG == 1 && KLANE < 2) f(Shape<32, 64, 64, 4, 2, 1, 2, 4, false, WX, 1, KLANE>());
+        break;
+    case RS_64x64:
+        if constexpr (AX && WX)
+            f(Shape<64, 64, 32, 4, 2, 2, 2, 4, true, true, NSEG, 0>());
+        else if constexpr (!AX && NSEG == 1)
             f(Shape<64, 64, 64, 3, 2, 2, 2, 3, false, WX, 1, KLANE>());
-        else if (p.waves == 8)
-            f(Shape<128, 128, 64, 2, 2, 2, 4, 4, false, WX, 1, KLANE>());
+        break;
+    case RS_64x128:
+        if constexpr (AX && WX)
+            f(Shape<64, 128, 32, 3, 1, 2, 2, 4, true, true, NSEG, 0>());
+        else if constexpr (!AX && NSEG == 1 && KLANE < 2)
+            f(Shape<64, 128, 64, 3, 2, 2, 2, 2, false, WX, 1, KLANE>());
+        break;
+    case RS_128x128_W8:
+        if constexpr (!AX && NSEG == 1) f(Shape<128, 128, 64, 2, 2, 2, 4, 4, false, WX, 1, KLANE>());
+        break;
+    default:
+        if constexpr (AX && WX)
+            f(Shape<128, 128, 32, 2, 1, 2, 2, 4, true, true, NSEG, 0>());
+        else if constexpr (AX || NSEG > 1)
+            f(Shape<128, 128, 64, 2, 1, 2, 2, 2, AX, WX, NSEG, 0>());
         else
             f(Shape<128, 128, 64, 2, 1, 2, 2, 2, false, WX, 1, KLANE>());
     }
@@ -521,7 +610,7 @@ int64_t replay(const RingArgs<kMaxSeg> &r, const GemmArgs &g, const int64_t *a_b
         std::vector<uint32_t> kl(kWaves * 64 * 2), low(kl.size());   // as the kernel's kl, kl_low
         for (size_t i = 0; T::KLANE && i < kl.size(); ++i) {
             const uint32_t c8 = 8u * ring_k_chunk((uint32_t)(i / 128) * NA + (i & 1u), (uint32_t)(i / 2 % 64));
-            kl[i] = 2u * (ring_digits<T::PK == 2>(r.a_dk, c8) - c8);
+            kl[i] = 2u * (ring_digits<T::SHORT>(r.a_dk, c8) - c8);
             low[i] = c8 - fdiv(c8, r.a_dk.fext[0]) * r.a_dk.ext[0];
         }
         RingWalk ao = ring_walk_begin(r.a_steps), wo = ring_walk_begin(r.w_steps);
@@ -539,14 +628,14 @@ int64_t replay(const RingArgs<kMaxSeg> &r, const GemmArgs &g, const int64_t *a_b
                     const size_t at_kl = (wave * 64 + lane) * 2;
                     for (uint32_t j = 0; j < NA; ++j) {
                         const uint32_t b1 = wave * NA + j;
-                        const uint32_t off = ring_block_offset<T::AX, BM, T::PK == 2>(A.dx, A.base, A.kss, m0, r.M, wave * NA, j, lane) + (T::KLANE ? kl[at_kl + (j & 1u)] : 0u);
+                        const uint32_t off = ring_block_offset<T::AX, BM, T::SHORT>(A.dx, A.base, A.kss, m0, r.M, wave * NA, j, lane) + (T::KLANE ? kl[at_kl + (j & 1u)] : 0u);
                         const int64_t at = ka - (int64_t)kRingBias + (int64_t)off + 1024 * (int64_t)(j % 4u);   // (the instruction's offset)
                         if (at < 0 || at + 16 > a_bytes[seg] || at % 16) ++errors;
                         lds_a[b1 * 64 + lane] = at / 2;
                     }
                     for (uint32_t j = 0; j < NW; ++j) {
                         const uint32_t b1 = wave * NW + j;
-                        const uint32_t off = ring_block_offset<T::WX, BN, T::PK == 2>(r.w.dx, r.w.base, r.w.kss, n0, r.N, wave * NW, j, lane);
+                        const uint32_t off = ring_block_offset<T::WX, BN, T::SHORT>(r.w.dx, r.w.base, r.w.kss, n0, r.N, wave * NW, j, lane);
                         const int64_t at = kw - (int64_t)kRingBias + (int64_t)off + 1024 * (int64_t)(j % 4u);
                         if (at < 0 || at + 16 > w_bytes || at % 16) ++errors;
                         lds_w[b1 * 64 + lane] = at / 2;
@@ -556,7 +645,7 @@ int64_t replay(const RingArgs<kMaxSeg> &r, const GemmArgs &g, const int64_t *a_b
                             ring_runs_next(r.a_runs, low[at_kl + par], kl[at_kl + par]);
                         } else {
                             const uint32_t c8 = 8u * ring_k_chunk(wave * NA + par, lane);
-                            kl[at_kl + par] = 2u * (ring_digits<T::PK == 2>(r.a_dk, (s + 1) * BK + c8) - c8);
+                            kl[at_kl + par] = 2u * (ring_digits<T::SHORT>(r.a_dk, (s + 1) * BK + c8) - c8);
                         }
                     }
                 }
@@ -604,7 +693,7 @@ int64_t replay(const RingArgs<kMaxSeg> &r, const GemmArgs &g, const int64_t *a_b
             for (uint32_t cv = 0; cv < BN / 8; ++cv) {
                 const uint32_t m = m0 + row, n = n0 + 8 * cv;
                 if (m >= r.M || n >= r.N) continue;
-                const int64_t off = r.store_mapped ? (int64_t)(uint32_t)(r.obase + ring_digits<T::PK == 2>(r.on, n) + ring_digits<T::PK == 2>(r.om, m)) : (int64_t)m * r.N + n;
+                const int64_t off = r.store_mapped ? (int64_t)(uint32_t)(r.obase + ring_digits<T::SHORT>(r.on, n) + ring_digits<T::SHORT>(r.om, m)) : (int64_t)m * r.N + n;
                 if (off % 8 || off < 0 || off + 8 > (int64_t)g.M * g.N || written[(size_t)off / 8]++) ++errors;
             }
     }

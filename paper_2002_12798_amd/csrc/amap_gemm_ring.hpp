@@ -63,7 +63,7 @@ struct RingArgs : RingCommon {
 // Index x of a dimension -> its offset.  The digits of a dimension nest (digit j + 1 counts what digit j wraps; the plan
 // refuses others), so n digits take n - 1 divisions, and the one digit that most dimensions have none; digits_offset4
 // takes eight, with nothing to decide.  The short way is the faster one where a product has few tiles and the decode
-// is not hidden behind another tile's work (shapes of PK = 2: the 64 x 64 tiles, and 128 x 128 up to 512 of them):
+// is not hidden behind another tile's work (the tiles smaller than 128 x 128, and those with 8 wavefronts):
 // attention output of one sequence, M = 512, K = N = 1024, 6.5 us of kernel time against 7.0, M = 999, K = N = 768
 // 6.4 / 6.9.  With several tiles a compute unit its branches cost more than they save: 1x1 conv behind a concat,
 // M = 100352, K = 320, N = 256, 27.5 us against 25.7.
@@ -152,8 +152,12 @@ AMAP_HD uint32_t ring_c_slot(uint32_t row, uint32_t cv) {
     return row * (2u * BN) + ((cv ^ (BN >= 128 ? row & 15u : (row >> 1) & 7u)) << 4);
 }
 
+// The tiles there are (W8: 8 wavefronts).
+enum RingShape { RS_32x64 = 0, RS_64x64, RS_64x128, RS_128x128, RS_128x128_W8 };
+
 // A product as the ring kernel runs it: tile, wavefronts, forms of the operands (X: runs along m / n), arguments.
 struct RingPlan {
+    RingShape shape;
     int bm, bn, waves;
     bool ax, wx;
     int klane;    // runs of A along k shorter than a k-step: 1 of one length (k has two digits), 2 more digits

@@ -1,12 +1,12 @@
 """Branches of the GEMM kernel on smaller tiles beyond the forms of test_gemm_ring.py: runs of A along k of every kind of
-length, with two and with more digits of k.  On the CPU the host replay, on the GPU bit for bit against the general kernel,
+length, with two and with more digits of k; the tiles between 32 x 64 and 128 x 128.  On the CPU the host replay, on the GPU bit for bit against the general kernel,
 which adds the same products in the same order."""
 import numpy as np
 import pytest
 
 from paper_2002_12798_amd import binding as B
 from paper_2002_12798_amd import synth
-from tests.test_gemm_ring import _replay, dev, merge  # noqa: F401  (dev: fixture)
+from tests.test_gemm_ring import _replay, conv, dev, merge  # noqa: F401  (dev: fixture)
 
 
 def three_digits(g, h, s, d):
@@ -38,7 +38,7 @@ def test_replay_of_short_runs(case, monkeypatch, capfd):
         assert "runs shorter than a step" in capfd.readouterr().err
 
 
-def _against_general(dev, shapes, a, n, w_map, monkeypatch, capfd, seed, expect):  # noqa: F811
+def _against_general(dev, shapes, a, n, w_map, monkeypatch, capfd, seed, expect, out_map=None):  # noqa: F811
     import torch
     m, k = B.dst_shape(a)
     rng = np.random.default_rng(seed)
@@ -47,8 +47,8 @@ def _against_general(dev, shapes, a, n, w_map, monkeypatch, capfd, seed, expect)
     w = dev.to_device(w)
 
     def run():
-        out = torch.full((m, n), 0x5A5A, dtype=torch.int16, device="cuda")
-        B.amap_gemm_gather([t.data_ptr() for t in srcs], a, w.data_ptr(), w_map, n, None, out.data_ptr(), 0)
+        out = torch.full(B.dst_shape(out_map) if out_map else (m, n), 0x5A5A, dtype=torch.int16, device="cuda")
+        B.amap_gemm_gather([t.data_ptr() for t in srcs], a, w.data_ptr(), w_map, n, out_map, out.data_ptr(), 0)
         torch.cuda.synchronize()
         return dev.to_host(out)
 
@@ -72,4 +72,48 @@ def test_short_runs_against_the_general_kernel(dev, case, monkeypatch, capfd):  
         print(f"[gpu] short runs {shapes} N={n} w={'nk' if w else 'kn'}", flush=True)
         assert _replay(a, n, w) == (B.AMAP_OK, 0)
         _against_general(dev, shapes, a, n, w, monkeypatch, capfd, 900 + case, "runs shorter than a step")
+        monkeypatch.undo()
+
+
+TILES = [
+    # chain -> [M,K], N, weight along k, what the plan says: every instance, partial tiles in M and N, few and many k-steps
+    *[(merge(1, 16, 518, 128), 264, w, "32 x 64 per workgroup of 2") for w in (False, True)],
+    *[(merge(3, 20, 111, 80), 264, w, "32 x 64 per workgroup of 2") for w in (False, True)],          # in short runs
+    *[(merge(1, 20, 2341, 64), 760, w, "64 x 128 per workgroup of 4") for w in (False, True)],
+    *[(merge(5, 20, 469, 80), 760, w, "64 x 128 per workgroup of 4") for w in (False, True)],
+    (merge(1, 8, 7700, 64), 1672, False, "128 x 128 per workgroup of 8"),                             # more than three per unit
+    (conv(40, [320], 12), 72, False, "64 x 64 per workgroup of 4"),                                   # A along m
+    (conv(7, [96, 128, 256, 128], 12), 136, False, "64 x 64 per workgroup of 4"),                     # gathered
+    (conv(16, [256], 28), 120, False, "64 x 128 per workgroup of 4"),
+    (conv(11, [96, 32, 32, 96], 28), 264, False, "64 x 128 per workgroup of 4"),
+    (conv(2, [288], 4), 8, False, "64 x 64 per workgroup of 4"),                                      # smaller than a tile
+]
+
+
+@pytest.mark.parametrize("case", range(len(TILES)))
+def test_replay_of_tiles(case, monkeypatch, capfd):
+    (shapes, ops), n, along_k, expect = TILES[case]
+    a = B.amap_compose(shapes, 2, ops)
+    m, k = B.dst_shape(a)
+    w = B.amap_compose([(n, k)], 2, [("transpose", (1, 0))]) if along_k else None
+    store = B.amap_compose([(m, n)], 2, [("reshape", (m, n // 8, 8)), ("transpose", (1, 0, 2))])
+    monkeypatch.setenv("AMAP_PLAN_TRACE", "1")
+    for out_map in (None, store):
+        capfd.readouterr()
+        assert _replay(a, n, w, out_map) == (B.AMAP_OK, 0)
+        assert expect in capfd.readouterr().err
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", range(len(TILES)))
+def test_tiles_against_the_general_kernel(dev, case, monkeypatch, capfd):  # noqa: F811
+    (shapes, ops), n, along_k, expect = TILES[case]
+    a = B.amap_compose(shapes, 2, ops)
+    m, k = B.dst_shape(a)
+    w = B.amap_compose([(n, k)], 2, [("transpose", (1, 0))]) if along_k else None
+    store = B.amap_compose([(m, n)], 2, [("reshape", (m, n // 8, 8)), ("transpose", (1, 0, 2))])
+    for out_map in (None, store):
+        print(f"[gpu] tiles {shapes} N={n} w={'nk' if along_k else 'kn'} store={out_map is not None}", flush=True)
+        assert _replay(a, n, w, out_map) == (B.AMAP_OK, 0)
+        _against_general(dev, shapes, a, n, w, monkeypatch, capfd, 700 + case, expect, out_map)
         monkeypatch.undo()
