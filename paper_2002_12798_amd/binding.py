@@ -354,15 +354,25 @@ def _reads(m):
     return m._reads
 
 
+_TABLE = tuple(C.c_void_p * n for n in range(17))
+
+
 def _src_array(src_ptrs, maps, what):
     """Source table sized to the maps it serves; a table too short for a source id a map reads is an error
     here, before the library sees it (NULL entries are the library's to judge: an empty map reads none)."""
     n_src, given = 0, len(src_ptrs)
     for m in maps:
-        n, ids = _reads(m)
-        n_src = max(n_src, n)
+        n, ids = m._reads or _reads(m)
+        if n > n_src:
+            n_src = n
         if ids and ids[-1] >= given:
             raise AmapError(AMAP_E_INVALID, f"{what}: no pointer for source {next(i for i in ids if i >= given)}")
+    if n_src <= given <= 16 and given:   # the common table, integers only: as it is (0.3 of 0.6 us)
+        for p in src_ptrs:
+            if type(p) is not int:
+                break
+        else:
+            return _TABLE[given](*src_ptrs)
     return _ptr_array(src_ptrs, n_src)
 
 
@@ -372,13 +382,18 @@ def _src_array(src_ptrs, maps, what):
 _addr = C.c_void_p
 
 
+_execute = _L.amap_execute   # (looked up once: a call is issued in about 5 us)
+
+
 def amap_execute(src_ptrs, dst_ptr, m, stream=0, kernel_id=None):
     """src_ptrs: device addresses (ints) indexed by source id; dst_ptr: device address."""
-    arr = _src_array(src_ptrs, [m], "amap_execute")
+    arr = _src_array(src_ptrs, (m,), "amap_execute")
     if not type(dst_ptr) is type(stream) is int:
         dst_ptr, stream = _addr(dst_ptr), _addr(stream)
     if kernel_id is None:
-        _check(_L.amap_execute(arr, dst_ptr, m.handle, stream), "amap_execute")
+        st = _execute(arr, dst_ptr, m._h, stream)
+        if st:
+            _check(st, "amap_execute")
     else:
         _check(_L.amap_execute_kernel(arr, dst_ptr, m.handle, stream, int(kernel_id)), "amap_execute_kernel")
 

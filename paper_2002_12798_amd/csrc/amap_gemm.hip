@@ -24,6 +24,7 @@
 #include <memory>
 
 #include "amap_gemm_ring.hpp"
+#include "amap_launch.hpp"
 
 using namespace amap_dev;
 using namespace amap_detail;
@@ -1166,24 +1167,23 @@ amap_status gemm_launch(const void *const *A_srcs, bool by_id, const amap_t *A_m
         g.tiles_n = (uint32_t)((N + T2N - 1) / T2N);
         const uint32_t ntiles = g.tiles_m * g.tiles_n;
         const dim3 grid2(t2_workgroups(ntiles, (uint32_t)n_cu)), block2(kGemmThreads);
-        (void)hipGetLastError();   // an earlier, unrelated error on this thread is not this launch's
+        hipError_t e2;
 #define AMAP_T2_LAUNCH(E)                                                                                   \
     do {                                                                                                    \
         if (g.store_mapped && w_km)                                                                         \
-            hipLaunchKernelGGL((amap_gemm_tile256_kernel<true, true, E>), grid2, block2, kT2Lds, hs, g);    \
+            e2 = launch_kernel(amap_gemm_tile256_kernel<true, true, E>, grid2, block2, kT2Lds, hs, g);    \
         else if (g.store_mapped)                                                                            \
-            hipLaunchKernelGGL((amap_gemm_tile256_kernel<true, false, E>), grid2, block2, kT2Lds, hs, g);   \
+            e2 = launch_kernel(amap_gemm_tile256_kernel<true, false, E>, grid2, block2, kT2Lds, hs, g);   \
         else if (w_km)                                                                                      \
-            hipLaunchKernelGGL((amap_gemm_tile256_kernel<false, true, E>), grid2, block2, kT2Lds, hs, g);   \
+            e2 = launch_kernel(amap_gemm_tile256_kernel<false, true, E>, grid2, block2, kT2Lds, hs, g);   \
         else                                                                                                \
-            hipLaunchKernelGGL((amap_gemm_tile256_kernel<false, false, E>), grid2, block2, kT2Lds, hs, g);  \
+            e2 = launch_kernel(amap_gemm_tile256_kernel<false, false, E>, grid2, block2, kT2Lds, hs, g);  \
     } while (0)
         if (edge256)
             AMAP_T2_LAUNCH(true);
         else
             AMAP_T2_LAUNCH(false);
 #undef AMAP_T2_LAUNCH
-        const hipError_t e2 = hipGetLastError();
         if (e2 != hipSuccess) {
             set_last_error("amap_gemm_tile256_kernel", hipGetErrorString(e2));
             return AMAP_E_HIP;
@@ -1198,7 +1198,7 @@ amap_status gemm_launch(const void *const *A_srcs, bool by_id, const amap_t *A_m
     }
     if (const char *tr = std::getenv("AMAP_PLAN_TRACE"); tr && tr[0] != '0')
         std::fprintf(stderr, "amap gemm: 256 x 128 tiles, %lld x %lld x %lld\n", (long long)M, (long long)N, (long long)K);
-    const size_t lds = kLdsBytes;
+    const uint32_t lds = kLdsBytes;
     static thread_local bool attr_done = false;
     if (!attr_done) {
 #define AMAP_GEMM_FN(AM, WM, E) \
@@ -1221,13 +1221,13 @@ amap_status gemm_launch(const void *const *A_srcs, bool by_id, const amap_t *A_m
     }
     const dim3 grid(g.tiles_m * g.tiles_n), block(kGemmThreads);
     const bool seg = g.n_seg > 1;
-    (void)hipGetLastError();   // an earlier, unrelated error on this thread is not this launch's
+    hipError_t e;
 #define AMAP_GEMM_AWE(AM, WM, E)                                                                       \
     do {                                                                                               \
         if (seg)                                                                                       \
-            hipLaunchKernelGGL((amap_gemm_kernel<AM, WM, E, true>), grid, block, lds, hs, g);          \
+            e = launch_kernel(amap_gemm_kernel<AM, WM, E, true>, grid, block, lds, hs, g);          \
         else                                                                                           \
-            hipLaunchKernelGGL((amap_gemm_kernel<AM, WM, E, false>), grid, block, lds, hs, g);         \
+            e = launch_kernel(amap_gemm_kernel<AM, WM, E, false>, grid, block, lds, hs, g);         \
     } while (0)
 #define AMAP_GEMM(WM)                                                                                  \
     do {                                                                                               \
@@ -1248,7 +1248,6 @@ amap_status gemm_launch(const void *const *A_srcs, bool by_id, const amap_t *A_m
         AMAP_GEMM(W_MAPPED_K);
 #undef AMAP_GEMM_AWE
 #undef AMAP_GEMM
-    const hipError_t e = hipGetLastError();
     if (e != hipSuccess) {
         set_last_error("amap_gemm_kernel", hipGetErrorString(e));
         return AMAP_E_HIP;

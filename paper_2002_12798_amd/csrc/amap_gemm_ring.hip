@@ -18,6 +18,7 @@
 // and so read less (64 x 128, M = 2400, K = 1280: 11.0 against 9.9 us), two steps per barrier, more stages, reads or loads
 // placed elsewhere among the matrix instructions.
 #include "amap_gemm_ring.hpp"
+#include "amap_launch.hpp"
 
 #include <algorithm>
 #include <cstring>
@@ -310,9 +311,7 @@ amap_status launch(const RingArgs<kMaxSeg> &full, uint32_t grid, hipStream_t str
     RingArgs<T::NSEG> g;
     static_cast<RingCommon &>(g) = full;
     for (int i = 0; i < T::NSEG; ++i) g.a[i] = full.a[i];
-    (void)hipGetLastError();   // an earlier, unrelated error on this thread is not this launch's
-    hipLaunchKernelGGL(amap_gemm_ring_kernel<T>, dim3(grid), dim3(64 * T::WVM * T::WVN), lds, stream, g);
-    const hipError_t e = hipGetLastError();
+    const hipError_t e = launch_kernel(amap_gemm_ring_kernel<T>, dim3(grid), dim3(64 * T::WVM * T::WVN), lds, stream, g);
     if (e != hipSuccess) {
         set_last_error("amap_gemm_ring_kernel", hipGetErrorString(e));
         return AMAP_E_HIP;

@@ -12,6 +12,7 @@
 #include <type_traits>
 
 #include "amap_index.hpp"
+#include "amap_launch.hpp"
 #include "amap_plan.hpp"
 
 using namespace amap_dev;
@@ -973,18 +974,13 @@ __global__ __launch_bounds__(kProgramThreads) void amap_program_kernel(const Pro
 
 // ------------------------------------------------------------------ host side
 
-// An error left on this thread by an earlier, unrelated HIP call must not be read as the failure
-// of the launch that follows: called right before every launch, launch_failed right after it.
-void clear_stale_error() { (void)hipGetLastError(); }
-
-// true if the launch just made left an error
-bool launch_failed(const char *what) {
-    const hipError_t e = hipGetLastError();
-    if (e == hipSuccess) return false;
+// the status of a launch, its text left for amap_last_error
+amap_status launched(hipError_t e, const char *what) {
+    if (e == hipSuccess) return AMAP_OK;
     char detail[200];
     std::snprintf(detail, sizeof(detail), "%s (%s)", hipGetErrorString(e), hipGetErrorName(e));
     set_last_error(what, detail);
-    return true;
+    return AMAP_E_HIP;
 }
 
 bool overlaps(const void *a, int64_t an, const void *b, int64_t bn) {
@@ -1005,12 +1001,12 @@ amap_status check_pointers(const amap *m, const void *const *src, const void *ds
 }
 
 // one launch of the piece kernel; args.p[].src must already hold device pointers
-amap_status launch_pieces(const LaunchArgs &args, uint32_t blocks, size_t lds, int es, char *d, hipStream_t stream) {
+amap_status launch_pieces(const LaunchArgs &args, uint32_t blocks, uint32_t lds, int es, char *d, hipStream_t stream) {
     bool grouped = false;
     for (uint32_t k = 0; k < args.n_pieces; ++k)
         grouped = grouped || (args.p[k].kind != PK_ROWS && args.p[k].group_n > 1);
     const dim3 grid(blocks), block(64u << args.nwlog);
-    clear_stale_error();
+    hipError_t e = hipSuccess;
     const char *tr = std::getenv("AMAP_PLAN_TRACE");
     const bool trace = tr && tr[0] && tr[0] != '0';   // one line per launch on stderr: the kernel that takes it
     auto say = [&](const char *kernel) {
@@ -1019,7 +1015,7 @@ amap_status launch_pieces(const LaunchArgs &args, uint32_t blocks, size_t lds, i
     if (args.n_pieces == 1 && rows_is_plain(args.p[0], es)) {
         say("amap_rows_kernel");
         const DevPiece &P = args.p[0];
-#define AMAP_LAUNCH_ROWS(ES, NT) hipLaunchKernelGGL((amap_rows_kernel<ES, NT>), grid, block, 0, stream, P, d)
+#define AMAP_LAUNCH_ROWS(ES, NT) e = launch_kernel(amap_rows_kernel<ES, NT>, grid, block, 0, stream, P, d)
         switch ((es == 2 ? 0 : 4) + (int)(args.nt & 3)) {
         case 0: AMAP_LAUNCH_ROWS(2, 0); break;
         case 1: AMAP_LAUNCH_ROWS(2, 1); break;
@@ -1031,11 +1027,11 @@ amap_status launch_pieces(const LaunchArgs &args, uint32_t blocks, size_t lds, i
         default: AMAP_LAUNCH_ROWS(4, 3); break;
         }
 #undef AMAP_LAUNCH_ROWS
-        return launch_failed("amap_rows_kernel") ? AMAP_E_HIP : AMAP_OK;
+        return launched(e, "amap_rows_kernel");
     }
     if (launch_is_plain_rows(args, es)) {
         say("amap_rows_multi_kernel");
-#define AMAP_LAUNCH_ROWSM(ES, NT) hipLaunchKernelGGL((amap_rows_multi_kernel<ES, NT>), grid, block, 0, stream, args, d)
+#define AMAP_LAUNCH_ROWSM(ES, NT) e = launch_kernel(amap_rows_multi_kernel<ES, NT>, grid, block, 0, stream, args, d)
         switch ((es == 2 ? 0 : 4) + (int)(args.nt & 3)) {
         case 0: AMAP_LAUNCH_ROWSM(2, 0); break;
         case 1: AMAP_LAUNCH_ROWSM(2, 1); break;
@@ -1047,16 +1043,16 @@ amap_status launch_pieces(const LaunchArgs &args, uint32_t blocks, size_t lds, i
         default: AMAP_LAUNCH_ROWSM(4, 3); break;
         }
 #undef AMAP_LAUNCH_ROWSM
-        return launch_failed("amap_rows_multi_kernel") ? AMAP_E_HIP : AMAP_OK;
+        return launched(e, "amap_rows_multi_kernel");
     }
     if (launch_is_tile16(args, es)) {
         say("amap_tile16_kernel");
 #define AMAP_LAUNCH_T16(ES, NT)                                                                              \
     do {                                                                                                     \
         if (grouped)                                                                                         \
-            hipLaunchKernelGGL((amap_tile16_kernel<ES, NT, true>), grid, block, lds, stream, args, d);       \
+            e = launch_kernel(amap_tile16_kernel<ES, NT, true>, grid, block, lds, stream, args, d);       \
         else                                                                                                 \
-            hipLaunchKernelGGL((amap_tile16_kernel<ES, NT, false>), grid, block, lds, stream, args, d);      \
+            e = launch_kernel(amap_tile16_kernel<ES, NT, false>, grid, block, lds, stream, args, d);      \
     } while (0)
         switch ((es == 2 ? 0 : 4) + (int)(args.nt & 3)) {
         case 0: AMAP_LAUNCH_T16(2, 0); break;
@@ -1069,7 +1065,7 @@ amap_status launch_pieces(const LaunchArgs &args, uint32_t blocks, size_t lds, i
         default: AMAP_LAUNCH_T16(4, 3); break;
         }
 #undef AMAP_LAUNCH_T16
-        return launch_failed("amap_tile16_kernel") ? AMAP_E_HIP : AMAP_OK;
+        return launched(e, "amap_tile16_kernel");
     }
     if (launch_is_flat(args, es)) {
         say("amap_flat_kernel");
@@ -1077,9 +1073,9 @@ amap_status launch_pieces(const LaunchArgs &args, uint32_t blocks, size_t lds, i
 #define AMAP_LAUNCH_FLAT(ES, NT)                                                                             \
     do {                                                                                                     \
         if (rag)                                                                                             \
-            hipLaunchKernelGGL((amap_flat_kernel<ES, NT, true>), grid, block, lds, stream, args, d);         \
+            e = launch_kernel(amap_flat_kernel<ES, NT, true>, grid, block, lds, stream, args, d);         \
         else                                                                                                 \
-            hipLaunchKernelGGL((amap_flat_kernel<ES, NT, false>), grid, block, lds, stream, args, d);        \
+            e = launch_kernel(amap_flat_kernel<ES, NT, false>, grid, block, lds, stream, args, d);        \
     } while (0)
         switch ((es == 2 ? 0 : 4) + (int)(args.nt & 3)) {
         case 0: AMAP_LAUNCH_FLAT(2, 0); break;
@@ -1092,15 +1088,15 @@ amap_status launch_pieces(const LaunchArgs &args, uint32_t blocks, size_t lds, i
         default: AMAP_LAUNCH_FLAT(4, 3); break;
         }
 #undef AMAP_LAUNCH_FLAT
-        return launch_failed("amap_flat_kernel") ? AMAP_E_HIP : AMAP_OK;
+        return launched(e, "amap_flat_kernel");
     }
     say("amap_pieces_kernel");
 #define AMAP_LAUNCH(ES, NT)                                                                                  \
     do {                                                                                                     \
         if (grouped)                                                                                         \
-            hipLaunchKernelGGL((amap_pieces_kernel<ES, NT, true>), grid, block, lds, stream, args, d);       \
+            e = launch_kernel(amap_pieces_kernel<ES, NT, true>, grid, block, lds, stream, args, d);       \
         else                                                                                                 \
-            hipLaunchKernelGGL((amap_pieces_kernel<ES, NT, false>), grid, block, lds, stream, args, d);      \
+            e = launch_kernel(amap_pieces_kernel<ES, NT, false>, grid, block, lds, stream, args, d);      \
     } while (0)
     switch ((es == 2 ? 0 : 4) + (int)(args.nt & 3)) {
     case 0: AMAP_LAUNCH(2, 0); break;
@@ -1113,20 +1109,21 @@ amap_status launch_pieces(const LaunchArgs &args, uint32_t blocks, size_t lds, i
     default: AMAP_LAUNCH(4, 3); break;
     }
 #undef AMAP_LAUNCH
-    return launch_failed("amap_pieces_kernel") ? AMAP_E_HIP : AMAP_OK;
+    return launched(e, "amap_pieces_kernel");
 }
 
-void patch_sources(LaunchArgs &args, const void *const *src, int es) {
-    for (uint32_t k = 0; k < args.n_pieces; ++k) {
-        const uintptr_t id = (uintptr_t)args.p[k].src;
-        args.p[k].src = id ? (const char *)src[id - 1] + (size_t)args.p[k].swin * (size_t)es : nullptr;
-    }
+// the piece with its source's address in place of the id
+void patch_source(DevPiece &p, const void *const *src, int es) {
+    const uintptr_t id = (uintptr_t)p.src;
+    p.src = id ? (const char *)src[id - 1] + (size_t)p.swin * (size_t)es : nullptr;
 }
 
 amap_status launch_strided(const amap *m, const Plan &plan, const void *const *src, void *dst, hipStream_t stream) {
     for (size_t i = 0; i < plan.launches.size(); ++i) {
-        LaunchArgs args = plan.launches[i];
-        patch_sources(args, src, m->elem);
+        const LaunchArgs &planned = plan.launches[i];
+        LaunchArgs args;   // the pieces there are, not the whole 4 KB; no kernel uses an entry beyond them
+        std::memcpy(&args, &planned, offsetof(LaunchArgs, p) + planned.n_pieces * sizeof(DevPiece));
+        for (uint32_t k = 0; k < args.n_pieces; ++k) patch_source(args.p[k], src, m->elem);
         amap_status st = launch_pieces(args, plan.grid[i], plan.lds_bytes[i], m->elem, (char *)dst, stream);
         if (st != AMAP_OK) return st;
     }
@@ -1148,12 +1145,9 @@ amap_status launch_program(const amap *m, const Plan &plan, const void *const *s
     for (int i = 0; i < plan.n_prog_src && i < (int)m->src_shapes.size(); ++i) t.p[i] = src[i];
     const uint32_t total = (uint32_t)volume_of(m->shape);
     const uint32_t grid = (total + kProgramThreads - 1) / kProgramThreads;
-    clear_stale_error();
-    if (m->elem == 2)
-        hipLaunchKernelGGL(amap_program_kernel<2>, dim3(grid), dim3(kProgramThreads), 0, stream, plan.prog, t, (char *)dst, total);
-    else
-        hipLaunchKernelGGL(amap_program_kernel<4>, dim3(grid), dim3(kProgramThreads), 0, stream, plan.prog, t, (char *)dst, total);
-    return launch_failed("amap_program_kernel") ? AMAP_E_HIP : AMAP_OK;
+    const hipError_t e = m->elem == 2 ? launch_kernel(amap_program_kernel<2>, dim3(grid), dim3(kProgramThreads), 0, stream, plan.prog, t, (char *)dst, total)
+                                      : launch_kernel(amap_program_kernel<4>, dim3(grid), dim3(kProgramThreads), 0, stream, plan.prog, t, (char *)dst, total);
+    return launched(e, "amap_program_kernel");
 }
 
 }  // namespace
@@ -1213,13 +1207,13 @@ extern "C" amap_status amap_execute_multi(const void *const *src, void *const *d
             base = std::min(base, (uintptr_t)dst[i]);
         }
         if (base == UINTPTR_MAX) return AMAP_OK;  // nothing to write
-        LaunchArgs cur;
+        LaunchArgs cur;   // (entries beyond n_pieces stay unset)
         uint32_t blocks = 0, lds = 0;
-        std::memset(&cur, 0, sizeof(cur));
+        cur.n_pieces = cur.nwlog = cur.nt = cur.xcd_remap = 0;
         auto flush = [&]() -> amap_status {
             if (cur.n_pieces == 0) return AMAP_OK;
             amap_status st = launch_pieces(cur, blocks, lds, es, reinterpret_cast<char *>(base), s);
-            std::memset(&cur, 0, sizeof(cur));
+            cur.n_pieces = cur.nwlog = cur.nt = cur.xcd_remap = 0;
             blocks = 0;
             lds = 0;
             return st;
@@ -1239,8 +1233,7 @@ extern "C" amap_status amap_execute_multi(const void *const *src, void *const *d
             }
             const uint64_t shift = ((uintptr_t)dst[i] - base) / (uint64_t)es;  // dst pointers are 16-byte aligned
             for (size_t j = 0; j < plan->launches.size(); ++j) {
-                LaunchArgs a = plan->launches[j];
-                patch_sources(a, src, es);
+                const LaunchArgs &a = plan->launches[j];
                 const bool fits = cur.n_pieces == 0 ||
                                   (cur.nwlog == a.nwlog && cur.n_pieces + a.n_pieces <= (uint32_t)kMaxPiecesPerLaunch &&
                                    (uint64_t)blocks + plan->grid[j] < (1u << 31));
@@ -1256,10 +1249,11 @@ extern "C" amap_status amap_execute_multi(const void *const *src, void *const *d
                 }
                 cur.xcd_remap |= a.xcd_remap;
                 for (uint32_t k = 0; k < a.n_pieces; ++k) {
-                    DevPiece p = a.p[k];
+                    DevPiece &p = cur.p[cur.n_pieces++];
+                    p = a.p[k];
+                    patch_source(p, src, es);
                     p.first_block += blocks;
                     p.dwin += shift;
-                    cur.p[cur.n_pieces++] = p;
                 }
                 blocks += plan->grid[j];
                 lds = std::max<uint32_t>(lds, plan->lds_bytes[j]);
