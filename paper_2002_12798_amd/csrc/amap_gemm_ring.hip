@@ -412,8 +412,8 @@ static const RingCost kCostX[] = {{}, {5.86f, .193f, .193f, .398f, .239f, .01f, 
 
 static const struct { int bm, bn, waves; } kRingTile[] = {{32, 64, 2}, {64, 64, 4}, {64, 128, 4}, {128, 128, 4}, {128, 128, 8}};
 
-// The shape of a product's tiles, and its estimate.  Along k the 32 x 64 and 64 x 128 tiles have to promise 5 %: below that the
-// estimate errs as often as it gains (222 products of the 304: 2.3 % faster in the mean, three slower by more than 2 %).
+// The shape of a product's tiles, and its estimate.  Along k the 32 x 64 and 64 x 128 tiles have to promise 4 %: below that the
+// estimate errs as often as it gains (222 products of the 304: 2.9 % faster in the mean, five slower by 2 % and more).
 static RingShape ring_shape(const GemmArgs &g, const RingPlan &p, uint32_t n_cu, double &best) {
     RingShape shape = RS_128x128;
     best = 1e30;
@@ -446,10 +446,10 @@ static RingShape ring_shape(const GemmArgs &g, const RingPlan &p, uint32_t n_cu,
         const double old = best;
         // three stages of 64 x 128 while two workgroups find room on every compute unit: M = 2400, K = 1280, N = 768 10.7 -> 9.5 us,
         // M = 1322, K = N = 2048 22.3 -> 20.2; beyond, the 128 x 128 tiles, with less LDS traffic, are up to 1.4 times as fast
-        if (q64x128 <= 2.0) consider(RS_64x128, 0.95);
+        if (q64x128 <= 2.0) consider(RS_64x128, 0.96);
         // few tiles and a long walk: M = 518, K = 2560, N = 512 12.0 -> 9.8 us.  Fewer than 16 tiles of 64 x 64 stay (M = 70,
         // K = 1024, N = 120 6.4 and 6.3 us).
-        if (tiles(64, 64) >= 16) consider(RS_32x64, best < old ? 1.0 : 0.95);
+        if (tiles(64, 64) >= 16) consider(RS_32x64, best < old ? 1.0 : 0.96);
     }
     return shape;
 }
