@@ -438,10 +438,10 @@ static RingShape ring_shape(const GemmArgs &g, const RingPlan &p, uint32_t n_cu,
         return shape;
     }
     // 8 wavefronts per 128 x 128 tile while at most two workgroups share a compute unit (288 tiles of K = 768: 13.7 against
-    // 15.1 us with 4) and from three tiles per unit on (M = 7680, K = N = 2048 63.7 against 66.7, M = 4900, K = 1024, N = 3072 36.6
-    // against 38.0); 4 in between (M = 4180, K = 1024, N = 2048 28.9 against 29.8, M = 2682, N = 3072 21.0 against 25.3)
+    // 15.1 us with 4) and, in a long walk, from three tiles per unit on (M = 7680, K = N = 2048 63.7 against 66.7, M = 4900, K = 1024,
+    // N = 3072 36.6 against 38.0; K = 960, M = 6886, N = 2880 47.3 against 46.7); 4 in between (M = 4180, K = 1024, N = 2048 28.9 against 29.8, M = 2682, N = 3072 21.0 against 25.3)
     const bool small = share_of(tiles(64, 64), k64, n_cu, 0.19, 0.35) < share_of(tiles(128, 128), k64, n_cu, 0.47, 1.4);
-    consider(small ? RS_64x64 : q128 <= 2.0 || q128 > 3.0 ? RS_128x128_W8 : RS_128x128);
+    consider(small ? RS_64x64 : q128 <= 2.0 || (q128 > 3.0 && g.K >= 1024) ? RS_128x128_W8 : RS_128x128);
     if (p.klane < 2) {
         const double old = best;
         // three stages of 64 x 128 while two workgroups find room on every compute unit: M = 2400, K = 1280, N = 768 10.7 -> 9.5 us,

@@ -158,7 +158,7 @@ AMAP_HD RagUnit rag_unit(const DevPiece &P, uint32_t t) {
         rest = q;
     }
     RagUnit u;
-    u.doff = d + (P.flat == 1 ? r0 : r0 * P.eP + c0);
+    u.doff = d + (P.flat == 1 ? r0 : r0 * (uint32_t)P.ssP + c0);
     u.soff = s + (P.flat == 1 ? r0 * P.eP + c0 : r0);
     const uint32_t rleft = P.EQ - r0, cleft = P.eP - c0;
     u.rcount = rleft < (1u << P.lqlog) ? rleft : (1u << P.lqlog);
@@ -178,7 +178,7 @@ struct RagRow {
 AMAP_HD RagRow rag_row(const DevPiece &P, const RagUnit &u, uint32_t r) {
     const uint32_t V = 1u << P.vlog, left = P.eP - u.c0;
     RagRow w;
-    w.a = u.doff + r * P.eP;
+    w.a = u.doff + r * (uint32_t)P.ssP;
     const uint32_t end = w.a + left, next = (w.a + u.ccount + V - 1u) & ~(V - 1u);
     w.lo = u.c0 ? (w.a + V - 1u) & ~(V - 1u) : w.a;
     w.hi = u.ccount == left || next > end ? end : next;

@@ -406,7 +406,12 @@ static FlatShape flat_shape(const KPiece &kp, int es, int64_t dst_volume) {
     int64_t EQc = Q.extent;
     if (env_int("AMAP_TILE_CHAIN_VEC", 1)) q_chain(kp, iP, iQ, EQc);
     const int64_t tile_bytes = (int64_t)common_pow2((uint32_t)V, {P.extent, EQc}, {}) * es;
-    if (tile_bytes >= 16) return none;
+    // dst without vectors of two elements: the tile forms move single elements there, whatever the extents allow
+    std::vector<int64_t> ds_rest;
+    for (int k = 0; k < n; ++k)
+        if (k != iP) ds_rest.push_back(kp.dims[k].ds);
+    const bool no_dst_vec = common_pow2((uint32_t)V, {kp.dbase}, ds_rest) == 1;
+    if (tile_bytes >= 16 && !no_dst_vec) return none;
     for (int dir = 1; dir <= 2; ++dir) {
         // dir 1: rows are contiguous in the source, from Q outwards, until P's source stride is reached;
         // dir 2: in dst, from P outwards, until Q's dst stride is reached
@@ -422,7 +427,18 @@ static FlatShape flat_shape(const KPiece &kp, int es, int64_t dst_volume) {
             chain.push_back(next);
             C *= kp.dims[next].extent;
         }
-        if (flat_stride(iR) != C) continue;
+        // Rows of dst further apart than they are long, an odd number of elements from one to the next (channels padded by one, joined
+        // to an odd number): the column-blocked form takes them, it stores row by row.  Tokens of 32 fp32 channels padded to 33,
+        // [64,919,33], 26.9 -> 8.1 us, concat of 127 + 64 fp32 channels 33.9 -> 10.6, of 255 + 64 2-byte ones 69 -> 16.2.
+        // Whole blocks of 64 rows only; 2-byte source rows from even elements only (12 channels of 35 x 35 padded to 13:
+        // 6.0 us element by element, 6.9 as blocks).
+        std::vector<int64_t> ss_rest;
+        for (int k = 0; k < n; ++k)
+            if (k != iR) ss_rest.push_back(kp.dims[k].ss);
+        const bool pitched = dir == 2 && no_dst_vec && flat_stride(iR) > C && kp.dims[iR].extent >= 64 &&
+                             (es == 4 || common_pow2(2, {kp.sbase}, ss_rest) == 2);
+        if (flat_stride(iR) != C && !pitched) continue;
+        if (tile_bytes >= 16 && !pitched) continue;
         const int64_t ER = kp.dims[iR].extent;
         // rows of 2 .. 7 elements belong to the interleaving row forms (a block of 64 such rows is too little work)
         if (C < 8 || ER < (int64_t)kFlatMinRows) continue;
@@ -430,7 +446,7 @@ static FlatShape flat_shape(const KPiece &kp, int es, int64_t dst_volume) {
         // whole 16-byte vectors on the dst side and along the rows?  If not, only the blocked form with dst as
         // the contiguous side remains: its stores take any alignment and its loads along the rows end element by element
         // (a transposition of 4097 x 4099 elements: 74.8 us element by element)
-        bool aligned = kp.dbase % V == 0 && ER % V == 0;
+        bool aligned = kp.dbase % V == 0 && ER % V == 0 && !pitched;
         for (int k = 0; k < n; ++k) {
             const bool in_chain = std::find(chain.begin(), chain.end(), k) != chain.end();
             if (k == iP || k == iR) continue;            // dst stride 1; in dir 2 the block loop walks dst in steps of C
@@ -440,10 +456,7 @@ static FlatShape flat_shape(const KPiece &kp, int es, int64_t dst_volume) {
         if (!aligned) {
             if (dir == 1) continue;
             // where dst still offers vectors along P, the tile forms (cut into whole-vector part + tail) keep the piece
-            std::vector<int64_t> ds_all;
-            for (int k = 0; k < n; ++k)
-                if (k != iP) ds_all.push_back(kp.dims[k].ds);
-            if (common_pow2((uint32_t)V, {kp.dbase}, ds_all) >= 2) continue;
+            if (!no_dst_vec) continue;
         }
         // as many rows per block as fit LDS: 64, 32 or 16 (rows of 1225 = 35 x 35 positions: 16 at a time)
         const int64_t lds_limit = (int64_t)kFlatLdsBytes;
@@ -461,7 +474,7 @@ static FlatShape flat_shape(const KPiece &kp, int es, int64_t dst_volume) {
         // several loops (padded or cropped images).  From 16 rows on (a block of 64 is then partly empty): what is left for
         // fewer rows are gathered rows ([128,55,55,48] 145 -> 13.8 us in cache, 145 -> 19.7 cold).
         const int64_t cb_rag = 128 / es;
-        const bool rag_ok = tile_bytes < 8;
+        const bool rag_ok = tile_bytes < 8 || pitched;
         // long rows of one loop under few channels, the source contiguous: the cut into a whole-vector part and a
         // one-element tail is faster there (concat of 64 + 64 + 96 + 32 channels of 35 x 35 positions: 26.8 against 34.6 us)
         if (dir == 1 && chain.size() == 1 && rlog == 4 && ER < 128) continue;
@@ -524,6 +537,7 @@ static bool plan_flat(const KPiece &kp, int es, int64_t dst_volume, uint32_t nwl
     lds = (uint32_t)(f.C * std::min<int64_t>(f.ER, rows) * es);
     if (f.cb) {
         dp.rag_cb = (uint32_t)f.cb;
+        dp.ssP = (int32_t)kp.dims[f.iR].ds;   // dir 2: from one row of dst to the next
         // LDS row stride: an odd number of dwords; with dst as the contiguous side a block loads up to V - 1 columns more
         dp.rag_w = (uint32_t)(f.cb + (es == 2 ? 2 : 1) + (f.dir == 2 ? V : 0));
         dp.rag_slog = ilog2((uint32_t)(f.cb / V));
@@ -946,6 +960,16 @@ std::vector<std::vector<Member>> find_groups(const amap &m, std::vector<char> &g
 
 }  // namespace
 
+static bool flat_on() { return env_int("AMAP_FLAT", 1) && env_int("AMAP_GATHER", 1) && env_int("AMAP_VEC_BYTES", 16) >= 16; }
+
+// every member of a group that is no constant has a flat form of its own
+static bool all_flat(const std::vector<Member> &g, const amap &m) {
+    if (!flat_on()) return false;
+    for (const Member &mem : g)
+        if (!mem.kp->fill && !flat_shape(*mem.kp, m.elem, volume_of(m.shape)).dir) return false;
+    return true;
+}
+
 // Plan a group as one tile piece: out[0] is the head (geometry, total P
 // extent), out[i] the entry of member i.  False if the members do not share
 // one vector width / source chain, in which case they are planned one by one.
@@ -1101,6 +1125,9 @@ static bool plan_strided_nw(const amap &m, int family, int nw_forced, Plan &out,
             bool fits = true;
             for (const Member &mem : g) fits = fits && (int)mem.dims.size() <= kMaxLoops;
             if (!fits || !plan_group(m, g, family, nwlog, dps, lds, vb)) continue;
+            // vectors of 4 bytes (dst rows of an odd number of 4-byte elements): flat tiles take the pieces one by one
+            // ([64,919,33] of 32 channels and a constant one: 26.9 -> 8.1 us)
+            if (family < 0 && vb <= 4 && all_flat(g, m)) continue;
             int64_t vol = 0;
             for (const Member &mem : g) vol += mem.kp->volume();
             emit(dps, lds, vb, dps[0].kind == PK_TILE ? AMAP_K_TILE : AMAP_K_WAVE, vol);
@@ -1143,8 +1170,7 @@ static std::vector<KPiece> split_ragged(const KPiece &kp, int es, int64_t dst_vo
     }
     if (iP < 0 || iQ < 0 || iP == iQ) return out;
     // a flat tile takes the piece whole (under the same switches as in plan_piece)
-    const bool flat_on = env_int("AMAP_FLAT", 1) && env_int("AMAP_GATHER", 1) && env_int("AMAP_VEC_BYTES", 16) >= 16;
-    if (flat_on && flat_shape(kp, es, dst_volume).dir) return out;
+    if (flat_on() && flat_shape(kp, es, dst_volume).dir) return out;
     std::vector<int64_t> ds_others;
     for (int k = 0; k < (int)kp.dims.size(); ++k)
         if (k != iP) ds_others.push_back(kp.dims[k].ds);

@@ -81,7 +81,7 @@ TILES = [
     *[(merge(3, 20, 111, 80), 264, w, "32 x 64 per workgroup of 2") for w in (False, True)],          # in short runs
     *[(merge(1, 20, 2341, 64), 760, w, "64 x 128 per workgroup of 4") for w in (False, True)],
     *[(merge(5, 20, 469, 80), 760, w, "64 x 128 per workgroup of 4") for w in (False, True)],
-    (merge(1, 8, 7700, 64), 1672, False, "128 x 128 per workgroup of 8"),                             # more than three per unit
+    (merge(3, 16, 1300, 64), 3336, False, "128 x 128 per workgroup of 8"),                            # more than three per unit
     (conv(40, [320], 12), 72, False, "64 x 64 per workgroup of 4"),                                   # A along m
     (conv(7, [96, 128, 256, 128], 12), 136, False, "64 x 64 per workgroup of 4"),                     # gathered
     (conv(16, [256], 28), 120, False, "64 x 128 per workgroup of 4"),
