@@ -1148,16 +1148,16 @@ amap_status gemm_launch(const void *const *A_srcs, bool by_id, const amap_t *A_m
                 set_last_error("amap_gemm_tile256_kernel: cannot query the device");
                 return AMAP_E_HIP;
             }
+        }
 #define AMAP_T2_FNS(E)                                                                                                                                     \
     reinterpret_cast<const void *>(amap_gemm_tile256_kernel<false, false, E>), reinterpret_cast<const void *>(amap_gemm_tile256_kernel<true, false, E>), \
         reinterpret_cast<const void *>(amap_gemm_tile256_kernel<false, true, E>), reinterpret_cast<const void *>(amap_gemm_tile256_kernel<true, true, E>)
-            for (const void *fn : {AMAP_T2_FNS(false), AMAP_T2_FNS(true)})
-                if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, kT2Lds) != hipSuccess) {
-                    (void)hipGetLastError();
-                    n_cu = 0;
-                    set_last_error("amap_gemm_tile256_kernel: cannot reserve its LDS stages");
-                    return AMAP_E_HIP;
-                }
+        static LdsReservation reserved;
+        const hipError_t r = reserved.on_current_device({AMAP_T2_FNS(false), AMAP_T2_FNS(true)}, kT2Lds);
+#undef AMAP_T2_FNS
+        if (r != hipSuccess) {
+            set_last_error("amap_gemm_tile256_kernel: cannot reserve its LDS stages", hipGetErrorString(r));
+            return AMAP_E_HIP;
         }
         if (const char *tr = std::getenv("AMAP_PLAN_TRACE"); tr && tr[0] != '0')
             std::fprintf(stderr, "amap gemm: 256 x 256 tiles%s%s, %lld x %lld x %lld\n", w_km ? " (W runs along k)" : "", edge256 ? " (partial last tiles)" : "",
@@ -1199,25 +1199,19 @@ amap_status gemm_launch(const void *const *A_srcs, bool by_id, const amap_t *A_m
     if (const char *tr = std::getenv("AMAP_PLAN_TRACE"); tr && tr[0] != '0')
         std::fprintf(stderr, "amap gemm: 256 x 128 tiles, %lld x %lld x %lld\n", (long long)M, (long long)N, (long long)K);
     const uint32_t lds = kLdsBytes;
-    static thread_local bool attr_done = false;
-    if (!attr_done) {
+    static LdsReservation reserved;
 #define AMAP_GEMM_FN(AM, WM, E) \
     reinterpret_cast<const void *>(amap_gemm_kernel<AM, WM, E, false>), reinterpret_cast<const void *>(amap_gemm_kernel<AM, WM, E, true>)
-        for (const void *fn :
-             {AMAP_GEMM_FN(A_RUNS_K, W_PLAIN, false), AMAP_GEMM_FN(A_RUNS_K, W_MAPPED_N, false),
-              AMAP_GEMM_FN(A_RUNS_K, W_MAPPED_K, false), AMAP_GEMM_FN(A_RUNS_K, W_PLAIN, true),
-              AMAP_GEMM_FN(A_RUNS_K, W_MAPPED_N, true), AMAP_GEMM_FN(A_RUNS_K, W_MAPPED_K, true),
-              AMAP_GEMM_FN(A_RUNS_M, W_PLAIN, false), AMAP_GEMM_FN(A_RUNS_M, W_MAPPED_N, false),
-              AMAP_GEMM_FN(A_RUNS_M, W_MAPPED_K, false), AMAP_GEMM_FN(A_RUNS_M, W_PLAIN, true),
-              AMAP_GEMM_FN(A_RUNS_M, W_MAPPED_N, true), AMAP_GEMM_FN(A_RUNS_M, W_MAPPED_K, true)}) {
+    const hipError_t r = reserved.on_current_device(
+        {AMAP_GEMM_FN(A_RUNS_K, W_PLAIN, false), AMAP_GEMM_FN(A_RUNS_K, W_MAPPED_N, false), AMAP_GEMM_FN(A_RUNS_K, W_MAPPED_K, false),
+         AMAP_GEMM_FN(A_RUNS_K, W_PLAIN, true), AMAP_GEMM_FN(A_RUNS_K, W_MAPPED_N, true), AMAP_GEMM_FN(A_RUNS_K, W_MAPPED_K, true),
+         AMAP_GEMM_FN(A_RUNS_M, W_PLAIN, false), AMAP_GEMM_FN(A_RUNS_M, W_MAPPED_N, false), AMAP_GEMM_FN(A_RUNS_M, W_MAPPED_K, false),
+         AMAP_GEMM_FN(A_RUNS_M, W_PLAIN, true), AMAP_GEMM_FN(A_RUNS_M, W_MAPPED_N, true), AMAP_GEMM_FN(A_RUNS_M, W_MAPPED_K, true)},
+        (int)lds);
 #undef AMAP_GEMM_FN
-            if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) {
-                (void)hipGetLastError();
-                set_last_error("amap_gemm_kernel: cannot reserve its LDS stage");
-                return AMAP_E_HIP;
-            }
-        }
-        attr_done = true;
+    if (r != hipSuccess) {
+        set_last_error("amap_gemm_kernel: cannot reserve its LDS stage", hipGetErrorString(r));
+        return AMAP_E_HIP;
     }
     const dim3 grid(g.tiles_m * g.tiles_n), block(kGemmThreads);
     const bool seg = g.n_seg > 1;

@@ -300,13 +300,12 @@ amap_status launch(const RingArgs<kMaxSeg> &full, uint32_t grid, hipStream_t str
     constexpr int kRing = T::NST * (T::BM + T::BN) * T::BK * 2, kTile = T::BM * T::BN * 2, lds = kRing > kTile ? kRing : kTile;
     static_assert(lds <= 160 * 1024, "what a compute unit has");
     if constexpr (lds > 65536) {   // what a launch may ask for without it
-        static thread_local bool reserved = false;
-        if (!reserved && hipFuncSetAttribute(reinterpret_cast<const void *>(amap_gemm_ring_kernel<T>), hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess) {
-            (void)hipGetLastError();
-            set_last_error("amap_gemm_ring_kernel: cannot reserve its LDS stages");
+        static LdsReservation reserved;
+        const hipError_t r = reserved.on_current_device({reinterpret_cast<const void *>(amap_gemm_ring_kernel<T>)}, lds);
+        if (r != hipSuccess) {
+            set_last_error("amap_gemm_ring_kernel: cannot reserve its LDS stages", hipGetErrorString(r));
             return AMAP_E_HIP;
         }
-        reserved = true;
     }
     RingArgs<T::NSEG> g;
     static_cast<RingCommon &>(g) = full;

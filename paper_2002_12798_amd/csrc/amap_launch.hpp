@@ -1,8 +1,10 @@
-// One kernel launch.
+// One kernel launch, and the LDS it may ask for.
 #pragma once
 
 #include <hip/hip_runtime.h>
 
+#include <atomic>
+#include <initializer_list>
 #include <tuple>
 #include <type_traits>
 
@@ -19,5 +21,27 @@ inline hipError_t launch_kernel(void (*kernel)(P...), dim3 grid, dim3 block, uin
     if (e != hipSuccess) (void)hipGetLastError();   // reported here, not to the next caller who asks
     return e;
 }
+
+// Dynamic LDS beyond 64 KB is an attribute of a kernel on one device: asked for once per device, whichever thread comes first.
+// (Two threads may both ask; devices from the 65th on are asked for at every launch.)
+class LdsReservation {
+  public:
+    hipError_t on_current_device(std::initializer_list<const void *> kernels, int bytes) {
+        int dev = 0;
+        hipError_t e = hipGetDevice(&dev);
+        const uint64_t bit = dev >= 0 && dev < 64 ? 1ull << dev : 0;
+        if (e == hipSuccess && (devices_.load(std::memory_order_acquire) & bit)) return hipSuccess;
+        for (const void *kernel : kernels)
+            if (e == hipSuccess) e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+        if (e == hipSuccess)
+            devices_.fetch_or(bit, std::memory_order_release);
+        else
+            (void)hipGetLastError();
+        return e;
+    }
+
+  private:
+    std::atomic<uint64_t> devices_{0};
+};
 
 }  // namespace amap_detail

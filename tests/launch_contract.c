@@ -1,0 +1,122 @@
+/* A caller whose HIP runtime is the few functions below: what the library asks of the runtime on its way to a launch, without a
+ * GPU.  The definitions of the executable come before those of the real runtime.  Modes:
+ *   devices  every launch of more than 64 KB of dynamic LDS finds the attribute set for its kernel on the current device, also on
+ *            the second device that a thread uses, and after a device that refused it
+ *   errors   an error that another call left on the thread neither fails a launch nor is cleared by it; the launch's own error
+ *            fails the call and does not stay behind */
+#include <stdint.h>
+#include <stdio.h>
+#include <string.h>
+
+#include "amap.h"
+
+typedef struct { uint32_t x, y, z; } dim3_t;
+enum { OK = 0, INVALID = 1, LEFT_BEHIND = 719, LAUNCH_FAILED = 700, MAX_LDS_ATTRIBUTE = 8 };
+
+static int device = 0, last_error = OK, launches = 0, fail_launch = 0, refuse_attribute = 0, unreserved = 0, wide_launches = 0;
+static struct { const void *kernel; int device, bytes; } reserved[256];
+static int n_reserved = 0;
+
+int hipGetDevice(int *d) { *d = device; return OK; }
+int hipDeviceGetAttribute(int *v, int attr, int d) { (void)attr; (void)d; *v = 256; return OK; }
+int hipGetLastError(void) { const int e = last_error; last_error = OK; return e; }
+int hipFuncSetAttribute(const void *kernel, int attr, int value)
+{
+    if (attr != MAX_LDS_ATTRIBUTE || refuse_attribute || n_reserved == 256) return last_error = INVALID;
+    reserved[n_reserved].kernel = kernel;
+    reserved[n_reserved].device = device;
+    reserved[n_reserved++].bytes = value;
+    return OK;
+}
+int hipLaunchKernel(const void *kernel, dim3_t grid, dim3_t block, void **args, size_t lds, void *stream)
+{
+    int found = lds <= 65536;
+    (void)args; (void)stream;
+    if (fail_launch) return last_error = LAUNCH_FAILED;
+    if (!grid.x || !block.x) return last_error = INVALID;
+    for (int i = 0; i < n_reserved; ++i)
+        found |= reserved[i].kernel == kernel && reserved[i].device == device && (size_t)reserved[i].bytes >= lds;
+    unreserved += !found;
+    wide_launches += lds > 65536;
+    ++launches;
+    return OK;
+}
+
+static amap_t *layout(int64_t a, int64_t b, int64_t c, int64_t d, int merge)
+{
+    const int64_t shape[4] = {a, b, c, d}, perm[4] = {0, 2, 1, 3}, rows[2] = {a * c, b * d};
+    amap_src_desc src = {4, shape, AMAP_B16};
+    amap_op ops[2];
+    amap_t *m = NULL;
+    memset(ops, 0, sizeof(ops));
+    ops[0].kind = AMAP_TRANSPOSE; ops[0].n = 4; ops[0].a = perm;
+    ops[1].kind = AMAP_RESHAPE;   ops[1].n = 2; ops[1].a = rows;
+    return amap_compose(&src, 1, ops, merge ? 2 : 1, &m) == AMAP_OK ? m : NULL;
+}
+
+/* addresses that nothing reads */
+static const void *const srcs[1] = {(const void *)((uintptr_t)1 << 40)};
+static const void *const weight = (const void *)((uintptr_t)2 << 40);
+static void *const out = (void *)((uintptr_t)3 << 40);
+
+/* one product per GEMM kernel that asks for more than 64 KB: 64 x 128 tiles, 256 x 256 tiles, the general kernel */
+static const struct { int64_t b, h, s, d, n; } products[3] = {{1, 20, 2341, 64, 760}, {16, 16, 512, 64, 4096}, {1, 9, 300, 8, 256}};
+
+static amap_status product(int i)
+{
+    amap_t *m = layout(products[i].b, products[i].h, products[i].s, products[i].d, 1);
+    const amap_status st = m ? amap_gemm_gather(srcs, m, weight, NULL, products[i].n, NULL, out, NULL) : AMAP_E_INVALID;
+    amap_free(m);
+    return st;
+}
+
+#define EXPECT(x)                                             \
+    do {                                                      \
+        if (!(x)) {                                           \
+            printf("FAIL line %d: %s\n", __LINE__, #x);       \
+            return 1;                                         \
+        }                                                     \
+    } while (0)
+
+int main(int argc, char **argv)
+{
+    launches = n_reserved = 0;
+    if (argc == 2 && !strcmp(argv[1], "devices")) {
+        const int walk[6] = {0, 0, 1, 0, 3, 1};
+        for (int i = 0; i < 3; ++i) {
+            device = 2;
+            refuse_attribute = 1;
+            EXPECT(product(i) == AMAP_E_HIP && launches == 0 && last_error == OK);
+        }
+        refuse_attribute = 0;
+        for (int w = 0; w < 6; ++w)
+            for (int i = 0; i < 3; ++i) {
+                device = walk[w];
+                EXPECT(product(i) == AMAP_OK);
+                EXPECT(wide_launches == 3 * w + i + 1 && unreserved == 0);
+            }
+        device = 2;   /* refused before, asked again */
+        for (int i = 0; i < 3; ++i) EXPECT(product(i) == AMAP_OK && unreserved == 0);
+        const int asked = n_reserved;
+        for (int i = 0; i < 3; ++i) EXPECT(product(i) == AMAP_OK && n_reserved == asked);   /* once per device is enough */
+    } else if (argc == 2 && !strcmp(argv[1], "errors")) {
+        amap_t *m = layout(2, 8, 64, 64, 0);
+        EXPECT(m);
+        for (int i = -1; i < 3; ++i) {
+            const int before = launches;
+            last_error = LEFT_BEHIND;
+            EXPECT((i < 0 ? amap_execute(srcs, out, m, NULL) : product(i)) == AMAP_OK);
+            EXPECT(launches == before + 1 && last_error == LEFT_BEHIND);
+            last_error = OK;
+            fail_launch = 1;
+            EXPECT((i < 0 ? amap_execute(srcs, out, m, NULL) : product(i)) == AMAP_E_HIP);
+            EXPECT(last_error == OK && strlen(amap_last_error()) > 0);
+            fail_launch = 0;
+        }
+        amap_free(m);
+    } else {
+        return 2;
+    }
+    printf("OK\n");
+    return 0;
+}

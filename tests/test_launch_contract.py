@@ -1,0 +1,34 @@
+"""What the library asks of the HIP runtime around a launch, from a C caller that stands in for the runtime (no GPU)."""
+import os
+import subprocess
+
+import pytest
+
+from paper_2002_12798_amd import binding as B
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+@pytest.fixture(scope="module")
+def caller(tmp_path_factory):
+    import torch
+    exe = str(tmp_path_factory.mktemp("launch") / "launch_contract")
+    rt_dirs = [os.path.join(os.path.dirname(torch.__file__), "lib"), "/opt/rocm/lib"]
+    subprocess.run(["gcc", "-std=c99", "-Wall", "-Wextra", "-Werror", "-I", os.path.join(ROOT, "include"),
+                    os.path.join(ROOT, "tests", "launch_contract.c"), "-o", exe, B.LIB_PATH, "-rdynamic", "-Wl,--allow-shlib-undefined"]
+                   + [f"-Wl,-rpath,{d}" for d in [os.path.dirname(B.LIB_PATH)] + rt_dirs], check=True)
+    env = dict(os.environ, LD_LIBRARY_PATH=":".join(rt_dirs + [os.environ.get("LD_LIBRARY_PATH", "")]))
+
+    def run(mode):
+        r = subprocess.run([exe, mode], capture_output=True, text=True, env=env, timeout=120)
+        assert (r.returncode, r.stdout.strip()) == (0, "OK"), (r.stdout, r.stderr)
+    return run
+
+
+def test_lds_is_reserved_on_every_device(caller):
+    """A kernel's attribute belongs to the device that was current when it was set."""
+    caller("devices")
+
+
+def test_errors_of_other_calls_pass_through(caller):
+    caller("errors")
