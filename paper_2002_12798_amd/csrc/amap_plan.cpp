@@ -359,6 +359,9 @@ static std::vector<int> q_chain(const KPiece &kp, int iP, int iQ, int64_t &EQ) {
     return chain;
 }
 
+// AMAP_FLAT=2: flat tiles wherever they apply, also where a rule by size prefers another form (the tests ask for it)
+static bool flat_everywhere() { return env_int("AMAP_FLAT", 1) == 2; }
+
 struct FlatShape {
     int dir = 0;             // 0: the piece has no flat form
     int iR = -1;             // the loop that is cut into blocks of rows
@@ -962,12 +965,30 @@ std::vector<std::vector<Member>> find_groups(const amap &m, std::vector<char> &g
 
 static bool flat_on() { return env_int("AMAP_FLAT", 1) && env_int("AMAP_GATHER", 1) && env_int("AMAP_VEC_BYTES", 16) >= 16; }
 
-// every member of a group that is no constant has a flat form of its own
-static bool all_flat(const std::vector<Member> &g, const amap &m) {
+// Whether the pieces of a group whose tile would move 4-byte vectors go to flat tiles instead, each piece on its own.  They do
+// where each has a flat form and their workgroups are enough to keep the chip busy, or are through at once: a source-contiguous
+// workgroup of 32 .. 64 KB takes 5 to 10 us by itself, one below 8 KB is a single wavefront (9 x 6 images of 48 + 16 2-byte channels
+// into a border, 32 of them 4.4 / 5.5).  us as one tile / as flat pieces, concat of images to channels-last:
+//   4-byte, 15 x 15, 64 + 64   16 images (32 workgroups) 5.9 / 7.2    32 (64) 9.0 / 8.2      128 27.7 / 10.5
+//           17 x 17, 4 sources 4 (44) 7.3 / 7.7                       8 (88) 10.4 / 7.7      13 x 13, 8 (48) 7.1 / 6.8
+//           7 x 7, 4 sources   2 (14, 12 KB each) 5.1 / 4.8           32 9.0 / 4.8
+//   2-byte, two elements to a vector, 14 x 25, 64 + 64   48 (96) 7.1 / 8.1   64 (128) 8.2 / 8.2   96 11.2 / 8.5
+//           14 x 25, 4 sources 8 (56) 6.1 / 7.1               16 (112) 8.5 / 7.3
+// Rows of dst an odd number of elements apart (column-blocked, 9 KB a workgroup): [64,919,33] of 32 fp32 channels and a constant
+// one 26.9 / 8.1.
+static bool flat_instead(const std::vector<Member> &g, const amap &m, uint32_t nwlog) {
     if (!flat_on()) return false;
-    for (const Member &mem : g)
-        if (!mem.kp->fill && !flat_shape(*mem.kp, m.elem, volume_of(m.shape)).dir) return false;
-    return true;
+    uint64_t workgroups = 0;
+    uint32_t most_lds = 0;
+    for (const Member &mem : g) {
+        if (mem.kp->fill) continue;
+        DevPiece dp{};
+        uint32_t lds = 0;
+        if (!plan_flat(*mem.kp, m.elem, volume_of(m.shape), nwlog, dp, lds)) return false;
+        workgroups += dp.n_blocks;
+        most_lds = std::max(most_lds, lds);
+    }
+    return flat_everywhere() || (most_lds >= (8u << 10) && most_lds <= (16u << 10)) || workgroups >= (m.elem == 4 ? 48u : 112u);
 }
 
 // Plan a group as one tile piece: out[0] is the head (geometry, total P
@@ -1125,9 +1146,7 @@ static bool plan_strided_nw(const amap &m, int family, int nw_forced, Plan &out,
             bool fits = true;
             for (const Member &mem : g) fits = fits && (int)mem.dims.size() <= kMaxLoops;
             if (!fits || !plan_group(m, g, family, nwlog, dps, lds, vb)) continue;
-            // vectors of 4 bytes (dst rows of an odd number of 4-byte elements): flat tiles take the pieces one by one
-            // ([64,919,33] of 32 channels and a constant one: 26.9 -> 8.1 us)
-            if (family < 0 && vb <= 4 && all_flat(g, m)) continue;
+            if (family < 0 && vb <= 4 && flat_instead(g, m, nwlog)) continue;
             int64_t vol = 0;
             for (const Member &mem : g) vol += mem.kp->volume();
             emit(dps, lds, vb, dps[0].kind == PK_TILE ? AMAP_K_TILE : AMAP_K_WAVE, vol);
