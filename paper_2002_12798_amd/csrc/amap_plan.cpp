@@ -389,6 +389,29 @@ static bool rows16_fill_chip_once(int64_t C, int64_t ER, int es, int64_t dst_vol
     return blocks >= 2 * kComputeUnits && blocks <= per_cu * kComputeUnits;
 }
 
+// Rows of dst that begin at any element (see flat_shape): as column-blocked flat tiles, or as the tiles of single elements (4-byte)
+// and the single elements (2-byte) that are left otherwise?  Blocks are 4 wavefronts each and make the launch the general kernel's
+// where other forms stand beside them, so a small call is over sooner without.  us without / as blocks, concat of images to
+// channels-last, MB of dst:
+//   rows an odd number of elements apart (every piece begins at any element)
+//     4-byte  17 + 96, 13 x 13, 0.6 MB 4.2 / 4.5, 1.2 5.0 / 4.6, 2.4 7.2 / 5.0    64 + 31, 15 x 15, 0.7 MB 4.1 / 4.5, 1.4 5.0 / 4.6
+//             16 and a constant one, 28 x 28, 0.6 MB 4.5 / 4.3, 35 x 35, 1.0 5.7 / 4.3    8 + 9, 28 x 28, 0.9 MB 5.3 / 4.4
+//     2-byte  64 + 96 + 129, 14 x 14, 0.5 MB 5.0 / 6.1, 1.8 7.8 / 6.6             127 + 64, 14 x 14, 0.3 MB 4.5 / 5.1, 1.2 5.6 / 5.3
+//   an even number (a piece behind one of an odd number of channels; its neighbours keep their forms)
+//     4-byte  17 + 33, 14 x 14, 1.3 MB 5.6 / 5.8, 2.5 8.3 / 6.4                   31 + 127, 14 x 14, 1.0 MB 4.5 / 5.4, 2.0 5.7 / 5.7
+//     2-byte  31 + 127, 14 x 14, 2.0 MB 5.8 / 6.8, 28 x 28, 4.0 9.3 / 7.1, 13 x 6 (blocks of 39 rows on average) 3.2 6.8 / 8.6
+// A block of 64 rows takes about the same time with 8 columns as with 64, single elements take their number:
+//   2-byte    8 + 9, 56 x 56, batch 64 10.6 / 16.1     12 + 13 15.9 / 16.6        14 + 15, 56 x 56, 5.8 MB 11.1 / 10.8, 11.7 20.4 / 16.8
+//             16 + 17, 28 x 28, 1.7 MB 5.3 / 5.5, 3.3 7.1 / 7.1, 6.6 12.3 / 11.3      20 + 21, 2.1 MB 5.9 / 5.7, 4.1 9.9 / 7.4  24 + 25, 2.5 MB 6.7 / 5.7, 9.8 19.2 / 11.6
+static bool pitched_pays(int es, int64_t columns, int64_t rows, int64_t pitch, int64_t dst_volume) {
+    if (flat_everywhere()) return true;
+    if (es == 4) return dst_volume * es >= (pitch % 2 ? 3 << 18 : 2 << 20);
+    const int64_t block_rows = (rows + 63) / 64 * 64, filled = columns * rows / block_rows;   // empty rows of the last block count
+    if (filled < 14) return false;
+    const int64_t least = (pitch % 2 ? 1 << 20 : 3 << 20) * block_rows / rows;
+    return dst_volume * es >= std::max<int64_t>(least, filled < 16 ? 8 << 20 : (48 << 20) / filled);
+}
+
 // The row of the flat side may be several loops that continue one another on that side only (the
 // y and x loops of a 7 x 7 image that lands inside a padded image, or comes from a crop): on the other
 // side every loop of the chain has a stride of its own.
@@ -439,7 +462,7 @@ static FlatShape flat_shape(const KPiece &kp, int es, int64_t dst_volume) {
         for (int k = 0; k < n; ++k)
             if (k != iR) ss_rest.push_back(kp.dims[k].ss);
         const bool pitched = dir == 2 && no_dst_vec && flat_stride(iR) > C && kp.dims[iR].extent >= 64 &&
-                             (es == 4 || common_pow2(2, {kp.sbase}, ss_rest) == 2);
+                             (es == 4 || common_pow2(2, {kp.sbase}, ss_rest) == 2) && pitched_pays(es, C, kp.dims[iR].extent, flat_stride(iR), dst_volume);
         if (flat_stride(iR) != C && !pitched) continue;
         if (tile_bytes >= 16 && !pitched) continue;
         const int64_t ER = kp.dims[iR].extent;

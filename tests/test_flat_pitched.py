@@ -32,10 +32,12 @@ NOT_FLAT = 8        # (a source walked backwards)
 def _planned(case, es, monkeypatch, capfd):
     shapes, ops = CASES[case]
     monkeypatch.setenv("AMAP_PLAN_TRACE", "1")
+    monkeypatch.setenv("AMAP_FLAT", "2")   # also where a call is small enough to do without
     capfd.readouterr()
     m = B.amap_compose(shapes, es, ops)
     err = capfd.readouterr().err
     monkeypatch.delenv("AMAP_PLAN_TRACE")
+    monkeypatch.delenv("AMAP_FLAT")
     return shapes, ops, m, err
 
 
@@ -45,6 +47,28 @@ def test_replay(case, es, monkeypatch, capfd):
     _, _, m, err = _planned(case, es, monkeypatch, capfd)
     assert ("flat-blocked-dst" in err.split("plan: begin")[-1]) == (case != NOT_FLAT and (es == 4 or case not in ODD_ROWS))
     assert B.amap_plan_selfcheck(m) == 0 and B.amap_check_cover(m) == (0, 0)
+
+
+@pytest.mark.parametrize("es, channels, size, batch, blocked", [
+    (4, (17, 96), 16, 6, ()), (4, (17, 96), 16, 7, (17, 96)),                             # 0.75 MB of dst
+    (4, (31, 127), 14, 16, ()), (4, (31, 127), 14, 17, (127,)),                           # 2 MB where a neighbour keeps its form
+    (2, (64, 97), 16, 12, ()), (2, (64, 97), 16, 13, (64, 97)),                           # 1 MB
+    (2, (31, 129), 16, 38, ()), (2, (31, 129), 16, 39, (129,)),                           # 3 MB
+    (2, (8, 9), 56, 64, ()), (2, (12, 13), 56, 128, ()),                                  # few columns to a block, however large
+    (2, (14, 15), 56, 46, ()), (2, (14, 15), 56, 47, (14, 15)),                           # 8 MB
+    (2, (16, 17), 56, 14, ()), (2, (16, 17), 56, 16, (16, 17)),                           # 3.1 and 3 MB for 16 and 17 columns
+    (2, (24, 25), 56, 6, ()), (2, (24, 25), 56, 7, (24, 25)),                             # 2.1 and 2 MB for 24 and 25
+    (2, (32, 33), 10, 150, ()), (2, (32, 33), 10, 170, (32, 33)),                         # as 25 and 26: blocks of 100 rows and 28 empty ones
+    (2, (8, 255), 28, 4, (255,)),
+])
+def test_small_calls_keep_their_forms(es, channels, size, batch, blocked, monkeypatch, capfd):
+    monkeypatch.setenv("AMAP_PLAN_TRACE", "1")
+    capfd.readouterr()
+    m = B.amap_compose([(batch, c, size, size) for c in channels], es, [("concat", 1), ("transpose", (0, 2, 3, 1))])
+    lines = [line.split() for line in capfd.readouterr().err.split("plan: begin")[-1].splitlines()[1:]]
+    got = sorted(int(line[-1].split("=")[1]) // (batch * size * size) for line in lines if line[2] == "flat-blocked-dst")
+    assert got == sorted(blocked)
+    assert batch > 20 or B.amap_plan_selfcheck(m) == 0
 
 
 def test_fewer_rows_than_a_block_keep_their_forms(monkeypatch, capfd):
