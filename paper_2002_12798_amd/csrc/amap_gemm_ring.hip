@@ -390,7 +390,8 @@ static double share_of(uint64_t tiles, double k64, uint32_t n_cu, double step, d
 // loads and the last stores, `tile` per tile of the busiest compute unit, and for every 64 k of its tiles s1 where it has one
 // and all units do, s2 for two (they share the unit), `more` for each further one; from s0 to s1 up to one tile per unit (the
 // fewer units work, the faster each).  What lies between whole numbers of tiles per unit counts for `up` of the next one.
-// Fitted to 304 products of K = 32 .. 2560 with 1 to 2000 tiles.
+// Fitted to 304 products of K = 32 .. 2560, each row over the tiles per unit at which its shape is considered: along k 64 x 128
+// and 128 x 128 by 8 wavefronts up to two, by 4 beyond two (its s0 is never used; 8 wavefronts beyond two are counted as 4).
 struct RingCost {
     float launch, s0, s1, s2, more, tile, up;
 };
@@ -411,17 +412,20 @@ static const RingCost kCostX[] = {{}, {5.86f, .193f, .193f, .398f, .239f, .01f, 
 
 static const struct { int bm, bn, waves; } kRingTile[] = {{32, 64, 2}, {64, 64, 4}, {64, 128, 4}, {128, 128, 4}, {128, 128, 8}};
 
-// The shape of a product's tiles, and its estimate.  Along k the 32 x 64 and 64 x 128 tiles have to promise 4 %: below that the
-// estimate errs as often as it gains (222 products of the 304: 2.9 % faster in the mean, five slower by 2 % and more).
+// The shape of a product's tiles, and its estimate.  Measured on 668 products that the figures above were not fitted to (the lines at
+// K = 640 and 768 below were drawn on them): along k (579) 1.8 % faster in the mean than by 64 x 64 and 128 x 128 tiles alone, seven
+// slower by 2 to 6 % (a margin that the other shapes have to promise, 4 %: 1.4 %, six; 6 %: 0.8 %, six), and 1.0 % off the best shape
+// each has, 39 by more than 5 %: most of them just above one 64 x 128 tile per unit, where 8 wavefronts on 128 x 128 are taken and
+// 64 x 64 tiles are 10 % faster.  Along m (89) 17 % faster, none slower, 1.5 % off the best.
 static RingShape ring_shape(const GemmArgs &g, const RingPlan &p, uint32_t n_cu, double &best) {
     RingShape shape = RS_128x128;
     best = 1e30;
     const double k64 = g.K / 64.0;
     auto tiles = [&](int bm, int bn) { return (uint64_t)((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn); };
     const double q128 = (double)tiles(128, 128) / n_cu, q64x128 = (double)tiles(64, 128) / n_cu;
-    auto consider = [&](RingShape s, double less = 1.0) {
+    auto consider = [&](RingShape s) {
         const double t = estimate((p.ax ? kCostX : p.klane ? kCostRuns : kCostK)[s], tiles(kRingTile[s].bm, kRingTile[s].bn), k64, n_cu);
-        if (t < less * best) best = t, shape = s;
+        if (t < best) best = t, shape = s;
     };
     if (p.ax || g.n_seg > 1) {
         // a weight along k with A along m, sources gathered along k: 128 x 128 only
@@ -436,20 +440,27 @@ static RingShape ring_shape(const GemmArgs &g, const RingPlan &p, uint32_t n_cu,
         }
         return shape;
     }
-    // 8 wavefronts per 128 x 128 tile while at most two workgroups share a compute unit (288 tiles of K = 768: 13.7 against
-    // 15.1 us with 4) and, in a long walk, from three tiles per unit on (M = 7680, K = N = 2048 63.7 against 66.7, M = 4900, K = 1024,
-    // N = 3072 36.6 against 38.0; K = 960, M = 6886, N = 2880 47.3 against 46.7); 4 in between (M = 4180, K = 1024, N = 2048 28.9 against 29.8, M = 2682, N = 3072 21.0 against 25.3)
+    // 128 x 128 tiles come two to a compute unit.  8 wavefronts each where the last such pair is (mostly) whole, 4 where a single
+    // tile is left over, which 8 finish no sooner; us by 8 / by 4:
+    //   up to two tiles per unit   1.69 K = 768 14.5 / 15.6   1.97 K = 1024 19.2 / 20.1   1.69 K = 2048 30.4 / 32.0
+    //   two to three               2.06 K = 1024 29.2 / 28.1  2.56 K = 1024 30.6 / 29.0   2.88 K = 2048 53.2 / 52.5
+    //   three to four              3.47 K = 2048 59.0 / 61.6  3.50 K = 1024 33.5 / 35.6   3.44 K = 960 36.6 / 39.5
+    //                              3.56 K = 640 27.1 / 27.2   3.09 K = 512 22.3 / 21.2    3.25 K = 384 20.5 / 19.1
+    //   four to five               4.12 K = 1024 44.6 / 43.4  4.19 K = 1280 54.6 / 53.1   beyond: level (8.25 K = 768 62.1 / 62.8)
+    const bool by8 = q128 <= 2.0 || (q128 > 3.0 && q128 <= 4.0 && g.K >= 768);
     const bool small = share_of(tiles(64, 64), k64, n_cu, 0.19, 0.35) < share_of(tiles(128, 128), k64, n_cu, 0.47, 1.4);
-    consider(small ? RS_64x64 : q128 <= 2.0 || (q128 > 3.0 && g.K >= 1024) ? RS_128x128_W8 : RS_128x128);
+    consider(small ? RS_64x64 : q128 <= 2.0 ? RS_128x128_W8 : RS_128x128);
     if (p.klane < 2) {
-        const double old = best;
-        // three stages of 64 x 128 while two workgroups find room on every compute unit: M = 2400, K = 1280, N = 768 10.7 -> 9.5 us,
-        // M = 1322, K = N = 2048 22.3 -> 20.2; beyond, the 128 x 128 tiles, with less LDS traffic, are up to 1.4 times as fast
-        if (q64x128 <= 2.0) consider(RS_64x128, 0.96);
+        // three stages of 64 x 128 while two workgroups find room on every compute unit and the walk is long enough to pay for them:
+        // M = 2400, K = 1280, N = 768 10.7 -> 9.5 us, M = 1322, K = N = 2048 22.3 -> 20.2, M = 825, K = 768, N = 2304 8.0 -> 7.4,
+        // M = 1864, K = 640, N = 1000 8.3 -> 7.7, but M = 396, K = 512, N = 4096 5.4 -> 5.9, M = 1020, N = 1536 6.0 -> 6.2; beyond, the
+        // 128 x 128 tiles, with less LDS traffic, are up to 1.4 times as fast
+        if (q64x128 <= 2.0 && g.K >= 640) consider(RS_64x128);
         // few tiles and a long walk: M = 518, K = 2560, N = 512 12.0 -> 9.8 us.  Fewer than 16 tiles of 64 x 64 stay (M = 70,
         // K = 1024, N = 120 6.4 and 6.3 us).
-        if (tiles(64, 64) >= 16) consider(RS_32x64, best < old ? 1.0 : 0.96);
+        if (tiles(64, 64) >= 16) consider(RS_32x64);
     }
+    if (shape == RS_128x128 && by8) shape = RS_128x128_W8;
     return shape;
 }
 

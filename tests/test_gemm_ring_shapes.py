@@ -104,6 +104,28 @@ def test_replay_of_tiles(case, monkeypatch, capfd):
         assert expect in capfd.readouterr().err
 
 
+@pytest.mark.parametrize("m, k, n, expect", [
+    # 128 x 128 tiles per compute unit: up to two and, from K = 768 on, between three and four 8 wavefronts, 4 otherwise
+    (2682, 1024, 3072, "128 x 128 per workgroup of 8"),     # 1.97
+    (2778, 1024, 3072, "128 x 128 per workgroup of 4"),     # 2.06
+    (4185, 768, 3072, "128 x 128 per workgroup of 8"),      # 3.09
+    (4194, 512, 3072, "128 x 128 per workgroup of 4"),
+    (5595, 1024, 3072, "128 x 128 per workgroup of 4"),     # 4.13
+    # 64 x 128 tiles from K = 640 on
+    (396, 512, 4096, "64 x 64 per workgroup of 4"),
+    (396, 640, 4096, "64 x 128 per workgroup of 4"),
+])
+def test_the_rule_for_the_tile(m, k, n, expect, monkeypatch, capfd):
+    """(blocks of rows that are no whole 256: not for the 256 x 256 tiles)"""
+    b = 2 if m % 2 == 0 else 3
+    shapes, ops = merge(b, k // 64, m // b, 64)
+    a = B.amap_compose(shapes, 2, ops)
+    monkeypatch.setenv("AMAP_PLAN_TRACE", "1")
+    capfd.readouterr()
+    assert _replay(a, n)[0] == B.AMAP_OK
+    assert expect in capfd.readouterr().err
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("case", range(len(TILES)))
 def test_tiles_against_the_general_kernel(dev, case, monkeypatch, capfd):  # noqa: F811
