@@ -87,7 +87,7 @@ def test_replay(case):
 
 
 def test_forms_reach_every_kernel_shape(monkeypatch, capfd):
-    """Every instance of the kernel there is: tile and wavefronts, A along m or k, gathered, in short runs, W along n or k."""
+    """Tile and wavefronts, A along m or k, gathered, in short runs, W along n or k (every instance there is: test_gemm_ring_shapes.py)."""
     monkeypatch.setenv("AMAP_PLAN_TRACE", "1")
     capfd.readouterr()
     for case in range(len(FORMS)):

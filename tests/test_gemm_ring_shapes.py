@@ -6,7 +6,7 @@ import pytest
 
 from paper_2002_12798_amd import binding as B
 from paper_2002_12798_amd import synth
-from tests.test_gemm_ring import _replay, conv, dev, merge  # noqa: F401  (dev: fixture)
+from tests.test_gemm_ring import FORMS, _replay, conv, dev, merge  # noqa: F401  (dev: fixture)
 
 
 def three_digits(g, h, s, d):
@@ -102,6 +102,37 @@ def test_replay_of_tiles(case, monkeypatch, capfd):
         capfd.readouterr()
         assert _replay(a, n, w, out_map) == (B.AMAP_OK, 0)
         assert expect in capfd.readouterr().err
+
+
+def _routes(cases, monkeypatch, capfd):
+    """For each product, with the weight along n and along k: what its plan says of tile, A and W."""
+    monkeypatch.setenv("AMAP_PLAN_TRACE", "1")
+    for (shapes, ops), n, *_ in cases:
+        a = B.amap_compose(shapes, 2, ops)
+        k = B.dst_shape(a)[1]
+        for w in (None, B.amap_compose([(n, k)], 2, [("transpose", (1, 0))])):
+            capfd.readouterr()
+            _replay(a, n, w)
+            line = [x for x in capfd.readouterr().err.splitlines() if x.startswith("amap gemm: ring")]
+            yield ", ".join(line[0].split(", ")[1:4]) if line else None
+
+
+def test_the_cases_reach_every_instance(monkeypatch, capfd):
+    seen = set(_routes(FORMS + RUNS + TILES, monkeypatch, capfd)) - {None}
+    tile = {t: f"{t} per workgroup of {w} wavefronts" for t, w in (("32 x 64", 2), ("64 x 64", 4), ("64 x 128", 4), ("128 x 128", 4))}
+    wide8, short, decoded = "128 x 128 per workgroup of 8 wavefronts", " in runs shorter than a step", " in runs shorter than a step (k decoded)"
+    want = {f"{t}, A along k{runs}, W along {w}" for t in (*tile.values(), wide8) for runs in ("", short) for w in "nk"}
+    want |= {f"{t}, A along k{decoded}, W along {w}" for t in (tile["64 x 64"], tile["128 x 128"], wide8) for w in "nk"}
+    want |= {f"{tile[t]}, A along m{g}, W along n" for t in ("64 x 64", "64 x 128", "128 x 128") for g in ("", " gathered")}
+    want |= {f"{tile['128 x 128']}, A along m{g}, W along k" for g in ("", " gathered")}
+    want |= {f"{tile['128 x 128']}, A along k gathered, W along {w}" for w in "nk"}
+    assert seen == want
+
+
+def test_runs_of_one_length_are_carried_and_others_decoded(monkeypatch, capfd):
+    """The first eight cases of RUNS merge heads (k has two digits), the others have three."""
+    for i, route in enumerate(_routes(RUNS, monkeypatch, capfd)):
+        assert "in runs shorter than a step" in route and ("(k decoded)" in route) == (i // 2 >= 8)
 
 
 @pytest.mark.parametrize("m, k, n, expect", [
