@@ -516,6 +516,9 @@ __host__ __device__ __forceinline__ size_t t2_store_col(const GemmArgs &g, uint3
     if constexpr (MAPPED) return (size_t)(g.obase + digits_offset4(g.on, n_lane));
     return (size_t)n_lane;
 }
+// A mapped store: lane l of a wavefront decodes rows l and 64 + l of the 128 rows of its block; row `row` of the block's 32-row band i
+// is the (i / 2)th of lane t2_store_lane
+__host__ __device__ __forceinline__ uint32_t t2_store_lane(uint32_t i, uint32_t row) { return 32u * (i & 1u) + row; }
 template <bool MAPPED>
 __host__ __device__ __forceinline__ size_t t2_store_row(const GemmArgs &g, uint32_t m) {
     if constexpr (MAPPED) return (size_t)digits_offset4(g.om, m);
@@ -769,7 +772,7 @@ __global__ __launch_bounds__(kGemmThreads, 1) void amap_gemm_tile256_kernel(cons
                 const uint32_t m = m_base + i * 32u + row;
                 size_t off = col_off;
                 if constexpr (STORE_MAPPED)
-                    off += (uint32_t)__builtin_amdgcn_ds_bpermute((int)(4u * (32u * (i & 1) + row)), (int)row_off[i >> 1]);
+                    off += (uint32_t)__builtin_amdgcn_ds_bpermute((int)(4u * t2_store_lane((uint32_t)i, row)), (int)row_off[i >> 1]);
                 else
                     off += t2_store_row<false>(gs, m);
                 if (!EDGE || (m < g.M && n_lane < g.N)) __builtin_nontemporal_store(x, reinterpret_cast<u32x4 *>(g.C + off));
@@ -1370,6 +1373,26 @@ amap_status replay_tile256(const GemmArgs &g, int64_t a_bytes, int64_t w_bytes, 
         std::vector<int64_t> got_a, got_w, want_a, want_w;
         for (uint32_t blk = 0; blk < nwg; ++blk) {
             std::vector<T2Cursor> fetched, consumed;
+            T2Stream ld = {};
+            // EDGE: the clamped offsets, kept from tile to tile as the kernel keeps them
+            std::vector<uint32_t> a_edge(4 * 8 * 64), w_edge(a_edge.size());
+            auto cursor_edges = [&]() {
+                if (!EDGE) return;
+                uint32_t tm, tn;
+                tile_of_block(ld.c.tile, g.tiles_m, g.tiles_n, tm, tn);
+                const uint32_t rv = t2_rows_valid(g, tm), cv = t2_cols_valid(g, tn);
+                for (uint32_t at = 0; at < a_edge.size(); ++at) {
+                    a_edge[at] = t2_a_load_edge(g, at / 512, at % 64, at / 64 % 8, rv);
+                    w_edge[at] = t2_w_load_edge<W_KM>(g, at / 512, at % 64, at / 64 % 8, cv);
+                }
+            };
+            auto cursor_next = [&]() {
+                if (t2_stream_next<W_KM>(g, g, ld, nwg, ntiles) && ld.c.tile < ntiles) cursor_edges();
+            };
+            auto a_offset = [&](uint32_t wave, uint32_t j, uint32_t lane) { return EDGE ? a_edge[(wave * 8 + j) * 64 + lane] : t2_a_load(g, t2_a_lane(g, wave, lane, j & 1u), j); };
+            auto w_offset = [&](uint32_t wave, uint32_t j, uint32_t lane) {
+                return EDGE ? w_edge[(wave * 8 + j) * 64 + lane] : t2_w_load<W_KM>(g, t2_w_lane<W_KM>(g, wave, lane, j & 1u), j);
+            };
             // one batch of loads of all four wavefronts for the cursor's k-step
             auto fetch = [&](const T2Stream &st) {
                 const T2Cursor &c = st.c;
@@ -1386,9 +1409,7 @@ amap_status replay_tile256(const GemmArgs &g, int64_t a_bytes, int64_t w_bytes, 
                 for (uint32_t wave = 0; wave < 4; ++wave)
                     for (uint32_t j = 0; j < 8; ++j)
                         for (uint32_t lane = 0; lane < 64; ++lane) {
-                            const int64_t ao = ka + (int64_t)(EDGE ? t2_a_load_edge(g, wave, lane, j, rv) : t2_a_load(g, t2_a_lane(g, wave, lane, j & 1u), j));
-                            const int64_t wo = wk + (int64_t)(EDGE ? t2_w_load_edge<W_KM>(g, wave, lane, j, cv)
-                                                                   : t2_w_load<W_KM>(g, t2_w_lane<W_KM>(g, wave, lane, j & 1u), j));
+                            const int64_t ao = ka + (int64_t)a_offset(wave, j, lane), wo = wk + (int64_t)w_offset(wave, j, lane);
                             if (ao < 0 || ao + 16 > a_bytes) ++errors;
                             if (wo < 0 || wo + 16 > w_bytes) ++errors;
                             got_a.push_back(ao);
@@ -1419,26 +1440,21 @@ amap_status replay_tile256(const GemmArgs &g, int64_t a_bytes, int64_t w_bytes, 
             // loads issued after the stream has passed the workgroup's last tile: bounds only (nobody reads them)
             auto stale = [&](const T2Stream &st) {
                 const int64_t ka = st.a_tile + st.a_step, wk = st.w_tile + st.w_step;
-                uint32_t tm, tn;
-                tile_of_block(st.c.tile - nwg, g.tiles_m, g.tiles_n, tm, tn);   // the tile whose state the stream kept
-                const uint32_t rv = EDGE ? t2_rows_valid(g, tm) : (uint32_t)T2M, cv = EDGE ? t2_cols_valid(g, tn) : (uint32_t)T2N;
                 for (uint32_t wave = 0; wave < 4; ++wave)
                     for (uint32_t j = 0; j < 8; ++j)
                         for (uint32_t lane = 0; lane < 64; ++lane) {
-                            const int64_t ao = ka + (int64_t)(EDGE ? t2_a_load_edge(g, wave, lane, j, rv) : t2_a_load(g, t2_a_lane(g, wave, lane, j & 1u), j));
-                            const int64_t wo = wk + (int64_t)(EDGE ? t2_w_load_edge<W_KM>(g, wave, lane, j, cv)
-                                                                   : t2_w_load<W_KM>(g, t2_w_lane<W_KM>(g, wave, lane, j & 1u), j));
+                            const int64_t ao = ka + (int64_t)a_offset(wave, j, lane), wo = wk + (int64_t)w_offset(wave, j, lane);
                             if (ao < 0 || ao + 16 > a_bytes) ++errors;
                             if (wo < 0 || wo + 16 > w_bytes) ++errors;
                         }
             };
-            T2Stream ld = {};
             ld.c = T2Cursor{blk, 0};
             if (ld.c.tile < ntiles) {
                 t2_stream_tile<W_KM>(g, ld);
+                cursor_edges();
                 for (int p = 0; p < 2; ++p) {
                     fetch(ld);
-                    t2_stream_next<W_KM>(g, g, ld, nwg, ntiles);
+                    cursor_next();
                 }
             }
             for (uint32_t c_tile = blk; c_tile < ntiles; c_tile += nwg) {
@@ -1446,7 +1462,7 @@ amap_status replay_tile256(const GemmArgs &g, int64_t a_bytes, int64_t w_bytes, 
                     consumed.push_back(T2Cursor{c_tile, ks * (uint32_t)T2K});
                     if (ld.c.tile < ntiles) {
                         fetch(ld);
-                        t2_stream_next<W_KM>(g, g, ld, nwg, ntiles);
+                        cursor_next();
                     } else {
                         stale(ld);   // the stream stands still past the last tile; its loads are issued all the same
                     }
@@ -1456,14 +1472,22 @@ amap_status replay_tile256(const GemmArgs &g, int64_t a_bytes, int64_t w_bytes, 
                 tile_of_block(c_tile, g.tiles_m, g.tiles_n, tm, tn);
                 for (uint32_t wave = 0; wave < 4; ++wave) {
                     const uint32_t wm = wave >> 1, wn = wave & 1u;
+                    const uint32_t m_base = tm * (uint32_t)T2M + wm * 128u;
+                    size_t row_off[2][64] = {};
+                    for (uint32_t at = 0; at < 128 && g.store_mapped; ++at) {
+                        const uint32_t m = m_base + at;
+                        row_off[at / 64][at % 64] = t2_store_row<true>(g, EDGE && m >= g.M ? g.M - 1u : m);
+                    }
                     for (uint32_t lane = 0; lane < 64; ++lane) {
-                        const uint32_t m_base = tm * (uint32_t)T2M + wm * 128u, n_lane = tn * (uint32_t)T2N + wn * 128u + (lane & 15u) * 8u;
+                        const uint32_t n_lane = tn * (uint32_t)T2N + wn * 128u + (lane & 15u) * 8u;
                         const size_t col_off = g.store_mapped ? t2_store_col<true>(g, n_lane) : t2_store_col<false>(g, n_lane);
                         for (uint32_t i = 0; i < 4; ++i)
                             for (uint32_t pp = 0; pp < 8; ++pp) {
-                                const uint32_t m = m_base + i * 32u + 4u * pp + (lane >> 4);
+                                const uint32_t row = 4u * pp + (lane >> 4), m = m_base + i * 32u + row;
                                 if (EDGE && !(m < g.M && n_lane < g.N)) continue;   // the kernel's store mask
-                                const size_t off = col_off + (g.store_mapped ? t2_store_row<true>(g, m) : t2_store_row<false>(g, m));
+                                const size_t off = col_off + (g.store_mapped ? row_off[i >> 1][t2_store_lane(i, row)] : t2_store_row<false>(g, m));
+                                const size_t want = g.store_mapped ? (size_t)(g.obase + digits_offset4(g.om, m) + digits_offset4(g.on, n_lane)) : (size_t)m * g.N + n_lane;
+                                if (off != want) ++errors;
                                 if (off % 8 || (int64_t)off + 8 > c_elems) {
                                     ++errors;
                                     continue;

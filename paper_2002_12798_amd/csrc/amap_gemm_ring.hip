@@ -79,7 +79,7 @@ __device__ __forceinline__ void ring_load(const char *base, const uint32_t (&off
 template <class T>
 __global__ __launch_bounds__(64 * T::WVM * T::WVN, T::OCC) void amap_gemm_ring_kernel(const RingArgs<T::NSEG> g) {
     constexpr int BM = T::BM, BN = T::BN, BK = T::BK, NST = T::NST;
-    constexpr int kWaves = T::WVM * T::WVN, kThreads = 64 * kWaves;
+    constexpr int kWaves = T::WVM * T::WVN;
     constexpr int XM = BM / T::WVM, XN = BN / T::WVN;         // a wavefront's part of the tile
     constexpr bool AX = T::AX, WX = T::WX;
     constexpr uint32_t kABytes = BM * BK * 2, kWBytes = BN * BK * 2, kStage = kABytes + kWBytes;
@@ -271,26 +271,24 @@ __global__ __launch_bounds__(64 * T::WVM * T::WVN, T::OCC) void amap_gemm_ring_k
                 *reinterpret_cast<__attribute__((address_space(3))) u32x2 *>(ring_c_slot<BN>(row, chunk) + ((half ^ ((row >> 4) & 1u)) << 3)) = o;
             }
     __syncthreads();
-    constexpr uint32_t kCv = BN / 8;   // 16-byte chunks per row
-    const uint32_t cv = tid % kCv, n = n0 + cv * 8u;
+    typedef RingStore<BM, BN, kWaves> Store;
+    const uint32_t cv = tid % Store::kCv, n = n0 + cv * 8u;
     const bool n_ok = n < g.N;
     const uint32_t n_off = g.store_mapped ? g.obase + ring_digits<T::SHORT>(g.on, n_ok ? n : 0u) : n;
     // A mapped store: a lane decodes one of its wavefront's rows, and every store asks the lane that has its row (see the
-    // epilogue of the 256 x 256 kernel).  Store p of a wavefront covers kWaveRows rows, the workgroup's wavefronts kRows.
-    constexpr uint32_t kWaveRows = 64 / kCv, kRows = kThreads / kCv, kPasses = BM / kRows;
-    static_assert(kPasses * kWaveRows <= 64, "a row per lane");
+    // epilogue of the 256 x 256 kernel).
     uint32_t row_off = 0;
     if (g.store_mapped) {
-        const uint32_t m = m0 + lane / kWaveRows % kPasses * kRows + wave * kWaveRows + lane % kWaveRows;
+        const uint32_t m = m0 + Store::row_of_lane(wave, lane);
         row_off = ring_digits<T::SHORT>(g.om, m < g.M ? m : g.M - 1u);
     }
 #pragma unroll
-    for (uint32_t p = 0; p < kPasses; ++p) {
-        const uint32_t row = p * kRows + tid / kCv, m = m0 + row;
+    for (uint32_t p = 0; p < Store::kPasses; ++p) {
+        const uint32_t row = Store::row_of_store(p, tid), m = m0 + row;
         u32x4 x = *reinterpret_cast<lds_u32x4 *>(ring_c_slot<BN>(row, cv));
         if ((row >> 4) & 1u) x = u32x4{x.z, x.w, x.x, x.y};
         size_t off = (size_t)m * g.N + n_off;
-        if (g.store_mapped) off = n_off + (uint32_t)__builtin_amdgcn_ds_bpermute((int)(4u * (p * kWaveRows + lane / kCv)), (int)row_off);
+        if (g.store_mapped) off = n_off + (uint32_t)__builtin_amdgcn_ds_bpermute((int)(4u * Store::lane_of_store(p, lane)), (int)row_off);
         if (m < g.M && n_ok) __builtin_nontemporal_store(x, reinterpret_cast<u32x4 *>(g.C + off));
     }
 }
@@ -698,13 +696,24 @@ int64_t replay(const RingArgs<kMaxSeg> &r, const GemmArgs &g, const int64_t *a_b
                         }
                     }
         }
-        for (uint32_t row = 0; row < BM; ++row)
-            for (uint32_t cv = 0; cv < BN / 8; ++cv) {
-                const uint32_t m = m0 + row, n = n0 + 8 * cv;
-                if (m >= r.M || n >= r.N) continue;
-                const int64_t off = r.store_mapped ? (int64_t)(uint32_t)(r.obase + ring_digits<T::SHORT>(r.on, n) + ring_digits<T::SHORT>(r.om, m)) : (int64_t)m * r.N + n;
-                if (off % 8 || off < 0 || off + 8 > (int64_t)g.M * g.N || written[(size_t)off / 8]++) ++errors;
+        // the stores: the rows that a wavefront's lanes decode, then every lane of every pass
+        typedef RingStore<BM, BN, kWaves> Store;
+        for (uint32_t wave = 0; wave < (uint32_t)kWaves; ++wave) {
+            uint32_t row_off[64] = {};
+            for (uint32_t lane = 0; lane < 64 && r.store_mapped; ++lane) {
+                const uint32_t m = m0 + Store::row_of_lane(wave, lane);
+                row_off[lane] = ring_digits<T::SHORT>(r.om, m < r.M ? m : r.M - 1u);
             }
+            for (uint32_t p = 0; p < Store::kPasses; ++p)
+                for (uint32_t lane = 0; lane < 64; ++lane) {
+                    const uint32_t tid = wave * 64 + lane, m = m0 + Store::row_of_store(p, tid), n = n0 + 8 * (tid % Store::kCv);
+                    if (m >= r.M || n >= r.N) continue;
+                    const int64_t off = r.store_mapped ? (int64_t)(uint32_t)(r.obase + ring_digits<T::SHORT>(r.on, n) + row_off[Store::lane_of_store(p, lane)])
+                                                       : (int64_t)m * r.N + n;
+                    const int64_t want = g.store_mapped ? (int64_t)(uint32_t)(g.obase + digits_offset4(g.om, m) + digits_offset4(g.on, n)) : (int64_t)m * g.N + n;
+                    if (off != want || off % 8 || off < 0 || off + 8 > (int64_t)g.M * g.N || written[(size_t)off / 8]++) ++errors;
+                }
+        }
     }
     for (uint8_t w : written)
         if (w != 1) ++errors;

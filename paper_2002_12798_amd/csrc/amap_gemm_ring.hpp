@@ -152,6 +152,18 @@ AMAP_HD uint32_t ring_c_slot(uint32_t row, uint32_t cv) {
     return row * (2u * BN) + ((cv ^ (BN >= 128 ? row & 15u : (row >> 1) & 7u)) << 4);
 }
 
+// Stores of a staged output tile by WAVES wavefronts, BN / 8 lanes to a row: wavefront w's lane l stores row row_of_store(p, 64 w + l) at
+// pass p.  For a mapped store each lane decodes one row of its wavefront's, row_of_lane, and store p takes the offset from
+// lane_of_store(p, l) of the same wavefront.
+template <int BM, int BN, int WAVES>
+struct RingStore {
+    static constexpr uint32_t kCv = BN / 8, kWaveRows = 64 / kCv, kRows = WAVES * kWaveRows, kPasses = BM / kRows;
+    static_assert(kPasses * kWaveRows <= 64, "a row per lane");
+    static AMAP_HD uint32_t row_of_store(uint32_t p, uint32_t tid) { return p * kRows + tid / kCv; }
+    static AMAP_HD uint32_t row_of_lane(uint32_t wave, uint32_t lane) { return lane / kWaveRows % kPasses * kRows + wave * kWaveRows + lane % kWaveRows; }
+    static AMAP_HD uint32_t lane_of_store(uint32_t p, uint32_t lane) { return p * kWaveRows + lane / kCv; }
+};
+
 // The tiles there are (W8: 8 wavefronts).
 enum RingShape { RS_32x64 = 0, RS_64x64, RS_64x128, RS_128x128, RS_128x128_W8 };
 
