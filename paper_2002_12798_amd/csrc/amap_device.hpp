@@ -66,7 +66,7 @@ struct DevPiece {
     Loop loops[kMaxLoops];
     uint32_t nq;
     uint32_t eP, EQ;       // extents in elements along P (dst-contiguous) and the merged Q chain
-    int32_t ssP;           // source stride of P
+    int32_t ssP;           // source stride of P (TILE, WAVE, XLANE; ROWS with planes and column-blocked FLAT: as said there)
     uint32_t tilesP, tilesQ;
     FastDiv fdTP, fdTQ;
     uint32_t lqlog;        // log2(lanes along Q); lanes along P = 64 >> lqlog
@@ -137,6 +137,8 @@ struct LaunchArgs {
     uint32_t nwlog;      // workgroup size = 64 << nwlog
     uint32_t nt;         // PieceFlags every piece of the launch agrees on
     uint32_t xcd_remap;  // 1: remap workgroup indices so each XCD gets a contiguous range
+    // Only the first n_pieces are set: the host copies no more, so what lies beyond is anything.  A kernel may load it (touch_args
+    // does), but nothing may follow from it: every search over pieces ends at n_pieces, every group inside it.
     DevPiece p[kMaxPiecesPerLaunch];
 };
 

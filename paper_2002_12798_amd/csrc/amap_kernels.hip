@@ -754,7 +754,8 @@ __device__ __forceinline__ void tile_dispatch(const DevPiece &P, char *dst, uint
 
 // The first BYTES of the argument block, fetched side by side: read where they are needed, the fields of a piece are one
 // scalar-cache miss after the other in front of the first load (kernel times: concat of four branches [32,*,28,28] to NHWC
-// 8.7 -> 8.1 us, two branches of 14 x 14 4.7 -> 4.1 us, [64,35,35,288] to channel-major 23.0 -> 22.3 us).
+// 8.7 -> 8.1 us, two branches of 14 x 14 4.7 -> 4.1 us, [64,35,35,288] to channel-major 23.0 -> 22.3 us).  It may reach past the
+// pieces of the launch, where the block is not set: the values go nowhere.
 template <uint32_t BYTES>
 __device__ __forceinline__ void touch_args(const LaunchArgs &args) {
     const uint32_t *const a = reinterpret_cast<const uint32_t *>(&args);
