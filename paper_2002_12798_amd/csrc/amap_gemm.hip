@@ -525,6 +525,14 @@ __host__ __device__ __forceinline__ size_t t2_store_row(const GemmArgs &g, uint3
     return (size_t)m * g.N;
 }
 
+// The two together.  The offsets of a mapped store are sums modulo 2^32 (a map that stores backwards has negative steps, and only
+// the sum of both parts lies inside out): added in 64 bits they land 2^32 elements past it.
+template <bool MAPPED>
+__host__ __device__ __forceinline__ size_t t2_store_off(size_t col_off, size_t row_off) {
+    if constexpr (MAPPED) return (size_t)((uint32_t)col_off + (uint32_t)row_off);
+    return col_off + row_off;
+}
+
 // Workgroups of the persistent grid: as many as give every one the same number of tiles (288 tiles on 256 compute
 // units: 144 workgroups of two tiles each, not 256 of which 32 run a second tile while the others idle; the product
 // runs at the power limit, and the busy part of the chip then clocks higher: 46.9 -> 44.4 us on that shape).
@@ -770,11 +778,11 @@ __global__ __launch_bounds__(kGemmThreads, 1) void amap_gemm_tile256_kernel(cons
                 u32x4 x = *reinterpret_cast<lds_u32x4 *>(scr + row * 256u + ((chunk ^ (row & 15u)) << 4));
                 if (p >= 4) x = u32x4{x.z, x.w, x.x, x.y};
                 const uint32_t m = m_base + i * 32u + row;
-                size_t off = col_off;
+                size_t off;
                 if constexpr (STORE_MAPPED)
-                    off += (uint32_t)__builtin_amdgcn_ds_bpermute((int)(4u * t2_store_lane((uint32_t)i, row)), (int)row_off[i >> 1]);
+                    off = t2_store_off<true>(col_off, (uint32_t)__builtin_amdgcn_ds_bpermute((int)(4u * t2_store_lane((uint32_t)i, row)), (int)row_off[i >> 1]));
                 else
-                    off += t2_store_row<false>(gs, m);
+                    off = t2_store_off<false>(col_off, t2_store_row<false>(gs, m));
                 if (!EDGE || (m < g.M && n_lane < g.N)) __builtin_nontemporal_store(x, reinterpret_cast<u32x4 *>(g.C + off));
             }
         }
@@ -1485,7 +1493,8 @@ amap_status replay_tile256(const GemmArgs &g, int64_t a_bytes, int64_t w_bytes, 
                             for (uint32_t pp = 0; pp < 8; ++pp) {
                                 const uint32_t row = 4u * pp + (lane >> 4), m = m_base + i * 32u + row;
                                 if (EDGE && !(m < g.M && n_lane < g.N)) continue;   // the kernel's store mask
-                                const size_t off = col_off + (g.store_mapped ? row_off[i >> 1][t2_store_lane(i, row)] : t2_store_row<false>(g, m));
+                                const size_t off = g.store_mapped ? t2_store_off<true>(col_off, row_off[i >> 1][t2_store_lane(i, row)])
+                                                                  : t2_store_off<false>(col_off, t2_store_row<false>(g, m));
                                 const size_t want = g.store_mapped ? (size_t)(g.obase + digits_offset4(g.om, m) + digits_offset4(g.on, n_lane)) : (size_t)m * g.N + n_lane;
                                 if (off != want) ++errors;
                                 if (off % 8 || (int64_t)off + 8 > c_elems) {

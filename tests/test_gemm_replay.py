@@ -138,6 +138,23 @@ def test_replay_of_partial_last_tiles(case):
         assert B.amap_gemm_selfcheck(a, n, store, nwg) == 0
 
 
+BACKWARDS = [
+    # chains on the [M,N] product whose stores have negative steps along m, along n in blocks, and along both
+    lambda m, n: [("slice", 0, m - 1, -1, -1)],
+    lambda m, n: [("reshape", (m, n // 8, 8)), ("slice", 1, n // 8 - 1, -1, -1)],
+    lambda m, n: [("reshape", (m, n // 8, 8)), ("slice", 0, m - 1, -1, -1), ("slice", 1, n // 8 - 1, -1, -1), ("transpose", (1, 0, 2))],
+]
+
+
+@pytest.mark.parametrize("m, n", [(512, 512), (300, 264), (8, 16), (1000, 1000)])
+@pytest.mark.parametrize("chain", range(len(BACKWARDS)))
+def test_replay_of_stores_that_walk_backwards(chain, m, n):
+    a, wt = B.amap_compose([(m, 128)], 2, []), B.amap_compose([(n, 128)], 2, [("transpose", (1, 0))])
+    store = B.amap_compose([(m, n)], 2, BACKWARDS[chain](m, n))
+    for w in (None, wt):
+        assert B.amap_gemm_selfcheck(a, n, store, 256, w) == 0 and B.amap_gemm_selfcheck(a, n, store, 2, w) == 0
+
+
 def test_replay_of_random_partial_shapes():
     rng = np.random.default_rng(17)
     for _ in range(60):

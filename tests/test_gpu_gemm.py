@@ -440,6 +440,7 @@ T256_CASES = [
     (((4352, 128), []), 4096, None),
     (((2, 2, 512, 64), [("transpose", (1, 2, 0, 3)), ("reshape", (1024, 128))]), 512, None),       # K = 128 over two digits of k
     (((4352, 192), []), 4096, [("reshape", (4352, 64, 64)), ("transpose", (1, 0, 2))]),            # three k-steps, two tiles per workgroup, mapped store
+    (((512, 128), []), 512, [("slice", 0, 511, -1, -1)]),                                          # rows stored backwards
 ]
 
 
@@ -600,6 +601,7 @@ T256_EDGE_CASES = [
     (257, 128, 520, True, None),
     (520, 256, 200, False, [("reshape", (520, 25, 8)), ("transpose", (1, 0, 2))]),
     (4352 + 40, 128, 4096 + 8, False, None),                  # partial tiles, two k-steps, two tiles per workgroup
+    (300, 192, 264, True, [("reshape", (300, 33, 8)), ("slice", 0, 299, -1, -1), ("slice", 1, 32, -1, -1)]),   # stored backwards both ways
 ]
 
 
