@@ -410,11 +410,14 @@ static const RingCost kCostX[] = {{}, {5.86f, .193f, .193f, .398f, .239f, .01f, 
 
 static const struct { int bm, bn, waves; } kRingTile[] = {{32, 64, 2}, {64, 64, 4}, {64, 128, 4}, {128, 128, 4}, {128, 128, 8}};
 
-// The shape of a product's tiles, and its estimate.  Measured on 668 products that the figures above were not fitted to (the lines at
-// K = 640 and 768 below were drawn on them): along k (579) 1.8 % faster in the mean than by 64 x 64 and 128 x 128 tiles alone, seven
-// slower by 2 to 6 % (a margin that the other shapes have to promise, 4 %: 1.4 %, six; 6 %: 0.8 %, six), and 1.0 % off the best shape
-// each has, 39 by more than 5 %: most of them just above one 64 x 128 tile per unit, where 8 wavefronts on 128 x 128 are taken and
-// 64 x 64 tiles are 10 % faster.  Along m (89) 17 % faster, none slower, 1.5 % off the best.
+// The shape of a product's tiles, and its estimate.  Measured on products that the figures above were not fitted to, operands in three
+// sets of buffers in turn: along k (1694; the lines at K = 640, 768 and 960 below were drawn on half of them) 3.3 % faster in the mean than
+// by 64 x 64 and 128 x 128 tiles alone, nine slower by 2 to 17 % (the worst an N of 152, which 128 columns fill worse than 64), and
+// 1.1 % off the best shape each has, 142 by more than 5 %: most of them between one and two 64 x 128 tiles per unit, where 8 wavefronts
+// on 128 x 128 are taken and 64 x 64 or 64 x 128 tiles are up to 18 % faster.  With one set of buffers, all of it in the L2s, 64 x 64
+// tiles are ahead more often.
+// A margin that the other shapes have to promise costs more than it saves (579 products: none 1.8 %, 4 % 1.4, 6 % 0.8).  Along m (89)
+// 17 % faster, none slower, 1.5 % off the best.
 static RingShape ring_shape(const GemmArgs &g, const RingPlan &p, uint32_t n_cu, double &best) {
     RingShape shape = RS_128x128;
     best = 1e30;
@@ -451,9 +454,12 @@ static RingShape ring_shape(const GemmArgs &g, const RingPlan &p, uint32_t n_cu,
     if (p.klane < 2) {
         // three stages of 64 x 128 while two workgroups find room on every compute unit and the walk is long enough to pay for them:
         // M = 2400, K = 1280, N = 768 10.7 -> 9.5 us, M = 1322, K = N = 2048 22.3 -> 20.2, M = 825, K = 768, N = 2304 8.0 -> 7.4,
-        // M = 1864, K = 640, N = 1000 8.3 -> 7.7, but M = 396, K = 512, N = 4096 5.4 -> 5.9, M = 1020, N = 1536 6.0 -> 6.2; beyond, the
-        // 128 x 128 tiles, with less LDS traffic, are up to 1.4 times as fast
-        if (q64x128 <= 2.0 && g.K >= 640) consider(RS_64x128);
+        // M = 1864, K = 640, N = 1000 8.3 -> 7.7, but M = 396, K = 512, N = 4096 5.4 -> 5.9, M = 1020, N = 1536 6.0 -> 6.2.  Under two
+        // thirds of a tile per unit it has to be longer still (64 x 64 tiles are then one to a unit, and few units have two): 41 products
+        // of K = 640 .. 959 were 3 % slower as 64 x 128 (M = 345, K = 704, N = 3072 6.2 -> 6.7, 6.6 -> 7.0 with operands out of the L2s),
+        // 24 of K = 960 .. 1279 1 % faster, 10 with runs shorter than a step 3 %.  Beyond two tiles the 128 x 128 tiles, with less
+        // LDS traffic, are up to 1.4 times as fast
+        if (q64x128 <= 2.0 && g.K >= (p.klane || 3.0 * q64x128 >= 2.0 ? 640u : 960u)) consider(RS_64x128);
         // few tiles and a long walk: M = 518, K = 2560, N = 512 12.0 -> 9.8 us.  Fewer than 16 tiles of 64 x 64 stay (M = 70,
         // K = 1024, N = 120 6.4 and 6.3 us).
         if (tiles(64, 64) >= 16) consider(RS_32x64);

@@ -145,6 +145,11 @@ def test_runs_of_one_length_are_carried_and_others_decoded(monkeypatch, capfd):
     # 64 x 128 tiles from K = 640 on
     (396, 512, 4096, "64 x 64 per workgroup of 4"),
     (396, 640, 4096, "64 x 128 per workgroup of 4"),
+    # and below K = 960 from two thirds of a tile per unit on
+    (448, 704, 3072, "64 x 64 per workgroup of 4"),         # 0.66
+    (450, 704, 3072, "64 x 128 per workgroup of 4"),        # 0.75
+    (338, 896, 3072, "64 x 64 per workgroup of 4"),         # 0.56
+    (338, 960, 3072, "64 x 128 per workgroup of 4"),
 ])
 def test_the_rule_for_the_tile(m, k, n, expect, monkeypatch, capfd):
     """(blocks of rows that are no whole 256: not for the 256 x 256 tiles)"""
