@@ -117,7 +117,7 @@ struct DevPiece {
     // the contiguous side a row segment starts at any element: loads take 16-byte vectors from the segment's
     // start (under-aligned) and single elements at its end; stores take aligned 16-byte slots (see RagRow), for
     // which a block loads up to V - 1 columns more than its own; dst rows begin ssP elements apart (eP, or more where other
-    // pieces, or none, lie between them: an odd number of channels with a constant one beside them).  1 << rag_slog = rag_cb / V slots per row; LDS
+    // pieces, or none, lie between them: 32 channels with a constant one beside them).  1 << rag_slog = rag_cb / V slots per row; LDS
     // rows are rag_w elements apart.
     uint32_t rag_cb, rag_w, rag_slog;
     // XLANE only.  A dst row (the whole P run, fills beside it included) is xl_npv vectors long; a wavefront

@@ -453,10 +453,10 @@ static FlatShape flat_shape(const KPiece &kp, int es, int64_t dst_volume) {
             chain.push_back(next);
             C *= kp.dims[next].extent;
         }
-        // Rows of dst further apart than they are long, an odd number of elements from one to the next (channels padded by one, joined
-        // to an odd number): the column-blocked form takes them, it stores row by row.  Tokens of 32 fp32 channels padded to 33,
+        // Rows of dst further apart than they are long that begin at any element (channels padded by one, joined to an odd number, a
+        // piece behind an odd number of channels): the column-blocked form takes them, it stores row by row.  Tokens of 32 fp32 channels padded to 33,
         // [64,919,33], 26.9 -> 8.1 us, concat of 127 + 64 fp32 channels 33.9 -> 10.6, of 255 + 64 2-byte ones 69 -> 16.2.
-        // Whole blocks of 64 rows only; 2-byte source rows from even elements only (12 channels of 35 x 35 padded to 13:
+        // From 64 rows on (fewer leave a block partly empty); 2-byte source rows from even elements only (12 channels of 35 x 35 padded to 13:
         // 6.0 us element by element, 6.9 as blocks).
         std::vector<int64_t> ss_rest;
         for (int k = 0; k < n; ++k)
