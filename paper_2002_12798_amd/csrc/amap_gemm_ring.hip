@@ -411,19 +411,18 @@ static const RingCost kCostX[] = {{}, {5.86f, .193f, .193f, .398f, .239f, .01f, 
 static const struct { int bm, bn, waves; } kRingTile[] = {{32, 64, 2}, {64, 64, 4}, {64, 128, 4}, {128, 128, 4}, {128, 128, 8}};
 
 // The shape of a product's tiles, and its estimate.  Measured on products that the figures above were not fitted to, operands in three
-// sets of buffers in turn: along k (1694; the lines at K = 640, 768 and 960 below were drawn on half of them) 3.3 % faster in the mean than
-// by 64 x 64 and 128 x 128 tiles alone, nine slower by 2 to 17 % (the worst an N of 152, which 128 columns fill worse than 64), and
-// 1.1 % off the best shape each has, 142 by more than 5 %: most of them between one and two 64 x 128 tiles per unit, where 8 wavefronts
-// on 128 x 128 are taken and 64 x 64 or 64 x 128 tiles are up to 18 % faster.  With one set of buffers, all of it in the L2s, 64 x 64
-// tiles are ahead more often.
-// A margin that the other shapes have to promise costs more than it saves (579 products: none 1.8 %, 4 % 1.4, 6 % 0.8).  Along m (89)
-// 17 % faster, none slower, 1.5 % off the best.
+// sets of buffers in turn: along k (2481; the lines in K and in tiles per unit below were drawn on two thirds of them and on 960 others)
+// 3.2 % faster in the mean than by 64 x 64 and 128 x 128 tiles alone, 14 slower by 2 to 17 % (the worst an N of 152, which 128 columns
+// fill worse than 64), and 1.0 % off the best shape each has, 187 by more than 5 %: most of them between one and two 64 x 128 tiles per
+// unit, where 8 wavefronts on 128 x 128 are taken and 64 x 64 or 64 x 128 tiles are up to 18 % faster.  With one set of buffers, all of
+// it in the L2s, 64 x 64 tiles are ahead more often.  A margin that the other shapes have to promise costs more than it saves (579
+// products: none 1.8 %, 4 % 1.4, 6 % 0.8).  Along m (89) 17 % faster, none slower, 1.5 % off the best.
 static RingShape ring_shape(const GemmArgs &g, const RingPlan &p, uint32_t n_cu, double &best) {
     RingShape shape = RS_128x128;
     best = 1e30;
     const double k64 = g.K / 64.0;
     auto tiles = [&](int bm, int bn) { return (uint64_t)((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn); };
-    const double q128 = (double)tiles(128, 128) / n_cu, q64x128 = (double)tiles(64, 128) / n_cu;
+    const double q64x128 = (double)tiles(64, 128) / n_cu;
     auto consider = [&](RingShape s) {
         const double t = estimate((p.ax ? kCostX : p.klane ? kCostRuns : kCostK)[s], tiles(kRingTile[s].bm, kRingTile[s].bn), k64, n_cu);
         if (t < best) best = t, shape = s;
@@ -441,25 +440,28 @@ static RingShape ring_shape(const GemmArgs &g, const RingPlan &p, uint32_t n_cu,
         }
         return shape;
     }
-    // 128 x 128 tiles come two to a compute unit.  8 wavefronts each where the last such pair is (mostly) whole, 4 where a single
-    // tile is left over, which 8 finish no sooner; us by 8 / by 4:
-    //   up to two tiles per unit   1.69 K = 768 14.5 / 15.6   1.97 K = 1024 19.2 / 20.1   1.69 K = 2048 30.4 / 32.0
-    //   two to three               2.06 K = 1024 29.2 / 28.1  2.56 K = 1024 30.6 / 29.0   2.88 K = 2048 53.2 / 52.5
-    //   three to four              3.47 K = 2048 59.0 / 61.6  3.50 K = 1024 33.5 / 35.6   3.44 K = 960 36.6 / 39.5
-    //                              3.56 K = 640 27.1 / 27.2   3.09 K = 512 22.3 / 21.2    3.25 K = 384 20.5 / 19.1
-    //   four to five               4.12 K = 1024 44.6 / 43.4  4.19 K = 1280 54.6 / 53.1   beyond: level (8.25 K = 768 62.1 / 62.8)
-    const bool by8 = q128 <= 2.0 || (q128 > 3.0 && q128 <= 4.0 && g.K >= 768);
+    // 128 x 128 tiles come two to a compute unit.  8 wavefronts each where the busiest unit's last pair is whole, 4 where a single tile is
+    // left over, which 8 finish no sooner; beyond eight tiles that counts for little.  Time by 8 / by 4 in the mean (products), by
+    // the tiles of the busiest unit, K >= 768:
+    //   3  1.02 (57)   4  0.97 (34)   5  1.02 (62)   6  0.97 (37)   7  1.01 (20)   8  0.96 (23)   9 .. 12  0.99 (40)   more  0.99 (26)
+    // up to 2 (any K) 0.95;  below K = 768  3  1.00   4  0.98   5  1.02   6  1.01   7  0.99   8  0.97.  us by 8 / by 4: 1.97 tiles per unit,
+    // K = 1024 19.2 / 20.1   2.88, K = 2048 53.2 / 52.5   3.47, K = 2048 59.0 / 61.6   4.12, K = 1024 44.6 / 43.4   5.21, K = 1024 48.5 / 50.3
+    const uint64_t up128 = (tiles(128, 128) + n_cu - 1) / n_cu;
+    const bool by8 = up128 <= 2 || (g.K >= 768 && (up128 % 2 == 0 || up128 > 8));
     const bool small = share_of(tiles(64, 64), k64, n_cu, 0.19, 0.35) < share_of(tiles(128, 128), k64, n_cu, 0.47, 1.4);
-    consider(small ? RS_64x64 : q128 <= 2.0 ? RS_128x128_W8 : RS_128x128);
+    consider(small ? RS_64x64 : up128 <= 2 ? RS_128x128_W8 : RS_128x128);
     if (p.klane < 2) {
         // three stages of 64 x 128 while two workgroups find room on every compute unit and the walk is long enough to pay for them:
         // M = 2400, K = 1280, N = 768 10.7 -> 9.5 us, M = 1322, K = N = 2048 22.3 -> 20.2, M = 825, K = 768, N = 2304 8.0 -> 7.4,
         // M = 1864, K = 640, N = 1000 8.3 -> 7.7, but M = 396, K = 512, N = 4096 5.4 -> 5.9, M = 1020, N = 1536 6.0 -> 6.2.  Under two
         // thirds of a tile per unit it has to be longer still (64 x 64 tiles are then one to a unit, and few units have two): 41 products
         // of K = 640 .. 959 were 3 % slower as 64 x 128 (M = 345, K = 704, N = 3072 6.2 -> 6.7, 6.6 -> 7.0 with operands out of the L2s),
-        // 24 of K = 960 .. 1279 1 % faster, 10 with runs shorter than a step 3 %.  Beyond two tiles the 128 x 128 tiles, with less
-        // LDS traffic, are up to 1.4 times as fast
-        if (q64x128 <= 2.0 && g.K >= (p.klane || 3.0 * q64x128 >= 2.0 ? 640u : 960u)) consider(RS_64x128);
+        // 24 of K = 960 .. 1279 from 6 % faster to 8 % slower, 18 longer ones 4 % faster, runs shorter than a step 3 to 10 %.
+        // Above one and a half per unit (64 x 64 tiles come three to a unit and would need a fourth) less will do: M = 1305, K = 512,
+        // N = 3072 10.5 -> 9.1, M = 3717, N = 1024 4 % faster.  Beyond two the 128 x 128 tiles, with less LDS traffic, are up to 1.4 times
+        // as fast
+        const uint32_t least_k = q64x128 > 1.5 ? 384u : p.klane || 3.0 * q64x128 >= 2.0 ? 640u : 1280u;
+        if (q64x128 <= 2.0 && g.K >= least_k) consider(RS_64x128);
         // few tiles and a long walk: M = 518, K = 2560, N = 512 12.0 -> 9.8 us.  Fewer than 16 tiles of 64 x 64 stay (M = 70,
         // K = 1024, N = 120 6.4 and 6.3 us).
         if (tiles(64, 64) >= 16) consider(RS_32x64);

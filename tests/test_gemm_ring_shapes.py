@@ -136,20 +136,25 @@ def test_runs_of_one_length_are_carried_and_others_decoded(monkeypatch, capfd):
 
 
 @pytest.mark.parametrize("m, k, n, expect", [
-    # 128 x 128 tiles per compute unit: up to two and, from K = 768 on, between three and four 8 wavefronts, 4 otherwise
+    # 128 x 128 tiles of the busiest compute unit: up to two and, from K = 768 on, an even number or more than eight 8 wavefronts, 4 otherwise
     (2682, 1024, 3072, "128 x 128 per workgroup of 8"),     # 1.97
     (2778, 1024, 3072, "128 x 128 per workgroup of 4"),     # 2.06
     (4185, 768, 3072, "128 x 128 per workgroup of 8"),      # 3.09
     (4194, 512, 3072, "128 x 128 per workgroup of 4"),
     (5595, 1024, 3072, "128 x 128 per workgroup of 4"),     # 4.13
-    # 64 x 128 tiles from K = 640 on
+    (7164, 768, 3072, "128 x 128 per workgroup of 8"),      # 5.25
+    (8442, 768, 3072, "128 x 128 per workgroup of 4"),      # 6.19
+    (11262, 768, 3072, "128 x 128 per workgroup of 8"),     # 8.25
+    # 64 x 128 tiles from K = 640 on, above one and a half per unit from K = 384 on
+    (1305, 512, 3072, "64 x 128 per workgroup of 4"),       # 1.97
+    (1305, 320, 3072, "64 x 64 per workgroup of 4"),
     (396, 512, 4096, "64 x 64 per workgroup of 4"),
     (396, 640, 4096, "64 x 128 per workgroup of 4"),
-    # and below K = 960 from two thirds of a tile per unit on
+    # and below K = 1280 from two thirds of a tile per unit on
     (448, 704, 3072, "64 x 64 per workgroup of 4"),         # 0.66
     (450, 704, 3072, "64 x 128 per workgroup of 4"),        # 0.75
-    (338, 896, 3072, "64 x 64 per workgroup of 4"),         # 0.56
-    (338, 960, 3072, "64 x 128 per workgroup of 4"),
+    (338, 1216, 3072, "64 x 64 per workgroup of 4"),        # 0.56
+    (338, 1280, 3072, "64 x 128 per workgroup of 4"),
 ])
 def test_the_rule_for_the_tile(m, k, n, expect, monkeypatch, capfd):
     """(blocks of rows that are no whole 256: not for the 256 x 256 tiles)"""
