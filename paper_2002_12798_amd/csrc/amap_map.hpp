@@ -80,6 +80,7 @@ struct KPiece {
     // either side.  Once set, dbase / sbase are relative to them, so that every
     // offset inside the piece fits 32 bits even in tensors of 2^31 elements and more.
     int64_t dwin = 0, swin = 0;
+    int64_t loose = 0;   // Set by the launch planner only: elements of dst in those transposing pieces of the map that offer no vectors there
     std::vector<KDim> dims;
     int64_t volume() const {
         int64_t v = 1;

@@ -391,25 +391,50 @@ static bool rows16_fill_chip_once(int64_t C, int64_t ER, int es, int64_t dst_vol
 
 // Rows of dst that begin at any element (see flat_shape): as column-blocked flat tiles, or as the tiles of single elements (4-byte)
 // and the single elements (2-byte) that are left otherwise?  Blocks are 4 wavefronts each and make the launch the general kernel's
-// where other forms stand beside them, so a small call is over sooner without.  us without / as blocks, concat of images to
-// channels-last, MB of dst:
+// where other forms stand beside them, so a small call is over sooner without.  What counts is how much of dst lies in such pieces
+// (KPiece::loose), whatever stands beside them: 3100 joined and padded images with either form cross over between 0.6 and 0.8 MB of
+// them (4-byte) and at 1.0 to 1.2 (2-byte), time without / with blocks in the mean (single ones at 1.6 MB from 0.8 to 1.7)
+//   MB of such pieces        0.4    0.5    0.63   0.8    1.0    1.26   1.6    2.0
+//   4-byte  every piece      0.89   0.93   0.99   1.05   1.19   1.23   1.39   1.51     (rows an even number of elements apart)
+//           some pieces      0.91   0.95   0.97   1.02   1.12   1.17   1.24
+//   2-byte  every piece      0.82   0.82   0.89   0.96   1.02   1.20   1.22   1.52
+//           some pieces      0.90   0.88   0.94   0.95   1.00   1.03   1.08   1.32
+// ([24,192,16,20] padded by a constant channel on each side 10.9 us without, 5.1 with, 2.9 MB).  Less of them beside 2 MB and more of
+// dst in all, 50 calls each: 4-byte 1.12 (57 + 24 channels, 8 x 8, 2.1 MB 7.3 / 4.6), 2-byte 0.95.  us without / as blocks, concat of
+// images to channels-last, MB of dst:
 //   rows an odd number of elements apart (every piece begins at any element)
 //     4-byte  17 + 96, 13 x 13, 0.6 MB 4.2 / 4.5, 1.2 5.0 / 4.6, 2.4 7.2 / 5.0    64 + 31, 15 x 15, 0.7 MB 4.1 / 4.5, 1.4 5.0 / 4.6
 //             16 and a constant one, 28 x 28, 0.6 MB 4.5 / 4.3, 35 x 35, 1.0 5.7 / 4.3    8 + 9, 28 x 28, 0.9 MB 5.3 / 4.4
 //     2-byte  64 + 96 + 129, 14 x 14, 0.5 MB 5.0 / 6.1, 1.8 7.8 / 6.6             127 + 64, 14 x 14, 0.3 MB 4.5 / 5.1, 1.2 5.6 / 5.3
 //   an even number (a piece behind one of an odd number of channels; its neighbours keep their forms)
 //     4-byte  17 + 33, 14 x 14, 1.3 MB 5.6 / 5.8, 2.5 8.3 / 6.4                   31 + 127, 14 x 14, 1.0 MB 4.5 / 5.4, 2.0 5.7 / 5.7
-//     2-byte  31 + 127, 14 x 14, 2.0 MB 5.8 / 6.8, 28 x 28, 4.0 9.3 / 7.1, 13 x 6 (blocks of 39 rows on average) 3.2 6.8 / 8.6
+//     2-byte  31 + 127, 14 x 14, 2.0 MB 5.8 / 6.8, 28 x 28, 4.0 9.3 / 7.1, 13 x 6 (39 rows to a block in the mean) 3.2 6.8 / 8.6
 // A block of 64 rows takes about the same time with 8 columns as with 64, single elements take their number:
 //   2-byte    8 + 9, 56 x 56, batch 64 10.6 / 16.1     12 + 13 15.9 / 16.6        14 + 15, 56 x 56, 5.8 MB 11.1 / 10.8, 11.7 20.4 / 16.8
 //             16 + 17, 28 x 28, 1.7 MB 5.3 / 5.5, 3.3 7.1 / 7.1, 6.6 12.3 / 11.3      20 + 21, 2.1 MB 5.9 / 5.7, 4.1 9.9 / 7.4  24 + 25, 2.5 MB 6.7 / 5.7, 9.8 19.2 / 11.6
-static bool pitched_pays(int es, int64_t columns, int64_t rows, int64_t pitch, int64_t dst_volume) {
+static bool pitched_pays(int es, int64_t columns, int64_t rows, int64_t loose, int64_t dst_volume) {
     if (flat_everywhere()) return true;
-    if (es == 4) return dst_volume * es >= (pitch % 2 ? 3 << 18 : 2 << 20);
+    if (es == 4) return loose * es >= 3 << 18 || dst_volume * es >= 2 << 20;
     const int64_t block_rows = (rows + 63) / 64 * 64, filled = columns * rows / block_rows;   // empty rows of the last block count
     if (filled < 14) return false;
-    const int64_t least = (pitch % 2 ? 1 << 20 : 3 << 20) * block_rows / rows;
-    return dst_volume * es >= std::max<int64_t>(least, filled < 16 ? 8 << 20 : (48 << 20) / filled);
+    const int64_t least = (1 << 20) * block_rows / rows;
+    return loose * es >= std::max<int64_t>(least, filled < 16 ? 8 << 20 : (48 << 20) / filled);
+}
+
+// Element loops of a piece: along dst (dst stride 1) and along the source; -1 where there is none
+static void unit_loops(const KPiece &kp, int &iP, int &iQ) {
+    iP = iQ = -1;
+    for (int k = 0; k < (int)kp.dims.size(); ++k) {
+        if (kp.dims[k].ds == 1) iP = k;
+        if (kp.dims[k].ss == 1) iQ = k;
+    }
+}
+// dst without vectors of two elements: the tile forms move single elements there, whatever the extents allow
+static bool no_dst_vectors(const KPiece &kp, int es, int iP) {
+    std::vector<int64_t> ds_rest;
+    for (int k = 0; k < (int)kp.dims.size(); ++k)
+        if (k != iP) ds_rest.push_back(kp.dims[k].ds);
+    return common_pow2((uint32_t)(16 / es), {kp.dbase}, ds_rest) == 1;
 }
 
 // The row of the flat side may be several loops that continue one another on that side only (the
@@ -419,11 +444,8 @@ static FlatShape flat_shape(const KPiece &kp, int es, int64_t dst_volume) {
     FlatShape none, f;
     if (kp.fill || (es != 2 && es != 4)) return none;
     const int n = (int)kp.dims.size();
-    int iP = -1, iQ = -1;
-    for (int k = 0; k < n; ++k) {
-        if (kp.dims[k].ds == 1) iP = k;
-        if (kp.dims[k].ss == 1) iQ = k;
-    }
+    int iP, iQ;
+    unit_loops(kp, iP, iQ);
     if (iP < 0 || iQ < 0 || iP == iQ) return none;
     const int64_t V = 16 / es;
     const KDim &P = kp.dims[iP], &Q = kp.dims[iQ];
@@ -432,11 +454,7 @@ static FlatShape flat_shape(const KPiece &kp, int es, int64_t dst_volume) {
     int64_t EQc = Q.extent;
     if (env_int("AMAP_TILE_CHAIN_VEC", 1)) q_chain(kp, iP, iQ, EQc);
     const int64_t tile_bytes = (int64_t)common_pow2((uint32_t)V, {P.extent, EQc}, {}) * es;
-    // dst without vectors of two elements: the tile forms move single elements there, whatever the extents allow
-    std::vector<int64_t> ds_rest;
-    for (int k = 0; k < n; ++k)
-        if (k != iP) ds_rest.push_back(kp.dims[k].ds);
-    const bool no_dst_vec = common_pow2((uint32_t)V, {kp.dbase}, ds_rest) == 1;
+    const bool no_dst_vec = no_dst_vectors(kp, es, iP);
     if (tile_bytes >= 16 && !no_dst_vec) return none;
     for (int dir = 1; dir <= 2; ++dir) {
         // dir 1: rows are contiguous in the source, from Q outwards, until P's source stride is reached;
@@ -462,7 +480,7 @@ static FlatShape flat_shape(const KPiece &kp, int es, int64_t dst_volume) {
         for (int k = 0; k < n; ++k)
             if (k != iR) ss_rest.push_back(kp.dims[k].ss);
         const bool pitched = dir == 2 && no_dst_vec && flat_stride(iR) > C && kp.dims[iR].extent >= 64 &&
-                             (es == 4 || common_pow2(2, {kp.sbase}, ss_rest) == 2) && pitched_pays(es, C, kp.dims[iR].extent, flat_stride(iR), dst_volume);
+                             (es == 4 || common_pow2(2, {kp.sbase}, ss_rest) == 2) && pitched_pays(es, C, kp.dims[iR].extent, kp.loose, dst_volume);
         if (flat_stride(iR) != C && !pitched) continue;
         if (tile_bytes >= 16 && !pitched) continue;
         const int64_t ER = kp.dims[iR].extent;
@@ -1317,7 +1335,14 @@ bool plan_strided(const amap &m0, int family, Plan &out) {
     m.plan.reset();
     if (m.strided) {
         std::vector<KPiece> ks;
-        for (const KPiece &kp : m0.kpieces)
+        int64_t loose = 0;
+        for (const KPiece &kp : m.kpieces) {
+            int iP, iQ;
+            unit_loops(kp, iP, iQ);
+            if (!kp.fill && iP >= 0 && iQ >= 0 && iP != iQ && no_dst_vectors(kp, m.elem, iP)) loose += kp.volume();
+        }
+        for (KPiece &kp : m.kpieces) kp.loose = loose;
+        for (const KPiece &kp : m.kpieces)
             for (KPiece &p : split_ragged(kp, m.elem, volume_of(m.shape))) ks.push_back(std::move(p));
         if (ks.size() <= 4 * m0.kpieces.size() + 8) m.kpieces = std::move(ks);
     }

@@ -49,22 +49,27 @@ def test_replay(case, es, monkeypatch, capfd):
     assert B.amap_plan_selfcheck(m) == 0 and B.amap_check_cover(m) == (0, 0)
 
 
-@pytest.mark.parametrize("es, channels, size, batch, blocked", [
-    (4, (17, 96), 16, 6, ()), (4, (17, 96), 16, 7, (17, 96)),                             # 0.75 MB of dst
-    (4, (31, 127), 14, 16, ()), (4, (31, 127), 14, 17, (127,)),                           # 2 MB where a neighbour keeps its form
-    (2, (64, 97), 16, 12, ()), (2, (64, 97), 16, 13, (64, 97)),                           # 1 MB
-    (2, (31, 129), 16, 38, ()), (2, (31, 129), 16, 39, (129,)),                           # 3 MB
-    (2, (8, 9), 56, 64, ()), (2, (12, 13), 56, 128, ()),                                  # few columns to a block, however large
-    (2, (14, 15), 56, 46, ()), (2, (14, 15), 56, 47, (14, 15)),                           # 8 MB
-    (2, (16, 17), 56, 14, ()), (2, (16, 17), 56, 16, (16, 17)),                           # 3.1 and 3 MB for 16 and 17 columns
-    (2, (24, 25), 56, 6, ()), (2, (24, 25), 56, 7, (24, 25)),                             # 2.1 and 2 MB for 24 and 25
-    (2, (32, 33), 10, 150, ()), (2, (32, 33), 10, 170, (32, 33)),                         # as 25 and 26: blocks of 100 rows and 28 empty ones
-    (2, (8, 255), 28, 4, (255,)),
+@pytest.mark.parametrize("es, channels, size, batch, pad, blocked", [
+    # MB of dst in pieces that begin at any element
+    (4, (17, 96), 16, 6, (0, 0), ()), (4, (17, 96), 16, 7, (0, 0), (17, 96)),               # 0.75
+    (4, (64,), 16, 11, (1, 1), ()), (4, (64,), 16, 12, (1, 1), (64,)),                      # the same, 66 elements apart
+    (4, (31, 127), 14, 7, (0, 0), ()), (4, (31, 127), 14, 8, (0, 0), (127,)),               # the piece of 127 channels alone
+    (4, (57, 24), 8, 97, (0, 3), ()), (4, (57, 24), 8, 98, (0, 3), (24,)),                  # less than that, but 2 of dst in all
+    (2, (64, 97), 16, 12, (0, 0), ()), (2, (64, 97), 16, 13, (0, 0), (64, 97)),             # 1
+    (2, (192,), 16, 10, (1, 1), ()), (2, (192,), 16, 11, (1, 1), (192,)),
+    (2, (31, 129), 16, 15, (0, 0), ()), (2, (31, 129), 16, 16, (0, 0), (129,)),
+    (2, (8, 9), 56, 64, (0, 0), ()), (2, (12, 13), 56, 128, (0, 0), ()),                    # few columns to a block, however large
+    (2, (14, 15), 56, 46, (0, 0), ()), (2, (14, 15), 56, 47, (0, 0), (14, 15)),             # 8
+    (2, (16, 17), 56, 14, (0, 0), ()), (2, (16, 17), 56, 16, (0, 0), (16, 17)),             # 3.1 and 3 for 16 and 17 columns
+    (2, (24, 25), 56, 6, (0, 0), ()), (2, (24, 25), 56, 7, (0, 0), (24, 25)),               # 2.1 and 2 for 24 and 25
+    (2, (32, 33), 10, 150, (0, 0), ()), (2, (32, 33), 10, 170, (0, 0), (32, 33)),           # as 25 and 26: blocks of 100 rows and 28 empty ones
+    (2, (8, 255), 28, 4, (0, 0), (255,)),
 ])
-def test_small_calls_keep_their_forms(es, channels, size, batch, blocked, monkeypatch, capfd):
+def test_small_calls_keep_their_forms(es, channels, size, batch, pad, blocked, monkeypatch, capfd):
     monkeypatch.setenv("AMAP_PLAN_TRACE", "1")
     capfd.readouterr()
-    m = B.amap_compose([(batch, c, size, size) for c in channels], es, [("concat", 1), ("transpose", (0, 2, 3, 1))])
+    m = B.amap_compose([(batch, c, size, size) for c in channels], es,
+                       [("concat", 1), ("transpose", (0, 2, 3, 1)), ("pad", (0, 0, 0, pad[0]), (0, 0, 0, pad[1]), 0)])
     lines = [line.split() for line in capfd.readouterr().err.split("plan: begin")[-1].splitlines()[1:]]
     got = sorted(int(line[-1].split("=")[1]) // (batch * size * size) for line in lines if line[2] == "flat-blocked-dst")
     assert got == sorted(blocked)
