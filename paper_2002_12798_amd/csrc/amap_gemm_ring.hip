@@ -447,7 +447,8 @@ static RingShape ring_shape(const GemmArgs &g, const RingPlan &p, uint32_t n_cu,
     // up to 2 (any K) 0.95;  below K = 768  3  1.00   4  0.98   5  1.02   6  1.01   7  0.99   8  0.97.  us by 8 / by 4: 1.97 tiles per unit,
     // K = 1024 19.2 / 20.1   2.88, K = 2048 53.2 / 52.5   3.47, K = 2048 59.0 / 61.6   4.12, K = 1024 44.6 / 43.4   5.21, K = 1024 48.5 / 50.3
     const uint64_t up128 = (tiles(128, 128) + n_cu - 1) / n_cu;
-    const bool by8 = up128 <= 2 || (g.K >= 768 && (up128 % 2 == 0 || up128 > 8));
+    // (K = 768 and six tiles: 0.95 to 1.02; K = 768 .. 1023 and more than eight: 0.95 to 1.02 as well)
+    const bool by8 = up128 <= 2 || (up128 > 8 ? g.K >= 1024 : up128 % 2 == 0 && g.K >= (up128 == 6 ? 960u : 768u));
     const bool small = share_of(tiles(64, 64), k64, n_cu, 0.19, 0.35) < share_of(tiles(128, 128), k64, n_cu, 0.47, 1.4);
     consider(small ? RS_64x64 : up128 <= 2 ? RS_128x128_W8 : RS_128x128);
     if (p.klane < 2) {

@@ -136,15 +136,18 @@ def test_runs_of_one_length_are_carried_and_others_decoded(monkeypatch, capfd):
 
 
 @pytest.mark.parametrize("m, k, n, expect", [
-    # 128 x 128 tiles of the busiest compute unit: up to two and, from K = 768 on, an even number or more than eight 8 wavefronts, 4 otherwise
+    # 128 x 128 tiles of the busiest compute unit: 8 wavefronts for up to two, four and eight from K = 768 on, six from 960, more from 1024
     (2682, 1024, 3072, "128 x 128 per workgroup of 8"),     # 1.97
     (2778, 1024, 3072, "128 x 128 per workgroup of 4"),     # 2.06
     (4185, 768, 3072, "128 x 128 per workgroup of 8"),      # 3.09
     (4194, 512, 3072, "128 x 128 per workgroup of 4"),
     (5595, 1024, 3072, "128 x 128 per workgroup of 4"),     # 4.13
-    (7164, 768, 3072, "128 x 128 per workgroup of 8"),      # 5.25
-    (8442, 768, 3072, "128 x 128 per workgroup of 4"),      # 6.19
-    (11262, 768, 3072, "128 x 128 per workgroup of 8"),     # 8.25
+    (7164, 960, 3072, "128 x 128 per workgroup of 8"),      # 5.25
+    (7164, 896, 3072, "128 x 128 per workgroup of 4"),
+    (8442, 1024, 3072, "128 x 128 per workgroup of 4"),     # 6.19
+    (10216, 768, 3072, "128 x 128 per workgroup of 8"),     # 7.5
+    (11262, 960, 3072, "128 x 128 per workgroup of 4"),     # 8.25
+    (11262, 1024, 3072, "128 x 128 per workgroup of 8"),
     # 64 x 128 tiles from K = 640 on, above one and a half per unit from K = 384 on
     (1305, 512, 3072, "64 x 128 per workgroup of 4"),       # 1.97
     (1305, 320, 3072, "64 x 64 per workgroup of 4"),
