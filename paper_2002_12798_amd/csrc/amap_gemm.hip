@@ -1126,9 +1126,9 @@ amap_status gemm_launch(const void *const *A_srcs, bool by_id, const amap_t *A_m
         RingPlan rp;
         if (ring_plan(g, amode, wmode, tile256, 256, rp)) {
             if (const char *tr = std::getenv("AMAP_PLAN_TRACE"); tr && tr[0] != '0')
-                std::fprintf(stderr, "amap gemm: ring, %d x %d per workgroup of %d wavefronts, A along %c%s%s, W along %c, %lld x %lld x %lld\n", rp.bm, rp.bn,
+                std::fprintf(stderr, "amap gemm: ring, %d x %d per workgroup of %d wavefronts, A along %c%s%s, W along %c, %lld x %lld x %lld%s\n", rp.bm, rp.bn,
                              rp.waves, rp.ax ? 'm' : 'k', rp.n_seg > 1 ? " gathered" : "", rp.klane == 0 ? "" : rp.klane == 1 ? " in runs shorter than a step" : " in runs shorter than a step (k decoded)", rp.wx ? 'n' : 'k',
-                             (long long)M, (long long)N, (long long)K);
+                             (long long)M, (long long)N, (long long)K, rp.more);
             if (dry) {
                 *dry = g;
                 *ring = rp;

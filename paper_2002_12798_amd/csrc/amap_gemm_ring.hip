@@ -14,7 +14,8 @@
 // passes one barrier, issues the loads of step s + NST - 1 into the stage that step s - 1 has just left, and computes.
 // What bounds a step on small tiles is LDS: the loads' writes (64 bytes a clock and compute unit on their own) and the
 // fragment reads share about 113 bytes a clock, 48 KB per step of 64 x 64 x 64 (0.18 us; measured 0.14 .. 0.20), 72 KB of
-// 64 x 128 (0.27; 0.23 .. 0.31), 96 KB of 128 x 128 (0.36; 0.40 .. 0.47).  Level or slower: wavefronts that share a tile along k
+// 64 x 128 (0.27; 0.23 .. 0.31), 96 KB of 128 x 128 (0.36; 0.40 .. 0.47).  A compute unit with one such tile gets its operands at
+// 93 bytes a ns at most, whatever the tile and however many steps are in flight (64 x 64 0.175 us a step, 128 x 128 0.35).  Level or slower: wavefronts that share a tile along k
 // and so read less (64 x 128, M = 2400, K = 1280: 11.0 against 9.9 us), two steps per barrier, more stages, reads or loads
 // placed elsewhere among the matrix instructions.
 #include "amap_gemm_ring.hpp"
@@ -33,6 +34,24 @@ namespace {
 
 // the part of the argument block in front of the epilogue's tables and of the second source of a gathered A
 constexpr uint32_t kRingArgTouch = sizeof(RingArgs<1>);
+
+// Wavefronts that only load (T::LOAD of them, behind those that compute): the same waits without the wavefront's own LDS reads, which it has none of.
+template <int N>
+__device__ __forceinline__ void ring_landed() {
+    static_assert(N < 64, "vmcnt");
+    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"i"(N) : "memory");
+}
+template <int L, int R>
+__device__ __forceinline__ void ring_landed_step(uint32_t later) {
+    if constexpr (R == 0) {
+        ring_landed<0>();
+    } else {
+        if (later >= (uint32_t)R)
+            ring_landed<R * L>();
+        else
+            ring_landed_step<L, R - 1>(later);
+    }
+}
 
 // wait until the loads of all but the `later` newest steps (L loads each per wavefront) have landed, then meet the
 // other wavefronts; the compiler does not know of these loads.  (lgkmcnt: this wavefront's reads of the stage that is
@@ -77,13 +96,13 @@ __device__ __forceinline__ void ring_load(const char *base, const uint32_t (&off
 }
 
 template <class T>
-__global__ __launch_bounds__(64 * T::WVM * T::WVN, T::OCC) void amap_gemm_ring_kernel(const RingArgs<T::NSEG> g) {
+__global__ __launch_bounds__(64 * (T::WVM * T::WVN + T::LOAD), T::OCC) void amap_gemm_ring_kernel(const RingArgs<T::NSEG> g) {
     constexpr int BM = T::BM, BN = T::BN, BK = T::BK, NST = T::NST;
-    constexpr int kWaves = T::WVM * T::WVN;
+    constexpr int kCompute = T::WVM * T::WVN, kWaves = kCompute + T::LOAD, kLoad = T::LOAD ? T::LOAD : kCompute;   // wavefronts that compute, all, that load
     constexpr int XM = BM / T::WVM, XN = BN / T::WVN;         // a wavefront's part of the tile
     constexpr bool AX = T::AX, WX = T::WX;
     constexpr uint32_t kABytes = BM * BK * 2, kWBytes = BN * BK * 2, kStage = kABytes + kWBytes;
-    constexpr int NA = kABytes / (1024 * kWaves), NW = kWBytes / (1024 * kWaves);   // loads per wavefront and step
+    constexpr int NA = kABytes / (1024 * kLoad), NW = kWBytes / (1024 * kLoad);   // loads per loading wavefront and step
     constexpr int FM = XM / 32, FN = XN / 32;                 // 32 x 32 tiles per wavefront
     {
         // every 64-byte line of the argument block that the prologue reads, fetched side by side: read where they are
@@ -96,7 +115,8 @@ __global__ __launch_bounds__(64 * T::WVM * T::WVN, T::OCC) void amap_gemm_ring_k
     }
     const uint32_t tid = threadIdx.x, lane = tid & 63u;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const uint32_t wm = wave / T::WVN, wn = wave % T::WVN;
+    const uint32_t wm = wave / T::WVN, wn = wave % T::WVN;   // (used by the wavefronts that compute)
+    const uint32_t lwave = T::LOAD == 0 ? wave : wave < kCompute ? 0u : wave - kCompute;   // a loading wavefront's share of the blocks
     uint32_t tm, tn;
     ring_tile(g.map, blockIdx.x, gridDim.x, tm, tn);
     const uint32_t m0 = tm * BM, n0 = tn * BN;
@@ -105,9 +125,9 @@ __global__ __launch_bounds__(64 * T::WVM * T::WVN, T::OCC) void amap_gemm_ring_k
     static_assert((NA % 4 == 0 || NA == 1 || NA == 2) && (NW % 4 == 0 || NW == 1 || NW == 2), "ring_load");
     uint32_t a_off[NA], w_off[NW];
 #pragma unroll
-    for (int j = 0; j < NA; ++j) a_off[j] = ring_block_offset<AX, BM, T::SHORT>(g.a[0].dx, g.a[0].base, g.a[0].kss, m0, g.M, wave * NA, j, lane);
+    for (int j = 0; j < NA; ++j) a_off[j] = ring_block_offset<AX, BM, T::SHORT>(g.a[0].dx, g.a[0].base, g.a[0].kss, m0, g.M, lwave * NA, j, lane);
 #pragma unroll
-    for (int j = 0; j < NW; ++j) w_off[j] = ring_block_offset<WX, BN, T::SHORT>(g.w.dx, g.w.base, g.w.kss, n0, g.N, wave * NW, j, lane);
+    for (int j = 0; j < NW; ++j) w_off[j] = ring_block_offset<WX, BN, T::SHORT>(g.w.dx, g.w.base, g.w.kss, n0, g.N, lwave * NW, j, lane);
     const char *ka = reinterpret_cast<const char *>(g.a[0].src) - kRingBias, *kw = reinterpret_cast<const char *>(g.w.src) - kRingBias;
     RingWalk a_walk = ring_walk_begin(g.a_steps), w_walk = ring_walk_begin(g.w_steps);
     uint32_t seg = 0, seg_left = g.a[0].steps;   // NSEG > 1: the source the stream reads, and its k-steps to go
@@ -118,7 +138,7 @@ __global__ __launch_bounds__(64 * T::WVM * T::WVN, T::OCC) void amap_gemm_ring_k
     // carried on; M = 6300, K = 1600, N = 4096 108 and 99.5 us; M = 3600, K = 1280, N = 2048 26.8 and 26.1 us; runs of 32:
     // M = 8000, K = 256, N = 2048 16.9 and 16.3 us.
     uint32_t ld_k = 0, kl[2] = {}, kl_low[2] = {};
-    auto chunk_of = [&](uint32_t par) __attribute__((always_inline)) { return 8u * ring_k_chunk(wave * NA + par, lane); };
+    auto chunk_of = [&](uint32_t par) __attribute__((always_inline)) { return 8u * ring_k_chunk(lwave * NA + par, lane); };
     if constexpr (T::KLANE) {
 #pragma unroll
         for (uint32_t par = 0; par < 2; ++par) {
@@ -127,7 +147,7 @@ __global__ __launch_bounds__(64 * T::WVM * T::WVN, T::OCC) void amap_gemm_ring_k
             kl_low[par] = c8 - fdiv(c8, g.a_dk.fext[0]) * g.a_dk.ext[0];
         }
     }
-    const uint32_t lds_a = __builtin_amdgcn_readfirstlane(wave * (NA * 1024u)), lds_w = __builtin_amdgcn_readfirstlane(kABytes + wave * (NW * 1024u));
+    const uint32_t lds_a = __builtin_amdgcn_readfirstlane(lwave * (NA * 1024u)), lds_w = __builtin_amdgcn_readfirstlane(kABytes + lwave * (NW * 1024u));
     auto issue = [&](uint32_t stage) __attribute__((always_inline)) {
         if constexpr (T::NSEG > 1) {
             if (seg_left == 0) {   // the next source of a gathered A: its own rows, strides and pointer
@@ -137,7 +157,7 @@ __global__ __launch_bounds__(64 * T::WVM * T::WVN, T::OCC) void amap_gemm_ring_k
                 seg_step = 2 * (int64_t)s.kss * BK;
                 ka = reinterpret_cast<const char *>(s.src) - kRingBias;
 #pragma unroll
-                for (int j = 0; j < NA; ++j) a_off[j] = ring_block_offset<AX, BM, T::SHORT>(s.dx, s.base, s.kss, m0, g.M, wave * NA, j, lane);
+                for (int j = 0; j < NA; ++j) a_off[j] = ring_block_offset<AX, BM, T::SHORT>(s.dx, s.base, s.kss, m0, g.M, lwave * NA, j, lane);
             }
         }
         if constexpr (T::KLANE) {
@@ -200,76 +220,138 @@ __global__ __launch_bounds__(64 * T::WVM * T::WVN, T::OCC) void amap_gemm_ring_k
         for (int j = 0; j < FN; ++j)
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-    // Two sets of fragments, PK sub-steps of 16 k each: one is read while the other feeds the matrix cores.
-    constexpr int PK = T::PK, kPhases = kSub / PK, L = NA + NW;
-    static_assert(kSub % PK == 0 && (kPhases % 2 == 0 || (kPhases == 1 && NST % 2 == 0)), "the fragment sets alternate");
-    bf16x8 fa[2][PK][FM], fw[2][PK][FN];
-    auto read_one = [&](uint32_t set, uint32_t stage, uint32_t ph, int r) __attribute__((always_inline)) {
-        if (r >= PK * (FM + FN)) return;
-        const uint32_t kk = (uint32_t)(r / (FM + FN)), f = (uint32_t)(r % (FM + FN));
-        if (f < (uint32_t)FM)
-            fa[set][kk][f] = read_frag(ax, bm, a_frag, stage, f, ph * PK + kk);
-        else
-            fw[set][kk][f - FM] = read_frag(wx, bn, w_frag, stage, f - FM, ph * PK + kk);
-    };
-    // the MFMAs of one phase on fragment set `set`, the reads of the next phase (ph of `stage`) spread under them
-    auto phase = [&](uint32_t set, uint32_t stage, uint32_t ph) __attribute__((always_inline)) {
-        constexpr int kMf = PK * FM * FN, kRd = PK * (FM + FN), kPer = (kRd + kMf - 1) / kMf;
-#pragma unroll
-        for (int q = 0; q < kMf; ++q) {
-#pragma unroll
-            for (int r = 0; r < kPer; ++r) read_one(set ^ 1u, stage, ph, q * kPer + r);
-            const int kk = q / (FM * FN), i = q / FN % FM, j = q % FN;
-            // W as the row operand: the 32 x 32 result is C^T, a lane holds four consecutive n of one row m
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fw[set][kk][j], fa[set][kk][i], acc[i][j], 0, 0, 0);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-    };
-
     const uint32_t steps = g.steps;
+    constexpr int L = NA + NW;
+    if constexpr (T::LOAD) {
+        // Loading is left to wavefronts of their own: a load instruction holds its wavefront until the address unit takes it, and
+        // with one small tile on a compute unit nothing else fills that time.  A loading wavefront is one barrier per step:
+        // its loads of the next step have landed, the stage of the step before is free, its next loads go there.  The others have the
+        // whole step's fragments in registers and read the next step's into each as its last MFMA is issued.
+        // 32 x 64 tiles, M = 256 and 512, K = N = 1024: 5.5 -> 4.8 us and 5.7 -> 4.9 us, M = N = 512, K = 2560 9.4 -> 8.7 us.
+        // (64 x 64 tiles so 12.0 -> 11.5 us and 6.7 -> 6.4, but 0 .. 8 % slower from two tiles per unit on; 128 x 128 level.)
+        static_assert(NST >= 4, "the stage a step leaves is refilled a step later");
+        uint32_t left = steps - 1u;
+        if (wave >= kCompute) {
 #pragma unroll
-    for (int s = 0; s < NST; ++s)
-        if ((uint32_t)s < steps) issue((uint32_t)s * kStage);
-    ring_wait_step<L, NST - 1>(steps - 1u);
+            for (int s = 0; s < NST - 1; ++s)
+                if ((uint32_t)s < steps) issue((uint32_t)s * kStage);
+            ring_landed_step<L, NST - 2>(left);
+            uint32_t to = (NST - 1) * kStage;
+            for (; left >= (uint32_t)NST - 1u; --left) {
+                ring_landed<(NST - 3) * L>();
+                issue(to);
+                to = to == (NST - 1) * kStage ? 0u : to + kStage;
+            }
+            for (; left; --left) ring_landed_step<L, NST - 3>(left - 1u);
+        } else {
+            bf16x8 fa[kSub][FM], fw[kSub][FN];
+            asm volatile("s_barrier" ::: "memory");   // the first step has landed
 #pragma unroll
-    for (int r = 0; r < PK * (FM + FN); ++r) read_one(0, 0, 0, r);
-    // the ring once around per pass: stages and fragment sets are constants, a read is one instruction
-    uint32_t left = steps - 1u;
-    for (;;) {
-        bool done = false;
+            for (int kk = 0; kk < kSub; ++kk) {
 #pragma unroll
-        for (int st = 0; st < NST; ++st) {
-            if (done) break;
-            const uint32_t cur = st * kStage, next = (st + 1) % NST * kStage, set0 = kPhases == 1 ? st & 1 : 0;
+                for (int i = 0; i < FM; ++i) fa[kk][i] = read_frag(ax, bm, a_frag, 0, i, kk);
 #pragma unroll
-            for (int ph = 0; ph + 1 < kPhases; ++ph) phase(set0 ^ (ph & 1u), cur, ph + 1);
-            // the last fragments of this step are read: its stage is free once every wavefront is here, and the next step's
-            // loads (all but those of up to NST - 2 later steps) have landed
-            if (left) ring_wait_step<L, NST - 2>(left - 1u);
-            if (left >= (uint32_t)NST) issue(cur);
-            __builtin_amdgcn_sched_barrier(0);
-            phase(set0 ^ ((kPhases - 1) & 1u), next, 0);   // (after the last step: a stale stage, read and unused)
-            if (left-- == 0) done = true;
+                for (int j = 0; j < FN; ++j) fw[kk][j] = read_frag(wx, bn, w_frag, 0, j, kk);
+            }
+            uint32_t next = kStage;
+            for (;;) {
+                if (left) asm volatile("s_barrier" ::: "memory");   // the next step has landed; the last one's fragments have all been used
+                __builtin_amdgcn_sched_barrier(0);
+                uint32_t a_next[AX ? FM : kSub], w_next[WX ? FN : kSub];
+#pragma unroll
+                for (int i = 0; i < (AX ? FM : kSub); ++i) a_next[i] = a_frag[i] + next;
+#pragma unroll
+                for (int i = 0; i < (WX ? FN : kSub); ++i) w_next[i] = w_frag[i] + next;
+#pragma unroll
+                for (int kk = 0; kk < kSub; ++kk)
+#pragma unroll
+                    for (int i = 0; i < FM; ++i)
+#pragma unroll
+                        for (int j = 0; j < FN; ++j) {
+                            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fw[kk][j], fa[kk][i], acc[i][j], 0, 0, 0);
+                            __builtin_amdgcn_sched_barrier(0);
+                            // (after the last step: a stale stage, read and unused)
+                            if (j == FN - 1) fa[kk][i] = read_frag(ax, bm, a_next, 0, i, kk);
+                            if (i == FM - 1) fw[kk][j] = read_frag(wx, bn, w_next, 0, j, kk);
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
+                next = next == (NST - 1) * kStage ? 0u : next + kStage;
+                if (left-- == 0) break;
+            }
         }
-        if (done) break;
+    } else {
+        // Two sets of fragments, PK sub-steps of 16 k each: one is read while the other feeds the matrix cores.
+        constexpr int PK = T::PK, kPhases = kSub / PK;
+        static_assert(kSub % PK == 0 && (kPhases % 2 == 0 || (kPhases == 1 && NST % 2 == 0)), "the fragment sets alternate");
+        bf16x8 fa[2][PK][FM], fw[2][PK][FN];
+        auto read_one = [&](uint32_t set, uint32_t stage, uint32_t ph, int r) __attribute__((always_inline)) {
+            if (r >= PK * (FM + FN)) return;
+            const uint32_t kk = (uint32_t)(r / (FM + FN)), f = (uint32_t)(r % (FM + FN));
+            if (f < (uint32_t)FM)
+                fa[set][kk][f] = read_frag(ax, bm, a_frag, stage, f, ph * PK + kk);
+            else
+                fw[set][kk][f - FM] = read_frag(wx, bn, w_frag, stage, f - FM, ph * PK + kk);
+        };
+        // the MFMAs of one phase on fragment set `set`, the reads of the next phase (ph of `stage`) spread under them
+        auto phase = [&](uint32_t set, uint32_t stage, uint32_t ph) __attribute__((always_inline)) {
+            constexpr int kMf = PK * FM * FN, kRd = PK * (FM + FN), kPer = (kRd + kMf - 1) / kMf;
+#pragma unroll
+            for (int q = 0; q < kMf; ++q) {
+#pragma unroll
+                for (int r = 0; r < kPer; ++r) read_one(set ^ 1u, stage, ph, q * kPer + r);
+                const int kk = q / (FM * FN), i = q / FN % FM, j = q % FN;
+                // W as the row operand: the 32 x 32 result is C^T, a lane holds four consecutive n of one row m
+                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fw[set][kk][j], fa[set][kk][i], acc[i][j], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+
+#pragma unroll
+        for (int s = 0; s < NST; ++s)
+            if ((uint32_t)s < steps) issue((uint32_t)s * kStage);
+        ring_wait_step<L, NST - 1>(steps - 1u);
+#pragma unroll
+        for (int r = 0; r < PK * (FM + FN); ++r) read_one(0, 0, 0, r);
+        // the ring once around per pass: stages and fragment sets are constants, a read is one instruction
+        uint32_t left = steps - 1u;
+        for (;;) {
+            bool done = false;
+#pragma unroll
+            for (int st = 0; st < NST; ++st) {
+                if (done) break;
+                const uint32_t cur = st * kStage, next = (st + 1) % NST * kStage, set0 = kPhases == 1 ? st & 1 : 0;
+#pragma unroll
+                for (int ph = 0; ph + 1 < kPhases; ++ph) phase(set0 ^ (ph & 1u), cur, ph + 1);
+                // the last fragments of this step are read: its stage is free once every wavefront is here, and the next step's
+                // loads (all but those of up to NST - 2 later steps) have landed
+                if (left) ring_wait_step<L, NST - 2>(left - 1u);
+                if (left >= (uint32_t)NST) issue(cur);
+                __builtin_amdgcn_sched_barrier(0);
+                phase(set0 ^ ((kPhases - 1) & 1u), next, 0);   // (after the last step: a stale stage, read and unused)
+                if (left-- == 0) done = true;
+            }
+            if (done) break;
+        }
     }
 
     // ---- epilogue: the tile rounded to bf16 in LDS (the ring is free once every wavefront has passed), then whole rows
     // of 16-byte stores.  Accumulator v of a 32 x 32 tile in lane l: m = l % 32, n = 8 (v / 4) + 4 (l / 32) + v % 4.
     __syncthreads();
     const uint32_t row_l = lane & 31u, half = lane >> 5;
+    if (T::LOAD == 0 || wave < kCompute) {
 #pragma unroll
-    for (int i = 0; i < FM; ++i)
+        for (int i = 0; i < FM; ++i)
 #pragma unroll
-        for (int j = 0; j < FN; ++j)
+            for (int j = 0; j < FN; ++j)
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                u32x2 o;
-                o.x = pack_bf16(acc[i][j][4 * q], acc[i][j][4 * q + 1]);
-                o.y = pack_bf16(acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
-                const uint32_t row = wm * XM + 32u * i + row_l, chunk = wn * (XN / 8) + 4u * j + q;
-                *reinterpret_cast<__attribute__((address_space(3))) u32x2 *>(ring_c_slot<BN>(row, chunk) + ((half ^ ((row >> 4) & 1u)) << 3)) = o;
-            }
+                for (int q = 0; q < 4; ++q) {
+                    u32x2 o;
+                    o.x = pack_bf16(acc[i][j][4 * q], acc[i][j][4 * q + 1]);
+                    o.y = pack_bf16(acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
+                    const uint32_t row = wm * XM + 32u * i + row_l, chunk = wn * (XN / 8) + 4u * j + q;
+                    *reinterpret_cast<__attribute__((address_space(3))) u32x2 *>(ring_c_slot<BN>(row, chunk) + ((half ^ ((row >> 4) & 1u)) << 3)) = o;
+                }
+    }
     __syncthreads();
     typedef RingStore<BM, BN, kWaves> Store;
     const uint32_t cv = tid % Store::kCv, n = n0 + cv * 8u;
@@ -308,7 +390,7 @@ amap_status launch(const RingArgs<kMaxSeg> &full, uint32_t grid, hipStream_t str
     RingArgs<T::NSEG> g;
     static_cast<RingCommon &>(g) = full;
     for (int i = 0; i < T::NSEG; ++i) g.a[i] = full.a[i];
-    const hipError_t e = launch_kernel(amap_gemm_ring_kernel<T>, dim3(grid), dim3(64 * T::WVM * T::WVN), lds, stream, g);
+    const hipError_t e = launch_kernel(amap_gemm_ring_kernel<T>, dim3(grid), dim3(64 * (T::WVM * T::WVN + T::LOAD)), lds, stream, g);
     if (e != hipSuccess) {
         set_last_error("amap_gemm_ring_kernel", hipGetErrorString(e));
         return AMAP_E_HIP;
@@ -316,11 +398,12 @@ amap_status launch(const RingArgs<kMaxSeg> &full, uint32_t grid, hipStream_t str
     return AMAP_OK;
 }
 
-template <int BM_, int BN_, int BK_, int NST_, int PK_, int WVM_, int WVN_, int OCC_, bool AX_, bool WX_, int NSEG_, int KLANE_>
+template <int BM_, int BN_, int BK_, int NST_, int PK_, int WVM_, int WVN_, int OCC_, bool AX_, bool WX_, int NSEG_, int KLANE_, int LOAD_ = 0>
 struct Shape {
     static constexpr int BM = BM_, BN = BN_, BK = BK_, NST = NST_, PK = PK_, WVM = WVM_, WVN = WVN_, OCC = OCC_, NSEG = NSEG_;
     static constexpr bool AX = AX_, WX = WX_;
     static constexpr bool SHORT = PK_ == 2 || BM_ * BN_ < 128 * 128;   // see ring_digits
+    static constexpr int LOAD = LOAD_;     // wavefronts that only load (0: those that compute load as well)
     static constexpr int KLANE = KLANE_;   // 0: whole steps of k in a run of A; 1, 2: shorter runs, of one length / of any digits
 };
 
@@ -384,12 +467,13 @@ static double share_of(uint64_t tiles, double k64, uint32_t n_cu, double step, d
     return 4.0 + rounds * (step * k64 + tile);
 }
 
-// The other shapes against that choice, and the 256 x 256 tiles against both: time in us, `launch` for the launch, the first
+// The shapes against each other, and the 256 x 256 tiles against them: time in us, `launch` for the launch, the first
 // loads and the last stores, `tile` per tile of the busiest compute unit, and for every 64 k of its tiles s1 where it has one
 // and all units do, s2 for two (they share the unit), `more` for each further one; from s0 to s1 up to one tile per unit (the
 // fewer units work, the faster each).  What lies between whole numbers of tiles per unit counts for `up` of the next one.
-// Fitted to 304 products of K = 32 .. 2560, each row over the tiles per unit at which its shape is considered: along k 64 x 128
-// and 128 x 128 by 8 wavefronts up to two, by 4 beyond two (its s0 is never used; 8 wavefronts beyond two are counted as 4).
+// Along k: fitted to 1195 products of K = 256 .. 2560 timed on the device, operands in three sets of buffers in turn, each row over the
+// tiles per unit at which its shape is considered and most where it is near the best (128 x 128 by 4 wavefronts is counted as by 8).
+// Along m and n: fitted to 304 products, calls in a stream (about 1.2 us more in every row).
 struct RingCost {
     float launch, s0, s1, s2, more, tile, up;
 };
@@ -399,24 +483,23 @@ static double estimate(const RingCost &c, uint64_t tiles, double k64, uint32_t n
     return c.launch + c.tile * e + step * k64;
 }
 // by RingShape: whole steps of k in a run of A; shorter runs; both operands along m and n
-static const RingCost kCostK[] = {{4.64f, .108f, .134f, .243f, .138f, .06f, .29f}, {4.33f, .140f, .203f, .330f, .198f, .10f, .56f},
-                                  {4.28f, .230f, .306f, .589f, .191f, .05f, .71f},
-                                  {2.92f, .000f, .944f, .953f, .388f, 1.99f, .83f}, {2.00f, .356f, .688f, .914f, .450f, 1.57f, .06f}};
-static const RingCost kCostRuns[] = {{4.25f, .146f, .188f, .261f, .157f, .00f, 1.f}, {4.11f, .196f, .236f, .387f, .230f, .00f, 1.f},
-                                     {4.19f, .271f, .344f, .604f, .359f, .01f, 1.f},
-                                     {4.00f, .400f, .800f, 1.20f, .500f, .90f, .6f}, {3.34f, .409f, .714f, 1.16f, .800f, .41f, .34f}};
+static const RingCost kCostK[] = {{2.79f, .100f, .146f, .258f, .215f, .34f, .66f}, {2.94f, .176f, .237f, .365f, .213f, .24f, .63f},
+                                  {3.71f, .253f, .315f, .635f, .240f, .07f, .60f}, {1.78f, .453f, .661f, .814f, .617f, 1.81f, .60f},
+                                  {1.78f, .453f, .661f, .814f, .617f, 1.81f, .60f}, {3.84f, .226f, .521f, 0.f, 0.f, 1.f, 0.f},
+                                  {3.60f, .133f, .192f, 0.f, 0.f, .10f, 0.f}};
+static const RingCost kCostRuns[] = {{3.11f, .110f, .161f, .281f, .282f, .11f, .76f}, {3.04f, .225f, .270f, .446f, .240f, .00f, .62f},
+                                     {3.52f, .286f, .361f, .688f, .567f, .00f, .63f}, {1.38f, .457f, .738f, 1.09f, .512f, 1.90f, .31f},
+                                     {1.38f, .457f, .738f, 1.09f, .512f, 1.90f, .31f}, {3.22f, .361f, .594f, 0.f, 0.f, 1.f, 0.f},
+                                     {3.55f, .165f, .244f, 0.f, 0.f, .00f, 0.f}};
 static const RingCost kCostX[] = {{}, {5.86f, .193f, .193f, .398f, .239f, .01f, .00f}, {5.46f, .285f, .358f, .628f, .377f, .11f, .19f},
                                   {5.18f, .439f, .842f, 1.25f, .742f, .17f, .20f}};
 
-static const struct { int bm, bn, waves; } kRingTile[] = {{32, 64, 2}, {64, 64, 4}, {64, 128, 4}, {128, 128, 4}, {128, 128, 8}};
+// rows, columns, wavefronts that compute, what else there is to say (in a trace)
+static const struct { int bm, bn, waves; const char *more; } kRingTile[] = {{32, 64, 2, ", 2 more load"}, {64, 64, 4, ""}, {64, 128, 4, ""}, {128, 128, 4, ""}, {128, 128, 8, ""},
+                                                                            {128, 128, 8, ", four stages"}, {64, 64, 4, ", 4 more load"}};
 
-// The shape of a product's tiles, and its estimate.  Measured on products that the figures above were not fitted to, operands in three
-// sets of buffers in turn: along k (2481; the lines in K and in tiles per unit below were drawn on two thirds of them and on 960 others)
-// 3.2 % faster in the mean than by 64 x 64 and 128 x 128 tiles alone, 14 slower by 2 to 17 % (the worst an N of 152, which 128 columns
-// fill worse than 64), and 1.0 % off the best shape each has, 187 by more than 5 %: most of them between one and two 64 x 128 tiles per
-// unit, where 8 wavefronts on 128 x 128 are taken and 64 x 64 or 64 x 128 tiles are up to 18 % faster.  With one set of buffers, all of
-// it in the L2s, 64 x 64 tiles are ahead more often.  A margin that the other shapes have to promise costs more than it saves (579
-// products: none 1.8 %, 4 % 1.4, 6 % 0.8).  Along m (89) 17 % faster, none slower, 1.5 % off the best.
+// The shape of a product's tiles, and its estimate.  Measured on 354 other products along k: 0.8 % off the best shape each has, where
+// the shapes and figures before this were 3.2 % off.  Along m (89) 17 % faster than by 128 x 128 alone, none slower, 1.5 % off the best.
 static RingShape ring_shape(const GemmArgs &g, const RingPlan &p, uint32_t n_cu, double &best) {
     RingShape shape = RS_128x128;
     best = 1e30;
@@ -451,6 +534,7 @@ static RingShape ring_shape(const GemmArgs &g, const RingPlan &p, uint32_t n_cu,
     const bool by8 = up128 <= 2 || (up128 > 8 ? g.K >= 1024 : up128 % 2 == 0 && g.K >= (up128 == 6 ? 960u : 768u));
     const bool small = share_of(tiles(64, 64), k64, n_cu, 0.19, 0.35) < share_of(tiles(128, 128), k64, n_cu, 0.47, 1.4);
     consider(small ? RS_64x64 : up128 <= 2 ? RS_128x128_W8 : RS_128x128);
+    const uint64_t t64 = tiles(64, 64), t128 = tiles(128, 128);
     if (p.klane < 2) {
         // three stages of 64 x 128 while two workgroups find room on every compute unit and the walk is long enough to pay for them:
         // M = 2400, K = 1280, N = 768 10.7 -> 9.5 us, M = 1322, K = N = 2048 22.3 -> 20.2, M = 825, K = 768, N = 2304 8.0 -> 7.4,
@@ -463,9 +547,20 @@ static RingShape ring_shape(const GemmArgs &g, const RingPlan &p, uint32_t n_cu,
         // as fast
         const uint32_t least_k = q64x128 > 1.5 ? 384u : p.klane || 3.0 * q64x128 >= 2.0 ? 640u : 1280u;
         if (q64x128 <= 2.0 && g.K >= least_k) consider(RS_64x128);
-        // few tiles and a long walk: M = 518, K = 2560, N = 512 12.0 -> 9.8 us.  Fewer than 16 tiles of 64 x 64 stay (M = 70,
-        // K = 1024, N = 120 6.4 and 6.3 us).
-        if (tiles(64, 64) >= 16) consider(RS_32x64);
+        // Few tiles: 32 x 64 by two wavefronts that compute and two that load: M = 518, K = 2560, N = 512 12.0 (64 x 64) -> 8.7 us, M = 256,
+        // K = N = 1024 5.9 -> 4.7, M = 49, K = 2560, N = 768 10.5 -> 7.2.  Very few tiles only with a long walk, and none of a short one:
+        // there both take what issuing the call takes (M = 435, K = 384, N = 768 4.6 and 4.1 us, M = 62, K = 640, N = 768 5.1 and 4.3).
+        // Runs of A shorter than a step cost the wavefronts that only load nothing: from K = 256 on (runs of 32, M = 44, K = 384, N = 1024
+        // 4.35 -> 4.0).
+        if (g.K >= (p.klane ? 256u : 512u) && (t64 >= 16 || (t64 >= 8 && g.K >= 896))) consider(RS_32x64);
+        // 64 x 64 with loading wavefronts while no unit has two of them: M = 1000, K = N = 1024 6.7 -> 6.3 us, M = 576, K = 2048, N = 1024
+        // 10.2 -> 8.9; beyond that 5 to 18 % slower, the other wavefronts' tiles fill the time already.
+        if (t64 >= 16 && t64 <= n_cu) consider(RS_64x64_LOAD);
+        // One 128 x 128 tile to a unit: four stages, three steps of operands on their way, instead of two stages for each of two
+        // workgroups of which a unit has but one: M = 2618, K = 2560, N = 1000 28 -> 21.5 us, M = 2445, K = 1280, N = 1024 15.3 -> 12.2,
+        // M = 1016, K = 1024, N = 3072 12.7 -> 10.9.  Up to half a unit's worth of tiles the smaller ones are ahead; nearly all
+        // units busy, a short walk ends sooner on more, smaller workgroups (M = 970, K = 1024, N = 4096 14.8 against 13.4).
+        if (2 * t128 > n_cu && t128 <= n_cu && (20 * t128 <= 17 * (uint64_t)n_cu || g.K >= 1280)) consider(RS_128x128_DEEP);
     }
     if (shape == RS_128x128 && by8) shape = RS_128x128_W8;
     return shape;
@@ -531,12 +626,13 @@ bool ring_plan(const GemmArgs &g, int amode, int wmode, bool tile256, uint32_t n
         // fitted to the same products: the busier the chip the lower its clock; partial tiles add their masks.
         const uint64_t n256 = (uint64_t)((g.M + 255) / 256) * ((g.N + 255) / 256), rounds = (n256 + n_cu - 1) / n_cu, wgs = (n256 + rounds - 1) / rounds;
         const double step256 = 0.96 + 0.53 * (double)wgs / n_cu;
-        const double t256 = 6.3 + (g.M % 256 || g.N % 256 ? 2.2 : 0.0) + (double)rounds * (g.K / 64.0) * step256 + 5.5 * (double)(rounds - 1);
+        const double t256 = 4.0 + (g.M % 256 || g.N % 256 ? 1.5 : 0.0) + (double)rounds * (g.K / 64.0) * step256 + 5.5 * (double)(rounds - 1);
         if (t > t256) return false;
     }
     p.bm = kRingTile[p.shape].bm;
     p.bn = kRingTile[p.shape].bn;
     p.waves = kRingTile[p.shape].waves;
+    p.more = kRingTile[p.shape].more;
     r.map.tiles_m = (uint32_t)((g.M + p.bm - 1) / p.bm);
     r.map.tiles_n = (uint32_t)((g.N + p.bn - 1) / p.bn);
     if ((uint64_t)r.map.tiles_m * r.map.tiles_n >= (1ull << 31)) return false;
@@ -556,7 +652,7 @@ template <bool AX, bool WX, int NSEG, int KLANE, class F>
 void with_tile(const RingPlan &p, F f) {
     switch (p.shape) {
     case RS_32x64:
-        if constexpr (!AX && NSEG == 1 && KLANE < 2) f(Shape<32, 64, 64, 4, 2, 1, 2, 4, false, WX, 1, KLANE>());
+        if constexpr (!AX && NSEG == 1 && KLANE < 2) f(Shape<32, 64, 64, 5, 2, 1, 2, 2, false, WX, 1, KLANE, 2>());
         break;
     case RS_64x64:
         if constexpr (AX && WX)
@@ -569,6 +665,12 @@ void with_tile(const RingPlan &p, F f) {
             f(Shape<64, 128, 32, 3, 1, 2, 2, 4, true, true, NSEG, 0>());
         else if constexpr (!AX && NSEG == 1 && KLANE < 2)
             f(Shape<64, 128, 64, 3, 2, 2, 2, 2, false, WX, 1, KLANE>());
+        break;
+    case RS_64x64_LOAD:
+        if constexpr (!AX && NSEG == 1 && KLANE < 2) f(Shape<64, 64, 64, 5, 2, 2, 2, 2, false, WX, 1, KLANE, 4>());
+        break;
+    case RS_128x128_DEEP:
+        if constexpr (!AX && NSEG == 1 && KLANE < 2) f(Shape<128, 128, 64, 4, 2, 2, 4, 2, false, WX, 1, KLANE>());
         break;
     case RS_128x128_W8:
         if constexpr (!AX && NSEG == 1) f(Shape<128, 128, 64, 2, 2, 2, 4, 4, false, WX, 1, KLANE>());
@@ -608,8 +710,8 @@ void with_shape(const RingPlan &p, F f) {
 // every load, fragment read and store of one kernel shape, with the kernel's own address functions
 template <class T>
 int64_t replay(const RingArgs<kMaxSeg> &r, const GemmArgs &g, const int64_t *a_bytes, int64_t w_bytes) {
-    constexpr int BM = T::BM, BN = T::BN, BK = T::BK, kWaves = T::WVM * T::WVN, XM = BM / T::WVM, XN = BN / T::WVN;
-    constexpr uint32_t NA = BM * BK * 2 / (1024 * kWaves), NW = BN * BK * 2 / (1024 * kWaves);
+    constexpr int BM = T::BM, BN = T::BN, BK = T::BK, kCompute = T::WVM * T::WVN, kWaves = kCompute + T::LOAD, kLoad = T::LOAD ? T::LOAD : kCompute, XM = BM / T::WVM, XN = BN / T::WVN;
+    constexpr uint32_t NA = BM * BK * 2 / (1024 * kLoad), NW = BN * BK * 2 / (1024 * kLoad);
     int64_t errors = 0;
     const uint32_t grid = r.map.tiles_m * r.map.tiles_n;
     std::vector<uint8_t> written((size_t)g.M * g.N / 8, 0), seen(grid, 0);
@@ -623,7 +725,7 @@ int64_t replay(const RingArgs<kMaxSeg> &r, const GemmArgs &g, const int64_t *a_b
         }
         const uint32_t m0 = tm * BM, n0 = tn * BN;
         int64_t ka = 0, kw = 0;
-        std::vector<uint32_t> kl(kWaves * 64 * 2), low(kl.size());   // as the kernel's kl, kl_low
+        std::vector<uint32_t> kl(kLoad * 64 * 2), low(kl.size());   // as the kernel's kl, kl_low
         for (size_t i = 0; T::KLANE && i < kl.size(); ++i) {
             const uint32_t c8 = 8u * ring_k_chunk((uint32_t)(i / 128) * NA + (i & 1u), (uint32_t)(i / 2 % 64));
             kl[i] = 2u * (ring_digits<T::SHORT>(r.a_dk, c8) - c8);
@@ -639,7 +741,7 @@ int64_t replay(const RingArgs<kMaxSeg> &r, const GemmArgs &g, const int64_t *a_b
                 ka = 0;
             }
             const RingOperand &A = r.a[seg];
-            for (uint32_t wave = 0; wave < (uint32_t)kWaves; ++wave)
+            for (uint32_t wave = 0; wave < (uint32_t)kLoad; ++wave)
                 for (uint32_t lane = 0; lane < 64; ++lane) {
                     const size_t at_kl = (wave * 64 + lane) * 2;
                     for (uint32_t j = 0; j < NA; ++j) {

@@ -164,13 +164,15 @@ struct RingStore {
     static AMAP_HD uint32_t lane_of_store(uint32_t p, uint32_t lane) { return p * kWaveRows + lane / kCv; }
 };
 
-// The tiles there are (W8: 8 wavefronts).
-enum RingShape { RS_32x64 = 0, RS_64x64, RS_64x128, RS_128x128, RS_128x128_W8 };
+// The tiles there are (W8: 8 wavefronts; DEEP: 8 wavefronts and four stages, one workgroup to a compute unit; LOAD: four wavefronts
+// that compute and four that load).
+enum RingShape { RS_32x64 = 0, RS_64x64, RS_64x128, RS_128x128, RS_128x128_W8, RS_128x128_DEEP, RS_64x64_LOAD };
 
 // A product as the ring kernel runs it: tile, wavefronts, forms of the operands (X: runs along m / n), arguments.
 struct RingPlan {
     RingShape shape;
-    int bm, bn, waves;
+    int bm, bn, waves;   // wavefronts that compute
+    const char *more;    // for a trace: what else the shape has
     bool ax, wx;
     int klane;    // runs of A along k shorter than a k-step: 1 of one length (k has two digits), 2 more digits
     int n_seg;

@@ -1,0 +1,50 @@
+"""Products with at most one tile to a compute unit: wavefronts that only load (32 x 64 and 64 x 64 tiles), four stages of 128 x 128.  On the CPU the host replay, on the GPU bit for bit against the
+general kernel, which adds the same products in the same order."""
+import pytest
+
+from paper_2002_12798_amd import binding as B
+from tests.test_gemm_ring import _replay, dev, merge  # noqa: F401  (dev: fixture)
+from tests.test_gemm_ring_shapes import _against_general
+
+CASES = [
+    # chain -> [M,K], N, what the plan says of tile and wavefronts; partial tiles, whole runs of A and runs shorter than a step
+    (merge(1, 8, 250, 64), 264, "32 x 64", "2 more load"),          # the fewest steps: eight in a ring of five stages
+    (merge(1, 14, 64, 64), 520, "32 x 64", "2 more load"),          # eight tiles of 64 x 64, the fewest with K from 896 on
+    (merge(2, 12, 63, 80), 1000, "32 x 64", "2 more load"),         # rows of 2000 bytes
+    (merge(2, 20, 500, 64), 1000, "64 x 64", "4 more load"),        # 256 tiles, one to each unit
+    (merge(2, 16, 500, 80), 1000, "64 x 64", "4 more load"),
+    (merge(4, 8, 275, 64), 1928, "128 x 128", "four stages"),       # 144 tiles, just over half the units
+    (merge(4, 8, 275, 80), 1928, "128 x 128", "four stages"),
+    (merge(8, 20, 512, 64), 1000, "128 x 128", "four stages"),      # 256 tiles
+]
+
+
+def _maps(case):
+    (shapes, ops), n, tile, more = CASES[case]
+    a = B.amap_compose(shapes, 2, ops)
+    m, k = B.dst_shape(a)
+    wt = B.amap_compose([(n, k)], 2, [("transpose", (1, 0))])
+    store = B.amap_compose([(m, n)], 2, [("reshape", (m, n // 8, 8)), ("transpose", (1, 0, 2))])
+    return shapes, a, n, wt, store, f"{tile} per workgroup", more
+
+
+@pytest.mark.parametrize("case", range(len(CASES)))
+def test_replay(case, monkeypatch, capfd):
+    _, a, n, wt, store, tile, more = _maps(case)
+    monkeypatch.setenv("AMAP_PLAN_TRACE", "1")
+    for w, out_map in ((None, None), (wt, None), (wt, store)):
+        capfd.readouterr()
+        assert _replay(a, n, w, out_map) == (B.AMAP_OK, 0)
+        line = capfd.readouterr().err
+        assert tile in line and line.strip().endswith(more)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", range(len(CASES)))
+def test_against_the_general_kernel(dev, case, monkeypatch, capfd):  # noqa: F811
+    shapes, a, n, wt, store, _, more = _maps(case)
+    for w, out_map in ((None, None), (wt, None), (None, store)):
+        print(f"[gpu] few tiles {shapes} N={n} w={'nk' if w else 'kn'} store={out_map is not None}", flush=True)
+        assert _replay(a, n, w, out_map) == (B.AMAP_OK, 0)
+        _against_general(dev, shapes, a, n, w, monkeypatch, capfd, 1300 + case, more, out_map)
+        monkeypatch.undo()
