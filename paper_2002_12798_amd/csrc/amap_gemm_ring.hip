@@ -364,15 +364,24 @@ __global__ __launch_bounds__(64 * (T::WVM * T::WVN + T::LOAD), T::OCC) void amap
         const uint32_t m = m0 + Store::row_of_lane(wave, lane);
         row_off = ring_digits<T::SHORT>(g.om, m < g.M ? m : g.M - 1u);
     }
+    const uint32_t M = g.M, N = g.N;
+    uint16_t *const C = g.C;
+    const bool mapped = g.store_mapped;
+    auto store_tile = [&](auto stream) __attribute__((always_inline)) {
 #pragma unroll
-    for (uint32_t p = 0; p < Store::kPasses; ++p) {
-        const uint32_t row = Store::row_of_store(p, tid), m = m0 + row;
-        u32x4 x = *reinterpret_cast<lds_u32x4 *>(ring_c_slot<BN>(row, cv));
-        if ((row >> 4) & 1u) x = u32x4{x.z, x.w, x.x, x.y};
-        size_t off = (size_t)m * g.N + n_off;
-        if (g.store_mapped) off = n_off + (uint32_t)__builtin_amdgcn_ds_bpermute((int)(4u * Store::lane_of_store(p, lane)), (int)row_off);
-        if (m < g.M && n_ok) __builtin_nontemporal_store(x, reinterpret_cast<u32x4 *>(g.C + off));
-    }
+        for (uint32_t p = 0; p < Store::kPasses; ++p) {
+            const uint32_t row = Store::row_of_store(p, tid), m = m0 + row;
+            u32x4 x = *reinterpret_cast<lds_u32x4 *>(ring_c_slot<BN>(row, cv));
+            if ((row >> 4) & 1u) x = u32x4{x.z, x.w, x.x, x.y};
+            size_t off = (size_t)m * N + n_off;
+            if (mapped) off = n_off + (uint32_t)__builtin_amdgcn_ds_bpermute((int)(4u * Store::lane_of_store(p, lane)), (int)row_off);
+            if (m < M && n_ok) store_c(C + off, x, stream);
+        }
+    };
+    if constexpr (AX)   // (large, most of them)
+        store_tile(std::true_type{});
+    else
+        stores_by_kind(g.stream, store_tile);
 }
 
 template <class T>
@@ -611,10 +620,11 @@ bool ring_plan(const GemmArgs &g, int amode, int wmode, bool tile256, uint32_t n
     if (!nested(r.a[0].dx) || !nested(r.w.dx) || (p.klane && !nested(r.a_dk)) || (g.store_mapped && (!nested(g.om) || !nested(g.on)))) return false;
     for (uint32_t j = 1; j < g.n_seg; ++j)
         if (!nested(r.a[j].dx)) return false;
-    r.store_mapped = g.store_mapped;
+    r.store_mapped = (uint16_t)g.store_mapped;
     r.obase = g.obase;
     r.om = g.om;
     r.on = g.on;
+    r.stream = stores_stream(g.M, g.N, g.store_mapped ? g.on.ext[0] : g.N);
 
     // ---- the tile
     double t;

@@ -52,7 +52,8 @@ struct RingCommon {
     Digits a_dk;      // runs of A shorter than a step: k per lane
     RingRuns a_runs;
     RingOperand w;
-    uint32_t store_mapped, obase;
+    uint16_t store_mapped, stream;   // stream: the product goes past the caches (see stores_stream)
+    uint32_t obase;
     Digits om, on;
 };
 template <int NSEG>

@@ -1,4 +1,5 @@
-"""Products with at most one tile to a compute unit: wavefronts that only load (32 x 64 and 64 x 64 tiles), four stages of 128 x 128.  On the CPU the host replay, on the GPU bit for bit against the
+"""Products with at most one tile to a compute unit: wavefronts that only load (32 x 64 and 64 x 64 tiles), four stages of 128 x 128, and
+stores through the caches where rows or runs are no whole 64-byte pieces.  On the CPU the host replay, on the GPU bit for bit against the
 general kernel, which adds the same products in the same order."""
 import pytest
 
@@ -48,3 +49,14 @@ def test_against_the_general_kernel(dev, case, monkeypatch, capfd):  # noqa: F81
         assert _replay(a, n, w, out_map) == (B.AMAP_OK, 0)
         _against_general(dev, shapes, a, n, w, monkeypatch, capfd, 1300 + case, more, out_map)
         monkeypatch.undo()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("m, k, n, tile256", [(333, 64, 1000, ""),        # through the caches
+                                              (16800, 64, 1000, ""),      # past them again: more than 32 MB
+                                              (300, 128, 1000, "1")])     # partial 256 x 256 tiles, through the caches
+def test_rows_of_no_whole_pieces(dev, m, k, n, tile256, monkeypatch, capfd):  # noqa: F811
+    a = B.amap_compose([(m, k)], 2, [])
+    monkeypatch.setenv("AMAP_GEMM_TILE256", tile256)
+    print(f"[gpu] rows of no whole pieces {m} x {k} x {n}", flush=True)
+    _against_general(dev, [(m, k)], a, n, None, monkeypatch, capfd, 1400, "256 x 256 tiles" if tile256 else "amap gemm: ring")
