@@ -1191,13 +1191,13 @@ amap_status gemm_launch(const void *const *A_srcs, bool by_id, const amap_t *A_m
 #define AMAP_T2_LAUNCH(E)                                                                                   \
     do {                                                                                                    \
         if (g.store_mapped && w_km)                                                                         \
-            e2 = launch_kernel(amap_gemm_tile256_kernel<true, true, E>, grid2, block2, kT2Lds, hs, g);    \
+            e2 = launch_kernel<amap_gemm_tile256_kernel<true, true, E>>(grid2, block2, kT2Lds, hs, g);    \
         else if (g.store_mapped)                                                                            \
-            e2 = launch_kernel(amap_gemm_tile256_kernel<true, false, E>, grid2, block2, kT2Lds, hs, g);   \
+            e2 = launch_kernel<amap_gemm_tile256_kernel<true, false, E>>(grid2, block2, kT2Lds, hs, g);   \
         else if (w_km)                                                                                      \
-            e2 = launch_kernel(amap_gemm_tile256_kernel<false, true, E>, grid2, block2, kT2Lds, hs, g);   \
+            e2 = launch_kernel<amap_gemm_tile256_kernel<false, true, E>>(grid2, block2, kT2Lds, hs, g);   \
         else                                                                                                \
-            e2 = launch_kernel(amap_gemm_tile256_kernel<false, false, E>, grid2, block2, kT2Lds, hs, g);  \
+            e2 = launch_kernel<amap_gemm_tile256_kernel<false, false, E>>(grid2, block2, kT2Lds, hs, g);  \
     } while (0)
         if (edge256)
             AMAP_T2_LAUNCH(true);
@@ -1239,9 +1239,9 @@ amap_status gemm_launch(const void *const *A_srcs, bool by_id, const amap_t *A_m
 #define AMAP_GEMM_AWE(AM, WM, E)                                                                       \
     do {                                                                                               \
         if (seg)                                                                                       \
-            e = launch_kernel(amap_gemm_kernel<AM, WM, E, true>, grid, block, lds, hs, g);          \
+            e = launch_kernel<amap_gemm_kernel<AM, WM, E, true>>(grid, block, lds, hs, g);          \
         else                                                                                           \
-            e = launch_kernel(amap_gemm_kernel<AM, WM, E, false>, grid, block, lds, hs, g);         \
+            e = launch_kernel<amap_gemm_kernel<AM, WM, E, false>>(grid, block, lds, hs, g);         \
     } while (0)
 #define AMAP_GEMM(WM)                                                                                  \
     do {                                                                                               \

@@ -399,7 +399,7 @@ amap_status launch(const RingArgs<kMaxSeg> &full, uint32_t grid, hipStream_t str
     RingArgs<T::NSEG> g;
     static_cast<RingCommon &>(g) = full;
     for (int i = 0; i < T::NSEG; ++i) g.a[i] = full.a[i];
-    const hipError_t e = launch_kernel(amap_gemm_ring_kernel<T>, dim3(grid), dim3(64 * (T::WVM * T::WVN + T::LOAD)), lds, stream, g);
+    const hipError_t e = launch_kernel<amap_gemm_ring_kernel<T>>(dim3(grid), dim3(64 * (T::WVM * T::WVN + T::LOAD)), lds, stream, g);
     if (e != hipSuccess) {
         set_last_error("amap_gemm_ring_kernel", hipGetErrorString(e));
         return AMAP_E_HIP;

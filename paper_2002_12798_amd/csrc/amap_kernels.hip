@@ -1016,7 +1016,7 @@ amap_status launch_pieces(const LaunchArgs &args, uint32_t blocks, uint32_t lds,
     if (args.n_pieces == 1 && rows_is_plain(args.p[0], es)) {
         say("amap_rows_kernel");
         const DevPiece &P = args.p[0];
-#define AMAP_LAUNCH_ROWS(ES, NT) e = launch_kernel(amap_rows_kernel<ES, NT>, grid, block, 0, stream, P, d)
+#define AMAP_LAUNCH_ROWS(ES, NT) e = launch_kernel<amap_rows_kernel<ES, NT>>(grid, block, 0, stream, P, d)
         switch ((es == 2 ? 0 : 4) + (int)(args.nt & 3)) {
         case 0: AMAP_LAUNCH_ROWS(2, 0); break;
         case 1: AMAP_LAUNCH_ROWS(2, 1); break;
@@ -1032,7 +1032,7 @@ amap_status launch_pieces(const LaunchArgs &args, uint32_t blocks, uint32_t lds,
     }
     if (launch_is_plain_rows(args, es)) {
         say("amap_rows_multi_kernel");
-#define AMAP_LAUNCH_ROWSM(ES, NT) e = launch_kernel(amap_rows_multi_kernel<ES, NT>, grid, block, 0, stream, args, d)
+#define AMAP_LAUNCH_ROWSM(ES, NT) e = launch_kernel<amap_rows_multi_kernel<ES, NT>>(grid, block, 0, stream, args, d)
         switch ((es == 2 ? 0 : 4) + (int)(args.nt & 3)) {
         case 0: AMAP_LAUNCH_ROWSM(2, 0); break;
         case 1: AMAP_LAUNCH_ROWSM(2, 1); break;
@@ -1051,9 +1051,9 @@ amap_status launch_pieces(const LaunchArgs &args, uint32_t blocks, uint32_t lds,
 #define AMAP_LAUNCH_T16(ES, NT)                                                                              \
     do {                                                                                                     \
         if (grouped)                                                                                         \
-            e = launch_kernel(amap_tile16_kernel<ES, NT, true>, grid, block, lds, stream, args, d);       \
+            e = launch_kernel<amap_tile16_kernel<ES, NT, true>>(grid, block, lds, stream, args, d);       \
         else                                                                                                 \
-            e = launch_kernel(amap_tile16_kernel<ES, NT, false>, grid, block, lds, stream, args, d);      \
+            e = launch_kernel<amap_tile16_kernel<ES, NT, false>>(grid, block, lds, stream, args, d);      \
     } while (0)
         switch ((es == 2 ? 0 : 4) + (int)(args.nt & 3)) {
         case 0: AMAP_LAUNCH_T16(2, 0); break;
@@ -1074,9 +1074,9 @@ amap_status launch_pieces(const LaunchArgs &args, uint32_t blocks, uint32_t lds,
 #define AMAP_LAUNCH_FLAT(ES, NT)                                                                             \
     do {                                                                                                     \
         if (rag)                                                                                             \
-            e = launch_kernel(amap_flat_kernel<ES, NT, true>, grid, block, lds, stream, args, d);         \
+            e = launch_kernel<amap_flat_kernel<ES, NT, true>>(grid, block, lds, stream, args, d);         \
         else                                                                                                 \
-            e = launch_kernel(amap_flat_kernel<ES, NT, false>, grid, block, lds, stream, args, d);        \
+            e = launch_kernel<amap_flat_kernel<ES, NT, false>>(grid, block, lds, stream, args, d);        \
     } while (0)
         switch ((es == 2 ? 0 : 4) + (int)(args.nt & 3)) {
         case 0: AMAP_LAUNCH_FLAT(2, 0); break;
@@ -1095,9 +1095,9 @@ amap_status launch_pieces(const LaunchArgs &args, uint32_t blocks, uint32_t lds,
 #define AMAP_LAUNCH(ES, NT)                                                                                  \
     do {                                                                                                     \
         if (grouped)                                                                                         \
-            e = launch_kernel(amap_pieces_kernel<ES, NT, true>, grid, block, lds, stream, args, d);       \
+            e = launch_kernel<amap_pieces_kernel<ES, NT, true>>(grid, block, lds, stream, args, d);       \
         else                                                                                                 \
-            e = launch_kernel(amap_pieces_kernel<ES, NT, false>, grid, block, lds, stream, args, d);      \
+            e = launch_kernel<amap_pieces_kernel<ES, NT, false>>(grid, block, lds, stream, args, d);      \
     } while (0)
     switch ((es == 2 ? 0 : 4) + (int)(args.nt & 3)) {
     case 0: AMAP_LAUNCH(2, 0); break;
@@ -1146,8 +1146,8 @@ amap_status launch_program(const amap *m, const Plan &plan, const void *const *s
     for (int i = 0; i < plan.n_prog_src && i < (int)m->src_shapes.size(); ++i) t.p[i] = src[i];
     const uint32_t total = (uint32_t)volume_of(m->shape);
     const uint32_t grid = (total + kProgramThreads - 1) / kProgramThreads;
-    const hipError_t e = m->elem == 2 ? launch_kernel(amap_program_kernel<2>, dim3(grid), dim3(kProgramThreads), 0, stream, plan.prog, t, (char *)dst, total)
-                                      : launch_kernel(amap_program_kernel<4>, dim3(grid), dim3(kProgramThreads), 0, stream, plan.prog, t, (char *)dst, total);
+    const hipError_t e = m->elem == 2 ? launch_kernel<amap_program_kernel<2>>(dim3(grid), dim3(kProgramThreads), 0, stream, plan.prog, t, (char *)dst, total)
+                                      : launch_kernel<amap_program_kernel<4>>(dim3(grid), dim3(kProgramThreads), 0, stream, plan.prog, t, (char *)dst, total);
     return launched(e, "amap_program_kernel");
 }
 
