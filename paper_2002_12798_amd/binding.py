@@ -143,6 +143,14 @@ _L.amap_layout_copy.argtypes = [_vp, C.c_int, _ip, _ip, _ip, _pp]
 
 raw = _L  # the raw CDLL, for callers that pre-marshal their arguments
 
+# The ordinary call goes from the interpreter to the library through this extension; what it does not take (its answer is
+# negative then) goes through ctypes below, and errors are raised there.
+from . import _amap_call as _call  # noqa: E402
+
+_call.library(*(C.cast(f, _vp).value for f in (_L.amap_execute, _L.amap_execute_multi, _L.amap_gemm_fused, _L.amap_gemm_fused_store,
+                                               _L.amap_gemm_mapped, _L.amap_gemm_gather)))
+_gemm, _gather = _call.gemm, _call.gather
+
 
 def _status_str(s):
     return _L.amap_status_str(int(s)).decode()
@@ -166,6 +174,7 @@ class Map:
 
     def __init__(self, handle):
         self._h = C.c_void_p(handle)
+        self._at = handle   # the same as an integer
         self._reads = None  # what _reads() found out (a map never changes)
 
     handle = property(operator.attrgetter("_h"))
@@ -412,12 +421,19 @@ def amap_execute_multi(src_ptrs, dst_ptrs, maps, stream=0):
 
 
 def amap_gemm_fused(a_src_ptr, a_map, w_ptr, n, out_ptr, stream=0):
+    st = _gemm(a_src_ptr, a_map, w_ptr, None, n, None, out_ptr, stream)
+    if st >= 0:
+        return _check(st, "amap_gemm_fused")
     if not type(a_src_ptr) is type(w_ptr) is type(out_ptr) is type(stream) is int:
         a_src_ptr, w_ptr, out_ptr, stream = _addr(a_src_ptr), _addr(w_ptr), _addr(out_ptr), _addr(stream)
     _check(_L.amap_gemm_fused(a_src_ptr, a_map.handle, w_ptr, int(n), out_ptr, stream), "amap_gemm_fused")
 
 
 def amap_gemm_fused_store(a_src_ptr, a_map, w_ptr, n, out_map, out_ptr, stream=0):
+    if out_map is not None:
+        st = _gemm(a_src_ptr, a_map, w_ptr, None, n, out_map, out_ptr, stream)
+        if st >= 0:
+            return _check(st, "amap_gemm_fused_store")
     if not type(a_src_ptr) is type(w_ptr) is type(out_ptr) is type(stream) is int:
         a_src_ptr, w_ptr, out_ptr, stream = _addr(a_src_ptr), _addr(w_ptr), _addr(out_ptr), _addr(stream)
     _check(_L.amap_gemm_fused_store(a_src_ptr, a_map.handle, w_ptr, int(n), out_map.handle, out_ptr, stream),
@@ -425,6 +441,10 @@ def amap_gemm_fused_store(a_src_ptr, a_map, w_ptr, n, out_map, out_ptr, stream=0
 
 
 def amap_gemm_mapped(a_src_ptr, a_map, w_src_ptr, w_map, out_map, out_ptr, stream=0):
+    if w_map is not None:
+        st = _gemm(a_src_ptr, a_map, w_src_ptr, w_map, 0, out_map, out_ptr, stream)
+        if st >= 0:
+            return _check(st, "amap_gemm_mapped")
     if not type(a_src_ptr) is type(w_src_ptr) is type(out_ptr) is type(stream) is int:
         a_src_ptr, w_src_ptr, out_ptr, stream = _addr(a_src_ptr), _addr(w_src_ptr), _addr(out_ptr), _addr(stream)
     _check(_L.amap_gemm_mapped(a_src_ptr, a_map.handle, w_src_ptr, w_map.handle,
@@ -433,6 +453,9 @@ def amap_gemm_mapped(a_src_ptr, a_map, w_src_ptr, w_map, out_map, out_ptr, strea
 
 def amap_gemm_gather(a_src_ptrs, a_map, w_src_ptr, w_map, n, out_map, out_ptr, stream=0):
     """a_src_ptrs: device pointers by source id of a_map (None for ids the map does not use)."""
+    st = _gather(a_src_ptrs, a_map, w_src_ptr, w_map, n, out_map, out_ptr, stream)
+    if st >= 0:
+        return _check(st, "amap_gemm_gather")
     if not type(w_src_ptr) is type(out_ptr) is type(stream) is int:
         w_src_ptr, out_ptr, stream = _addr(w_src_ptr), _addr(out_ptr), _addr(stream)
     _check(_L.amap_gemm_gather(_ptr_array(a_src_ptrs, _reads(a_map)[0]), a_map.handle, w_src_ptr,

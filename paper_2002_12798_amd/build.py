@@ -1,14 +1,16 @@
-"""Build libamap.so (HIP kernels + host composer + C ABI) for gfx950 with hipcc."""
+"""Build libamap.so (HIP kernels + host composer + C ABI) for gfx950 with hipcc, and the binding's native part with gcc."""
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
+import sysconfig
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(_HERE)
 CSRC = os.path.join(_HERE, "csrc")
 LIB = os.path.join(_HERE, "libamap.so")
+CALL = os.path.join(_HERE, "_amap_call.so")   # CPython extension: from a Python call to the library
 
 SOURCES = ["amap_compose.cpp", "amap_graph.cpp", "amap_layout.cpp", "amap_host.cpp", "amap_plan.cpp", "amap_plan_check.cpp", "amap_kernels.hip",
            "amap_gemm.hip", "amap_gemm_ring.hip"]
@@ -61,6 +63,12 @@ def build_lib(verbose: bool = False, extra=()) -> str:
     return LIB
 
 
+def build_call() -> str:
+    subprocess.run(["gcc", "-O2", "-std=c99", "-fPIC", "-shared", "-Wall", "-Wextra", "-I", sysconfig.get_path("include"),
+                    os.path.join(CSRC, "amap_call.c"), "-o", CALL], check=True)
+    return CALL
+
+
 # Wavefronts per SIMD of the map kernels.  They are bound by memory and every form inlined into amap_pieces_kernel shares its
 # registers: 74 instead of 66 VGPRs for the sake of one form took it from 7 to 6 and the cross-lane form from 213 to 230 us
 # ([8192,8,64,64] 2-byte elements to channels-last, 1.07 GB).
@@ -103,3 +111,4 @@ def kernel_usage(stderr: str) -> dict:
 
 if __name__ == "__main__":
     print(build_lib(verbose=True))
+    print(build_call())

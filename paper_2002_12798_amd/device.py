@@ -44,7 +44,15 @@ _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 _get_device = getattr(torch._C, "_cuda_getDevice", torch.cuda.current_device)
 
 
+if _raw_stream is not None:
+    B._call.torch(_raw_stream, _get_device, torch.cuda.is_initialized)
+_execute, _execute_multi, _current_stream = B._call.execute, B._call.execute_multi, B._call.current_stream
+
+
 def current_stream() -> int:
+    handle = _current_stream()
+    if handle is not None:
+        return handle
     if _raw_stream is None or not torch.cuda.is_initialized():
         return torch.cuda.current_stream().cuda_stream
     return _raw_stream(_get_device())
@@ -52,6 +60,12 @@ def current_stream() -> int:
 
 def execute(m, srcs, dst=None, kernel_id=None, stream=None) -> torch.Tensor:
     """dst <- map(srcs) on the current stream; returns dst (allocated if None)."""
+    if dst is not None and kernel_id is None:
+        st = _execute(m, srcs, dst, stream)
+        if st == 0:
+            return dst
+        if st > 0:
+            raise B.AmapError(st, "amap_execute")
     if dst is None:
         dst = empty_dst(m)
     ptrs = [0 if s is None else s.data_ptr() for s in srcs]
@@ -61,6 +75,12 @@ def execute(m, srcs, dst=None, kernel_id=None, stream=None) -> torch.Tensor:
 
 def execute_multi(maps, srcs, dsts=None, stream=None):
     """dsts[i] <- maps[i](srcs), all maps in shared launches; returns the dst tensors."""
+    if dsts is not None:
+        st = _execute_multi(maps, srcs, dsts, stream)
+        if st == 0:
+            return dsts
+        if st > 0:
+            raise B.AmapError(st, "amap_execute_multi")
     if dsts is None:
         dsts = [empty_dst(m) for m in maps]
     B.amap_execute_multi([0 if s is None else s.data_ptr() for s in srcs], [d.data_ptr() for d in dsts], maps,
