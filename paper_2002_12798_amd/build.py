@@ -72,7 +72,7 @@ def build_call() -> str:
 # Wavefronts per SIMD of the map kernels.  They are bound by memory and every form inlined into amap_pieces_kernel shares its
 # registers: 74 instead of 66 VGPRs for the sake of one form took it from 7 to 6 and the cross-lane form from 213 to 230 us
 # ([8192,8,64,64] 2-byte elements to channels-last, 1.07 GB).
-MIN_OCCUPANCY = {"amap_rows_kernel": 8, "amap_rows_multi_kernel": 8, "amap_tile16_kernel": 8, "amap_flat_kernel": 8,
+MIN_OCCUPANCY = {"amap_rows_kernel": 8, "amap_rows_few_kernel": 8, "amap_rows_multi_kernel": 8, "amap_tile16_kernel": 8, "amap_flat_kernel": 8,
                  "amap_pieces_kernelILi2E": 7, "amap_pieces_kernelILi4E": 6}
 
 

@@ -113,6 +113,79 @@ AMAP_HD void rows_offsets_fixed(const DevPiece &P, uint32_t r, uint32_t &doff, u
     soff = s;
 }
 
+// ---- one plain row piece of few loops, or up to three that differ in source and dst alone (Q, K and V of one projection), as a
+// kernel argument of at most kFewBytes.  The runtime issues a launch with up to 112 bytes of arguments in 2.75 us, with 120 to 352 in 3.1 to
+// 3.8 and with the 3.9 KB of a LaunchArgs in 4.1, which is what bounds a call on less than about 10 MB.
+struct FewPiece {
+    const char *src;
+    char *dst;
+};
+template <int N, int L>
+struct RowsFew {
+    FewPiece p[N];
+    uint32_t n_units;                 // vectors of a piece
+    uint32_t ext[L - 1], mul[L - 1];  // the last loop takes what is left and needs no division
+    int32_t ds[L], ss[L];
+    uint8_t shift[4];
+};
+typedef RowsFew<1, 5> RowsOne;
+typedef RowsFew<3, 4> RowsThree;
+constexpr uint32_t kFewBytes = 112;
+static_assert(sizeof(RowsOne) <= kFewBytes && sizeof(RowsThree) <= kFewBytes, "see above");
+
+template <int N, int L>
+AMAP_HD void rows_few_offsets(const RowsFew<N, L> &F, uint32_t r, uint32_t &doff, uint32_t &soff) {
+    uint32_t d = 0, s = 0;
+#if defined(__HIP_DEVICE_COMPILE__)
+#pragma unroll
+#endif
+    for (int k = 0; k < L; ++k) {
+        uint32_t dig = r;
+        if (k + 1 < L) {
+            r = fdiv(r, FastDiv{F.mul[k], F.shift[k]});
+            dig -= r * F.ext[k];
+        }
+        d += dig * (uint32_t)F.ds[k];
+        s += dig * (uint32_t)F.ss[k];
+    }
+    doff = d;
+    soff = s;
+}
+// The loops of a piece in that form; false if it has more, fills or walks backwards (the origin goes into the addresses, so a lane's
+// part must not be negative).
+template <int N, int L>
+inline bool rows_few_loops(const DevPiece &P, RowsFew<N, L> &F) {
+    if (P.nloops > (uint32_t)L) return false;
+    F.n_units = P.n_units;
+    F.shift[3] = 0;
+    for (int k = 0; k < L; ++k) {   // (a loop past nloops is all zero: it hands r on and adds nothing)
+        const Loop &l = P.loops[k];
+        if (l.ds < 0 || l.ss < 0) return false;
+        F.ds[k] = l.ds;
+        F.ss[k] = l.ss;
+        if (k + 1 < L) {
+            F.ext[k] = l.extent;
+            F.mul[k] = l.fd.mul;
+            F.shift[k] = (uint8_t)l.fd.shift;
+        }
+    }
+    return true;
+}
+// What P reads and writes under a call's addresses (src: the source's, or what the host checks instead; dst: the launch's).
+inline FewPiece rows_few_piece(const DevPiece &P, const void *src, char *dst, int es) {
+    return FewPiece{(const char *)src + (uint64_t)P.sbase * (uint64_t)es, dst + (P.dwin + P.dbase) * (uint64_t)es};
+}
+// pieces 1 .. n - 1 differ from piece 0 in where they read and write alone
+inline bool rows_few_alike(const LaunchArgs &a) {
+    for (uint32_t k = 1; k < a.n_pieces; ++k) {
+        const DevPiece &P = a.p[k], &H = a.p[0];
+        if (P.n_units != H.n_units || P.n_blocks != H.n_blocks || P.nloops != H.nloops) return false;
+        for (uint32_t j = 0; j < (uint32_t)kMaxLoops; ++j)
+            if (P.loops[j].extent != H.loops[j].extent || P.loops[j].ds != H.loops[j].ds || P.loops[j].ss != H.loops[j].ss) return false;
+    }
+    return true;
+}
+
 // ---- flat tiles (see DevPiece::flat): workgroup t -> element offsets of its block on both sides
 // (of row r0, c = 0), and the number of rows in the block
 // rows per block = 1 << P.lqlog (16, 32 or 64: as many as fit LDS)

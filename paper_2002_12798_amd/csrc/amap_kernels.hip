@@ -816,6 +816,49 @@ __global__ __launch_bounds__(kMaxThreads) void amap_rows_kernel(const DevPiece P
     rows_move<16, NT>(P, dst + (size_t)P.dwin * ES, ES, doff, soff, ok);
 }
 
+// The same for few loops and up to kFewOutput bytes: arguments of at most kFewBytes instead of 352 bytes or 3.9 KB (see RowsFew), five or
+// four loop slots instead of eight.  Same schedule.  In a stream of calls, us before / now: bf16 heads merged [2,12,67,80] 4.2 / 3.15,
+// fp32 [14,12,139,80] 4.65 / 3.7, bf16 [16,12,512,64] 5.5 / 5.1; Q, K and V split by heads from 7 x 66 rows 6.35 / 3.3, 6 x 512 7.25 / 5.75,
+// 12 x 512 (57 MB moved) 11.75 / 11.05.  Beyond what the L2s hold the other two are ahead, whose workgroups start less closely together:
+// 16 x 512 (75 MB) 15.2 / 15.8, [52,12,512,64] merged (82 MB) 15.3 / 15.75, [64,12,512,64] 18.2 / 18.65.
+constexpr uint64_t kFewOutput = 32ull << 20;
+template <int ES, int NT, int N, int L>
+__global__ __launch_bounds__(kMaxThreads) void amap_rows_few_kernel(const RowsFew<N, L> F) {
+    const uint32_t threads = blockDim.x;
+    uint32_t b = blockIdx.x;
+    FewPiece p = F.p[0];
+    if constexpr (N > 1) {
+        const uint32_t blocks = (F.n_units + threads * kRowsUnroll - 1) / (threads * kRowsUnroll);   // (threads: a power of two)
+#pragma unroll
+        for (int k = 1; k < N; ++k)
+            if (blockIdx.x >= blocks * k) {
+                b = blockIdx.x - blocks * k;
+                p = F.p[k];
+            }
+    }
+    uint32_t doff[kRowsUnroll], soff[kRowsUnroll], v[kRowsUnroll][4];
+    bool ok[kRowsUnroll];
+    const uint32_t base = b * (threads * kRowsUnroll) + threadIdx.x;
+#pragma unroll
+    for (int u = 0; u < kRowsUnroll; ++u) {
+        const uint32_t r = base + u * threads;
+        ok[u] = r < F.n_units;
+        rows_few_offsets(F, r, doff[u], soff[u]);
+    }
+#pragma unroll
+    for (int u = 0; u < kRowsUnroll; ++u) {
+        if (ok[u]) {
+            gld<16, (NT & PF_NT_LOAD) != 0>(v[u], p.src + (size_t)soff[u] * ES);
+        } else {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) v[u][k] = 0;
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < kRowsUnroll; ++u)
+        if (ok[u]) gst<16, (NT & PF_NT_STORE) != 0>(p.dst + (size_t)doff[u] * ES, v[u]);
+}
+
 // The same for a launch of several plain row pieces: the piece is looked up, the rest is alike.
 template <int ES, int NT>
 __global__ __launch_bounds__(kMaxThreads) void amap_rows_multi_kernel(const LaunchArgs args, char *dst) {
@@ -1001,6 +1044,21 @@ amap_status check_pointers(const amap *m, const void *const *src, const void *ds
     return AMAP_OK;
 }
 
+// one launch of amap_rows_few_kernel
+template <int N, int L>
+hipError_t launch_few(const RowsFew<N, L> &F, uint32_t nt, int es, dim3 grid, dim3 block, hipStream_t stream) {
+    switch ((es == 2 ? 0 : 4) + (int)(nt & 3)) {
+    case 0: return launch_kernel<amap_rows_few_kernel<2, 0, N, L>>(grid, block, 0, stream, F);
+    case 1: return launch_kernel<amap_rows_few_kernel<2, 1, N, L>>(grid, block, 0, stream, F);
+    case 2: return launch_kernel<amap_rows_few_kernel<2, 2, N, L>>(grid, block, 0, stream, F);
+    case 3: return launch_kernel<amap_rows_few_kernel<2, 3, N, L>>(grid, block, 0, stream, F);
+    case 4: return launch_kernel<amap_rows_few_kernel<4, 0, N, L>>(grid, block, 0, stream, F);
+    case 5: return launch_kernel<amap_rows_few_kernel<4, 1, N, L>>(grid, block, 0, stream, F);
+    case 6: return launch_kernel<amap_rows_few_kernel<4, 2, N, L>>(grid, block, 0, stream, F);
+    default: return launch_kernel<amap_rows_few_kernel<4, 3, N, L>>(grid, block, 0, stream, F);
+    }
+}
+
 // one launch of the piece kernel; args.p[].src must already hold device pointers
 amap_status launch_pieces(const LaunchArgs &args, uint32_t blocks, uint32_t lds, int es, char *d, hipStream_t stream) {
     bool grouped = false;
@@ -1010,12 +1068,18 @@ amap_status launch_pieces(const LaunchArgs &args, uint32_t blocks, uint32_t lds,
     hipError_t e = hipSuccess;
     const char *tr = std::getenv("AMAP_PLAN_TRACE");
     const bool trace = tr && tr[0] && tr[0] != '0';   // one line per launch on stderr: the kernel that takes it
-    auto say = [&](const char *kernel) {
-        if (trace) std::fprintf(stderr, "amap launch: %s, %u workgroups of %u lanes, %u pieces\n", kernel, blocks, 64u << args.nwlog, args.n_pieces);
+    auto say = [&](const char *kernel, const char *more = "") {
+        if (trace) std::fprintf(stderr, "amap launch: %s, %u workgroups of %u lanes, %u pieces%s\n", kernel, blocks, 64u << args.nwlog, args.n_pieces, more);
     };
     if (args.n_pieces == 1 && rows_is_plain(args.p[0], es)) {
-        say("amap_rows_kernel");
         const DevPiece &P = args.p[0];
+        RowsOne one;
+        if (P.src && 16ull * P.n_units <= kFewOutput && rows_few_loops(P, one)) {
+            say("amap_rows_kernel", ", few loops");
+            one.p[0] = rows_few_piece(P, P.src, d, es);
+            return launched(launch_few(one, args.nt, es, grid, block, stream), "amap_rows_few_kernel");
+        }
+        say("amap_rows_kernel");
 #define AMAP_LAUNCH_ROWS(ES, NT) e = launch_kernel<amap_rows_kernel<ES, NT>>(grid, block, 0, stream, P, d)
         switch ((es == 2 ? 0 : 4) + (int)(args.nt & 3)) {
         case 0: AMAP_LAUNCH_ROWS(2, 0); break;
@@ -1031,6 +1095,19 @@ amap_status launch_pieces(const LaunchArgs &args, uint32_t blocks, uint32_t lds,
         return launched(e, "amap_rows_kernel");
     }
     if (launch_is_plain_rows(args, es)) {
+        RowsThree three;
+        if (args.n_pieces <= 3 && 16ull * args.p[0].n_units * args.n_pieces <= kFewOutput && rows_few_alike(args) && rows_few_loops(args.p[0], three)) {
+            bool data = true;
+            for (uint32_t k = 0; k < 3; ++k) {
+                const DevPiece &P = args.p[k < args.n_pieces ? k : 0];
+                data = data && P.src;
+                three.p[k] = rows_few_piece(P, P.src, d, es);
+            }
+            if (data) {
+                say("amap_rows_multi_kernel", ", few loops");
+                return launched(launch_few(three, args.nt, es, grid, block, stream), "amap_rows_few_kernel");
+            }
+        }
         say("amap_rows_multi_kernel");
 #define AMAP_LAUNCH_ROWSM(ES, NT) e = launch_kernel<amap_rows_multi_kernel<ES, NT>>(grid, block, 0, stream, args, d)
         switch ((es == 2 ? 0 : 4) + (int)(args.nt & 3)) {

@@ -58,8 +58,21 @@ struct Replay {
                 uint32_t d, s;
                 {
                     if (r >= P.n_units) continue;
-                    if (alone && rows_is_plain(P, m.elem))
+                    if (alone && rows_is_plain(P, m.elem)) {
                         rows_offsets_fixed(P, r, d, s);
+                        // the same piece as amap_rows_few_kernel is handed it: its origin in the addresses
+                        RowsOne one;
+                        RowsThree three;
+                        uint32_t fd, fs;
+                        if (sid >= 0 && rows_few_loops(P, one)) {
+                            rows_few_offsets(one, r, fd, fs);
+                            errors += (uint64_t)P.dbase + fd != d || (uint64_t)P.sbase + fs != s;
+                        }
+                        if (sid >= 0 && rows_few_loops(P, three)) {
+                            rows_few_offsets(three, r, fd, fs);
+                            errors += (uint64_t)P.dbase + fd != d || (uint64_t)P.sbase + fs != s;
+                        }
+                    }
                     else
                         rows_offsets(P, r, d, s);
                 }
