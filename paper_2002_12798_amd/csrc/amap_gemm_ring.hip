@@ -86,6 +86,11 @@ __device__ __forceinline__ void ring_load(const char *base, const uint32_t (&off
                 "global_load_lds_dwordx4 %2, %4 offset:2048\n\tglobal_load_lds_dwordx4 %3, %4 offset:3072" ::"v"(off[j]),
                 "v"(off[j + 1 < N ? j + 1 : 0]), "v"(off[j + 2 < N ? j + 2 : 0]), "v"(off[j + 3 < N ? j + 3 : 0]), "s"(base), "s"(at)
                 : "memory");
+        else if (j + 3 == N)
+            asm volatile("s_mov_b32 m0, %4\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %3\n\tglobal_load_lds_dwordx4 %1, %3 offset:1024\n\t"
+                         "global_load_lds_dwordx4 %2, %3 offset:2048" ::"v"(off[j]),
+                         "v"(off[j + 1 < N ? j + 1 : 0]), "v"(off[j + 2 < N ? j + 2 : 0]), "s"(base), "s"(at)
+                         : "memory");
         else if (j + 2 <= N)
             asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %2\n\tglobal_load_lds_dwordx4 %1, %2 offset:1024" ::"v"(off[j]),
                          "v"(off[j + 1 < N ? j + 1 : 0]), "s"(base), "s"(at)
@@ -122,7 +127,7 @@ __global__ __launch_bounds__(64 * (T::WVM * T::WVN + T::LOAD), T::OCC) void amap
     const uint32_t m0 = tm * BM, n0 = tn * BN;
 
     // ---- per-lane byte offsets of this wavefront's load blocks, and the scalar bases they are added to
-    static_assert((NA % 4 == 0 || NA == 1 || NA == 2) && (NW % 4 == 0 || NW == 1 || NW == 2), "ring_load");
+    static_assert(NA >= 1 && NW >= 1, "ring_load");
     uint32_t a_off[NA], w_off[NW];
 #pragma unroll
     for (int j = 0; j < NA; ++j) a_off[j] = ring_block_offset<AX, BM, T::SHORT>(g.a[0].dx, g.a[0].base, g.a[0].kss, m0, g.M, lwave * NA, j, lane);
@@ -495,17 +500,17 @@ static double estimate(const RingCost &c, uint64_t tiles, double k64, uint32_t n
 static const RingCost kCostK[] = {{2.79f, .100f, .146f, .258f, .215f, .34f, .66f}, {2.94f, .176f, .237f, .365f, .213f, .24f, .63f},
                                   {3.71f, .253f, .315f, .635f, .240f, .07f, .60f}, {1.78f, .453f, .661f, .814f, .617f, 1.81f, .60f},
                                   {1.78f, .453f, .661f, .814f, .617f, 1.81f, .60f}, {3.84f, .226f, .521f, 0.f, 0.f, 1.f, 0.f},
-                                  {3.60f, .133f, .192f, 0.f, 0.f, .10f, 0.f}};
+                                  {3.60f, .133f, .192f, 0.f, 0.f, .10f, 0.f}, {5.10f, .339f, .604f, 0.f, 0.f, 0.f, 0.f}};
 static const RingCost kCostRuns[] = {{3.11f, .110f, .161f, .281f, .282f, .11f, .76f}, {3.04f, .225f, .270f, .446f, .240f, .00f, .62f},
                                      {3.52f, .286f, .361f, .688f, .567f, .00f, .63f}, {1.38f, .457f, .738f, 1.09f, .512f, 1.90f, .31f},
                                      {1.38f, .457f, .738f, 1.09f, .512f, 1.90f, .31f}, {3.22f, .361f, .594f, 0.f, 0.f, 1.f, 0.f},
-                                     {3.55f, .165f, .244f, 0.f, 0.f, .00f, 0.f}};
+                                     {3.55f, .165f, .244f, 0.f, 0.f, .00f, 0.f}, {4.30f, .600f, .720f, 0.f, 0.f, 0.f, 0.f}};
 static const RingCost kCostX[] = {{}, {5.86f, .193f, .193f, .398f, .239f, .01f, .00f}, {5.46f, .285f, .358f, .628f, .377f, .11f, .19f},
                                   {5.18f, .439f, .842f, 1.25f, .742f, .17f, .20f}};
 
 // rows, columns, wavefronts that compute, what else there is to say (in a trace)
 static const struct { int bm, bn, waves; const char *more; } kRingTile[] = {{32, 64, 2, ", 2 more load"}, {64, 64, 4, ""}, {64, 128, 4, ""}, {128, 128, 4, ""}, {128, 128, 8, ""},
-                                                                            {128, 128, 8, ", four stages"}, {64, 64, 4, ", 4 more load"}};
+                                                                            {128, 128, 8, ", four stages"}, {64, 64, 4, ", 4 more load"}, {192, 128, 8, ""}};
 
 // The shape of a product's tiles, and its estimate.  Measured on 354 other products along k: 0.8 % off the best shape each has, where
 // the shapes and figures before this were 3.2 % off.  Along m (89) 17 % faster than by 128 x 128 alone, none slower, 1.5 % off the best.
@@ -570,6 +575,11 @@ static RingShape ring_shape(const GemmArgs &g, const RingPlan &p, uint32_t n_cu,
         // M = 1016, K = 1024, N = 3072 12.7 -> 10.9.  Up to half a unit's worth of tiles the smaller ones are ahead; nearly all
         // units busy, a short walk ends sooner on more, smaller workgroups (M = 970, K = 1024, N = 4096 14.8 against 13.4).
         if (2 * t128 > n_cu && t128 <= n_cu && (20 * t128 <= 17 * (uint64_t)n_cu || g.K >= 1280)) consider(RS_128x128_DEEP);
+        // A few more 128 x 128 tiles than units put two on some of them while the others wait: 192 x 128 go once around, with half as much again
+        // for the matrix cores to each byte that a unit is handed. 512 <= K < 768 4 % faster (26 products), from 768 on 8 % (73):
+        // M = 2048, K = 768, N = 2304 12.5 -> 11.4 us, M = 9618, K = 1600, N = 512 26.5 -> 24.0; K = 384 0 to 3 % slower. (160 x 128, or
+        // four stages: 0 to 4 % faster.)
+        if (t128 > n_cu && tiles(192, 128) <= n_cu && g.K >= 512) consider(RS_192x128);
     }
     if (shape == RS_128x128 && by8) shape = RS_128x128_W8;
     return shape;
@@ -675,6 +685,9 @@ void with_tile(const RingPlan &p, F f) {
             f(Shape<64, 128, 32, 3, 1, 2, 2, 4, true, true, NSEG, 0>());
         else if constexpr (!AX && NSEG == 1 && KLANE < 2)
             f(Shape<64, 128, 64, 3, 2, 2, 2, 2, false, WX, 1, KLANE>());
+        break;
+    case RS_192x128:
+        if constexpr (!AX && NSEG == 1 && KLANE < 2) f(Shape<192, 128, 64, 3, 2, 2, 4, 2, false, WX, 1, KLANE>());
         break;
     case RS_64x64_LOAD:
         if constexpr (!AX && NSEG == 1 && KLANE < 2) f(Shape<64, 64, 64, 5, 2, 2, 2, 2, false, WX, 1, KLANE, 4>());

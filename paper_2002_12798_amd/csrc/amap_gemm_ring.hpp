@@ -167,7 +167,7 @@ struct RingStore {
 
 // The tiles there are (W8: 8 wavefronts; DEEP: 8 wavefronts and four stages, one workgroup to a compute unit; LOAD: four wavefronts
 // that compute and four that load).
-enum RingShape { RS_32x64 = 0, RS_64x64, RS_64x128, RS_128x128, RS_128x128_W8, RS_128x128_DEEP, RS_64x64_LOAD };
+enum RingShape { RS_32x64 = 0, RS_64x64, RS_64x128, RS_128x128, RS_128x128_W8, RS_128x128_DEEP, RS_64x64_LOAD, RS_192x128 };
 
 // A product as the ring kernel runs it: tile, wavefronts, forms of the operands (X: runs along m / n), arguments.
 struct RingPlan {

@@ -1,5 +1,5 @@
-"""Products with at most one tile to a compute unit: wavefronts that only load (32 x 64 and 64 x 64 tiles), four stages of 128 x 128, and
-stores through the caches where rows or runs are no whole 64-byte pieces.  On the CPU the host replay, on the GPU bit for bit against the
+"""Products with at most one tile to a compute unit: wavefronts that only load (32 x 64 and 64 x 64 tiles), four stages of 128 x 128, tiles of
+192 x 128, and stores through the caches where rows or runs are no whole 64-byte pieces.  On the CPU the host replay, on the GPU bit for bit against the
 general kernel, which adds the same products in the same order."""
 import pytest
 
@@ -17,6 +17,9 @@ CASES = [
     (merge(4, 8, 275, 64), 1928, "128 x 128", "four stages"),       # 144 tiles, just over half the units
     (merge(4, 8, 275, 80), 1928, "128 x 128", "four stages"),
     (merge(8, 20, 512, 64), 1000, "128 x 128", "four stages"),      # 256 tiles
+    (merge(5, 8, 300, 64), 3000, "192 x 128", ""),                  # eight steps in a ring of three stages, 192 tiles
+    (merge(5, 8, 300, 80), 3000, "192 x 128", ""),
+    (merge(2, 12, 1150, 64), 2304, "192 x 128", ""),                # 216 tiles
 ]
 
 
