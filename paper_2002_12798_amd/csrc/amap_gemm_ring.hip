@@ -505,23 +505,23 @@ static const RingCost kCostRuns[] = {{3.11f, .110f, .161f, .281f, .282f, .11f, .
                                      {3.52f, .286f, .361f, .688f, .567f, .00f, .63f}, {1.38f, .457f, .738f, 1.09f, .512f, 1.90f, .31f},
                                      {1.38f, .457f, .738f, 1.09f, .512f, 1.90f, .31f}, {3.22f, .361f, .594f, 0.f, 0.f, 1.f, 0.f},
                                      {3.55f, .165f, .244f, 0.f, 0.f, .00f, 0.f}, {4.30f, .600f, .720f, 0.f, 0.f, 0.f, 0.f}};
-static const RingCost kCostX[] = {{}, {5.86f, .193f, .193f, .398f, .239f, .01f, .00f}, {5.46f, .285f, .358f, .628f, .377f, .11f, .19f},
-                                  {5.18f, .439f, .842f, 1.25f, .742f, .17f, .20f}};
+static const RingCost kCostX[] = {{}, {2.67f, .439f, .537f, .567f, .238f, .347f, .475f}, {2.63f, .495f, .673f, .714f, .306f, .505f, .623f},
+                                  {2.38f, .646f, 1.16f, 1.25f, .389f, 1.23f, .279f}};
 
 // rows, columns, wavefronts that compute, what else there is to say (in a trace)
 static const struct { int bm, bn, waves; const char *more; } kRingTile[] = {{32, 64, 2, ", 2 more load"}, {64, 64, 4, ""}, {64, 128, 4, ""}, {128, 128, 4, ""}, {128, 128, 8, ""},
                                                                             {128, 128, 8, ", four stages"}, {64, 64, 4, ", 4 more load"}, {192, 128, 8, ""}};
 
 // The shape of a product's tiles, and its estimate.  Measured on 354 other products along k: 0.8 % off the best shape each has, where
-// the shapes and figures before this were 3.2 % off.  Along m (89) 17 % faster than by 128 x 128 alone, none slower, 1.5 % off the best.
+// the shapes and figures before this were 3.2 % off.  Along m (700) 2 % off the best.
 static RingShape ring_shape(const GemmArgs &g, const RingPlan &p, uint32_t n_cu, double &best) {
     RingShape shape = RS_128x128;
     best = 1e30;
     const double k64 = g.K / 64.0;
     auto tiles = [&](int bm, int bn) { return (uint64_t)((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn); };
     const double q64x128 = (double)tiles(64, 128) / n_cu;
-    auto consider = [&](RingShape s) {
-        const double t = estimate((p.ax ? kCostX : p.klane ? kCostRuns : kCostK)[s], tiles(kRingTile[s].bm, kRingTile[s].bn), k64, n_cu);
+    auto consider = [&](RingShape s, double times = 1.0) {
+        const double t = times * estimate((p.ax ? kCostX : p.klane ? kCostRuns : kCostK)[s], tiles(kRingTile[s].bm, kRingTile[s].bn), k64, n_cu);
         if (t < best) best = t, shape = s;
     };
     if (p.ax || g.n_seg > 1) {
@@ -529,10 +529,11 @@ static RingShape ring_shape(const GemmArgs &g, const RingPlan &p, uint32_t n_cu,
         consider(RS_128x128);
         // Smaller tiles where 128 x 128 leave compute units idle, or N or M half of a tile empty: M = 15408, K = 608, N = 128
         // 13.7 -> 8.9 us, M = 8624, K = 256, N = 512 9.3 -> 8.2, M = 50176, K = 288, N = 64 10.1 -> 8.7; M = 100352, K = 320, N = 256
-        // stays (25.9 against 29).  Fewer than 16 tiles of at most 8 steps stay too: the call takes what issuing it takes, give or
-        // take 1 us.
-        if (p.ax && p.wx && (tiles(128, 128) >= 16 || g.K > 256)) {
-            consider(RS_64x64);
+        // stays (25.9 against 29).  Few tiles of a short walk too: M = 832, K = 224, N = 128 6.2 -> 4.5, M = 768, K = 96, N = 128
+        // 5.2 -> 4.0; but the fewest of all, where the call takes what issuing it takes (M = 288, K = 256, N = 128 5.3 and 4.2).
+        if (p.ax && p.wx && (tiles(128, 128) >= 16 || g.M > 512 || g.K > 256)) {
+            // rows of C of no whole 64-byte pieces: narrower tiles share more of them (M = 10976, K = 256, N = 120 5.4 against 4.8 us)
+            consider(RS_64x64, g.N % 32 && g.N > 64 ? 1.06 : 1.0);
             consider(RS_64x128);
         }
         return shape;

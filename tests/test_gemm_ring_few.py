@@ -4,7 +4,7 @@ general kernel, which adds the same products in the same order."""
 import pytest
 
 from paper_2002_12798_amd import binding as B
-from tests.test_gemm_ring import _replay, dev, merge  # noqa: F401  (dev: fixture)
+from tests.test_gemm_ring import _replay, conv, dev, merge  # noqa: F401  (dev: fixture)
 from tests.test_gemm_ring_shapes import _against_general
 
 CASES = [
@@ -63,3 +63,29 @@ def test_rows_of_no_whole_pieces(dev, m, k, n, tile256, monkeypatch, capfd):  # 
     monkeypatch.setenv("AMAP_GEMM_TILE256", tile256)
     print(f"[gpu] rows of no whole pieces {m} x {k} x {n}", flush=True)
     _against_general(dev, [(m, k)], a, n, None, monkeypatch, capfd, 1400, "256 x 256 tiles" if tile256 else "amap gemm: ring")
+
+
+# A along m: few tiles of a short walk, on either side of 512 rows
+CONV = [(conv(8, [64], 8), 120, "128 x 128"), (conv(9, [64], 8), 160, "64 x 64"), (conv(17, [96, 32], 8), 64, "64 x 64"), (conv(50, [64], 12), 120, "64 x 128")]
+
+
+@pytest.mark.parametrize("case", range(len(CONV)))
+def test_replay_along_m(case, monkeypatch, capfd):
+    (shapes, ops), n, tile = CONV[case]
+    a = B.amap_compose(shapes, 2, ops)
+    m = B.dst_shape(a)[0]
+    store = B.amap_compose([(m, n)], 2, [("reshape", (m, n // 8, 8)), ("transpose", (1, 0, 2))])
+    monkeypatch.setenv("AMAP_PLAN_TRACE", "1")
+    for out_map in (None, store):
+        capfd.readouterr()
+        assert _replay(a, n, None, out_map) == (B.AMAP_OK, 0)
+        assert f"ring, {tile} per workgroup of 4 wavefronts, A along m" in capfd.readouterr().err
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", range(len(CONV)))
+def test_along_m_against_the_general_kernel(dev, case, monkeypatch, capfd):  # noqa: F811
+    (shapes, ops), n, tile = CONV[case]
+    a = B.amap_compose(shapes, 2, ops)
+    print(f"[gpu] few tiles along m {shapes} N={n}", flush=True)
+    _against_general(dev, shapes, a, n, None, monkeypatch, capfd, 1500 + case, f"ring, {tile} per workgroup")
