@@ -180,7 +180,7 @@ class Map:
     handle = property(operator.attrgetter("_h"))
 
     def __del__(self):
-        h, self._h = getattr(self, "_h", None), None
+        h, self._h, self._at = getattr(self, "_h", None), None, None
         if h and _L is not None:  # _L is gone when the interpreter shuts down
             _L.amap_free(h)
 
@@ -518,7 +518,7 @@ class GraphDME:
         return out
 
     def __del__(self):
-        h, self._h = getattr(self, "_h", None), None
+        h, self._h, self._at = getattr(self, "_h", None), None, None
         if h and _L is not None:
             _L.amap_graph_free(h)
 
@@ -573,6 +573,6 @@ class LayoutGraph:
         return out
 
     def __del__(self):
-        h, self._h = getattr(self, "_h", None), None
+        h, self._h, self._at = getattr(self, "_h", None), None, None
         if h and _L is not None:
             _L.amap_layout_free(h)

@@ -64,7 +64,7 @@ def test_what_is_handed_over(call):
         ("gather", [64, None], two._at, 128, None, 24, None, 256, 7)]
 
 
-@pytest.mark.parametrize("bad", [b"bytes", "text", 1.5, 1 << 64, Tensor(1.5), Tensor(RuntimeError("no storage")), object()], ids=repr)
+@pytest.mark.parametrize("bad", [b"bytes", "text", 1.5, 1 << 64, Tensor(1.5), Tensor(RuntimeError("no storage")), object()], ids=lambda v: type(v).__name__)
 def test_what_is_left_to_ctypes(call, bad):
     m, two = _map((8, 16)), _map((8, 16), (8, 16), ops=[("concat", 0)])
     x, out = Tensor(64), Tensor(128)
@@ -95,3 +95,9 @@ def test_the_current_stream_before_and_after_cuda_is_initialised(call):
     finally:
         import torch
         call.torch(device._raw_stream, device._get_device, torch.cuda.is_initialized)
+
+
+def test_a_map_given_back_is_not_handed_over(call):
+    m = _map((8, 16))
+    m.__del__()
+    assert call.execute(m, [Tensor(64)], Tensor(128), 0) == -1 and call.gemm(64, m, 64, None, 8, None, 128, 0) == -1 and call.seen == []
