@@ -145,7 +145,10 @@ raw = _L  # the raw CDLL, for callers that pre-marshal their arguments
 
 # The ordinary call goes from the interpreter to the library through this extension; what it does not take (its answer is
 # negative then) goes through ctypes below, and errors are raised there.
-from . import _amap_call as _call  # noqa: E402
+try:
+    from . import _amap_call as _call  # noqa: E402
+except ImportError as e:
+    raise ImportError(f"{os.path.join(_HERE, '_amap_call.so')}: {e}; run `python -c 'import __graft_entry__ as g; g.build()'`") from e
 
 _call.library(*(C.cast(f, _vp).value for f in (_L.amap_execute, _L.amap_execute_multi, _L.amap_gemm_fused, _L.amap_gemm_fused_store,
                                                _L.amap_gemm_mapped, _L.amap_gemm_gather)))

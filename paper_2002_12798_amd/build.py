@@ -60,6 +60,7 @@ def build_lib(verbose: bool = False, extra=()) -> str:
     if wrong:
         os.remove(LIB)
         raise RuntimeError("; ".join(wrong))
+    build_call()   # the binding needs both
     return LIB
 
 
@@ -111,4 +112,3 @@ def kernel_usage(stderr: str) -> dict:
 
 if __name__ == "__main__":
     print(build_lib(verbose=True))
-    print(build_call())
