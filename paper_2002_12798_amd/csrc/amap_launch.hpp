@@ -10,21 +10,26 @@
 
 namespace amap_detail {
 
-// A kernel's handle on each device, asked for at its first launch there.
+// A kernel's handle on each device, asked for at its first launch there; null where there is none, and no error of the asking is left.
 class KernelHandle {
   public:
     hipFunction_t on_current_device(const void *kernel) {
         int dev = 0;
-        if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kDevices) return nullptr;
+        if (hipGetDevice(&dev) != hipSuccess) return none();
+        if (dev < 0 || dev >= kDevices) return nullptr;
         hipFunction_t f = at_[dev].load(std::memory_order_acquire);
         if (!f) {   // (two threads may both ask, and are told the same)
-            if (hipGetFuncBySymbol(&f, kernel) != hipSuccess) return nullptr;
+            if (hipGetFuncBySymbol(&f, kernel) != hipSuccess) return none();
             at_[dev].store(f, std::memory_order_release);
         }
         return f;
     }
 
   private:
+    static hipFunction_t none() {
+        (void)hipGetLastError();
+        return nullptr;
+    }
     static constexpr int kDevices = 64;
     std::atomic<hipFunction_t> at_[kDevices] = {};
 };

@@ -3,7 +3,9 @@
  *   devices  every launch of more than 64 KB of dynamic LDS finds the attribute set for its kernel on the current device, also on
  *            the second device that a thread uses, and after a device that refused it
  *   errors   an error that another call left on the thread neither fails a launch nor is cleared by it; the launch's own error
- *            fails the call and does not stay behind */
+ *            fails the call and does not stay behind
+ *   lookup   a kernel whose handle cannot be had is launched by its address, and the failed look-up leaves no error on the thread
+ * A kernel's handle is looked up on the current device; a launch by handle goes to that device, one by address too. */
 #include <stdint.h>
 #include <stdio.h>
 #include <string.h>
@@ -11,9 +13,10 @@
 #include "amap.h"
 
 typedef struct { uint32_t x, y, z; } dim3_t;
-enum { OK = 0, INVALID = 1, LEFT_BEHIND = 719, LAUNCH_FAILED = 700, MAX_LDS_ATTRIBUTE = 8 };
+enum { OK = 0, INVALID = 1, LEFT_BEHIND = 719, LAUNCH_FAILED = 700, NOT_FOUND = 500, MAX_LDS_ATTRIBUTE = 8 };
 
 static int device = 0, last_error = OK, launches = 0, fail_launch = 0, refuse_attribute = 0, unreserved = 0, wide_launches = 0;
+static int fail_lookup = 0, by_address = 0, lookups = 0;
 static struct { const void *kernel; int device, bytes; } reserved[256];
 static int n_reserved = 0;
 
@@ -28,18 +31,42 @@ int hipFuncSetAttribute(const void *kernel, int attr, int value)
     reserved[n_reserved++].bytes = value;
     return OK;
 }
-int hipLaunchKernel(const void *kernel, dim3_t grid, dim3_t block, void **args, size_t lds, void *stream)
+typedef struct { const void *kernel; int device; } handle_t;
+static handle_t handles[256];
+static int n_handles = 0;
+int hipGetFuncBySymbol(handle_t **f, const void *kernel)
+{
+    ++lookups;
+    if (fail_lookup || n_handles == 256) return last_error = NOT_FOUND;
+    handles[n_handles].kernel = kernel;
+    handles[n_handles].device = device;
+    *f = &handles[n_handles++];
+    return OK;
+}
+static int launch(const void *kernel, int on, unsigned grid, unsigned block, size_t lds)
 {
     int found = lds <= 65536;
-    (void)args; (void)stream;
     if (fail_launch) return last_error = LAUNCH_FAILED;
-    if (!grid.x || !block.x) return last_error = INVALID;
+    if (!grid || !block || on != device) return last_error = INVALID;
     for (int i = 0; i < n_reserved; ++i)
-        found |= reserved[i].kernel == kernel && reserved[i].device == device && (size_t)reserved[i].bytes >= lds;
+        found |= reserved[i].kernel == kernel && reserved[i].device == on && (size_t)reserved[i].bytes >= lds;
     unreserved += !found;
     wide_launches += lds > 65536;
     ++launches;
     return OK;
+}
+int hipLaunchKernel(const void *kernel, dim3_t grid, dim3_t block, void **args, size_t lds, void *stream)
+{
+    (void)args; (void)stream;
+    ++by_address;
+    return launch(kernel, device, grid.x, block.x, lds);
+}
+int hipModuleLaunchKernel(const handle_t *f, unsigned gx, unsigned gy, unsigned gz, unsigned bx, unsigned by, unsigned bz, unsigned lds, void *stream,
+                          void **args, void **extra)
+{
+    (void)stream; (void)args;
+    if (gy != 1 || gz != 1 || by != 1 || bz != 1 || extra) return last_error = INVALID;
+    return launch(f->kernel, f->device, gx, bx, lds);
 }
 
 static amap_t *layout(int64_t a, int64_t b, int64_t c, int64_t d, int merge)
@@ -97,8 +124,9 @@ int main(int argc, char **argv)
             }
         device = 2;   /* refused before, asked again */
         for (int i = 0; i < 3; ++i) EXPECT(product(i) == AMAP_OK && unreserved == 0);
-        const int asked = n_reserved;
-        for (int i = 0; i < 3; ++i) EXPECT(product(i) == AMAP_OK && n_reserved == asked);   /* once per device is enough */
+        const int asked = n_reserved, looked = lookups;
+        for (int i = 0; i < 3; ++i) EXPECT(product(i) == AMAP_OK && n_reserved == asked && lookups == looked);   /* once per device is enough */
+        EXPECT(by_address == 0);
     } else if (argc == 2 && !strcmp(argv[1], "errors")) {
         amap_t *m = layout(2, 8, 64, 64, 0);
         EXPECT(m);
@@ -113,6 +141,19 @@ int main(int argc, char **argv)
             EXPECT(last_error == OK && strlen(amap_last_error()) > 0);
             fail_launch = 0;
         }
+        EXPECT(by_address == 0);
+        amap_free(m);
+    } else if (argc == 2 && !strcmp(argv[1], "lookup")) {
+        amap_t *m = layout(2, 8, 64, 64, 0);
+        EXPECT(m);
+        fail_lookup = 1;
+        for (int i = -1; i < 3; ++i) {
+            EXPECT((i < 0 ? amap_execute(srcs, out, m, NULL) : product(i)) == AMAP_OK);
+            EXPECT(by_address == i + 2 && last_error == OK);
+        }
+        fail_lookup = 0;   /* asked again, and found */
+        for (int i = -1; i < 3; ++i) EXPECT((i < 0 ? amap_execute(srcs, out, m, NULL) : product(i)) == AMAP_OK);
+        EXPECT(by_address == 4 && launches == 8 && last_error == OK);
         amap_free(m);
     } else {
         return 2;

@@ -32,3 +32,8 @@ def test_lds_is_reserved_on_every_device(caller):
 
 def test_errors_of_other_calls_pass_through(caller):
     caller("errors")
+
+
+def test_a_failed_look_up_leaves_no_error(caller):
+    """The kernel's handle is a short cut: without it the launch goes by the kernel's address."""
+    caller("lookup")
