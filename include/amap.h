@@ -324,7 +324,8 @@ amap_status amap_layout_copy(const amap_layout_graph_t *g, int index, int *op, i
                              amap_t **map);
 
 /* ---- execution (device pointers; asynchronous on `stream`) --------------
- * `stream` is a hipStream_t passed as void* (NULL = the default stream).
+ * `stream` is a hipStream_t passed as void* (NULL = the default stream of the current device).
+ * A call runs on its stream's device, which need not be the current one.
  * No allocation, no synchronisation, no host access to device memory. */
 
 /* dst[i] = src[src_id][g(i)] or fill, for every index i of dst: the rewritten

@@ -1115,6 +1115,11 @@ amap_status gemm_launch(const void *const *A_srcs, bool by_id, const amap_t *A_m
     g.tiles_m = (uint32_t)((M + BM - 1) / BM);
     g.tiles_n = (uint32_t)((N + BN - 1) / BN);
     hipStream_t hs = reinterpret_cast<hipStream_t>(stream);
+    const StreamDevice device(dry ? nullptr : hs);
+    if (device.status() != hipSuccess) {
+        set_last_error("the stream's device", hipGetErrorString(device.status()));
+        return AMAP_E_HIP;
+    }
     // ---- the common case runs on 256 x 256 tiles (see amap_gemm_tile256_kernel)
     // 0: always the general kernel (tests compare the others with it); 1: the 256 x 256 tiles wherever they take the product
     const char *t256 = std::getenv("AMAP_GEMM_TILE256");

@@ -1238,6 +1238,8 @@ extern "C" amap_status amap_execute_kernel(const void *const *src, void *dst, co
     amap_status st = check_pointers(map, src, dst);
     if (st != AMAP_OK) return st;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
+    const StreamDevice device(s);
+    if (device.status() != hipSuccess) return launched(device.status(), "the stream's device");
     try {
         if (kernel_id < 0) {
             const Plan *plan = plan_of(*map);
@@ -1285,6 +1287,8 @@ extern "C" amap_status amap_execute_multi(const void *const *src, void *const *d
             base = std::min(base, (uintptr_t)dst[i]);
         }
         if (base == UINTPTR_MAX) return AMAP_OK;  // nothing to write
+        const StreamDevice device(s);
+        if (device.status() != hipSuccess) return launched(device.status(), "the stream's device");
         LaunchArgs cur;   // (entries beyond n_pieces stay unset)
         uint32_t blocks = 0, lds = 0;
         cur.n_pieces = cur.nwlog = cur.nt = cur.xcd_remap = 0;

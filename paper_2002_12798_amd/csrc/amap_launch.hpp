@@ -10,6 +10,38 @@
 
 namespace amap_detail {
 
+// A call runs on its stream's device: that one is current while this object lives, the caller's again afterwards.  Kernel handles and
+// reserved LDS belong to a device, and are asked for on the current one.  (The null stream is the current device's.  A stream that the
+// runtime cannot tell of is left to the launch.)
+class StreamDevice {
+  public:
+    explicit StreamDevice(hipStream_t stream) {
+        int here = 0;
+        hipDevice_t there = 0;
+        if (!stream) return;
+        if (hipGetDevice(&here) != hipSuccess || hipStreamGetDevice(stream, &there) != hipSuccess) {
+            (void)hipGetLastError();
+            return;
+        }
+        if ((int)there == here) return;
+        status_ = hipSetDevice((int)there);
+        if (status_ == hipSuccess)
+            back_to_ = here;
+        else
+            (void)hipGetLastError();
+    }
+    ~StreamDevice() {
+        if (back_to_ >= 0 && hipSetDevice(back_to_) != hipSuccess) (void)hipGetLastError();
+    }
+    StreamDevice(const StreamDevice &) = delete;
+    StreamDevice &operator=(const StreamDevice &) = delete;
+    hipError_t status() const { return status_; }
+
+  private:
+    hipError_t status_ = hipSuccess;
+    int back_to_ = -1;
+};
+
 // A kernel's handle on each device, asked for at its first launch there; null where there is none, and no error of the asking is left.
 class KernelHandle {
   public:

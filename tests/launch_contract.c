@@ -5,7 +5,10 @@
  *   errors   an error that another call left on the thread neither fails a launch nor is cleared by it; the launch's own error
  *            fails the call and does not stay behind
  *   lookup   a kernel whose handle cannot be had is launched by its address, and the failed look-up leaves no error on the thread
- * A kernel's handle is looked up on the current device; a launch by handle goes to that device, one by address too. */
+ *   streams  a stream of a device that is not the current one: the launch, its kernel's handle and the LDS are that device's, and the
+ *            caller's device is current again afterwards; a stream that cannot be asked is left to the launch
+ * A kernel's handle is looked up on the current device and is good there only; a launch by address finds the kernel on the stream's device.
+ * (A stream here is its device + 1.) */
 #include <stdint.h>
 #include <stdio.h>
 #include <string.h>
@@ -16,11 +19,25 @@ typedef struct { uint32_t x, y, z; } dim3_t;
 enum { OK = 0, INVALID = 1, LEFT_BEHIND = 719, LAUNCH_FAILED = 700, NOT_FOUND = 500, MAX_LDS_ATTRIBUTE = 8 };
 
 static int device = 0, last_error = OK, launches = 0, fail_launch = 0, refuse_attribute = 0, unreserved = 0, wide_launches = 0;
-static int fail_lookup = 0, by_address = 0, lookups = 0;
+static int fail_lookup = 0, by_address = 0, lookups = 0, fail_stream = 0, fail_set = 0, device_calls = 0, ran_on = -1;
 static struct { const void *kernel; int device, bytes; } reserved[256];
 static int n_reserved = 0;
 
 int hipGetDevice(int *d) { *d = device; return OK; }
+int hipSetDevice(int d)
+{
+    ++device_calls;
+    if (fail_set) return last_error = INVALID;
+    device = d;
+    return OK;
+}
+int hipStreamGetDevice(void *stream, int *d)
+{
+    ++device_calls;
+    if (fail_stream) return last_error = INVALID;
+    *d = stream ? (int)(uintptr_t)stream - 1 : device;
+    return OK;
+}
 int hipDeviceGetAttribute(int *v, int attr, int d) { (void)attr; (void)d; *v = 256; return OK; }
 int hipGetLastError(void) { const int e = last_error; last_error = OK; return e; }
 int hipFuncSetAttribute(const void *kernel, int attr, int value)
@@ -43,11 +60,12 @@ int hipGetFuncBySymbol(handle_t **f, const void *kernel)
     *f = &handles[n_handles++];
     return OK;
 }
-static int launch(const void *kernel, int on, unsigned grid, unsigned block, size_t lds)
+static int launch(const void *kernel, int on, unsigned grid, unsigned block, size_t lds, const void *stream)
 {
     int found = lds <= 65536;
     if (fail_launch) return last_error = LAUNCH_FAILED;
-    if (!grid || !block || on != device) return last_error = INVALID;
+    if (!grid || !block || on != (stream ? (int)(uintptr_t)stream - 1 : device)) return last_error = INVALID;
+    ran_on = on;
     for (int i = 0; i < n_reserved; ++i)
         found |= reserved[i].kernel == kernel && reserved[i].device == on && (size_t)reserved[i].bytes >= lds;
     unreserved += !found;
@@ -57,16 +75,16 @@ static int launch(const void *kernel, int on, unsigned grid, unsigned block, siz
 }
 int hipLaunchKernel(const void *kernel, dim3_t grid, dim3_t block, void **args, size_t lds, void *stream)
 {
-    (void)args; (void)stream;
+    (void)args;
     ++by_address;
-    return launch(kernel, device, grid.x, block.x, lds);
+    return launch(kernel, stream ? (int)(uintptr_t)stream - 1 : device, grid.x, block.x, lds, stream);
 }
 int hipModuleLaunchKernel(const handle_t *f, unsigned gx, unsigned gy, unsigned gz, unsigned bx, unsigned by, unsigned bz, unsigned lds, void *stream,
                           void **args, void **extra)
 {
-    (void)stream; (void)args;
+    (void)args;
     if (gy != 1 || gz != 1 || by != 1 || bz != 1 || extra) return last_error = INVALID;
-    return launch(f->kernel, f->device, gx, bx, lds);
+    return launch(f->kernel, f->device, gx, bx, lds, stream);
 }
 
 static amap_t *layout(int64_t a, int64_t b, int64_t c, int64_t d, int merge)
@@ -89,10 +107,23 @@ static void *const out = (void *)((uintptr_t)3 << 40);
 /* one product per GEMM kernel that asks for more than 64 KB: 64 x 128 tiles, 256 x 256 tiles, the general kernel */
 static const struct { int64_t b, h, s, d, n; } products[3] = {{1, 20, 2341, 64, 760}, {16, 16, 512, 64, 4096}, {1, 9, 300, 8, 256}};
 
-static amap_status product(int i)
+static amap_status product_on(int i, void *stream)
 {
     amap_t *m = layout(products[i].b, products[i].h, products[i].s, products[i].d, 1);
-    const amap_status st = m ? amap_gemm_gather(srcs, m, weight, NULL, products[i].n, NULL, out, NULL) : AMAP_E_INVALID;
+    const amap_status st = m ? amap_gemm_gather(srcs, m, weight, NULL, products[i].n, NULL, out, stream) : AMAP_E_INVALID;
+    amap_free(m);
+    return st;
+}
+static amap_status product(int i) { return product_on(i, NULL); }
+
+/* every way to a launch: the layout call, the call of several maps, the products */
+enum { WAYS = 5 };
+static amap_status way(int i, void *stream)
+{
+    amap_t *m;
+    amap_status st = AMAP_E_INVALID;
+    if (i >= 2) return product_on(i - 2, stream);
+    if ((m = layout(2, 8, 64, 64, 0))) st = i == 0 ? amap_execute(srcs, out, m, stream) : amap_execute_multi(srcs, &out, (const amap_t *const *)&m, 1, stream);
     amap_free(m);
     return st;
 }
@@ -155,6 +186,28 @@ int main(int argc, char **argv)
         for (int i = -1; i < 3; ++i) EXPECT((i < 0 ? amap_execute(srcs, out, m, NULL) : product(i)) == AMAP_OK);
         EXPECT(by_address == 4 && launches == 8 && last_error == OK);
         amap_free(m);
+    } else if (argc == 2 && !strcmp(argv[1], "streams")) {
+        for (int i = 0; i < WAYS; ++i)
+            for (int k = 0; k < 9; ++k) {
+                void *const stream = (void *)(uintptr_t)(k % 3 + 1);
+                device = k / 3;
+                EXPECT(way(i, stream) == AMAP_OK && ran_on == k % 3 && device == k / 3 && unreserved == 0 && last_error == OK);
+                device_calls = 0;
+                EXPECT(way(i, NULL) == AMAP_OK && ran_on == k / 3 && unreserved == 0 && device_calls == 0);
+            }
+        EXPECT(by_address == 0);
+        device = 0;
+        for (int i = 0; i < WAYS; ++i) {
+            fail_launch = 1;   /* back on the caller's device after an error too */
+            EXPECT(way(i, (void *)2) == AMAP_E_HIP && device == 0 && last_error == OK);
+            fail_launch = 0;
+            fail_stream = 1;
+            EXPECT(way(i, (void *)1) == AMAP_OK && ran_on == 0 && last_error == OK);
+            fail_stream = 0;
+            fail_set = 1;
+            EXPECT(way(i, (void *)2) == AMAP_E_HIP && device == 0 && last_error == OK);
+            fail_set = 0;
+        }
     } else {
         return 2;
     }

@@ -37,3 +37,8 @@ def test_errors_of_other_calls_pass_through(caller):
 def test_a_failed_look_up_leaves_no_error(caller):
     """The kernel's handle is a short cut: without it the launch goes by the kernel's address."""
     caller("lookup")
+
+
+def test_a_stream_of_another_device(caller):
+    """The stream says where a call runs, whichever device is current."""
+    caller("streams")
