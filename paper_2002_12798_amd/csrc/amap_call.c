@@ -52,10 +52,6 @@ static int integer(PyObject *o, void **at) { return o != Py_None && address(o, a
 
 static int data_of(PyObject *tensor, void **at)
 {
-    if (tensor == Py_None) {
-        *at = NULL;
-        return 1;
-    }
     PyObject *p = PyObject_CallMethodNoArgs(tensor, s_data_ptr);
     if (!p) {
         PyErr_Clear();
@@ -64,6 +60,14 @@ static int data_of(PyObject *tensor, void **at)
     const int ok = integer(p, at);
     Py_DECREF(p);
     return ok;
+}
+
+/* a source, which a map may not need; an output is always there */
+static int source_of(PyObject *tensor, void **at)
+{
+    if (tensor != Py_None) return data_of(tensor, at);
+    *at = NULL;
+    return 1;
 }
 
 /* a map: the library's, how long a source table it expects and the last source that it reads (-1: none) */
@@ -157,7 +161,7 @@ static PyObject *call_execute(PyObject *self, PyObject *const *a, Py_ssize_t n)
     void *tab[MAX_TABLE], *dst, *map, *stream;
     Py_ssize_t given, n_src, last;
     (void)self;
-    UNLESS(p_execute && n == 4 && a[2] != Py_None && map_of(a[0], &map, &n_src, &last) && table(a[1], tab, &given, data_of));
+    UNLESS(p_execute && n == 4 && map_of(a[0], &map, &n_src, &last) && table(a[1], tab, &given, source_of));
     UNLESS(last < given && n_src <= MAX_TABLE && data_of(a[2], &dst) && stream_of(a[3], &stream));
     CALLED(p_execute(tab, dst, map, stream));
 }
@@ -168,7 +172,7 @@ static PyObject *call_execute_multi(PyObject *self, PyObject *const *a, Py_ssize
     void *tab[MAX_TABLE], *dst[MAX_TABLE], *maps[MAX_TABLE], *stream;
     Py_ssize_t given, n_dst, n_maps, n_src, last;
     (void)self;
-    UNLESS(p_multi && n == 4 && (PyList_CheckExact(a[0]) || PyTuple_CheckExact(a[0])) && table(a[1], tab, &given, data_of) && table(a[2], dst, &n_dst, data_of));
+    UNLESS(p_multi && n == 4 && (PyList_CheckExact(a[0]) || PyTuple_CheckExact(a[0])) && table(a[1], tab, &given, source_of) && table(a[2], dst, &n_dst, data_of));
     n_maps = PySequence_Fast_GET_SIZE(a[0]);
     UNLESS(n_maps >= 1 && n_maps <= n_dst);
     for (Py_ssize_t i = 0; i < n_maps; ++i) {

@@ -101,3 +101,14 @@ def test_a_map_given_back_is_not_handed_over(call):
     m = _map((8, 16))
     m.__del__()
     assert call.execute(m, [Tensor(64)], Tensor(128), 0) == -1 and call.gemm(64, m, 64, None, 8, None, 128, 0) == -1 and call.seen == []
+
+
+def test_no_output_is_none(call):
+    """An output that is not there is the caller's mistake and raised as one, in a call of one map and of several."""
+    from paper_2002_12798_amd import device
+    m, x = _map((8, 16)), Tensor(64)
+    for outs in ([None], [x, None], [None, x]):   # (one more than there are maps is looked at too)
+        assert call.execute_multi([m], [x], outs, 0) == -1
+        with pytest.raises(AttributeError):
+            device.execute_multi([m], [x], outs, stream=0)
+    assert call.seen == []
