@@ -31,7 +31,14 @@ static int initialized;   /* torch said so in this process (a fork asks again) *
 
 static void forked(void) { initialized = 0; }
 
-/* Each of these is 1, or 0 for a call that is not taken; no Python error is left behind. */
+/* Each of these is 1, or 0 for a call that is not taken.  An error is the other way's to raise again and is cleared; one that ends the
+ * program (an interrupt, an exit: no Exception) stays, and the call returns with it. */
+
+static int not_taken(void)
+{
+    if (PyErr_Occurred() && PyErr_ExceptionMatches(PyExc_Exception)) PyErr_Clear();
+    return 0;
+}
 
 static int address(PyObject *o, void **at)
 {
@@ -41,11 +48,7 @@ static int address(PyObject *o, void **at)
     }
     if (!PyLong_CheckExact(o)) return 0;
     *at = PyLong_AsVoidPtr(o);
-    if (!*at && PyErr_Occurred()) {
-        PyErr_Clear();
-        return 0;
-    }
-    return 1;
+    return *at || !PyErr_Occurred() || not_taken();
 }
 
 static int integer(PyObject *o, void **at) { return o != Py_None && address(o, at); }
@@ -53,10 +56,7 @@ static int integer(PyObject *o, void **at) { return o != Py_None && address(o, a
 static int data_of(PyObject *tensor, void **at)
 {
     PyObject *p = PyObject_CallMethodNoArgs(tensor, s_data_ptr);
-    if (!p) {
-        PyErr_Clear();
-        return 0;
-    }
+    if (!p) return not_taken();
     const int ok = integer(p, at);
     Py_DECREF(p);
     return ok;
@@ -82,10 +82,7 @@ static int map_of(PyObject *m, void **map, Py_ssize_t *n_src, Py_ssize_t *last)
         *last = n ? PyLong_AsSsize_t(PyTuple_GET_ITEM(ids, n - 1)) : -1;
         ok = *n_src >= 0;
     }
-    if (PyErr_Occurred()) {
-        PyErr_Clear();
-        ok = 0;
-    }
+    if (PyErr_Occurred()) ok = not_taken();
     Py_XDECREF(at);
     Py_XDECREF(reads);
     return ok;
@@ -99,9 +96,8 @@ static int handle_of(PyObject *m, void **map)
         return 1;
     }
     PyObject *at = PyObject_GetAttr(m, s_at);
-    const int ok = at && integer(at, map) && *map;
+    const int ok = (at && integer(at, map) && *map) || not_taken();
     Py_XDECREF(at);
-    PyErr_Clear();
     return ok;
 }
 
@@ -132,15 +128,13 @@ static int stream_of(PyObject *o, void **stream)
         r = PyObject_CallNoArgs(is_initialized);
         initialized = r ? PyObject_IsTrue(r) == 1 : 0;
         Py_XDECREF(r);
-        PyErr_Clear();
-        if (!initialized) return 0;
+        if (!initialized) return not_taken();
     }
     PyObject *dev = PyObject_CallNoArgs(get_device);
     r = dev ? PyObject_CallOneArg(raw_stream, dev) : NULL;
-    const int ok = r && integer(r, stream);
+    const int ok = (r && integer(r, stream)) || not_taken();
     Py_XDECREF(dev);
     Py_XDECREF(r);
-    PyErr_Clear();
     return ok;
 }
 
@@ -153,7 +147,7 @@ static int stream_of(PyObject *o, void **stream)
         return PyLong_FromLong(status_); \
     } while (0)
 #define UNLESS(x) \
-    if (!(x)) return PyLong_FromLong(NOT_TAKEN)
+    if (!(x)) return PyErr_Occurred() ? NULL : PyLong_FromLong(NOT_TAKEN)
 
 /* execute(map, tensors, tensor, stream or None) */
 static PyObject *call_execute(PyObject *self, PyObject *const *a, Py_ssize_t n)
@@ -187,11 +181,7 @@ static int count_of(PyObject *o, int64_t *n)
 {
     if (!PyLong_CheckExact(o)) return 0;
     *n = PyLong_AsLongLong(o);
-    if (*n == -1 && PyErr_Occurred()) {
-        PyErr_Clear();
-        return 0;
-    }
-    return 1;
+    return *n != -1 || !PyErr_Occurred() || not_taken();
 }
 
 /* gemm(address of A, map, address of W, map or None, n, store map or None, address of the product, stream) */
@@ -225,7 +215,10 @@ static PyObject *call_current_stream(PyObject *self, PyObject *none)
     void *stream;
     (void)self;
     (void)none;
-    if (!stream_of(Py_None, &stream)) Py_RETURN_NONE;
+    if (!stream_of(Py_None, &stream)) {
+        if (PyErr_Occurred()) return NULL;
+        Py_RETURN_NONE;
+    }
     return PyLong_FromVoidPtr(stream);
 }
 

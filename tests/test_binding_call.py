@@ -112,3 +112,38 @@ def test_no_output_is_none(call):
         with pytest.raises(AttributeError):
             device.execute_multi([m], [x], outs, stream=0)
     assert call.seen == []
+
+
+@pytest.mark.parametrize("stop", [KeyboardInterrupt, SystemExit])
+def test_an_interrupt_is_not_taken_for_a_call_to_leave(call, stop):
+    """What ends the program passes through; a data_ptr() that raised it is not asked again."""
+    from paper_2002_12798_amd import device
+
+    class Stops(Tensor):
+        def data_ptr(self):
+            self.at -= 1
+            if self.at == 63:
+                raise stop
+            return self.at
+
+    m, x = _map((8, 16)), Tensor(128)
+    calls = [lambda: device.execute(m, [Stops(64)], x, stream=0), lambda: device.execute(m, [x], Stops(64), stream=0),
+             lambda: device.execute_multi([m], [Stops(64)], [x], stream=0), lambda: device.execute_multi([m], [x], [Stops(64)], stream=0)]
+    for f in calls:
+        with pytest.raises(stop):
+            f()
+
+    def stopped(*args):
+        raise stop
+
+    try:
+        for fs in ((lambda dev: 1000, lambda: 3, stopped), (lambda dev: 1000, stopped, lambda: True), (stopped, lambda: 3, lambda: True)):
+            call.torch(*fs)
+            with pytest.raises(stop):
+                call.execute(m, [x], x, None)
+            with pytest.raises(stop):
+                call.current_stream()
+    finally:
+        import torch
+        call.torch(device._raw_stream, device._get_device, torch.cuda.is_initialized)
+    assert call.seen == []
