@@ -521,7 +521,7 @@ class GraphDME:
         return out
 
     def __del__(self):
-        h, self._h, self._at = getattr(self, "_h", None), None, None
+        h, self._h = getattr(self, "_h", None), None
         if h and _L is not None:
             _L.amap_graph_free(h)
 
@@ -576,6 +576,6 @@ class LayoutGraph:
         return out
 
     def __del__(self):
-        h, self._h, self._at = getattr(self, "_h", None), None, None
+        h, self._h = getattr(self, "_h", None), None
         if h and _L is not None:
             _L.amap_layout_free(h)

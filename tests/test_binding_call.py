@@ -147,3 +147,12 @@ def test_an_interrupt_is_not_taken_for_a_call_to_leave(call, stop):
         import torch
         call.torch(device._raw_stream, device._get_device, torch.cuda.is_initialized)
     assert call.seen == []
+
+
+def test_only_maps_hold_a_map_s_address(call):
+    """What is given back: a map's address with the map; a graph has none, before and after."""
+    layout = B.LayoutGraph()
+    graph = B.GraphDME([("input", (8, 16))], [0], 2)
+    for owner in (layout, graph):
+        owner.__del__()
+        assert owner._h is None and not hasattr(owner, "_at")
