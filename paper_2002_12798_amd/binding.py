@@ -148,7 +148,7 @@ raw = _L  # the raw CDLL, for callers that pre-marshal their arguments
 try:
     from . import _amap_call as _call  # noqa: E402
 except ImportError as e:
-    raise ImportError(f"{os.path.join(_HERE, '_amap_call.so')}: {e}; run `python -c 'import __graft_entry__ as g; g.build()'`") from e
+    raise ImportError(f"{e}; run `python -c 'import __graft_entry__ as g; g.build()'`") from e
 
 _call.library(*(C.cast(f, _vp).value for f in (_L.amap_execute, _L.amap_execute_multi, _L.amap_gemm_fused, _L.amap_gemm_fused_store,
                                                _L.amap_gemm_mapped, _L.amap_gemm_gather)))

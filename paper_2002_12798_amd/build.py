@@ -10,7 +10,8 @@ _HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(_HERE)
 CSRC = os.path.join(_HERE, "csrc")
 LIB = os.path.join(_HERE, "libamap.so")
-CALL = os.path.join(_HERE, "_amap_call.so")   # CPython extension: from a Python call to the library
+# CPython extension, from a Python call to the library: its name holds the interpreter's ABI, and another one looks for another name
+CALL = os.path.join(_HERE, "_amap_call" + sysconfig.get_config_var("EXT_SUFFIX"))
 
 SOURCES = ["amap_compose.cpp", "amap_graph.cpp", "amap_layout.cpp", "amap_host.cpp", "amap_plan.cpp", "amap_plan_check.cpp", "amap_kernels.hip",
            "amap_gemm.hip", "amap_gemm_ring.hip"]
@@ -67,6 +68,9 @@ def build_lib(verbose: bool = False, extra=()) -> str:
 def build_call() -> str:
     subprocess.run(["gcc", "-O2", "-std=c99", "-fPIC", "-shared", "-Wall", "-Wextra", "-I", sysconfig.get_path("include"),
                     os.path.join(CSRC, "amap_call.c"), "-o", CALL], check=True)
+    untagged = os.path.join(_HERE, "_amap_call.so")   # built so before: any interpreter would load it
+    if os.path.exists(untagged):
+        os.remove(untagged)
     return CALL
 
 
