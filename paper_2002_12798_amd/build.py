@@ -2,6 +2,7 @@
 from __future__ import annotations
 
 import os
+import shutil
 import subprocess
 import sys
 import sysconfig
@@ -61,12 +62,20 @@ def build_lib(verbose: bool = False, extra=()) -> str:
     if wrong:
         os.remove(LIB)
         raise RuntimeError("; ".join(wrong))
-    build_call()   # the binding needs both
+    build_call()
     return LIB
 
 
-def build_call() -> str:
-    subprocess.run(["gcc", "-O2", "-std=c99", "-fPIC", "-shared", "-Wall", "-Wextra", "-I", sysconfig.get_path("include"),
+def build_call():
+    """The extension's path, or None where it cannot be built: the binding does without."""
+    include = sysconfig.get_path("include")
+    lacks = "gcc" if not shutil.which("gcc") else "Python.h" if not os.path.exists(os.path.join(include, "Python.h")) else None
+    if lacks:
+        if os.path.exists(CALL):
+            os.remove(CALL)   # of another state of the source
+        print(f"{CALL} not built (no {lacks}): Python calls go through ctypes", file=sys.stderr)
+        return None
+    subprocess.run(["gcc", "-O2", "-std=c99", "-fPIC", "-shared", "-Wall", "-Wextra", "-I", include,
                     os.path.join(CSRC, "amap_call.c"), "-o", CALL], check=True)
     untagged = os.path.join(_HERE, "_amap_call.so")   # built so before: any interpreter would load it
     if os.path.exists(untagged):

@@ -2,6 +2,8 @@
 wavefronts per SIMD than the map kernels need."""
 import glob
 import os
+import subprocess
+import sys
 import sysconfig
 
 import pytest
@@ -38,3 +40,48 @@ def test_the_extension_is_for_one_python():
     assert build.CALL.endswith(sysconfig.get_config_var("EXT_SUFFIX")) and len(sysconfig.get_config_var("EXT_SUFFIX")) > len(".so")
     assert os.path.realpath(binding._call.__file__) == os.path.realpath(build.CALL)
     assert glob.glob(os.path.join(os.path.dirname(build.CALL), "_amap_call.so")) == []
+
+
+WITHOUT = """
+import sys
+sys.modules["paper_2002_12798_amd._amap_call"] = None
+from paper_2002_12798_amd import binding as B, device
+
+class Tensor:
+    shape = (64, 24)
+    def __init__(self, at): self.at = at
+    def data_ptr(self): return self.at
+
+seen = []
+def recorder(name):
+    def f(*args):
+        seen.append((name, [x if x is None or type(x) is int else x.value if hasattr(x, "value") else list(x) for x in args]))
+        return 0
+    return f
+B._execute = recorder("execute")
+for name in ("amap_execute_multi", "amap_gemm_fused", "amap_gemm_gather"):
+    setattr(B._L, name, recorder(name))
+m, x, y = B.amap_compose([(8, 64)], 2, []), Tensor(64), Tensor(128)
+assert device.execute(m, [x], y, stream=7) is y and device.execute_multi([m], [x], [y], stream=7) == [y]
+assert device.gemm_fused(x, m, Tensor(96), out=y, stream=7) is y
+B.amap_gemm_gather([64], m, 96, None, 24, None, 128, 7)
+h = m.handle.value
+assert seen == [("execute", [[64], 128, h, 7]), ("amap_execute_multi", [[64], [128], [h], 1, 7]), ("amap_gemm_fused", [64, h, 96, 24, 128, 7]),
+                ("amap_gemm_gather", [[64], h, 96, None, 24, None, 128, 7])], seen
+"""
+
+
+def test_without_the_extension_calls_go_through_ctypes():
+    """(The library is replaced by functions that write down what they were given.)"""
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    r = subprocess.run([sys.executable, "-W", "always", "-c", WITHOUT], cwd=root, capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0 and "through ctypes" in r.stderr, r.stderr
+
+
+def test_a_build_without_python_s_headers(monkeypatch, tmp_path, capfd):
+    """The library is what has to be built; an extension that cannot be is left out, an old one too."""
+    monkeypatch.setattr(build, "CALL", str(tmp_path / "_amap_call.x.so"))
+    (tmp_path / "_amap_call.x.so").write_bytes(b"old")
+    monkeypatch.setattr(sysconfig, "get_path", lambda name: str(tmp_path))
+    assert build.build_call() is None and not os.path.exists(build.CALL)
+    assert "Python.h" in capfd.readouterr().err
