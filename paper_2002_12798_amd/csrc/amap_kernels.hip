@@ -1075,7 +1075,7 @@ amap_status launch_pieces(const LaunchArgs &args, uint32_t blocks, uint32_t lds,
         const DevPiece &P = args.p[0];
         RowsOne one;
         if (P.src && 16ull * P.n_units <= kFewOutput && rows_few_loops(P, one)) {
-            say("amap_rows_kernel", ", few loops");
+            say("amap_rows_few_kernel", ", few loops");
             one.p[0] = rows_few_piece(P, P.src, d, es);
             return launched(launch_few(one, args.nt, es, grid, block, stream), "amap_rows_few_kernel");
         }
@@ -1104,7 +1104,7 @@ amap_status launch_pieces(const LaunchArgs &args, uint32_t blocks, uint32_t lds,
                 three.p[k] = rows_few_piece(P, P.src, d, es);
             }
             if (data) {
-                say("amap_rows_multi_kernel", ", few loops");
+                say("amap_rows_few_kernel", ", few loops");
                 return launched(launch_few(three, args.nt, es, grid, block, stream), "amap_rows_few_kernel");
             }
         }

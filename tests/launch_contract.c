@@ -7,6 +7,7 @@
  *   lookup   a kernel whose handle cannot be had is launched by its address, and the failed look-up leaves no error on the thread
  *   streams  a stream of a device that is not the current one: the launch, its kernel's handle and the LDS are that device's, and the
  *            caller's device is current again afterwards; a stream that cannot be asked is left to the launch
+ *   names    writes "ran <kernel>" to stderr for every launch, behind what the library's trace says of it
  * A kernel's handle is looked up on the current device and is good there only; a launch by address finds the kernel on the stream's device.
  * (A stream here is its device + 1.) */
 #include <stdint.h>
@@ -60,12 +61,25 @@ int hipGetFuncBySymbol(handle_t **f, const void *kernel)
     *f = &handles[n_handles++];
     return OK;
 }
+/* the kernels by name, as the library registers them when it is loaded */
+static struct { const void *kernel; const char *name; } names[512];
+static int n_names = 0, say_names = 0;
+void __hipRegisterFunction(void **modules, const void *kernel, char *symbol, const char *name, unsigned threads, void *tid, void *bid, dim3_t *block,
+                           dim3_t *grid, int *warp)
+{
+    (void)modules; (void)symbol; (void)threads; (void)tid; (void)bid; (void)block; (void)grid; (void)warp;
+    if (n_names == 512) return;
+    names[n_names].kernel = kernel;
+    names[n_names++].name = name;
+}
 static int launch(const void *kernel, int on, unsigned grid, unsigned block, size_t lds, const void *stream)
 {
     int found = lds <= 65536;
     if (fail_launch) return last_error = LAUNCH_FAILED;
     if (!grid || !block || on != (stream ? (int)(uintptr_t)stream - 1 : device)) return last_error = INVALID;
     ran_on = on;
+    for (int i = 0; say_names && i < n_names; ++i)
+        if (names[i].kernel == kernel) fprintf(stderr, "ran %s\n", names[i].name);
     for (int i = 0; i < n_reserved; ++i)
         found |= reserved[i].kernel == kernel && reserved[i].device == on && (size_t)reserved[i].bytes >= lds;
     unreserved += !found;
@@ -207,6 +221,18 @@ int main(int argc, char **argv)
             fail_set = 1;
             EXPECT(way(i, (void *)2) == AMAP_E_HIP && device == 0 && last_error == OK);
             fail_set = 0;
+        }
+    } else if (argc == 2 && !strcmp(argv[1], "names")) {
+        /* [a,b,c,d] with b and c exchanged; up to 32 MB and beyond, one map and several, rows of one element */
+        const struct { int64_t a, b, c, d, n; } calls[] = {{2, 8, 64, 64, 1}, {64, 12, 512, 64, 1}, {2, 8, 64, 64, 3}, {32, 12, 512, 64, 2}, {2, 8, 64, 64, 4},
+                                                           {8, 64, 4096, 1, 1}, {16, 288, 1225, 1, 1}, {3, 5, 7, 3, 1}};
+        say_names = 1;
+        for (unsigned i = 0; i < sizeof(calls) / sizeof(calls[0]); ++i) {
+            amap_t *m = layout(calls[i].a, calls[i].b, calls[i].c, calls[i].d, 0);
+            const amap_t *maps[4] = {m, m, m, m};
+            void *const outs[4] = {out, (char *)out + (1 << 26), (char *)out + (2 << 26), (char *)out + (3 << 26)};
+            EXPECT(m && (calls[i].n == 1 ? amap_execute(srcs, out, m, NULL) : amap_execute_multi(srcs, outs, maps, (int)calls[i].n, NULL)) == AMAP_OK);
+            amap_free(m);
         }
     } else {
         return 2;

@@ -61,13 +61,14 @@ def test_workloads_all_families(dev, name):
 
 
 def test_named_workloads_run_in_the_kernels_built_for_their_launch_shape(dev, monkeypatch, capfd):
-    """cfg0, cfg1 and cfg3 (one tile piece or group, plus fill rows) in amap_tile16_kernel, cfg2 and the GEMM's
-    materialising copy (one plain row piece) in amap_rows_kernel; a silent fall-back to the general kernel would
+    """cfg0, cfg1 and cfg3 (one tile piece or group, plus fill rows) in amap_tile16_kernel, cfg2's split
+    (one plain row piece) in amap_rows_kernel, its way back and the GEMM's materialising copy (the same, up to 32 MB) in
+    amap_rows_few_kernel; a silent fall-back to the general kernel would
     keep every parity test green and lose the speed."""
     import torch
     monkeypatch.setenv("AMAP_PLAN_TRACE", "1")
     for name, kernel in (("cfg0", "amap_tile16_kernel"), ("cfg1", "amap_tile16_kernel"), ("cfg3", "amap_tile16_kernel"),
-                         ("cfg2_fwd", "amap_rows_kernel"), ("cfg2_rev", "amap_rows_kernel"), ("cfg4", "amap_rows_kernel"),
+                         ("cfg2_fwd", "amap_rows_kernel"), ("cfg2_rev", "amap_rows_few_kernel"), ("cfg4", "amap_rows_few_kernel"),
                          ("up3x", "amap_pieces_kernel")):
         kw = {"n": 2} if name in ("cfg1", "cfg3", "up3x") else {}
         w = synth.workload(name, **kw)
