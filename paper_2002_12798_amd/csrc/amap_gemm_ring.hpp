@@ -160,6 +160,7 @@ template <int BM, int BN, int WAVES>
 struct RingStore {
     static constexpr uint32_t kCv = BN / 8, kWaveRows = 64 / kCv, kRows = WAVES * kWaveRows, kPasses = BM / kRows;
     static_assert(kPasses * kWaveRows <= 64, "a row per lane");
+    static_assert(kPasses >= 1 && BM % kRows == 0, "every row of the tile is stored");
     static AMAP_HD uint32_t row_of_store(uint32_t p, uint32_t tid) { return p * kRows + tid / kCv; }
     static AMAP_HD uint32_t row_of_lane(uint32_t wave, uint32_t lane) { return lane / kWaveRows % kPasses * kRows + wave * kWaveRows + lane % kWaveRows; }
     static AMAP_HD uint32_t lane_of_store(uint32_t p, uint32_t lane) { return p * kWaveRows + lane / kCv; }

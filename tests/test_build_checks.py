@@ -85,3 +85,15 @@ def test_a_build_without_python_s_headers(monkeypatch, tmp_path, capfd):
     monkeypatch.setattr(sysconfig, "get_path", lambda name: str(tmp_path))
     assert build.build_call() is None and not os.path.exists(build.CALL)
     assert "Python.h" in capfd.readouterr().err
+
+
+@pytest.mark.parametrize("rows, columns, waves, compiles", [(64, 64, 8, True), (192, 128, 8, True), (64, 64, 6, False), (192, 128, 12, True), (128, 128, 6, False),
+                                                            (64, 128, 32, False)])
+def test_a_tile_that_its_wavefronts_cannot_store_does_not_compile(rows, columns, waves, compiles, tmp_path):
+    """Whole passes over the tile's rows: others would leave the last ones unwritten, or store none."""
+    unit = tmp_path / "store.hip"
+    unit.write_text(f'#include "amap_gemm_ring.hpp"\ntemplate struct amap_gemm::RingStore<{rows}, {columns}, {waves}>;\n')
+    r = subprocess.run(["hipcc", "-x", "hip", "--offload-host-only", "-std=c++17", "-fsyntax-only", "-I", os.path.join(build.ROOT, "include"), "-I", build.CSRC,
+                        str(unit)], capture_output=True, text=True, timeout=300)
+    assert (r.returncode == 0) == compiles, r.stderr
+    assert compiles or "every row of the tile" in r.stderr
