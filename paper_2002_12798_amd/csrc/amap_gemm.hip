@@ -1139,9 +1139,9 @@ amap_status gemm_launch(const void *const *A_srcs, bool by_id, const amap_t *A_m
         RingPlan rp;
         if (ring_plan(g, amode, wmode, tile256, 256, rp)) {
             if (const char *tr = std::getenv("AMAP_PLAN_TRACE"); tr && tr[0] != '0')
-                std::fprintf(stderr, "amap gemm: ring, %d x %d per workgroup of %d wavefronts, A along %c%s%s, W along %c, %lld x %lld x %lld%s\n", rp.bm, rp.bn,
+                std::fprintf(stderr, "amap gemm: ring, %d x %d per workgroup of %d wavefronts, A along %c%s%s, W along %c, C %s the caches, %lld x %lld x %lld%s\n", rp.bm, rp.bn,
                              rp.waves, rp.ax ? 'm' : 'k', rp.n_seg > 1 ? " gathered" : "", rp.klane == 0 ? "" : rp.klane == 1 ? " in runs shorter than a step" : " in runs shorter than a step (k decoded)", rp.wx ? 'n' : 'k',
-                             (long long)M, (long long)N, (long long)K, rp.more);
+                             rp.args.stream ? "past" : "through", (long long)M, (long long)N, (long long)K, rp.more);
             if (dry) {
                 *dry = g;
                 *ring = rp;
@@ -1183,11 +1183,11 @@ amap_status gemm_launch(const void *const *A_srcs, bool by_id, const amap_t *A_m
             set_last_error("amap_gemm_tile256_kernel: cannot reserve its LDS stages", hipGetErrorString(r));
             return AMAP_E_HIP;
         }
-        if (const char *tr = std::getenv("AMAP_PLAN_TRACE"); tr && tr[0] != '0')
-            std::fprintf(stderr, "amap gemm: 256 x 256 tiles%s%s, %lld x %lld x %lld\n", w_km ? " (W runs along k)" : "", edge256 ? " (partial last tiles)" : "",
-                         (long long)M, (long long)N, (long long)K);
         g.a_row_ss = (uint32_t)g.dm.ss[0];
-        g.stream = (g.store_mapped ? g.on.ext[0] : g.N) % 32 == 0;
+        g.stream = !edge256 || (g.store_mapped ? g.on.ext[0] : g.N) % 32 == 0;   // (whole tiles have the one kind)
+        if (const char *tr = std::getenv("AMAP_PLAN_TRACE"); tr && tr[0] != '0')
+            std::fprintf(stderr, "amap gemm: 256 x 256 tiles%s%s, C %s the caches, %lld x %lld x %lld\n", w_km ? " (W runs along k)" : "",
+                         edge256 ? " (partial last tiles)" : "", g.stream ? "past" : "through", (long long)M, (long long)N, (long long)K);
         g.tiles_m = (uint32_t)((M + T2M - 1) / T2M);
         g.tiles_n = (uint32_t)((N + T2N - 1) / T2N);
         const uint32_t ntiles = g.tiles_m * g.tiles_n;

@@ -635,7 +635,7 @@ bool ring_plan(const GemmArgs &g, int amode, int wmode, bool tile256, uint32_t n
     r.obase = g.obase;
     r.om = g.om;
     r.on = g.on;
-    r.stream = stores_stream(g.M, g.N, g.store_mapped ? g.on.ext[0] : g.N);
+    r.stream = p.ax || stores_stream(g.M, g.N, g.store_mapped ? g.on.ext[0] : g.N);   // (A along m: the kernel has the one kind)
 
     // ---- the tile
     double t;

@@ -54,15 +54,45 @@ def test_against_the_general_kernel(dev, case, monkeypatch, capfd):  # noqa: F81
         monkeypatch.undo()
 
 
+THROUGH, PAST = ", C through the caches, ", ", C past the caches, "
+
+
+@pytest.mark.parametrize("m, n, heads, kind", [(333, 1000, None, THROUGH), (333, 1024, None, PAST), (333, 992, None, PAST), (333, 1008, None, THROUGH),
+                                               (16384, 1000, None, THROUGH), (16784, 1000, None, PAST),   # 33.5 MB: just over 32 MB
+                                               # a mapped store: the length of its runs, whatever N is
+                                               (330, 1024, 8, THROUGH), (330, 1024, 80, THROUGH), (330, 1024, 32, PAST), (16896, 1024, 16, PAST)])
+def test_the_kind_of_store(m, n, heads, kind, monkeypatch, capfd):
+    """Rows or runs of no whole 64-byte pieces go through the caches while the product fits them."""
+    n -= n % (heads or 1)
+    a = B.amap_compose([(m, 64)], 2, [])
+    out_map = B.amap_compose([(m, n)], 2, [("reshape", (m, n // heads, heads)), ("transpose", (1, 0, 2))]) if heads else None
+    monkeypatch.setenv("AMAP_PLAN_TRACE", "1")
+    capfd.readouterr()
+    assert _replay(a, n, None, out_map) == (B.AMAP_OK, 0)
+    assert kind in capfd.readouterr().err
+
+
+@pytest.mark.parametrize("n", [120, 128])
+def test_the_kind_of_store_along_m(n, monkeypatch, capfd):
+    """A product whose A runs along m is stored past the caches, whatever its rows."""
+    shapes, ops = conv(9, [64], 8)
+    monkeypatch.setenv("AMAP_PLAN_TRACE", "1")
+    capfd.readouterr()
+    assert _replay(B.amap_compose(shapes, 2, ops), n) == (B.AMAP_OK, 0)
+    err = capfd.readouterr().err
+    assert "A along m" in err and PAST in err
+
+
 @pytest.mark.gpu
-@pytest.mark.parametrize("m, k, n, tile256", [(333, 64, 1000, ""),        # through the caches
-                                              (16800, 64, 1000, ""),      # past them again: more than 32 MB
-                                              (300, 128, 1000, "1")])     # partial 256 x 256 tiles, through the caches
-def test_rows_of_no_whole_pieces(dev, m, k, n, tile256, monkeypatch, capfd):  # noqa: F811
+@pytest.mark.parametrize("m, k, n, tile256, kind", [(333, 64, 1000, "", THROUGH), (16800, 64, 1000, "", PAST),   # more than 32 MB
+                                                    # partial 256 x 256 tiles, at any size; whole ones have one kind
+                                                    (300, 128, 1000, "1", THROUGH), (300, 128, 1024, "1", PAST), (512, 128, 512, "1", PAST)])
+def test_rows_of_no_whole_pieces(dev, m, k, n, tile256, kind, monkeypatch, capfd):  # noqa: F811
     a = B.amap_compose([(m, k)], 2, [])
     monkeypatch.setenv("AMAP_GEMM_TILE256", tile256)
     print(f"[gpu] rows of no whole pieces {m} x {k} x {n}", flush=True)
-    _against_general(dev, [(m, k)], a, n, None, monkeypatch, capfd, 1400, "256 x 256 tiles" if tile256 else "amap gemm: ring")
+    said = _against_general(dev, [(m, k)], a, n, None, monkeypatch, capfd, 1400, "256 x 256 tiles" if tile256 else "amap gemm: ring")
+    assert kind in said
 
 
 # A along m: few tiles of a short walk, on either side of 512 rows

@@ -55,11 +55,13 @@ def _against_general(dev, shapes, a, n, w_map, monkeypatch, capfd, seed, expect,
     monkeypatch.setenv("AMAP_PLAN_TRACE", "1")
     capfd.readouterr()
     got = run()
-    assert expect in capfd.readouterr().err
+    said = capfd.readouterr().err
+    assert expect in said
     monkeypatch.setenv("AMAP_GEMM_TILE256", "0")
     general = run()
     assert "256 x 128 tiles" in capfd.readouterr().err
     assert np.array_equal(got, general)
+    return said
 
 
 @pytest.mark.gpu
