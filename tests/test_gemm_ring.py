@@ -52,8 +52,8 @@ FORMS = [
     (([(512, 128)], []), 256),                                       # two k-steps in a ring of three stages
     (([(200, 192)], []), 136),                                       # as many as stages
     (merge(2, 4, 256, 64), 512),                                     # four
-    (merge(9, 8, 200, 80), 1160),                                    # runs of 80 on 128 x 128 tiles of 8 wavefronts
-    (merge(16, 8, 200, 80), 3080),                                   # and of 4
+    (merge(9, 8, 200, 80), 1160),                                    # runs of 80 on 128 x 128 tiles of four stages
+    (merge(16, 8, 200, 80), 3080),                                   # and of 4 wavefronts
     (conv(3, [64, 128, 64], 12), 264),                               # gathered along m, ranges for either weight
 ]
 
@@ -87,7 +87,7 @@ def test_replay(case):
 
 
 def test_forms_reach_every_kernel_shape(monkeypatch, capfd):
-    """Tile and wavefronts, A along m or k, gathered, in short runs, W along n or k (every instance there is: test_gemm_ring_shapes.py)."""
+    """Tile, wavefronts and stages, A along m or k, gathered, in short runs, W along n or k (every instance there is: test_gemm_ring_shapes.py)."""
     monkeypatch.setenv("AMAP_PLAN_TRACE", "1")
     capfd.readouterr()
     for case in range(len(FORMS)):
@@ -95,9 +95,10 @@ def test_forms_reach_every_kernel_shape(monkeypatch, capfd):
         for w in (wt, wn):
             _replay(a, n, w)
     lines = [line.split(", ") for line in capfd.readouterr().err.splitlines() if line.startswith("amap gemm: ring")]
-    seen = {", ".join(line[1:4]) for line in lines}
+    seen = {", ".join(line[1:4] + line[6:]) for line in lines}
     small, wide8, wide4 = ("64 x 64 per workgroup of 4 wavefronts", "128 x 128 per workgroup of 8 wavefronts", "128 x 128 per workgroup of 4 wavefronts")
-    want = {f"{t}, A along k{runs}, W along {w}" for t in (small, wide8, wide4) for runs in ("", " in runs shorter than a step") for w in "nk"}
+    want = {f"{t}, A along k{runs}, W along {w}" for t in (small, wide4) for runs in ("", " in runs shorter than a step") for w in "nk"}
+    want |= {f"{wide8}, A along k, W along {w}" for w in "nk"} | {f"{wide8}, A along k in runs shorter than a step, W along {w}, four stages" for w in "nk"}
     want |= {f"{wide4}, A along {a}, W along {w}" for a in ("m", "m gathered", "k gathered") for w in "nk"}
     assert seen == want
 

@@ -84,6 +84,7 @@ TILES = [
     *[(merge(1, 20, 2341, 64), 760, w, "64 x 128 per workgroup of 4") for w in (False, True)],
     *[(merge(5, 20, 469, 80), 760, w, "64 x 128 per workgroup of 4") for w in (False, True)],
     (merge(3, 16, 1300, 64), 3336, False, "128 x 128 per workgroup of 8"),                            # more than three per unit
+    *[(merge(3, 4, 1500, 80), 1160, w, "128 x 128 per workgroup of 8") for w in (False, True)],       # between one and two per unit, in short runs
     (conv(40, [320], 12), 72, False, "64 x 64 per workgroup of 4"),                                   # A along m
     (conv(7, [96, 128, 256, 128], 12), 136, False, "64 x 64 per workgroup of 4"),                     # gathered
     (conv(16, [256], 28), 120, False, "64 x 128 per workgroup of 4"),
@@ -107,7 +108,7 @@ def test_replay_of_tiles(case, monkeypatch, capfd):
 
 
 def _routes(cases, monkeypatch, capfd):
-    """For each product, with the weight along n and along k: what its plan says of tile, A and W."""
+    """For each product, with the weight along n and along k: what its plan says of tile, A and W, and of the shape beyond its tile."""
     monkeypatch.setenv("AMAP_PLAN_TRACE", "1")
     for (shapes, ops), n, *_ in cases:
         a = B.amap_compose(shapes, 2, ops)
@@ -116,14 +117,19 @@ def _routes(cases, monkeypatch, capfd):
             capfd.readouterr()
             _replay(a, n, w)
             line = [x for x in capfd.readouterr().err.splitlines() if x.startswith("amap gemm: ring")]
-            yield ", ".join(line[0].split(", ")[1:4]) if line else None
+            parts = line[0].split(", ") if line else []
+            yield ", ".join(parts[1:4] + parts[6:]) if parts else None
 
 
 def test_the_cases_reach_every_instance(monkeypatch, capfd):
-    seen = set(_routes(FORMS + RUNS + TILES, monkeypatch, capfd)) - {None}
+    from tests.test_gemm_ring_few import CASES
+    seen = set(_routes(FORMS + RUNS + TILES + CASES, monkeypatch, capfd)) - {None}
     tile = {t: f"{t} per workgroup of {w} wavefronts" for t, w in (("32 x 64", 2), ("64 x 64", 4), ("64 x 128", 4), ("128 x 128", 4))}
     wide8, short, decoded = "128 x 128 per workgroup of 8 wavefronts", " in runs shorter than a step", " in runs shorter than a step (k decoded)"
-    want = {f"{t}, A along k{runs}, W along {w}" for t in (*tile.values(), wide8) for runs in ("", short) for w in "nk"}
+    few = [(tile["32 x 64"], ", 2 more load"), (tile["64 x 64"], ", 4 more load"), (wide8, ", four stages"),
+           ("192 x 128 per workgroup of 8 wavefronts", "")]
+    alone = [(t, "") for t in (tile["64 x 64"], tile["64 x 128"], tile["128 x 128"], wide8)]
+    want = {f"{t}, A along k{runs}, W along {w}{more}" for t, more in few + alone for runs in ("", short) for w in "nk"}
     want |= {f"{t}, A along k{decoded}, W along {w}" for t in (tile["64 x 64"], tile["128 x 128"], wide8) for w in "nk"}
     want |= {f"{tile[t]}, A along m{g}, W along n" for t in ("64 x 64", "64 x 128", "128 x 128") for g in ("", " gathered")}
     want |= {f"{tile['128 x 128']}, A along m{g}, W along k" for g in ("", " gathered")}
