@@ -9,7 +9,9 @@ from tests.test_gemm_ring_shapes import _against_general
 
 CASES = [
     # chain -> [M,K], N, what the plan says of tile and wavefronts; partial tiles, whole runs of A and runs shorter than a step
-    (merge(1, 8, 250, 64), 264, "32 x 64", "2 more load"),          # the fewest steps: eight in a ring of five stages
+    (merge(1, 8, 250, 32), 264, "32 x 64", "2 more load"),          # the fewest steps: four, all issued before the first is awaited
+    (merge(1, 10, 250, 32), 264, "32 x 64", "2 more load"),         # five, in a ring of five stages: one issued behind a barrier
+    (merge(1, 8, 250, 64), 264, "32 x 64", "2 more load"),          # eight, the fewest in whole runs
     (merge(1, 14, 64, 64), 520, "32 x 64", "2 more load"),          # eight tiles of 64 x 64, the fewest with K from 896 on
     (merge(2, 12, 63, 80), 1000, "32 x 64", "2 more load"),         # rows of 2000 bytes
     (merge(2, 20, 500, 64), 1000, "64 x 64", "4 more load"),        # 256 tiles, one to each unit
@@ -29,28 +31,33 @@ def _maps(case):
     m, k = B.dst_shape(a)
     wt = B.amap_compose([(n, k)], 2, [("transpose", (1, 0))])
     store = B.amap_compose([(m, n)], 2, [("reshape", (m, n // 8, 8)), ("transpose", (1, 0, 2))])
-    return shapes, a, n, wt, store, f"{tile} per workgroup", more
+    return shapes, a, n, wt, store, f"amap gemm: ring, {tile} per workgroup", f" {m} x {n} x {k}{', ' if more else ''}{more}"
+
+
+def _is(err, tile, end):
+    """Whether the one line of a product's plan says of the tile, and of the shape beyond it, what the case does."""
+    line = [x for x in err.splitlines() if x.startswith("amap gemm: ")]
+    return len(line) == 1 and line[0].startswith(tile) and line[0].endswith(end)
 
 
 @pytest.mark.parametrize("case", range(len(CASES)))
 def test_replay(case, monkeypatch, capfd):
-    _, a, n, wt, store, tile, more = _maps(case)
+    _, a, n, wt, store, tile, end = _maps(case)
     monkeypatch.setenv("AMAP_PLAN_TRACE", "1")
     for w, out_map in ((None, None), (wt, None), (wt, store)):
         capfd.readouterr()
         assert _replay(a, n, w, out_map) == (B.AMAP_OK, 0)
-        line = capfd.readouterr().err
-        assert tile in line and line.strip().endswith(more)
+        assert _is(capfd.readouterr().err, tile, end)
 
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("case", range(len(CASES)))
 def test_against_the_general_kernel(dev, case, monkeypatch, capfd):  # noqa: F811
-    shapes, a, n, wt, store, _, more = _maps(case)
+    shapes, a, n, wt, store, tile, end = _maps(case)
     for w, out_map in ((None, None), (wt, None), (None, store)):
         print(f"[gpu] few tiles {shapes} N={n} w={'nk' if w else 'kn'} store={out_map is not None}", flush=True)
         assert _replay(a, n, w, out_map) == (B.AMAP_OK, 0)
-        _against_general(dev, shapes, a, n, w, monkeypatch, capfd, 1300 + case, more, out_map)
+        assert _is(_against_general(dev, shapes, a, n, w, monkeypatch, capfd, 1300 + case, tile, out_map), tile, end)
         monkeypatch.undo()
 
 
