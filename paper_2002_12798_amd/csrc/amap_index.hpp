@@ -151,6 +151,24 @@ AMAP_HD void rows_few_offsets(const RowsFew<N, L> &F, uint32_t r, uint32_t &doff
     doff = d;
     soff = s;
 }
+// workgroup `block` of the launch -> the piece it works on, and which of that piece's workgroups it is (threads: a power of two)
+template <int N, int L>
+AMAP_HD FewPiece rows_few_block(const RowsFew<N, L> &F, uint32_t threads, uint32_t block, uint32_t &b) {
+    FewPiece p = F.p[0];
+    b = block;
+    if constexpr (N > 1) {
+        const uint32_t blocks = (F.n_units + threads * kRowsUnroll - 1) / (threads * kRowsUnroll);
+#if defined(__HIP_DEVICE_COMPILE__)
+#pragma unroll
+#endif
+        for (int k = 1; k < N; ++k)
+            if (block >= blocks * k) {
+                b = block - blocks * k;
+                p = F.p[k];
+            }
+    }
+    return p;
+}
 // The loops of a piece in that form; false if it has more, fills or walks backwards (the origin goes into the addresses, so a lane's
 // part must not be negative).
 template <int N, int L>

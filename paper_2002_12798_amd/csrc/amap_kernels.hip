@@ -825,17 +825,8 @@ constexpr uint64_t kFewOutput = 32ull << 20;
 template <int ES, int NT, int N, int L>
 __global__ __launch_bounds__(kMaxThreads) void amap_rows_few_kernel(const RowsFew<N, L> F) {
     const uint32_t threads = blockDim.x;
-    uint32_t b = blockIdx.x;
-    FewPiece p = F.p[0];
-    if constexpr (N > 1) {
-        const uint32_t blocks = (F.n_units + threads * kRowsUnroll - 1) / (threads * kRowsUnroll);   // (threads: a power of two)
-#pragma unroll
-        for (int k = 1; k < N; ++k)
-            if (blockIdx.x >= blocks * k) {
-                b = blockIdx.x - blocks * k;
-                p = F.p[k];
-            }
-    }
+    uint32_t b;
+    const FewPiece p = rows_few_block(F, threads, blockIdx.x, b);
     uint32_t doff[kRowsUnroll], soff[kRowsUnroll], v[kRowsUnroll][4];
     bool ok[kRowsUnroll];
     const uint32_t base = b * (threads * kRowsUnroll) + threadIdx.x;

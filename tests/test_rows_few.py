@@ -1,6 +1,9 @@
 """Plain row pieces as small kernel arguments: one piece of up to five loops, up to three pieces of four that differ in where they read
 and write.  The host replay compares the decode of every piece that has such a form (test_plan_replay.py walks random maps through
-it); here the launches on both sides of each limit, bit for bit against the oracle."""
+it); here whole launches walked on the CPU, and on the GPU those on both sides of each limit, bit for bit against the oracle."""
+import os
+import subprocess
+
 import numpy as np
 import pytest
 
@@ -19,6 +22,39 @@ ONE = [
     ((1, 40), 4, [("tile", 0, 9)], True),                                             # a loop that stands still in the source
     ((700, 8, 3072), 2, [(T, (1, 0, 2))], False),                                     # 34 MB
 ]
+
+
+@pytest.fixture(scope="module")
+def replay(tmp_path_factory):
+    """The library's launch of the kernel, walked on the CPU (rows_few_replay.cpp)."""
+    import torch
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    exe = str(tmp_path_factory.mktemp("few") / "rows_few_replay")
+    rt_dirs = [os.path.join(os.path.dirname(torch.__file__), "lib"), "/opt/rocm/lib"]
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Wextra", "-Wno-unknown-pragmas", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
+                    "-I", os.path.join(root, "include"), "-I", os.path.join(root, "paper_2002_12798_amd", "csrc"),
+                    os.path.join(root, "tests", "rows_few_replay.cpp"), "-o", exe, B.LIB_PATH, "-rdynamic", "-Wl,--allow-shlib-undefined"]
+                   + [f"-Wl,-rpath,{d}" for d in [os.path.dirname(B.LIB_PATH)] + rt_dirs], check=True)
+    env = dict(os.environ, LD_LIBRARY_PATH=":".join(rt_dirs + [os.environ.get("LD_LIBRARY_PATH", "")]))
+
+    def run(es, kernel, *maps):
+        r = subprocess.run([exe, str(es), kernel, *maps], capture_output=True, text=True, env=env, timeout=120)
+        assert (r.returncode, r.stdout.strip()) == (0, "OK"), (r.stdout, r.stderr)
+    return run
+
+
+@pytest.mark.parametrize("es", [2, 4])
+@pytest.mark.parametrize("kernel, maps", [
+    # pieces of whole workgroups, of one vector more and less, of less than one; outputs in any order in memory
+    ("few", ["4,8,8,64,12,0"]), ("few", ["5,7,3,24,02,0"]), ("few", ["1,1,1,16,--,0"]),
+    ("few", ["4,8,8,64,12,0", "4,8,8,64,12,1", "4,8,8,64,12,2"]), ("few", ["5,7,3,24,02,2", "5,7,3,24,02,0", "5,7,3,24,02,1"]),
+    ("few", ["1,1,257,8,--,1", "1,1,257,8,--,0"]), ("few", ["3,5,17,8,01,0", "3,5,17,8,01,1", "3,5,17,8,01,2"]), ("few", ["1,1,1,16,--,2", "1,1,1,16,--,1", "1,1,1,16,--,0"]),
+    # as many vectors, but in another order; four pieces
+    ("other", ["6,6,6,64,12,0", "6,6,6,64,01,1"]), ("other", ["6,6,6,64,12,0", "6,6,6,64,12,1", "6,6,6,64,02,2"]), ("other", ["4,8,8,64,12,0", "4,8,8,64,--,1"]),
+    ("other", [f"2,3,4,16,12,{i}" for i in range(4)]),
+])
+def test_the_launch_replayed(replay, kernel, maps, es):
+    replay(es, kernel, *maps)
 
 
 def _run(shapes, es, chains, dsts=None):
