@@ -171,7 +171,11 @@ static PyObject *call_execute_multi(PyObject *self, PyObject *const *a, Py_ssize
     UNLESS(n_maps >= 1 && n_maps <= n_dst);
     for (Py_ssize_t i = 0; i < n_maps; ++i) {
         UNLESS(i < PySequence_Fast_GET_SIZE(a[0]));
-        UNLESS(map_of(PySequence_Fast_GET_ITEM(a[0], i), &maps[i], &n_src, &last) && last < given && n_src <= MAX_TABLE);
+        PyObject *m = PySequence_Fast_GET_ITEM(a[0], i);
+        Py_INCREF(m);   /* (asking it for its attributes may take it out of the list) */
+        const int ok = map_of(m, &maps[i], &n_src, &last);
+        Py_DECREF(m);
+        UNLESS(ok && last < given && n_src <= MAX_TABLE);
     }
     UNLESS(stream_of(a[3], &stream));
     CALLED(p_multi(tab, dst, maps, (int)n_maps, stream));

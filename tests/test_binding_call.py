@@ -103,6 +103,29 @@ def test_a_map_given_back_is_not_handed_over(call):
     assert call.execute(m, [Tensor(64)], Tensor(128), 0) == -1 and call.gemm(64, m, 64, None, 8, None, 128, 0) == -1 and call.seen == []
 
 
+def test_a_map_that_leaves_the_list_while_it_is_asked(call):
+    """The list's reference may be the last one: the map lives until both of its attributes are read."""
+    asked = []
+
+    class Leaves:
+        @property
+        def _at(self):
+            maps.clear()
+            asked.append("_at")
+            return 64
+
+        @property
+        def _reads(self):
+            asked.append("_reads")
+
+        def __del__(self):
+            asked.append("gone")
+
+    maps = [Leaves()]
+    assert call.execute_multi(maps, [Tensor(64)], [Tensor(128)], 0) == -1
+    assert asked == ["_at", "_reads", "gone"] and call.seen == []
+
+
 def test_no_output_is_none(call):
     """An output that is not there is the caller's mistake and raised as one, in a call of one map and of several."""
     from paper_2002_12798_amd import device
