@@ -532,8 +532,10 @@ static RingShape ring_shape(const GemmArgs &g, const RingPlan &p, uint32_t n_cu,
         // stays (25.9 against 29).  Few tiles of a short walk too: M = 832, K = 224, N = 128 6.2 -> 4.5, M = 768, K = 96, N = 128
         // 5.2 -> 4.0; but the fewest of all, where the call takes what issuing it takes (M = 288, K = 256, N = 128 5.3 and 4.2).
         if (p.ax && p.wx && (tiles(128, 128) >= 16 || g.M > 512 || g.K > 256)) {
-            // rows of C of no whole 64-byte pieces: narrower tiles share more of them (M = 10976, K = 256, N = 120 5.4 against 4.8 us)
-            consider(RS_64x64, g.N % 32 && g.N > 64 ? 1.06 : 1.0);
+            // Rows of C of no whole 64-byte pieces that one tile of 128 columns holds: two tiles of 64 share a piece of each of them.  The 58
+            // products (N = 72 .. 120) whose shape the factor decides take 0.946 of the time without it, none more; wider rows are shared
+            // by any tiles, and 120 products with N = 136 .. 1096 took 1.036 of it (M = 3920, K = 32, N = 200 3.78 against 3.62 us).
+            consider(RS_64x64, g.N % 32 && g.N > 64 && g.N < 128 ? 1.06 : 1.0);
             consider(RS_64x128);
         }
         return shape;

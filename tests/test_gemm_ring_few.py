@@ -103,7 +103,9 @@ def test_rows_of_no_whole_pieces(dev, m, k, n, tile256, kind, monkeypatch, capfd
 
 
 # A along m: few tiles of a short walk, on either side of 512 rows
-CONV = [(conv(8, [64], 8), 120, "128 x 128"), (conv(9, [64], 8), 160, "64 x 64"), (conv(17, [96, 32], 8), 64, "64 x 64"), (conv(50, [64], 12), 120, "64 x 128")]
+CONV = [(conv(8, [64], 8), 120, "128 x 128"), (conv(9, [64], 8), 160, "64 x 64"), (conv(17, [96, 32], 8), 64, "64 x 64"), (conv(50, [64], 12), 120, "64 x 128"),
+        # rows of no whole 64-byte pieces: narrower tiles only where two tiles of 64 would share what one of 128 holds
+        (conv(245, [32], 4), 200, "64 x 64"), (conv(2, [128], 28), 360, "64 x 64"), (conv(10, [128], 12), 136, "64 x 64"), (conv(49, [64], 4), 120, "64 x 128")]
 
 
 @pytest.mark.parametrize("case", range(len(CONV)))
