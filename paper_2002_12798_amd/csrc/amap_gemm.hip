@@ -772,8 +772,8 @@ __global__ __launch_bounds__(kGemmThreads, 1) void amap_gemm_tile256_kernel(cons
                     const uint32_t chunk = (uint32_t)(jn * 4 + q) ^ (row_w & 15u);
                     *reinterpret_cast<__attribute__((address_space(3))) u32x2 *>(scr + row_w * 256u + (chunk << 4) + ((half_w ^ (row_w >> 4)) << 3)) = o;
                 }
-            // Rows of no whole 64-byte pieces through the caches: M = 9822, K = 1536, N = 1000 40.0 -> 38.9 us, M = 32192, K = 512 51.1 -> 45.9.
-            // (Whole tiles have none but with a store map, and keep the one kind.)
+            // Rows of no whole 64-byte pieces through the caches: M = 32192, K = 512, N = 1000 49.2 -> 41.2 us, M = 16000 26.0 -> 22.3,
+            // M = 9822, K = 1536 level (36.7).  (Whole tiles have none but with a store map, and keep the one kind.)
             auto store_rows = [&](auto stream) __attribute__((always_inline)) {
 #pragma unroll
                 for (int p = 0; p < kT2StoreRows; ++p) {   // (see landed(): each of them is issued, unless EDGE)

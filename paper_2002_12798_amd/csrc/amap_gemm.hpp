@@ -68,7 +68,7 @@ struct GemmArgs {
     // store side (Section 2, eq. "store"): element (m, n) of the product goes to
     // out[obase + om(m) + on(n)]; store_mapped = 0 means the plain row-major C
     uint32_t store_mapped, obase;
-    uint32_t stream;    // tile256 kernel, partial tiles: the product goes past the caches (rows or runs of whole 64-byte pieces; see stores_stream)
+    uint32_t stream;    // tile256 kernel: the product goes past the caches (always but for partial tiles whose rows or runs are no whole 64-byte pieces)
     Digits om, on;
     // W read through a map as well: element (k, n) of W is W[wbase + wk(k) + wn(n)]
     uint32_t wbase;
@@ -87,12 +87,14 @@ struct GemmArgs {
     Digits seg_dm[kMaxSeg], seg_dk[kMaxSeg];
 };
 
-// Whether the product is stored past the caches (non-temporal).  Not where its rows (or a mapped store's runs) are no whole 64-byte
-// pieces, which is what memory writes: a piece is then stored by two instructions, and past the caches each of them goes to memory by
-// itself.  us past the caches / through them: M = 126, K = 960, N = 1000 4.9 / 4.5   M = 469, K = 640 5.1 / 4.6   M = 16000, K = 512
-// 26.5 / 24.9.  Beyond what the L2s hold (32 MB) lines are written back before they are whole, and past the caches is ahead again
-// (M = 32192, K = 512, N = 1000 46.8 / 54.2), as it is with whole pieces at any size (M = 3000, K = 640, N = 1920 12.2 / 13.3; products
-// split into heads of 32 8 % faster in the mean).
+// Whether the ring kernel, with A along k, stores the product past the caches (non-temporal).  Not where its rows (or a mapped store's
+// runs) are no whole 64-byte pieces, which is what memory writes: a piece is then stored by two instructions, and past the caches each of
+// them goes to memory by itself.  us past the caches / through them, the ring kernel: M = 126, K = 960, N = 1000 4.7 / 4.3   M = 469, K = 640
+// 4.9 / 4.5   M = 16000, K = 512 24.4 / 23.1.  Beyond what the L2s hold (32 MB) lines are written back before they are whole, and past the
+// caches is ahead again (M = 32192, K = 512, N = 1000 44.5 / 54.1), as it is with whole pieces at any size (M = 3000, K = 640, N = 1920
+// 10.7 / 11.6; products split into heads of 32 8 % faster in the mean).
+// The other kernels: the ring kernel with A along m and whole 256 x 256 tiles store past the caches, partial 256 x 256 tiles by their rows or runs
+// alone, at any size (N = 1000, M = 32192, K = 512 49.2 / 41.2   M = 16000 26.0 / 22.3   N = 1024, M = 32192 37.8 / 39.1).
 inline bool stores_stream(uint64_t M, uint64_t N, uint32_t run) { return run % 32 == 0 || M * N * 2 > (32u << 20); }
 // f(true_type) or f(false_type), the stores past the caches or through them.  They differ in one bit of the instruction only, and the
 // compiler would merge the ends of the two arms into one kind.

@@ -383,7 +383,11 @@ __global__ __launch_bounds__(64 * (T::WVM * T::WVN + T::LOAD), T::OCC) void amap
             if (m < M && n_ok) store_c(C + off, x, stream);
         }
     };
-    if constexpr (AX)   // (large, most of them)
+    // A along m: past the caches only.  us through the caches by past them, over 190 pointwise convolutions: whole 64-byte pieces 1.00 (outputs
+    // of up to 1 MB, 40), 1.01 (4 MB, 9), 1.08 .. 1.10 (32 MB, 18), 1.19 (beyond, 3); rows of no whole pieces 0.94 .. 0.98 in the mean at
+    // any size, 0.63 to 1.28 one by one (120; M = 29008, K = 96, N = 1000 25.1 and 15.9 us, M = 65072, K = 512, N = 360 36.6 and 47.0):
+    // no line has been drawn for these.
+    if constexpr (AX)
         store_tile(std::true_type{});
     else
         stores_by_kind(g.stream, store_tile);
@@ -487,12 +491,14 @@ static double share_of(uint64_t tiles, double k64, uint32_t n_cu, double step, d
 // fewer units work, the faster each).  What lies between whole numbers of tiles per unit counts for `up` of the next one.
 // Along k: fitted to 1195 products of K = 256 .. 2560 timed on the device, operands in three sets of buffers in turn, each row over the
 // tiles per unit at which its shape is considered and most where it is near the best (128 x 128 by 4 wavefronts is counted as by 8).
-// Along m and n: fitted to 304 products, calls in a stream (about 1.2 us more in every row).
+// Along m and n: fitted to 700 pointwise convolutions, the device's time as well.
+// A row with s2 = 0 is of a shape that one tile per unit is all there is to: it has no figures beyond.
 struct RingCost {
     float launch, s0, s1, s2, more, tile, up;
 };
 static double estimate(const RingCost &c, uint64_t tiles, double k64, uint32_t n_cu) {
     const double q = (double)tiles / n_cu, up = (double)((tiles + n_cu - 1) / n_cu), e = q > 1.0 ? q + c.up * (up - q) : 1.0;
+    if (q > 1.0 && c.s2 == 0.f) return 1e30;
     const double step = c.s0 + (c.s1 - c.s0) * std::min(q, 1.0) + (c.s2 - c.s1) * (std::min(e, 2.0) - 1.0) + c.more * std::max(e - 2.0, 0.0);
     return c.launch + c.tile * e + step * k64;
 }
@@ -513,7 +519,8 @@ static const struct { int bm, bn, waves; const char *more; } kRingTile[] = {{32,
                                                                             {128, 128, 8, ", four stages"}, {64, 64, 4, ", 4 more load"}, {192, 128, 8, ""}};
 
 // The shape of a product's tiles, and its estimate.  Measured on 354 other products along k: 0.8 % off the best shape each has, where
-// the shapes and figures before this were 3.2 % off.  Along m (700) 2 % off the best.
+// the shapes and figures before this were 3.2 % off.  Along m 2 % off the best over the 700 that the figures were fitted to; of 140 others
+// 0.8 % over 119 (the worst 13 %), and 26 % over the 21 of the fewest tiles, which keep 128 x 128 (see below; none takes more than 5.5 us).
 static RingShape ring_shape(const GemmArgs &g, const RingPlan &p, uint32_t n_cu, double &best) {
     RingShape shape = RS_128x128;
     best = 1e30;
@@ -580,8 +587,9 @@ static RingShape ring_shape(const GemmArgs &g, const RingPlan &p, uint32_t n_cu,
         if (2 * t128 > n_cu && t128 <= n_cu && (20 * t128 <= 17 * (uint64_t)n_cu || g.K >= 1280)) consider(RS_128x128_DEEP);
         // A few more 128 x 128 tiles than units put two on some of them while the others wait: 192 x 128 go once around, with half as much again
         // for the matrix cores to each byte that a unit is handed. 512 <= K < 768 4 % faster (26 products), from 768 on 8 % (73):
-        // M = 2048, K = 768, N = 2304 12.5 -> 11.4 us, M = 9618, K = 1600, N = 512 26.5 -> 24.0; K = 384 0 to 3 % slower. (160 x 128, or
-        // four stages: 0 to 4 % faster.)
+        // M = 2048, K = 768, N = 2304 12.1 -> 11.1 us, stored by heads 12.5 -> 11.4, M = 9618, K = 1600, N = 512 21.2 -> 18.8, in runs of 80
+        // 24.5 -> 21.9 (one card, operands in three sets of buffers; 4 to 5 % on another); K = 384 0 to 3 % slower. (160 x 128, or four stages:
+        // 0 to 4 % faster.)
         if (t128 > n_cu && tiles(192, 128) <= n_cu && g.K >= 512) consider(RS_192x128);
     }
     if (shape == RS_128x128 && by8) shape = RS_128x128_W8;
